@@ -39,7 +39,7 @@ struct Layout {
     int64_t partial_off = -1;             // partial sums of the two-dimensional matrix-core kernels (one launch at a time)
     std::vector<int64_t> idx_off;         // per exec node id: int32 [(hist + T)][N] copy of a one-hot input's class indices, or -1
     int64_t wt_off = -1;                  // transposed copies of the matrices the streaming kernels read transposed (parameter layout)
-    int64_t flags_off = 0;                // per buffer id: 1 = frame tensor of the workspace (has history frames)
+    int64_t flags_off = 0;                // per buffer id: floats per frame of a frame tensor of the workspace (has history frames), else 0
     int64_t total = 0;
 };
 constexpr int64_t SYNC_BYTES = 1024;
@@ -48,7 +48,8 @@ int64_t g_layout_skew = 4352;      // bytes, a multiple of 256 (RNNG_LAYOUT_SKEW
 
 // partial_floats: floats per frame of the largest partial-sum tensor any launch of the window needs
 // transposed_copy: a streaming kernel of the window reads matrices transposed
-Layout make_layout(const Plan& P, int T, int N, int64_t partial_floats, bool transposed_copy) {
+// twins: the window's stream count is one that the matrix-core kernels serve
+Layout make_layout(const Plan& P, int T, int N, int64_t partial_floats, bool transposed_copy, bool twins) {
     Layout L;
     int n_alloc = 0;
     const int K = (int)P.xnodes.size();
@@ -62,11 +63,11 @@ Layout make_layout(const Plan& P, int T, int N, int64_t partial_floats, bool tra
     cur = align_up(cur, 256);
     L.sync_off = cur; cur += SYNC_BYTES;
     L.buf_off.assign(P.n_bufs, -1);
-    const int64_t F = (int64_t)(T + P.hist) * N;      // every frame tensor has P.hist history frames in front
+    const int64_t F = (int64_t)(T + P.hist) * N;
     (void)K;
     auto place = [&](int b) {
-        const int64_t rows = P.buf_alloc[b] == 2 ? N : F;
-        L.buf_off[b] = cur; cur = align_up(cur + rows * P.buf_dim[b] * 4, 256);
+        const int64_t frames = P.buf_alloc[b] == 2 ? 1 : T + P.hist;      // every frame tensor has P.hist history frames in front
+        L.buf_off[b] = cur; cur = align_up(cur + frames * P.frame_floats(b, N) * 4, 256);
         // Tensors of the same shape would lie a power of two apart, so the lines that a step polls
         // in several tensors at the same frame would all fall on the same memory channel: skew them.
         cur += g_layout_skew * (1 + n_alloc % 13);
@@ -80,8 +81,8 @@ Layout make_layout(const Plan& P, int T, int N, int64_t partial_floats, bool tra
     L.idx_off.assign(P.xnodes.size(), -1);
     for (size_t k = 0; k < P.xnodes.size(); ++k)
         if (P.xnodes[k].kind == NODE_INPUT && P.input_delayed[k]) { L.idx_off[k] = cur; cur = align_up(cur + F * 4, 256); }
-    // tile-blocked twins (whole 16-stream tiles only), behind everything else
-    if (N >= 16 && N % 16 == 0)
+    // tile-blocked twins, behind everything else
+    if (twins)
         for (int b = 0; b < P.n_bufs; ++b)
             if (P.buf_alloc[b] == 3) place(b);
     L.total = cur;
@@ -209,18 +210,17 @@ struct rnn_graph {
             }
         };
         if (prefer_streaming) try_streaming();      // (tests: the streaming variant on shapes the other variants would take)
-        // 1. wave-autonomous variant: weights in registers, no barriers (single-phase components)
-        const int wave_G[6] = {32, 64, 128, 256, 16, 8};
-        for (int i = 0; i < 6 && c.source.empty() && !c.stream; ++i) {
-            const int G = force_step_G > 0 ? force_step_G : wave_G[i];
-            if (G > max_workgroups()) { if (force_step_G > 0) break; continue; }
+        // 1. wave-autonomous variant: weights in registers, no barriers (single-phase components);
+        // first on the 32 workgroups of one XCD, which exchange through its L2
+        auto try_wave = [&](int G) {
+            if (!c.source.empty() || c.stream || G > max_workgroups()) return;
             c.source = jit_wave_source(plan, cp, backward, N, G);
             if (!c.source.empty()) {
                 c.wave = true; c.lp.ok = true; c.lp.G = G; c.lp.NB = step_nb_for(N); c.lp.lds_bytes = 0;
                 c.lp.xcd_stride = G <= 32 ? 8 : 1;
             }
-            if (force_step_G > 0) break;
-        }
+        };
+        try_wave(force_step_G > 0 ? force_step_G : 32);
         // 2. matrix-core variants for many streams (weights in LDS or registers, MFMA)
         // 2a. one-dimensional split: stream groups, as many as possible (every group halves the
         //     bytes a workgroup polls per step); unit chunks: as many as the compute units allow
@@ -228,8 +228,8 @@ struct rnn_graph {
         //     rows fit on chip
         JitChoice one_d;
         int one_d_rows = -1;
-        if (c.source.empty() && N > 8) {
-            for (int J : {4, 2, 1}) {
+        if (c.source.empty() && !c.stream && matrix_streams(cp, backward, N)) {
+            for (int J : {4, 3, 2, 1}) {
                 if (force_step_J > 0 && J != force_step_J) continue;
                 JitChoice best; int best_rows = -1;
                 for (int G : {256, 128, 64, 32, 16}) {
@@ -277,6 +277,7 @@ struct rnn_graph {
             }
         }
         if (c.source.empty() && !one_d.source.empty()) c = one_d;
+        if (force_step_G <= 0) for (int G : {64, 128, 256, 16, 8}) try_wave(G);
         // 3. LDS-resident variant
         if (c.source.empty() && plan_step_launch(plan.words.data(), backward ? cp.bwd_desc_off : cp.fwd_desc_off, N, force_step_G, c.lp))
             c.source = jit_step_source(plan, cp, backward, c.lp.NB);
@@ -313,6 +314,49 @@ struct rnn_graph {
             }
         }
         return false;
+    }
+    // true if a step launch of a window with N streams may exchange through tile-blocked twins
+    bool twins_needed(int N) {
+        if (!use_jit) return false;
+        for (size_t c = 0; c < plan.comps.size(); ++c) {
+            const CompPlan& cp = plan.comps[c];
+            if (!cp.recurrent) continue;
+            for (int backward = 0; backward < 2; ++backward) {
+                if (backward ? !cp.has_bwd_program : !cp.has_fwd_program) continue;
+                if (cp.chain >= 0 && chain_choice(cp.chain, backward != 0, N).blocked) return true;
+                if (jit_choice((int)c, backward != 0, N).blocked) return true;
+            }
+        }
+        return false;
+    }
+    // the workspace layout of a window of T frames and N streams (kept for the last shape asked for)
+    Layout cached_layout;
+    int cached_T = 0, cached_N = 0;
+    const Layout& layout_for(int T, int N) {
+        if (cached_T != T || cached_N != N) {
+            cached_layout = make_layout(plan, T, N, partial_frame_floats(N), transposed_copy(N), twins_needed(N));
+            cached_T = T; cached_N = N;
+        }
+        return cached_layout;
+    }
+    void drop_choices() { jit_choices.clear(); chain_choices.clear(); cached_T = cached_N = 0; }
+    // Whether the matrix-core kernels take a component at N streams.  From 9 streams on the
+    // weights-in-registers kernels do not exist.  From 2 streams on they lose where they need more
+    // workgroups than one XCD has (their exchange then crosses the XCDs and every lane multiplies for
+    // every stream, while the matrix instructions serve 16 streams at the price of one).  Windows of
+    // 128 frames, forward + BPTT, register against matrix-core build: 2 x 256 units, N = 8: 1.78
+    // against 0.80 ms; 512 units, N = 4 / 8: 0.99 / 3.23 against 0.99 / 1.04; 1,024 units, N = 2:
+    // 1.95 against 1.40; Elman 512, N = 4: 0.77 against 0.52.  Confined to one XCD: 256 units, N = 4:
+    // 0.55 against 0.66; 512, N = 2: 0.68 against 0.97; 1,024 units at N = 1 (64 workgroups): 1.03
+    // against 1.40.  Rows beyond 1,024 elements keep the register and streaming kernels.
+    bool matrix_streams(const CompPlan& cp, bool backward, int N) const {
+        if (N > 8) return true;
+        if (N < 2) return false;
+        StepLayout lay;
+        compute_step_layout(plan.words.data(), backward ? cp.bwd_desc_off : cp.fwd_desc_off, 256, 1, 1, lay);      // (only the sources are needed)
+        if (!lay.ok) return false;
+        for (int s = 0; s < lay.n_sources; ++s) if (lay.src[s].k_len > 1024) return false;
+        return true;
     }
     // Chains of recurrent components run side by side in one launch: all members in the
     // wave-autonomous build (N <= 8, member g on XCD g), or all in the matrix-core build (the 256
@@ -370,7 +414,9 @@ struct rnn_graph {
                     c.source = jit_chain_source(plan, members, backward, N, c.G);
             }
             if (c.source.empty()) c.split = false;
-            if (c.source.empty() && N > 8 && force_step_J <= 0) {
+            bool matrix = N > 8;      // (few streams: where a layer on its own would run on the matrix cores)
+            for (int m = ch.first; m <= ch.last && !matrix; ++m) matrix = jit_choice(m, backward, N).mstep;
+            if (c.source.empty() && matrix && force_step_J <= 0) {
                 // matrix-core members: each gets an equal share of the 256 workgroups; per member the
                 // most stream groups, then the most unit chunks that fit the share (as for a single
                 // component: fewer only while a workgroup does not fill a 16-row tile)
@@ -385,7 +431,7 @@ struct rnn_graph {
                     c.G.clear(); c.J.clear();
                     for (const CompPlan& m : members) {
                         int pg = 0, pj = 0, best_rows = -1;
-                        for (int J : {4, 2, 1}) {
+                        for (int J : {4, 3, 2, 1}) {
                             for (int G : {128, 64, 32, 16}) {
                                 if (G * J > share) continue;
                                 size_t lds = 0; int rows = 0;
@@ -525,12 +571,12 @@ hipError_t ensure_xcd_map(unsigned* scratch, hipStream_t s, const XcdMap** out) 
 // tensor through one buffer descriptor with 32-bit offsets and park idle lanes 1 GiB beyond:
 // every tensor of the window must stay below 1 GiB.
 bool wave_tensor_sizes_ok(const rnn_graph* g) {
-    int64_t maxdim = 1;
+    int64_t frame = 1;
     for (int b = 0; b < g->plan.n_bufs; ++b) {
         // the caller's input tensors are never stored by a step kernel
-        if (!g->caller_input(b)) maxdim = std::max<int64_t>(maxdim, g->plan.buf_dim[b]);
+        if (!g->caller_input(b)) frame = std::max<int64_t>(frame, g->layout.buf_off[b] >= 0 ? g->plan.frame_floats(b, g->N) : (int64_t)g->N * g->plan.buf_dim[b]);
     }
-    return (int64_t)g->Ti() * g->N * maxdim * 4 < (int64_t(1) << 30);
+    return (int64_t)g->Ti() * frame * 4 < (int64_t(1) << 30);
 }
 
 // The wave-autonomous kernels can store through ONE buffer descriptor when everything they store
@@ -543,7 +589,7 @@ bool wave_store_window_ok(const rnn_graph* g) {
         if (g->caller_input(b)) continue;
         const char* p = reinterpret_cast<const char*>(g->buf(b));
         if (p == nullptr) continue;      // no storage: never stored
-        const int64_t bytes = (int64_t)g->Ti() * g->N * g->plan.buf_dim[b] * 4;
+        const int64_t bytes = (int64_t)g->Ti() * g->plan.frame_floats(b, g->N) * 4;
         if (p < g->ws || p + bytes > g->ws + g->layout.total) return false;
     }
     return true;
@@ -581,7 +627,9 @@ hipError_t fill_shared(rnn_graph* g, const std::vector<int>& bufs, bool with_bun
         }
     FillRanges fr; fr.count = 0;
     for (int b : list) {
-        const int64_t frame = (int64_t)g->N * g->plan.buf_dim[b];
+        const int64_t frame = g->plan.frame_floats(b, g->N);
+        const bool ragged = g->plan.buf_alloc[b] == 3 && frame != (int64_t)g->N * g->plan.buf_dim[b];
+        fr.twin_n[fr.count] = ragged ? g->N : 0; fr.twin_dim[fr.count] = ragged ? g->plan.buf_dim[b] : 0;
         fr.p[fr.count] = g->buf(b) + t0 * frame; fr.n[fr.count] = (t1 - t0) * frame;
         if (++fr.count == FILL_MAX_RANGES) {
             hipError_t e = launch_fill_sentinel_ranges(fr, s);
@@ -861,7 +909,7 @@ int64_t rnn_workspace_bytes(const rnn_graph* g, int32_t T, int32_t N) {
     if (!g) return fail(RNN_ERR_INVALID_ARGUMENT, "graph is NULL");
     if (T <= 0 || N <= 0) return fail(RNN_ERR_INVALID_ARGUMENT, "T and N must be positive");
     if ((int64_t)(T + g->plan.hist) * N >= (int64_t(1) << 31)) return fail(RNN_ERR_INVALID_ARGUMENT, "T * N exceeds 2^31 - 1");
-    return make_layout(g->plan, T, N, const_cast<rnn_graph*>(g)->partial_frame_floats(N), const_cast<rnn_graph*>(g)->transposed_copy(N)).total;
+    return const_cast<rnn_graph*>(g)->layout_for(T, N).total;
 }
 
 namespace {
@@ -928,18 +976,18 @@ int rnn_forward_range(rnn_graph* g, const float* d_weights, const float* const* 
         if (!d_inputs[i] && !g->is_onehot(P.input_nodes[i])) return fail(RNN_ERR_INVALID_ARGUMENT, "an input tensor pointer is NULL");
     if (!d_workspace) return fail(RNN_ERR_WORKSPACE, "workspace is NULL");
     if (reinterpret_cast<uintptr_t>(d_workspace) & 255) return fail(RNN_ERR_WORKSPACE, "workspace is not 256-byte aligned");
-    if (ws_bytes < make_layout(P, T, N, g->partial_frame_floats(N), g->transposed_copy(N)).total)
-        return fail(RNN_ERR_WORKSPACE, "workspace too small: need " + std::to_string(make_layout(P, T, N, g->partial_frame_floats(N), g->transposed_copy(N)).total) + " bytes");
+    if (ws_bytes < g->layout_for(T, N).total)
+        return fail(RNN_ERR_WORKSPACE, "workspace too small: need " + std::to_string(g->layout_for(T, N).total) + " bytes");
     if (g->cu_count == 0) {
         // The step kernels' launch shapes depend on how many workgroups the device keeps resident.
         int dev = 0, cus = 0;
         hipError_t qe = hipGetDevice(&dev);
         if (qe == hipSuccess) qe = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (qe != hipSuccess || cus <= 0) return fail_hip(qe, "device query");
-        if (cus != g->max_workgroups()) { g->jit_choices.clear(); g->chain_choices.clear(); }      // chosen for a whole device
+        if (cus != g->max_workgroups()) g->drop_choices();      // chosen for a whole device
         g->cu_count = cus;
     }
-    Layout L = make_layout(P, T, N, g->partial_frame_floats(N), g->transposed_copy(N));
+    Layout L = g->layout_for(T, N);
     if (ws_bytes < L.total) return fail(RNN_ERR_WORKSPACE, "workspace too small: need " + std::to_string(L.total) + " bytes");
     if (t_begin > 0) {
         // the earlier frames must be there: same window shape and workspace, computed up to t_begin
@@ -961,7 +1009,7 @@ int rnn_forward_range(rnn_graph* g, const float* d_weights, const float* const* 
     }
     std::memcpy(&g->blob[L.dims_off], P.buf_dim.data(), (size_t)P.n_bufs * 4);
     for (int b = 0; b < P.n_bufs; ++b) {
-        const int32_t flag = ((P.buf_alloc[b] == 1 || P.buf_alloc[b] == 3) && L.buf_off[b] >= 0) ? 1 : 0;
+        const int32_t flag = ((P.buf_alloc[b] == 1 || P.buf_alloc[b] == 3) && L.buf_off[b] >= 0) ? (int32_t)P.frame_floats(b, N) : 0;
         std::memcpy(&g->blob[L.flags_off + 4 * (int64_t)b], &flag, 4);
     }
     if (!P.words.empty()) std::memcpy(&g->blob[L.words_off], P.words.data(), P.words.size() * 4);
@@ -981,7 +1029,7 @@ int rnn_forward_range(rnn_graph* g, const float* d_weights, const float* const* 
         e = launch_fill(reinterpret_cast<float*>(g->ws + L.sync_off), SYNC_BYTES / 4, 0.0f, s);
         if (e != hipSuccess) return fail_hip(e, "control word reset");
         if (H > 0) {
-            e = launch_zero_history(g->view().buf_ptr, g->view().buf_dim, reinterpret_cast<const int32_t*>(g->ws + L.flags_off), P.n_bufs, (int64_t)H * N, s);
+            e = launch_zero_history(g->view().buf_ptr, reinterpret_cast<const int32_t*>(g->ws + L.flags_off), P.n_bufs, H, s);
             if (e != hipSuccess) return fail_hip(e, "history reset");
         }
     }
@@ -1047,7 +1095,7 @@ int rnn_forward_static(rnn_graph* g, const float* d_weights, const float* const*
         if (!d_outputs[i]) return fail(RNN_ERR_INVALID_ARGUMENT, "an output tensor pointer is NULL");
     if (T <= 0 || N <= 0) return fail(RNN_ERR_INVALID_ARGUMENT, "T and N must be positive");
     if (g->prof.mask != 0) return fail(RNN_ERR_SEQUENCE, "kernel-class timing creates events: switch it off for rnn_forward_static");
-    const int64_t need = make_layout(P, T, N, g->partial_frame_floats(N), g->transposed_copy(N)).total;
+    const int64_t need = g->layout_for(T, N).total;
     if (need > (int64_t)RNN_STATIC_WORKSPACE_BYTES)
         return fail(RNN_ERR_WORKSPACE, "the window needs " + std::to_string(need) + " bytes of workspace, the static workspace holds " +
                                            std::to_string((int64_t)RNN_STATIC_WORKSPACE_BYTES));
@@ -1106,7 +1154,7 @@ int rnn_shift_window(rnn_graph* g, int32_t frames, void* hip_stream) {
     // included: they then hold the frames right before the new window start.  Block by block in
     // stream order, so that source and destination of one copy never overlap.
     auto shift = [&](int b) -> hipError_t {
-        const int64_t fr = (int64_t)g->N * P.buf_dim[b];
+        const int64_t fr = P.frame_floats(b, g->N);
         float* y = g->buf(b);
         for (int t = 0; t + frames < Ti; t += frames) {
             const int n = std::min(frames, Ti - frames - t);
@@ -1120,7 +1168,7 @@ int rnn_shift_window(rnn_graph* g, int32_t frames, void* hip_stream) {
         if (g->layout.buf_off[b] < 0) continue;      // an input read in place: the caller shifts it
         hipError_t e = shift(b);
         if (e != hipSuccess) return fail_hip(e, "window shift");
-        if (P.twin_base >= 0 && g->layout.buf_off[P.twin_base + b] >= 0) {      // its tile-blocked twin has the same frame size
+        if (P.twin_base >= 0 && g->layout.buf_off[P.twin_base + b] >= 0) {      // its tile-blocked twin
             e = shift(P.twin_base + b);
             if (e != hipSuccess) return fail_hip(e, "window shift");
         }

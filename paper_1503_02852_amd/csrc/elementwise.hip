@@ -279,21 +279,19 @@ hipError_t launch_upload_words(uint32_t* d_dst, const uint32_t* h_src, int64_t n
 }
 
 namespace {
-// One workgroup per buffer: the first `rows` rows of a flagged buffer become zero.
-__global__ __launch_bounds__(256) void zero_history_kernel(float* const* __restrict__ buf_ptr, const int32_t* __restrict__ buf_dim,
-                                                           const int32_t* __restrict__ buf_flags, long long rows) {
+// blockIdx.x: the buffer.
+__global__ __launch_bounds__(256) void zero_history_kernel(float* const* __restrict__ buf_ptr, const int32_t* __restrict__ frame_floats, int frames) {
     const int b = blockIdx.x;
-    if (buf_flags[b] != 1) return;
+    const long long n = (long long)frames * frame_floats[b];
+    if (n <= 0) return;
     float* p = buf_ptr[b];
-    const long long n = rows * buf_dim[b];
-    for (long long i = threadIdx.x; i < n; i += 256) p[i] = 0.0f;
+    for (long long i = blockIdx.y * 256 + threadIdx.x; i < n; i += 256LL * gridDim.y) p[i] = 0.0f;
 }
 }  // namespace
 
-hipError_t launch_zero_history(float* const* buf_ptr, const int32_t* buf_dim, const int32_t* buf_flags, int n_bufs, int64_t rows,
-                               hipStream_t stream) {
-    if (n_bufs <= 0 || rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(zero_history_kernel, dim3((unsigned)n_bufs), dim3(256), 0, stream, buf_ptr, buf_dim, buf_flags, (long long)rows);
+hipError_t launch_zero_history(float* const* buf_ptr, const int32_t* frame_floats, int n_bufs, int frames, hipStream_t stream) {
+    if (n_bufs <= 0 || frames <= 0) return hipSuccess;
+    hipLaunchKernelGGL(zero_history_kernel, dim3((unsigned)n_bufs, 4), dim3(256), 0, stream, buf_ptr, frame_floats, frames);
     return hipGetLastError();
 }
 

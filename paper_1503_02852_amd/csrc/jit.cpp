@@ -466,8 +466,10 @@ bool emit_mstep_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, 
                       const std::string& ns, size_t* lds_bytes, int* rows) {
     const std::vector<PhasePlan>& phases = backward ? cp.bwd_phases : cp.fwd_phases;
     if (phases.size() != 1 || N_all < 1 || J < 1 || G * J > 256) return false;
-    if (J > 1 && N_all % (16 * J) != 0) return false;      // stream groups of whole 16-stream tiles
-    const int N = (N_all + J - 1) / J;                   // streams per workgroup
+    // streams per workgroup; several stream groups are made of whole 16-stream tiles (without twins
+    // equally many in each, else the last group may have fewer)
+    const int N = J > 1 && blocked ? ((N_all + 15) / 16 + J - 1) / J * 16 : (N_all + J - 1) / J;
+    if (J > 1 && (blocked ? (J - 1) * N >= N_all : N_all % (16 * J) != 0)) return false;
     StepLayout lay;
     compute_step_layout(P.words.data(), backward ? cp.bwd_desc_off : cp.fwd_desc_off, G, 1, N, lay);
     if (!lay.ok) return false;
@@ -512,11 +514,13 @@ bool emit_mstep_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, 
     }
     if (!ml.ok || (size_t)ml.total_floats * 4 > MSTEP_LDS_LIMIT) return false;
     if (blocked) {
-        if (N_all < 16 || N_all % 16 != 0 || N % 16 != 0 || P.twin_base < 0) return false;
+        if (P.twin_base < 0) return false;
         auto has_twin = [&](int b) { return b >= 0 && b < P.twin_base && P.buf_alloc[P.twin_base + b] == 3; };
         // (a helper member's sums are read element by element from the row-major tensor)
         if (!cp.helper) for (int b : backward ? cp.bwd_shared_bufs : cp.fwd_shared_bufs) if (!has_twin(b)) return false;
         for (int s = 0; s < ml.n_src; ++s) if (!has_twin(lay.src[s].buf) || lay.src[s].k_len != P.buf_dim[lay.src[s].buf]) return false;
+    } else {
+        for (int s = 0; s < ml.n_src; ++s) if (lay.src[s].k_len & 3) return false;      // polled rows are read with 128-bit loads
     }
     const StepPhase& ph = lay.ph[0];
     const int MT = (N + 15) / 16, NTU = (ph.n_tasks * ph.cmax + 15) / 16;
@@ -555,7 +559,7 @@ bool emit_mstep_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, 
       << "    static constexpr bool FLAT = " << (flat ? "true" : "false") << ", XB = " << (blocked ? "true" : "false")
       << ", HELPER = " << (cp.helper ? "true" : "false") << ";\n"
       ;
-    std::vector<std::pair<int, int>> ks, blk, used, ngr, csrc, ck0;
+    std::vector<std::pair<int, int>> ks, kps, blk, used, ngr, csrc, ck0;
     // The unrolled chunk sequence takes the sources in the order in which their values arrive: what
     // another component of the launch produces (it runs ahead) and the component's own values of
     // older frames first, the values that the other workgroups have produced in the step before
@@ -577,7 +581,7 @@ bool emit_mstep_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, 
         if (!seen_late) clate = c;
     }
     for (int s = 0; s < ml.n_src; ++s) {
-        ks.push_back({s, lay.src[s].k_len});
+        ks.push_back({s, lay.src[s].k_len}); kps.push_back({s, blocked ? twin_pad(lay.src[s].k_len) : lay.src[s].k_len});
         for (int t = 0; t < ph.n_tasks; ++t) if (ml.blk[s][t] >= 0) blk.push_back({s * STEP_MAX_TASKS + t, ml.blk[s][t]});
         for (int nt = 0; nt < NTU; ++nt) {
             bool any = false;
@@ -589,7 +593,7 @@ bool emit_mstep_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, 
         }
         ngr.push_back({s, ((lay.src[s].k_len + CW - 1) / CW + D - 1) / D});
     }
-    emit_switch("K", "s", ks, 0); emit_switch("blk_", "key", blk, -1); emit_switch("used_", "key", used, 0);
+    emit_switch("K", "s", ks, 0); emit_switch("KP", "s", kps, 0); emit_switch("blk_", "key", blk, -1); emit_switch("used_", "key", used, 0);
     emit_switch("ngr", "s", ngr, 0); emit_switch("csrc", "c", csrc, 0); emit_switch("ck0", "c", ck0, 0);
     // register-resident weights: index of (chunk, row tile) in the lane's register array
     std::vector<std::pair<int, int>> widx;
@@ -620,7 +624,7 @@ static const char* mstep_kernel_attributes(int NW) {
                    : "extern \"C\" __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))\n";
 }
 
-// RNNG_MSTEP_BLOCKED = 0: no exchange through tile-blocked twins (the row-major path, as for ragged stream counts).
+// RNNG_MSTEP_BLOCKED = 0: no exchange through tile-blocked twins (the row-major path).
 static std::vector<int> mstep_blocked_choices() {
     if (const char* env = std::getenv("RNNG_MSTEP_BLOCKED")) if (std::atoi(env) == 0) return {0};
     return {1, 0};
@@ -894,7 +898,7 @@ std::string jit_smstep_source(const Plan& P, const CompPlan& cp, bool backward, 
     // pass of the element-wise part, every exchanged tensor with a twin
     bool xb = N % 16 == 0 && (IPT == 1 || SPP % 16 == 0) && P.twin_base >= 0 && !mstep_blocked_choices().empty() && mstep_blocked_choices()[0] != 0;
     auto has_twin = [&](int b) { return b >= 0 && b < P.twin_base && P.buf_alloc[P.twin_base + b] == 3; };
-    for (int b : backward ? cp.bwd_shared_bufs : cp.fwd_shared_bufs) xb = xb && has_twin(b);
+    for (int b : backward ? cp.bwd_shared_bufs : cp.fwd_shared_bufs) xb = xb && has_twin(b) && P.buf_dim[b] % 16 == 0;
     for (int sidx = 0; sidx < lay.n_sources; ++sidx) xb = xb && has_twin(lay.src[sidx].buf) && lay.src[sidx].k_len == P.buf_dim[lay.src[sidx].buf];
     std::ostringstream o;
     o << "#include \"step_device.h\"\nusing namespace rnng;\n";

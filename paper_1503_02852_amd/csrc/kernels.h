@@ -61,9 +61,9 @@ hipError_t launch_squared_error_delta(const float* y, const float* d, float* ds,
 // The sums run over frames [t0, T); factors may reach back to frames before t0.
 hipError_t launch_colsum(const PlanView& pv, int tasks_off, int n_tasks, int max_dim, const float* weights, float* grads,
                          int T, int N, int t0, bool one_writer, hipStream_t stream);
-// Zeroes the first `rows` rows of every buffer whose flag is 1 (the history frames in front of a fresh window).
-hipError_t launch_zero_history(float* const* buf_ptr, const int32_t* buf_dim, const int32_t* buf_flags, int n_bufs, int64_t rows,
-                               hipStream_t stream);
+// Zeroes the history frames in front of a fresh window: `frames` frames of frame_floats[b] floats of
+// every buffer b (0: the buffer keeps none).
+hipError_t launch_zero_history(float* const* buf_ptr, const int32_t* frame_floats, int n_bufs, int frames, hipStream_t stream);
 hipError_t launch_fill(float* p, int64_t n, float v, hipStream_t stream);
 hipError_t launch_copy(float* dst, const float* src, int64_t n, hipStream_t stream);
 // dst[c][r] = src[r][c] for a row-major rows x cols matrix.
@@ -100,7 +100,10 @@ hipError_t launch_recurrent_steps(const PlanView& pv, const StepLaunchPlan& lp, 
 hipError_t launch_fill_sentinel(float* p, int64_t n, hipStream_t stream);
 // The same for up to FILL_MAX_RANGES ranges with one launch (a step launch's exchanged tensors).
 constexpr int FILL_MAX_RANGES = 16;
-struct FillRanges { float* p[FILL_MAX_RANGES]; long long n[FILL_MAX_RANGES]; int count; };
+// A range of frames of a tile-blocked twin whose tiles are not full names its tensor's stream count
+// and width (twin_n, twin_dim; 0: an ordinary range): the padding becomes zero, so that its pollers
+// neither wait for it nor add anything.
+struct FillRanges { float* p[FILL_MAX_RANGES]; long long n[FILL_MAX_RANGES]; int twin_n[FILL_MAX_RANGES], twin_dim[FILL_MAX_RANGES], count; };
 hipError_t launch_fill_sentinel_ranges(const FillRanges& r, hipStream_t stream);
 
 }  // namespace rnng

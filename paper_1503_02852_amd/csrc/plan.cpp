@@ -648,7 +648,7 @@ bool build_plan(const std::vector<GNode>& nodes, const std::vector<GEdge>& edges
             if (!cp.recurrent || cp.fwd_phases.size() != 1 || cp.bwd_phases.size() != 1) return;
             for (const std::vector<int>* list : {&cp.fwd_shared_bufs, &cp.bwd_shared_bufs})
                 for (int b : *list)
-                    if (b < P.twin_base && P.buf_alloc[b] == 1 && P.buf_dim[b] % 16 == 0) P.buf_alloc[P.twin_base + b] = 3;
+                    if (b < P.twin_base && P.buf_alloc[b] == 1) P.buf_alloc[P.twin_base + b] = 3;
         };
         for (const CompPlan& cp : P.comps) make_twins(cp);
         for (const ChainPlan& ch : P.chains) for (const CompPlan& cp : ch.members) make_twins(cp);

@@ -6,6 +6,7 @@
 
 #include "graph.h"
 #include "program.h"
+#include "step_layout.h"
 
 namespace rnng {
 
@@ -104,11 +105,12 @@ struct Plan {
     // Tile-blocked twins.  A many-stream step kernel polls an exchanged tensor in tiles of 16
     // streams x 16 units, and a wavefront's load is served at full rate only if its 1 KiB lies at
     // consecutive addresses (measured: 77 GB/s per workgroup against 35 GB/s for 16 rows of 64
-    // bytes).  Every tensor b that workgroups of a single-phase recurrent component exchange, and
-    // whose width is a multiple of 16, therefore has a twin with the id twin_base + b:
-    // [frame][stream / 16][unit / 16][(unit % 16) / 4][stream % 16][unit % 4], allocated for
-    // windows whose stream count is a multiple of 16.  The producing kernel stores each value
-    // twice (row-major for everyone else, blocked for the pollers).
+    // bytes).  Every tensor b that workgroups of a single-phase recurrent component exchange
+    // therefore has a twin with the id twin_base + b:
+    // [frame][stream / 16][unit / 16][(unit % 16) / 4][stream % 16][unit % 4], whole tiles whatever
+    // the stream count and the width (the padding holds zeros), allocated for windows whose stream
+    // count the matrix-core kernels serve.  The producing kernel stores each value twice (row-major
+    // for everyone else, blocked for the pollers).
     int twin_base = -1;
     std::vector<CompPlan> comps;
     std::vector<ChainPlan> chains;
@@ -131,6 +133,10 @@ struct Plan {
     std::vector<char> input_staged;               // per exec node id
     std::vector<char> input_delayed;              // per exec node id: an input node with a delayed out-connection
 
+    // floats per frame of buffer b in a window of N streams
+    int64_t frame_floats(int b, int N) const {
+        return buf_alloc[b] == 3 ? (int64_t)twin_pad(N) * twin_pad(buf_dim[b]) : (int64_t)N * buf_dim[b];
+    }
     int ybuf(int k) const { return k; }
     int dbuf(int k) const { return (int)xnodes.size() + k; }
     int abuf(int k) const { return 2 * (int)xnodes.size() + k; }

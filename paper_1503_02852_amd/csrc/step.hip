@@ -101,6 +101,16 @@ __global__ __launch_bounds__(256) void fill_bits_kernel(unsigned* __restrict__ p
 __global__ __launch_bounds__(256) void fill_ranges_kernel(const FillRanges r, unsigned v) {
     unsigned* __restrict__ p = reinterpret_cast<unsigned*>(r.p[blockIdx.y]);
     const long long n = r.n[blockIdx.y];
+    const int dim = r.twin_dim[blockIdx.y];
+    if (dim > 0) {      // [frame][stream / 16][unit / 16][(unit % 16) / 4][stream % 16][unit % 4]
+        const int N = r.twin_n[blockIdx.y], nt = (N + 15) >> 4, kt = (dim + 15) >> 4;
+        for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < (unsigned)n; i += 256 * gridDim.x) {
+            const unsigned tile = i >> 8;
+            const int k = (int)(tile % kt) * 16 + (int)((i >> 6) & 3) * 4 + (int)(i & 3), s = (int)(tile / kt % nt) * 16 + (int)((i >> 2) & 15);
+            p[i] = s < N && k < dim ? v : 0u;
+        }
+        return;
+    }
     for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += 256LL * gridDim.x) p[i] = v;
 }
 

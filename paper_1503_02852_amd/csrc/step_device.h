@@ -1322,7 +1322,9 @@ __device__ __forceinline__ void wave_step(PhaseRegs<PH>& r, const WaveRegs<MV>& 
 // 43 / 79 / 94 GB/s with 4 / 8 / 16) are in flight in D register sets, and a chunk that comes back
 // with a sentinel is loaded again by the wavefront that needs it.  With MM::XB the sources are
 // the tile-blocked twins of the exchanged tensors (a wavefront's load is 1 KiB of consecutive
-// addresses: 77 instead of 35 GB/s per workgroup).  One accumulator set serves all sources; the
+// addresses: 77 instead of 35 GB/s per workgroup), which are padded with zeros to whole tiles, so
+// that any stream count and any width takes this path (without twins a row of a source must be a
+// multiple of 16 bytes).  One accumulator set serves all sources; the
 // NW partial tiles meet in LDS, where the element-wise program runs with one thread per
 // (stream, unit) on the first STEP_THREADS threads.
 //
@@ -1332,7 +1334,8 @@ __device__ __forceinline__ void wave_step(PhaseRegs<PH>& r, const WaveRegs<MV>& 
 //   (wavefronts), NCH (chunks of all sources), CLATE (first chunk that holds the previous step's
 //   own values), NRW (weight quads in registers); bool FLAT (the chunk sequence is unrolled whole),
 //   XB, HELPER (a chain's helper member: its program only stores the sums of its products, which
-//   another member's program polls element by element); unsigned REGMASK; constexpr K(s), ngr(s) (groups of D chunks of source s), blk(s, task)
+//   another member's program polls element by element); unsigned REGMASK; constexpr K(s) (columns of
+//   source s), KP(s) (the same, padded to whole tiles with XB), ngr(s) (groups of D chunks of source s), blk(s, task)
 //   (row block of the task in source s, -1: none), used(s, nt), csrc(c) / ck0(c) (source and first
 //   column of chunk c), widx(c * 16 + nt) (register index of a weight quad).
 // =============================================================================================
@@ -1366,8 +1369,6 @@ RNNG_HD inline void compute_mstep_layout(const StepLayout& lay, int N, int nw, u
     if (ph.item_chunk * N > STEP_THREADS) return;
     m.n_src = lay.n_sources; m.cmax = ph.cmax;
     const int npad = (N + 15) / 16 * 16;
-    for (int s = 0; s < lay.n_sources; ++s)
-        if (lay.src[s].k_len & 3) return;               // rows are read with 128-bit loads
     int cur = 0, wsmax = 0;
     for (int s = 0; s < lay.n_sources; ++s) {
         int nb = 0;
@@ -1411,6 +1412,8 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
     const int T = a.T;
     const int n0 = wj * MM::NJ;                                            // first stream of this workgroup
     const int N = a.N - n0 < MM::NJ ? a.N - n0 : MM::NJ;                   // its streams
+    // rows of a polled frame, and those of this workgroup's streams (a twin's padded to whole tiles)
+    const int NF = MM::XB ? twin_pad(a.N) : a.N, NR = MM::XB ? twin_pad(N) : N;
     MShared& sh = ms;
     constexpr int NW = MM::NW, NTHR = 64 * NW, CW = 16 * NW;      // wavefronts, threads, columns of a chunk
     if (tid == 0) { compute_step_layout(a.words, a.desc_off, a.G, 1, MM::NJ, sh.lay); compute_mstep_layout(sh.lay, MM::NJ, NW, MM::REGMASK, (int)(MSTEP_LDS_LIMIT / 4), ms.ml); }
@@ -1540,7 +1543,7 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
 #pragma unroll
         for (int mt = 0; mt < MM::MT; ++mt) {
             const int n = mt * 16 + (lane & 15);
-            if (MM::XB) aoff[sidx][mt] = ((mt * (MM::K(sidx) / 16) + wave) * 256 + lane * 4) * 4;
+            if (MM::XB) aoff[sidx][mt] = ((mt * (MM::KP(sidx) / 16) + wave) * 256 + lane * 4) * 4;
             else aoff[sidx][mt] = n < N ? (n * MM::K(sidx) + wcol) * 4 : 0x7FFFFFF0;
         }
 
@@ -1559,19 +1562,21 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
     // the twins (the row-major copies, which nobody polls, are then stored plainly)
     const float* xbase[PH::NST > 0 ? PH::NST : 1];
     unsigned xvrun[PH::NST > 0 ? PH::NST : 1];
+    int xstride[PH::NST > 0 ? PH::NST : 1];      // floats per frame of the twin
     if constexpr (MM::XB) {
         cwords_t pw = (cwords_t)a.words + suni(ph.prog_off);
         cwords_t st = pw + PG_HEADER_WORDS + PH::NG * GA_WORDS + PH::NI * IV_WORDS + pw[PG_NOPS] * MO_WORDS;
 #pragma unroll
         for (int q = 0; q < PH::NST; ++q) {
-            xbase[q] = nullptr; xvrun[q] = WAVE_NO_STORE;
+            xbase[q] = nullptr; xvrun[q] = WAVE_NO_STORE; xstride[q] = 0;
             if (!PH::stshared(q) || !PH::sttwin(q)) continue;
             const int dim = suni(st[q * ST_WORDS + ST_DIM]);
+            xstride[q] = suni(twin_pad(a.N) * twin_pad(dim));
             xbase[q] = suni_ptr(((cbufs_t)a.buf_ptr)[a.twin_base + suni(st[q * ST_WORDS + ST_BUF])]);
             if (r.sptr[q] != nullptr) {
                 const int i = (int)(r.sptr[q] - r.sbase[q]) - r.n * dim;      // this thread's unit
-                const int off = ((r.n >> 4) * (dim >> 4) + (i >> 4)) * 256 + ((((i & 15) >> 2) << 4) + (r.n & 15)) * 4 + (i & 3);
-                xvrun[q] = (unsigned)((off + step_frame(a, 0) * r.sstride[q]) * 4);
+                const int off = ((r.n >> 4) * (twin_pad(dim) >> 4) + (i >> 4)) * 256 + ((((i & 15) >> 2) << 4) + (r.n & 15)) * 4 + (i & 3);
+                xvrun[q] = (unsigned)((off + step_frame(a, 0) * xstride[q]) * 4);
                 if (MStore::SW) xvrun[q] += (unsigned)((xbase[q] - a.store_base) * 4);
             }
         }
@@ -1618,9 +1623,9 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
             const StepSource& sc = sh.lay.src[sidx];
             const int frame = t + suni(sc.frame_off);
             const bool in_window = frame >= 0 && frame < T;
-            // (a twin's frame has the same size, and its stream tiles are as large as 16 rows)
-            const float* g = ((cbufs_t)a.buf_ptr)[(MM::XB ? a.twin_base : 0) + suni(sc.buf)] + ((size_t)(in_window ? frame : 0) * a.N + n0) * MM::K(sidx);
-            rs[sidx] = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g), 0, in_window ? N * MM::K(sidx) * 4 : 0, STEP_RSRC_FLAGS);
+            // (a twin's 16-stream tiles are as large as 16 padded rows)
+            const float* g = ((cbufs_t)a.buf_ptr)[(MM::XB ? a.twin_base : 0) + suni(sc.buf)] + ((size_t)(in_window ? frame : 0) * NF + n0) * MM::KP(sidx);
+            rs[sidx] = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g), 0, in_window ? NR * MM::KP(sidx) * 4 : 0, STEP_RSRC_FLAGS);
         }
         // A helper member has no values of its own to wait for and would otherwise poll each frame
         // of its sources while the producing member's stores are still under way, which slows that
@@ -1632,7 +1637,7 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
                 const StepSource& sc = sh.lay.src[0];
                 const int frame = step_frame(a, step + 1) + suni(sc.frame_off);
                 if (frame >= 0 && frame < T) {
-                    const float* p = ((cbufs_t)a.buf_ptr)[(MM::XB ? a.twin_base : 0) + suni(sc.buf)] + ((size_t)frame * a.N + n0) * MM::K(0);
+                    const float* p = ((cbufs_t)a.buf_ptr)[(MM::XB ? a.twin_base : 0) + suni(sc.buf)] + ((size_t)frame * NF + n0) * MM::KP(0);
                     int spins = 0;
                     while (__float_as_uint(load_coherent(p)) == STEP_SENTINEL && !dead) {
                         if (++spins > a.spin_limit) { dead = true; if (lane == 0) atomicExch(a.ctrl, 1u); break; }
@@ -1687,7 +1692,7 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
                 if (++spins > a.spin_limit) { dead = true; if (lane == 0) atomicExch(a.ctrl, 1u); break; }
                 __builtin_amdgcn_s_sleep(MSTEP_RETRY_SLEEP);
                 step_compiler_barrier();
-                load_chunk(again, rs[sidx], aoff[sidx], MM::K(sidx), MM::K(sidx) % CW != 0, k0, true);
+                load_chunk(again, rs[sidx], aoff[sidx], MM::KP(sidx), MM::KP(sidx) % CW != 0, k0, true);
                 if (!incomplete(again)) break;
             }
 #pragma unroll
@@ -1721,7 +1726,7 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
                 constexpr int i = decltype(ii)::value;
                 constexpr int sx = MM::csrc(i < NCH ? i : 0);
                 if (i == MM::CLATE) hold_off();
-                load_chunk(v[i], rs[sx], aoff[sx], MM::K(sx), MM::K(sx) % CW != 0, rot(StepIntC<sx>{}, MM::ck0(i < NCH ? i : 0)), i < NCH);
+                load_chunk(v[i], rs[sx], aoff[sx], MM::KP(sx), MM::KP(sx) % CW != 0, rot(StepIntC<sx>{}, MM::ck0(i < NCH ? i : 0)), i < NCH);
             });
 #pragma unroll
             for (int mt = 0; mt < MM::MT; ++mt)
@@ -1747,7 +1752,7 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
                 if (c == 0) { RNNG_STAMP(2); }
                 if (c == 1) { RNNG_STAMP(6); RNNG_STAMP(7); }
                 if (c + D - 1 == MM::CLATE) hold_off();
-                if (c + D - 1 < NCH) load_chunk(v[j], rs[sa], aoff[sa], MM::K(sa), MM::K(sa) % CW != 0, rot(StepIntC<sa>{}, MM::ck0(ca)), true);
+                if (c + D - 1 < NCH) load_chunk(v[j], rs[sa], aoff[sa], MM::KP(sa), MM::KP(sa) % CW != 0, rot(StepIntC<sa>{}, MM::ck0(ca)), true);
                 bad = c + 1 < NCH ? incomplete(v[i1]) : false;
                 multiply(StepIntC<sidx>{}, v[i], opb);
             });
@@ -1755,7 +1760,7 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
         hold_off();
         step_static_for<0, D - 1>([&](auto ii) {
             constexpr int i = decltype(ii)::value;
-            load_chunk(v[i], rs[0], aoff[0], MM::K(0), MM::K(0) % CW != 0, i * CW, i * CW < (MM::K(0) + CW - 1) / CW * CW);
+            load_chunk(v[i], rs[0], aoff[0], MM::KP(0), MM::KP(0) % CW != 0, i * CW, i * CW < (MM::K(0) + CW - 1) / CW * CW);
         });
 #pragma unroll
         for (int mt = 0; mt < MM::MT; ++mt)
@@ -1783,8 +1788,8 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
                     const bool on = same ? kj < KP : (sidx + 1 < MM::NSRC && kj < KPN);
                     const __amdgpu_buffer_rsrc_t rn = same ? rs[sidx] : rs[snext];
                     auto ahead = [&]() {
-                        if (same) load_chunk(v[j], rn, aoff[sidx], MM::K(sidx), MM::K(sidx) % CW != 0, kj, on);
-                        else load_chunk(v[j], rn, aoff[snext], MM::K(snext), MM::K(snext) % CW != 0, kj, on);
+                        if (same) load_chunk(v[j], rn, aoff[sidx], MM::KP(sidx), MM::KP(sidx) % CW != 0, kj, on);
+                        else load_chunk(v[j], rn, aoff[snext], MM::KP(snext), MM::KP(snext) % CW != 0, kj, on);
                     };
                     if (k0 < KP) {
                         // the weights of this chunk (tiles the source does not feed read the zero row)
@@ -1863,7 +1868,7 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
                 wave_store<PH, MStore>(r, q, s[PH::stslot(q)], PH::stshared(q) && !twin ? 2 : 0, a);
                 if (twin) {
                     const __amdgpu_buffer_rsrc_t rx = MStore::SW ? __builtin_amdgcn_make_buffer_rsrc(a.store_base, 0, (int)a.store_bytes, STEP_RSRC_FLAGS)
-                                                                 : __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(xbase[q]), 0, a.T * r.sstride[q] * 4, STEP_RSRC_FLAGS);
+                                                                 : __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(xbase[q]), 0, a.T * xstride[q] * 4, STEP_RSRC_FLAGS);
                     __builtin_amdgcn_raw_buffer_store_b32(step_shared_bits(s[PH::stslot(q)]), rx, (int)xvrun[q], 0, STEP_COHERENT_AUX);
                 }
             }
@@ -1882,7 +1887,7 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
         wave_store_advance<PH>(r);
         if constexpr (MM::XB) {
 #pragma unroll
-            for (int q = 0; q < PH::NST; ++q) xvrun[q] += (unsigned)(r.sdelta[q] * 4);
+            for (int q = 0; q < PH::NST; ++q) xvrun[q] += (unsigned)((a.backward ? -xstride[q] : xstride[q]) * 4);
         }
         RNNG_STAMP(5);
         step_lds_barrier();   // the tiles are written again in the next step

@@ -32,6 +32,9 @@ constexpr int STEP_PF_MAX_STEPS = 16;  // steps per block of early-loaded static
 constexpr int STEP_PF_PAIRS_PER_THREAD = 2;
 constexpr int STEP_MAX_GATHERS = 24;   // per program (loads are issued from an unrolled loop)
 
+// A tile-blocked twin (see plan.h) has whole 16 x 16 tiles: streams and units rounded up.
+RNNG_HD inline int twin_pad(int v) { return (v + 15) & ~15; }
+
 RNNG_HD inline int step_pow2_floor(int v) { int p = 1; while (p * 2 <= v) p *= 2; return p; }
 
 struct StepEdge { int w_off, k_len, transposed, src; };    // src = index into StepLayout::src
