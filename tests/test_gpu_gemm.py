@@ -1,0 +1,68 @@
+"""The batched products (forward, backward, weight gradients) at tile and chunk edges, each against
+float64 on the operands that the GPU used, and with operands whose bf16 parts are not finite."""
+import numpy as np
+import pytest
+
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def linear_pair(K, H, O, delay):
+    """x -> a -> o, both layers linear, squared error: nothing but products."""
+    g = wl.GraphSpec()
+    x = g.add_node(wl.INPUT, wl.LINEAR, K, name="x")
+    a = g.add_node(wl.ADD, wl.LINEAR, H, name="a")
+    o = g.add_node(wl.ADD, wl.LINEAR, O, is_output=wl.SQUARED_ERROR, name="o")
+    g.add_edge(x, a, wl.FULL, delay)
+    g.add_edge(a, o, wl.FULL, 0)
+    return g
+
+
+def check_product(got, A, B, what):
+    """got = A B in fp32: n products and additions, each rounded by at most 2^-24 of the sum of
+    magnitudes, and six more roundings for parts summed on their own and across workgroups."""
+    A, B = A.astype(np.float64), B.astype(np.float64)
+    bound = (A.shape[1] + 6) * 2.0 ** -24 * (np.abs(A) @ np.abs(B)) + 1e-37
+    worst = (np.abs(got - A @ B) / bound).max()
+    assert worst <= 1.0, (what, worst)
+
+
+@pytest.mark.parametrize("K,H,O,T,N,delay", [(1, 1, 1, 1, 1, 0), (31, 33, 5, 7, 9, 0), (32, 127, 61, 129, 1, 0), (33, 129, 128, 16, 8, 1),
+                                             (39, 250, 61, 50, 3, 2), (64, 130, 257, 65, 2, 0), (1050, 40, 30, 33, 1, 1), (4100, 96, 40, 40, 2, 0)])
+def test_products_at_tile_and_chunk_edges(K, H, O, T, N, delay):
+    from paper_1503_02852_amd.runner import window_for
+    w = wl.make_workload("pair", linear_pair(K, H, O, delay), T=T, N=N, seed=K + H, scale=0.5)
+    win = window_for(w)
+    win.step()
+    win.check()
+    a, do, da = (v.reshape(T * N, -1) for v in (win.node_output(1), win.node_state_grad(2), win.node_state_grad(1)))
+    x = np.concatenate([np.zeros((delay, N, K), np.float32), w.inputs[0]])[:T].reshape(T * N, K)
+    gw, _ = win.grads_unpacked()
+    check_product(a, x, w.weights[0].T, "x W'")
+    check_product(win.node_output(2).reshape(T * N, -1), a, w.weights[1].T, "a W'")
+    check_product(da, do, w.weights[1], "d W")
+    check_product(gw[1], do.T, a, "d' a")
+    check_product(gw[0], da.T, x, "d' x")
+
+
+def test_infinities_nan_and_the_ends_of_the_range():
+    """An infinity, a NaN or a value that bf16 rounds to infinity reaches the results that fp32
+    arithmetic gives it, and no others; tiny operands keep their products."""
+    from paper_1503_02852_amd.runner import window_for
+    K, H, T = 70, 140, 300
+    w = wl.make_workload("pair", linear_pair(K, H, 9, 0), T=T, N=1, seed=3, scale=0.5)
+    x = w.inputs[0].reshape(T, K)
+    x[3, 5], x[130, 40], x[131, 69], x[200, 0] = np.inf, -np.inf, np.nan, np.finfo(np.float32).max
+    x[201, 1], x[250] = -3.4e38, x[250] * np.float32(1e-36)
+    win = window_for(w)
+    win.forward()
+    a = win.node_output(1).reshape(T, H)
+    with np.errstate(all="ignore"):
+        ref = (x.astype(np.float64) @ w.weights[0].T.astype(np.float64)).astype(np.float32)
+        size = np.abs(x).astype(np.float64) @ np.abs(w.weights[0].T).astype(np.float64)
+    assert np.array_equal(np.isnan(a), np.isnan(ref)) and np.isnan(ref).any()
+    inf = np.isinf(ref)
+    assert inf.any() and np.array_equal(a[inf], ref[inf]) and not np.isinf(a[~inf & ~np.isnan(ref)]).any()
+    ok = np.isfinite(ref)
+    assert (np.abs(a[ok].astype(np.float64) - ref[ok]) <= (K + 6) * 2.0 ** -24 * size[ok] + K * 2.0 ** -126).all()
