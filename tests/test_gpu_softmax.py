@@ -1,0 +1,43 @@
+"""Row softmax and the cross-entropy output delta at the edges of the row widths that their kernels take."""
+import numpy as np
+import pytest
+
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("O", [1, 2, 63, 64, 65, 256, 257, 1023, 1024, 1025, 1027, 4096, 4097, 8191, 20480, 20483, 40960, 40963])
+def test_softmax_and_delta_at_row_width_edges(O):
+    from paper_1503_02852_amd.runner import window_for
+    K, T, N = 3, 5, 3
+    g = wl.GraphSpec()
+    x = g.add_node(wl.INPUT, wl.LINEAR, K, name="x")
+    o = g.add_node(wl.ADD, wl.SOFTMAX, O, is_output=wl.CROSS_ENTROPY, name="o")
+    g.add_edge(x, o, wl.FULL, 0)
+    w = wl.make_workload("softmax", g, T=T, N=N, seed=O, scale=2.0)
+    tg = w.targets[o]
+    tg.reshape(-1)[:4] = 0, O - 1, -1, min(O - 1, 4095)
+    win = window_for(w)
+    win.forward()
+    win.bptt()
+    loss = win.compute_grads(want_loss=True)
+    win.check()
+    X, W = w.inputs[0].reshape(T * N, K).astype(np.float64), w.weights[0].astype(np.float64)
+    s, mag = X @ W.T, (np.abs(X) @ np.abs(W).T).max()
+    d = s - s.max(axis=1, keepdims=True)
+    ref = np.exp(d) / np.exp(d).sum(axis=1, keepdims=True)
+    y = win.node_output(1).reshape(T * N, O)
+    # relative: the product's roundings reach the exponent (K + 6 of mag, own and in the sum), the
+    # exponential multiplies its argument by log2 e (three roundings of |d|), additions of one lane and across
+    # lanes (at most 64 for these widths), a reciprocal and products
+    rel = 2.0 ** -24 * (2 * (K + 6) * mag + 6 * np.abs(d) + 6 * np.abs(d).max() + 80)
+    assert (np.abs(y - ref) <= rel * ref + 1e-37).all(), (np.abs(y - ref) / (rel * ref + 1e-37)).max()
+    tg = tg.reshape(-1)
+    hot = np.zeros((T * N, O), np.float32)
+    hot[tg >= 0, tg[tg >= 0]] = 1.0
+    want = np.where(tg[:, None] >= 0, y - hot, np.float32(0.0))
+    assert (win.node_state_grad(1).reshape(T * N, O) == want).all()
+    l = -np.log(y[tg >= 0, tg[tg >= 0]].astype(np.float64))
+    # the logarithm: |result| times a few roundings, and 2^-21 near 1; a sum of up to four in fp32
+    assert abs(loss - l.sum()) <= 2.0 ** -22 * (4 * np.abs(l).sum() + 2 * len(l))
