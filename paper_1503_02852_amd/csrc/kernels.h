@@ -79,6 +79,12 @@ hipError_t launch_onehot_gather(float* C, const float* W, const int* idx, int n_
                                 int64_t shift_rows, int64_t total_rows, bool accumulate, hipStream_t stream);
 // ordered: the rows are added one after another in increasing order (one writer per element: the
 // sums are the same bits from run to run), else with float atomics from many workgroups.
+// One-hot weight gradient, G stored whole (no zeros needed in it, nothing is added to what it held).
+// Used where the matrix has at least as many columns as the window has rows: its write, which the scatter's zero fill
+// does as well, then takes longer than the pass over the rows that every row segment makes.
+bool onehot_grad_in_rows(int n_dst, int n_src, int64_t rows);
+hipError_t launch_onehot_grad_rows(float* G, const float* ds, const int* idx, int n_dst, int n_src, int64_t shift_rows, int64_t total_rows,
+                                   hipStream_t stream);
 hipError_t launch_onehot_scatter(float* G, const float* ds, const int* idx, int n_dst, int n_src, int64_t shift_rows, int64_t total_rows,
                                  bool ordered, hipStream_t stream);
 

@@ -662,7 +662,9 @@ bool build_plan(const std::vector<GNode>& nodes, const std::vector<GEdge>& edges
     for (int m = 0; m < M; ++m)
         if (xe[m].wkind == W_FULL)
             P.grad_gemms.push_back(GradGemmPlan{full_off(m), xn[xe[m].dst].dim, xn[xe[m].src].dim,
-                                                P.dbuf(xe[m].dst), P.ybuf(xe[m].src), xe[m].delay});
+                                                P.dbuf(xe[m].dst), P.ybuf(xe[m].src), xe[m].delay, true});
+    for (GradGemmPlan& a : P.grad_gemms)
+        for (const GradGemmPlan& b : P.grad_gemms) if (&a != &b && a.w_off == b.w_off) a.sole = false;
     P.colsum_off = (int)P.words.size();
     P.n_colsum = 0;
     auto emit_colsum = [&](int dim, int out_off, const std::vector<FactorH>& fs) {

@@ -30,6 +30,7 @@ struct GemmProblemPlan {
 // Weight gradient of one full edge: G[n_dst][n_src] = sum_t ds_dst(t)^T y_src(t - d).
 struct GradGemmPlan {
     int64_t w_off; int n_dst, n_src, dst_buf, src_buf, delay;
+    bool sole;           // no other connection has the same weights
 };
 
 struct PhasePlan {

@@ -162,3 +162,35 @@ def test_index_input_with_delayed_connections_in_a_carried_window():
         ref = go.bptt_window(spec.nodes, spec.edges, long.weights, long.biases, y_long, z_long, tl, a, T, N)
         check_against(win, first, ref, f"index input, advance {step}")
         assert abs(loss - ref["loss"]) <= 1e-4 * max(1.0, abs(ref["loss"]))
+
+
+@pytest.mark.parametrize("V,D,T,N,delay", [(4096, 3, 7, 3, 0), (4099, 257, 40, 2, 0), (20480, 9, 11, 1, 1), (20481, 52, 30, 3, 0), (41003, 27, 25, 5, 1),
+                                           (4097, 256, 1025, 1, 0), (4096, 5, 4096, 1, 0), (4096, 5, 4097, 1, 0), (4095, 260, 20, 2, 0)])
+def test_wide_index_input_gradients_over_a_buffer_that_held_something_else(V, D, T, N, delay):
+    """The gradient of a wide one-hot layer is stored whole and of large dense blocks too: nothing of
+    what the buffer held stays, between the blocks neither.  Sums of at most T N terms in fp32."""
+    from paper_1503_02852_amd.runner import window_for
+    g = wl.GraphSpec()
+    x = g.add_node(wl.INPUT, wl.LINEAR, V, name="x")
+    a = g.add_node(wl.ADD, wl.LINEAR, D, has_bias=True, name="a")
+    o = g.add_node(wl.ADD, wl.LINEAR, V + 1, has_bias=True, is_output=wl.SQUARED_ERROR, name="o")
+    g.add_edge(x, a, wl.FULL, delay); g.add_edge(a, o, wl.FULL, 0)
+    w = wl.make_workload("wide", g, T=T, N=N, seed=V, scale=0.1)
+    rng = np.random.default_rng(V)
+    idx = rng.integers(0, V, size=(T, N)).astype(np.int32)
+    idx.reshape(-1)[:4] = 0, V - 1, -1, V - 1
+    win = window_for(w)
+    win.set_onehot_inputs({x: idx})
+    win.grads.fill_(float("nan"))
+    win.step()
+    win.check()
+    da, do, act = (v.reshape(T * N, -1) for v in (win.node_state_grad(a), win.node_state_grad(o), win.node_output(a)))
+    cls = np.concatenate([np.full((delay, N), -1, np.int32), idx])[:T].reshape(-1)
+    ref, mag = np.zeros((V, D)), np.zeros((V, D))
+    np.add.at(ref, cls[cls >= 0], da[cls >= 0].astype(np.float64))
+    np.add.at(mag, cls[cls >= 0], np.abs(da[cls >= 0]).astype(np.float64))
+    gw, gb = win.grads_unpacked()
+    assert (np.abs(gw[0] - ref.T) <= T * N * 2.0 ** -24 * mag.T).all()
+    A, B = do.T.astype(np.float64), act.astype(np.float64)
+    assert (np.abs(gw[1] - A @ B) <= (T * N + 6) * 2.0 ** -24 * (np.abs(A) @ np.abs(B)) + 1e-37).all()
+    assert np.isfinite(win.grads.cpu().numpy()).all()
