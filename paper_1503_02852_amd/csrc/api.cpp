@@ -572,14 +572,16 @@ hipError_t ensure_xcd_map(unsigned* scratch, hipStream_t s, const XcdMap** out) 
 
 // The wave-autonomous kernels and the matrix-core kernels with weights in LDS address a stored
 // tensor through one buffer descriptor with 32-bit offsets and park idle lanes 1 GiB beyond:
-// every tensor of the window must stay below 1 GiB.
+// every tensor of the window must stay below 1 GiB, its twin (whose idle lanes walk the upper 2 GiB)
+// below 2 GiB: a width that is no multiple of 4 has a somewhat larger twin.
 bool wave_tensor_sizes_ok(const rnn_graph* g) {
-    int64_t frame = 1;
+    int64_t frame = 1, twin_frame = 0;
     for (int b = 0; b < g->plan.n_bufs; ++b) {
+        if (g->plan.buf_alloc[b] == 3) { if (g->layout.buf_off[b] >= 0) twin_frame = std::max(twin_frame, g->plan.frame_floats(b, g->N)); }
         // the caller's input tensors are never stored by a step kernel
-        if (!g->caller_input(b)) frame = std::max<int64_t>(frame, g->layout.buf_off[b] >= 0 ? g->plan.frame_floats(b, g->N) : (int64_t)g->N * g->plan.buf_dim[b]);
+        else if (!g->caller_input(b)) frame = std::max<int64_t>(frame, (int64_t)g->N * g->plan.buf_dim[b]);
     }
-    return (int64_t)g->Ti() * frame * 4 < (int64_t(1) << 30);
+    return (int64_t)g->Ti() * frame * 4 < (int64_t(1) << 30) && (int64_t)g->Ti() * twin_frame * 4 < (int64_t(1) << 31);
 }
 
 // The wave-autonomous kernels can store through ONE buffer descriptor when everything they store

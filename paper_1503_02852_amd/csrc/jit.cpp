@@ -557,7 +557,7 @@ bool emit_mstep_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, 
     o << "struct MM {\n    static constexpr int NJ = " << N << ", MT = " << MT << ", NSRC = " << ml.n_src << ", NTU = " << NTU
       << ", D = " << D << ", CMAX = " << ml.cmax << ", ACCS = " << ml.accstride << ", NW = " << NW << ", NCH = " << nch << ";\n"
       << "    static constexpr bool FLAT = " << (flat ? "true" : "false") << ", XB = " << (blocked ? "true" : "false")
-      << ", HELPER = " << (cp.helper ? "true" : "false") << ";\n"
+      << ", TAIL = " << (N_all % 16 != 0 ? "true" : "false") << ", HELPER = " << (cp.helper ? "true" : "false") << ";\n"
       ;
     std::vector<std::pair<int, int>> ks, kps, blk, used, ngr, csrc, ck0;
     // The unrolled chunk sequence takes the sources in the order in which their values arrive: what

@@ -106,9 +106,9 @@ hipError_t launch_recurrent_steps(const PlanView& pv, const StepLaunchPlan& lp, 
 hipError_t launch_fill_sentinel(float* p, int64_t n, hipStream_t stream);
 // The same for up to FILL_MAX_RANGES ranges with one launch (a step launch's exchanged tensors).
 constexpr int FILL_MAX_RANGES = 16;
-// A range of frames of a tile-blocked twin whose tiles are not full names its tensor's stream count
-// and width (twin_n, twin_dim; 0: an ordinary range): the padding becomes zero, so that its pollers
-// neither wait for it nor add anything.
+// A range of frames of a tile-blocked twin whose width is no multiple of 4 names its tensor's stream
+// count and width (twin_n, twin_dim; 0: an ordinary range): the padding becomes zero, so that its
+// pollers neither wait for it nor add anything.
 struct FillRanges { float* p[FILL_MAX_RANGES]; long long n[FILL_MAX_RANGES]; int twin_n[FILL_MAX_RANGES], twin_dim[FILL_MAX_RANGES], count; };
 hipError_t launch_fill_sentinel_ranges(const FillRanges& r, hipStream_t stream);
 

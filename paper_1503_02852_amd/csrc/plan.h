@@ -108,10 +108,11 @@ struct Plan {
     // consecutive addresses (measured: 77 GB/s per workgroup against 35 GB/s for 16 rows of 64
     // bytes).  Every tensor b that workgroups of a single-phase recurrent component exchange
     // therefore has a twin with the id twin_base + b:
-    // [frame][stream / 16][unit / 16][(unit % 16) / 4][stream % 16][unit % 4], whole tiles whatever
-    // the stream count and the width (the padding holds zeros), allocated for windows whose stream
-    // count the matrix-core kernels serve.  The producing kernel stores each value twice (row-major
-    // for everyone else, blocked for the pollers).
+    // [frame][stream / 16][unit / 4][stream % 16][unit % 4], with only the streams there are in the
+    // last block and the units rounded up to 4 (the padding holds zeros): with 16 streams a block
+    // (padding streams too, a window of 2 streams needed eight times the tensor) workspaces grew up
+    // to five times.  Allocated for windows whose stream count the matrix-core kernels serve.  The
+    // producing kernel stores each value twice (row-major for everyone else, blocked for the pollers).
     int twin_base = -1;
     std::vector<CompPlan> comps;
     std::vector<ChainPlan> chains;
@@ -136,7 +137,7 @@ struct Plan {
 
     // floats per frame of buffer b in a window of N streams
     int64_t frame_floats(int b, int N) const {
-        return buf_alloc[b] == 3 ? (int64_t)twin_pad(N) * twin_pad(buf_dim[b]) : (int64_t)N * buf_dim[b];
+        return buf_alloc[b] == 3 ? (int64_t)N * twin_pad(buf_dim[b]) : (int64_t)N * buf_dim[b];
     }
     int ybuf(int k) const { return k; }
     int dbuf(int k) const { return (int)xnodes.size() + k; }

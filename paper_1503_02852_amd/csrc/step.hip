@@ -102,12 +102,12 @@ __global__ __launch_bounds__(256) void fill_ranges_kernel(const FillRanges r, un
     unsigned* __restrict__ p = reinterpret_cast<unsigned*>(r.p[blockIdx.y]);
     const long long n = r.n[blockIdx.y];
     const int dim = r.twin_dim[blockIdx.y];
-    if (dim > 0) {      // [frame][stream / 16][unit / 16][(unit % 16) / 4][stream % 16][unit % 4]
-        const int N = r.twin_n[blockIdx.y], nt = (N + 15) >> 4, kt = (dim + 15) >> 4;
+    if (dim > 0) {      // the inverse of twin_offset, in a tensor below 2 GiB
+        const unsigned N = r.twin_n[blockIdx.y], width = twin_pad(dim);
         for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < (unsigned)n; i += 256 * gridDim.x) {
-            const unsigned tile = i >> 8;
-            const int k = (int)(tile % kt) * 16 + (int)((i >> 6) & 3) * 4 + (int)(i & 3), s = (int)(tile / kt % nt) * 16 + (int)((i >> 2) & 15);
-            p[i] = s < N && k < dim ? v : 0u;
+            const unsigned at = i % (N * width), first = at / (16 * width) * 16, rows = N - first < 16 ? N - first : 16;
+            const unsigned unit = (at - first * width) / (4 * rows) * 4 + (i & 3);
+            p[i] = unit < (unsigned)dim ? v : 0u;
         }
         return;
     }

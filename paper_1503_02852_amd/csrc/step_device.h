@@ -1322,9 +1322,9 @@ __device__ __forceinline__ void wave_step(PhaseRegs<PH>& r, const WaveRegs<MV>& 
 // 43 / 79 / 94 GB/s with 4 / 8 / 16) are in flight in D register sets, and a chunk that comes back
 // with a sentinel is loaded again by the wavefront that needs it.  With MM::XB the sources are
 // the tile-blocked twins of the exchanged tensors (a wavefront's load is 1 KiB of consecutive
-// addresses: 77 instead of 35 GB/s per workgroup), which are padded with zeros to whole tiles, so
-// that any stream count and any width takes this path (without twins a row of a source must be a
-// multiple of 16 bytes).  One accumulator set serves all sources; the
+// addresses: 77 instead of 35 GB/s per workgroup), whose units are padded with zeros to whole quads
+// and whose last block has only the streams there are, so that any stream count and any width takes
+// this path (without twins a row of a source must be a multiple of 16 bytes).  One accumulator set serves all sources; the
 // NW partial tiles meet in LDS, where the element-wise program runs with one thread per
 // (stream, unit) on the first STEP_THREADS threads.
 //
@@ -1333,9 +1333,9 @@ __device__ __forceinline__ void wave_step(PhaseRegs<PH>& r, const WaveRegs<MV>& 
 //   tiles), D (register sets of chunks), CMAX, ACCS (row stride of an accumulator tile), NW
 //   (wavefronts), NCH (chunks of all sources), CLATE (first chunk that holds the previous step's
 //   own values), NRW (weight quads in registers); bool FLAT (the chunk sequence is unrolled whole),
-//   XB, HELPER (a chain's helper member: its program only stores the sums of its products, which
+//   XB, TAIL (the window's last 16-stream block is not full), HELPER (a chain's helper member: its program only stores the sums of its products, which
 //   another member's program polls element by element); unsigned REGMASK; constexpr K(s) (columns of
-//   source s), KP(s) (the same, padded to whole tiles with XB), ngr(s) (groups of D chunks of source s), blk(s, task)
+//   source s), KP(s) (the same, padded to whole quads with XB), ngr(s) (groups of D chunks of source s), blk(s, task)
 //   (row block of the task in source s, -1: none), used(s, nt), csrc(c) / ck0(c) (source and first
 //   column of chunk c), widx(c * 16 + nt) (register index of a weight quad).
 // =============================================================================================
@@ -1412,8 +1412,6 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
     const int T = a.T;
     const int n0 = wj * MM::NJ;                                            // first stream of this workgroup
     const int N = a.N - n0 < MM::NJ ? a.N - n0 : MM::NJ;                   // its streams
-    // rows of a polled frame, and those of this workgroup's streams (a twin's padded to whole tiles)
-    const int NF = MM::XB ? twin_pad(a.N) : a.N, NR = MM::XB ? twin_pad(N) : N;
     MShared& sh = ms;
     constexpr int NW = MM::NW, NTHR = 64 * NW, CW = 16 * NW;      // wavefronts, threads, columns of a chunk
     if (tid == 0) { compute_step_layout(a.words, a.desc_off, a.G, 1, MM::NJ, sh.lay); compute_mstep_layout(sh.lay, MM::NJ, NW, MM::REGMASK, (int)(MSTEP_LDS_LIMIT / 4), ms.ml); }
@@ -1534,8 +1532,9 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
     // its byte offset in chunk 0 of each source (a stream beyond N: outside the descriptor)
     // With tile-blocked exchange (MM::XB) the source is the tensor's twin, whose 16 x 16 tiles
     // [(unit % 16) / 4][stream % 16][unit % 4] are 1 KiB of consecutive addresses each: the
-    // wavefront's load of a tile is lane l -> bytes 16 l, and the tiles of a stream tile's
-    // column blocks follow each other.
+    // wavefront's load of a tile is lane l -> bytes 16 l, and the tiles of a stream block's
+    // columns follow each other.  In a block of fewer than 16 streams (MM::TAIL) the quads are as
+    // much closer together, and the lanes of the missing streams load nothing.
     const int wcol = wave * 16 + 4 * (lane >> 4);
     int aoff[MM::NSRC][MM::MT];
 #pragma unroll
@@ -1543,7 +1542,7 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
 #pragma unroll
         for (int mt = 0; mt < MM::MT; ++mt) {
             const int n = mt * 16 + (lane & 15);
-            if (MM::XB) aoff[sidx][mt] = ((mt * (MM::KP(sidx) / 16) + wave) * 256 + lane * 4) * 4;
+            if (MM::XB) aoff[sidx][mt] = !MM::TAIL || n < N ? twin_offset(MM::TAIL ? N : MM::NJ, MM::KP(sidx), n, wcol) * 4 : 0x7FFFFFF0;
             else aoff[sidx][mt] = n < N ? (n * MM::K(sidx) + wcol) * 4 : 0x7FFFFFF0;
         }
 
@@ -1568,15 +1567,15 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
         cwords_t st = pw + PG_HEADER_WORDS + PH::NG * GA_WORDS + PH::NI * IV_WORDS + pw[PG_NOPS] * MO_WORDS;
 #pragma unroll
         for (int q = 0; q < PH::NST; ++q) {
-            xbase[q] = nullptr; xvrun[q] = WAVE_NO_STORE; xstride[q] = 0;
+            // (a lane without an element walks the 2 GiB that no twin reaches)
+            xbase[q] = nullptr; xvrun[q] = a.backward ? 0xFFFFFFF0u : 0x80000000u; xstride[q] = 0;
             if (!PH::stshared(q) || !PH::sttwin(q)) continue;
             const int dim = suni(st[q * ST_WORDS + ST_DIM]);
-            xstride[q] = suni(twin_pad(a.N) * twin_pad(dim));
+            xstride[q] = suni(a.N * twin_pad(dim));
             xbase[q] = suni_ptr(((cbufs_t)a.buf_ptr)[a.twin_base + suni(st[q * ST_WORDS + ST_BUF])]);
             if (r.sptr[q] != nullptr) {
                 const int i = (int)(r.sptr[q] - r.sbase[q]) - r.n * dim;      // this thread's unit
-                const int off = ((r.n >> 4) * (twin_pad(dim) >> 4) + (i >> 4)) * 256 + ((((i & 15) >> 2) << 4) + (r.n & 15)) * 4 + (i & 3);
-                xvrun[q] = (unsigned)((off + step_frame(a, 0) * xstride[q]) * 4);
+                xvrun[q] = (unsigned)((twin_offset(a.N, dim, r.n, i) + step_frame(a, 0) * xstride[q]) * 4);
                 if (MStore::SW) xvrun[q] += (unsigned)((xbase[q] - a.store_base) * 4);
             }
         }
@@ -1623,9 +1622,9 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
             const StepSource& sc = sh.lay.src[sidx];
             const int frame = t + suni(sc.frame_off);
             const bool in_window = frame >= 0 && frame < T;
-            // (a twin's 16-stream tiles are as large as 16 padded rows)
-            const float* g = ((cbufs_t)a.buf_ptr)[(MM::XB ? a.twin_base : 0) + suni(sc.buf)] + ((size_t)(in_window ? frame : 0) * NF + n0) * MM::KP(sidx);
-            rs[sidx] = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g), 0, in_window ? NR * MM::KP(sidx) * 4 : 0, STEP_RSRC_FLAGS);
+            // (a twin's 16-stream blocks are as large as 16 padded rows)
+            const float* g = ((cbufs_t)a.buf_ptr)[(MM::XB ? a.twin_base : 0) + suni(sc.buf)] + ((size_t)(in_window ? frame : 0) * a.N + n0) * MM::KP(sidx);
+            rs[sidx] = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g), 0, in_window ? N * MM::KP(sidx) * 4 : 0, STEP_RSRC_FLAGS);
         }
         // A helper member has no values of its own to wait for and would otherwise poll each frame
         // of its sources while the producing member's stores are still under way, which slows that
@@ -1637,7 +1636,7 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
                 const StepSource& sc = sh.lay.src[0];
                 const int frame = step_frame(a, step + 1) + suni(sc.frame_off);
                 if (frame >= 0 && frame < T) {
-                    const float* p = ((cbufs_t)a.buf_ptr)[(MM::XB ? a.twin_base : 0) + suni(sc.buf)] + ((size_t)frame * NF + n0) * MM::KP(0);
+                    const float* p = ((cbufs_t)a.buf_ptr)[(MM::XB ? a.twin_base : 0) + suni(sc.buf)] + ((size_t)frame * a.N + n0) * MM::KP(0);
                     int spins = 0;
                     while (__float_as_uint(load_coherent(p)) == STEP_SENTINEL && !dead) {
                         if (++spins > a.spin_limit) { dead = true; if (lane == 0) atomicExch(a.ctrl, 1u); break; }
@@ -1663,8 +1662,10 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
         auto load_chunk = [&](muintx4 (&dst)[MM::MT], const __amdgpu_buffer_rsrc_t& rsrc, const int (&base)[MM::MT], int K, bool k_ragged, int k0, bool on) {
 #pragma unroll
             for (int mt = 0; mt < MM::MT; ++mt) {
-                int off = base[mt] + (MM::XB ? k0 * 64 : k0 * 4);      // (blocked: k0 / 16 tiles of 1 KiB further)
-                if (k_ragged) off = k0 + (MM::XB ? wave * 16 : wcol) < K ? off : 0x7FFFFFF0;
+                // (blocked: k0 / 4 quads of each stream of the block further)
+                const int rows = !MM::TAIL || N - mt * 16 > 16 ? 16 : N - mt * 16;
+                int off = base[mt] + (MM::XB ? k0 * 4 * rows : k0 * 4);
+                if (k_ragged) off = k0 + (MM::XB && K % 16 == 0 ? wave * 16 : wcol) < K ? off : 0x7FFFFFF0;
                 off = on ? off : 0x7FFFFFF0;
                 dst[mt] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, STEP_COHERENT_AUX);
             }

@@ -32,8 +32,15 @@ constexpr int STEP_PF_MAX_STEPS = 16;  // steps per block of early-loaded static
 constexpr int STEP_PF_PAIRS_PER_THREAD = 2;
 constexpr int STEP_MAX_GATHERS = 24;   // per program (loads are issued from an unrolled loop)
 
-// A tile-blocked twin (see plan.h) has whole 16 x 16 tiles: streams and units rounded up.
-RNNG_HD inline int twin_pad(int v) { return (v + 15) & ~15; }
+// A tile-blocked twin (see plan.h) holds its units in quads: twin_pad(dim) per stream.  A frame of N streams
+// is one block of 16 streams after the other, the last one with the rows that are left, so padding a
+// row costs at most three units and padding the streams nothing.
+RNNG_HD inline int twin_pad(int v) { return (v + 3) & ~3; }
+// Floats from a frame's start to (stream n, unit i).
+RNNG_HD inline int twin_offset(int N, int dim, int n, int i) {
+    const int first = n & ~15, rows = N - first < 16 ? N - first : 16;
+    return first * twin_pad(dim) + (i >> 2) * 4 * rows + (n - first) * 4 + (i & 3);
+}
 
 RNNG_HD inline int step_pow2_floor(int v) { int p = 1; while (p * 2 <= v) p *= 2; return p; }
 

@@ -225,3 +225,22 @@ def test_headers_are_plain_c(tmp_path):
     src = tmp_path / "t.c"
     src.write_text('#include "rnngraph.h"\n#include "rnngraph_aux.h"\nint main(void) { return rnn_last_error() == 0; }\n')
     subprocess.run([gcc, "-std=c99", "-Wall", "-Werror", "-fsyntax-only", "-I", os.path.join(ROOT, "include"), str(src)], check=True)
+
+
+@pytest.mark.parametrize("layers,N", [([1024], 2), ([512], 4), ([256, 256], 8), ([512], 17), ([1020], 3)])
+def test_exchange_copies_are_no_larger_than_their_tensors(monkeypatch, layers, N):
+    """Few streams and ragged stream counts: the exchanged tensors' tile-blocked copies hold the
+    streams there are, so they take at most what their tensors take (with 16-stream tiles whatever
+    the count, a window of 2 streams took up to five times the workspace)."""
+    import workloads as wl
+    from paper_1503_02852_amd import binding
+    spec = wl.elman_net(40, layers[0], 61) if len(layers) == 1 and N < 9 else wl.lstm_net(40, layers, 61)
+    T = 1024
+
+    def workspace(blocked):
+        monkeypatch.setenv("RNNG_MSTEP_BLOCKED", blocked)
+        return binding.Graph(spec.node_array(), spec.edge_array()).workspace_bytes(T, N)
+
+    # activations and state gradients, each with a history frame and the space between two tensors
+    tensors = sum(2 * (4 * (T + 1) * N * n["dim"] + (1 << 16)) for n in spec.nodes if n["kind"] != wl.INPUT and not n["is_output"])
+    assert workspace("0") < workspace("1") <= workspace("0") + tensors

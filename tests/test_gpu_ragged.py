@@ -1,5 +1,7 @@
 """GPU parity of the matrix-core step kernels where neither the streams nor the units fill whole
-16 x 16 tiles: the tile-blocked exchange tensors are padded, and stream groups may be unequal."""
+16 x 16 tiles: units are padded to quads, the last block of streams is short, and stream groups may
+be unequal."""
+import numpy as np
 import pytest
 
 import workloads as wl
@@ -19,9 +21,44 @@ def test_ragged_widths_and_streams_run_on_the_matrix_cores(layers, N):
     assert rec and all(win.g.step_build(k, b)[0] == "matrix" for k in rec for b in (False, True))
 
 
-@pytest.mark.parametrize("layers,N", [([29, 21], 21), ([18], 9)])
+@pytest.mark.parametrize("units,N", [(512, 3), (513, 2), (1021, 2), (1021, 5), (250, 8)])
+def test_few_streams_run_on_the_matrix_cores_where_the_register_build_needs_several_xcds(units, N):
+    spec = wl.lstm_net(13, [units], 5)
+    win, _ = run_both(wl.make_workload("few", spec, T=7, N=N, seed=72, scale=0.4 / units ** 0.5, bias_scale=0.2, masked_fraction=0.2),
+                      label=f"{units} units, N={N}")
+    rec = [k for k in range(len(spec.nodes)) if win.g.step_build(k)[0] != "none"]
+    assert rec and all(win.g.step_build(k, b)[0] == "matrix" for k in rec for b in (False, True))
+
+
+@pytest.mark.parametrize("N,T", [(2, 16400), (17, 8200)])
+def test_long_windows_keep_their_step_kernel(N, T):
+    """Tensors far below the 1 GiB that a step kernel addresses, with copies that 16-stream tiles
+    whatever the stream count would have taken beyond it."""
+    from paper_1503_02852_amd.runner import Window
+    spec = wl.elman_net(8, 1024, 4)
+    (x,), (o,) = spec.input_nodes(), spec.output_nodes()
+    rng = np.random.default_rng(5)
+    out = {}
+    for frames in (T, 64):
+        win = Window(spec.node_array(), spec.edge_array(), frames, N)
+        if frames == T:
+            weights = win.weights.clone().uniform_(-0.03, 0.03)
+            inputs = rng.standard_normal((T, N, 8)).astype(np.float32)
+        win.weights.copy_(weights)
+        win.inputs[x] = win.weights.new_tensor(inputs[:frames])
+        win.forward()
+        win.check()
+        assert win.g.step_build(1)[0] == "matrix"
+        out[frames] = win.node_output(o)
+    assert np.isfinite(out[T]).all() and np.allclose(out[T][:64], out[64], rtol=1e-5, atol=1e-6)
+
+
+@pytest.mark.parametrize("layers,N", [([29, 21], 21), ([18], 9), ([513], 2), ([300], 7)])
 def test_ragged_windows_in_pieces_and_moved_ahead(monkeypatch, layers, N):
     """History frames of the padded exchange tensors, in both window forms."""
     monkeypatch.setitem(tw.WINDOW_NETS, "ragged", lambda: (wl.lstm_net(8, layers, 4), N))
+    if max(layers) > 100:      # (weights of 0.4 make a wide layer chaotic: 1e-7 in the inputs grows to 3e-5 in 24 frames of 513 units, at 0.07 it stays)
+        make = wl.make_workload
+        monkeypatch.setattr(wl, "make_workload", lambda *a, **k: make(*a, **{**k, "scale": 1.5 / max(layers) ** 0.5}))
     tw.test_window_computed_in_pieces_equals_the_window_at_once("ragged")
     tw.test_window_moved_ahead_with_carried_state("ragged")
