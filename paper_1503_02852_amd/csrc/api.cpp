@@ -41,6 +41,7 @@ struct Layout {
     int64_t wt_off = -1;                  // transposed copies of the matrices the streaming kernels read transposed (parameter layout)
     int64_t flags_off = 0;                // per buffer id: floats per frame of a frame tensor of the workspace (has history frames), else 0
     int64_t total = 0;
+    int64_t ragged_twin_bytes = 0;        // of total: twins that only windows of no whole 16 x 16 tiles need padding for
 };
 constexpr int64_t SYNC_BYTES = 1024;
 
@@ -84,7 +85,11 @@ Layout make_layout(const Plan& P, int T, int N, int64_t partial_floats, bool tra
     // tile-blocked twins, behind everything else
     if (twins)
         for (int b = 0; b < P.n_bufs; ++b)
-            if (P.buf_alloc[b] == 3) place(b);
+            if (P.buf_alloc[b] == 3) {
+                const int64_t at = cur;
+                place(b);
+                if (N % 16 != 0 || P.buf_dim[b] % 16 != 0) L.ragged_twin_bytes += cur - at;
+            }
     L.total = cur;
     return L;
 }
@@ -1087,7 +1092,10 @@ namespace {
 // Part of the library image: every GPU the library runs on holds its own copy of this array, at
 // its own address, until the process ends.  In host code the name is only a handle for
 // hipGetSymbolAddress; all device work goes through the address that call returns.
-static __device__ __align__(256) unsigned char scratch[RNN_STATIC_WORKSPACE_BYTES];
+// A window may need RNN_STATIC_WORKSPACE_BYTES beside the twins of ragged tiles, which come on top:
+// at most four times as many floats as their tensors (width 1), and the space between tensors.
+constexpr int64_t STATIC_ARRAY_BYTES = 5 * (int64_t)RNN_STATIC_WORKSPACE_BYTES + (1 << 20);
+static __device__ __align__(256) unsigned char scratch[STATIC_ARRAY_BYTES];
 constexpr int STATIC_MAX_DEVICES = 64;
 void* g_scratch_ptr[STATIC_MAX_DEVICES];      // per device: address of that GPU's copy (nullptr: not asked yet)
 std::mutex g_scratch_mutex;
@@ -1102,7 +1110,7 @@ int rnn_forward_static(rnn_graph* g, const float* d_weights, const float* const*
         if (!d_outputs[i]) return fail(RNN_ERR_INVALID_ARGUMENT, "an output tensor pointer is NULL");
     if (T <= 0 || N <= 0) return fail(RNN_ERR_INVALID_ARGUMENT, "T and N must be positive");
     if (g->prof.mask != 0) return fail(RNN_ERR_SEQUENCE, "kernel-class timing creates events: switch it off for rnn_forward_static");
-    const int64_t need = g->layout_for(T, N).total;
+    const int64_t need = g->layout_for(T, N).total - g->layout_for(T, N).ragged_twin_bytes;
     if (need > (int64_t)RNN_STATIC_WORKSPACE_BYTES)
         return fail(RNN_ERR_WORKSPACE, "the window needs " + std::to_string(need) + " bytes of workspace, the static workspace holds " +
                                            std::to_string((int64_t)RNN_STATIC_WORKSPACE_BYTES));
@@ -1123,7 +1131,7 @@ int rnn_forward_static(rnn_graph* g, const float* d_weights, const float* const*
         ws = g_scratch_ptr[dev];
     }
     g->no_alloc = true;
-    const int rc = rnn_forward_range(g, d_weights, d_inputs, T, N, 0, T, ws, RNN_STATIC_WORKSPACE_BYTES, hip_stream);
+    const int rc = rnn_forward_range(g, d_weights, d_inputs, T, N, 0, T, ws, STATIC_ARRAY_BYTES, hip_stream);
     g->no_alloc = false;
     if (rc != RNN_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);

@@ -60,6 +60,18 @@ def test_static_workspace_forward_equals_forward_two_calls_in_a_row(spec_fn):
                 assert nerr(gw[m], g) < 1e-3
 
 
+@pytest.mark.parametrize("spec_fn,T,N", [(lambda: wl.lstm_net(40, [512], 61), 40, 17), (lambda: wl.elman_net(40, 1024, 61), 900, 2),
+                                         (lambda: wl.elman_net(3, 1, 2), 60000, 9)])
+def test_static_workspace_does_not_count_the_copies_of_ragged_tiles(spec_fn, T, N):
+    """Windows that fit RNN_STATIC_WORKSPACE_BYTES but for the second copies of their exchanged tensors."""
+    spec = spec_fn()
+    w = wl.make_workload("static_ragged", spec, T=T, N=N, seed=75, scale=0.05)
+    win, ref, got = outputs_both_ways(w)
+    assert win.g.workspace_bytes(T, N) > 32 << 20
+    for k in spec.output_nodes():
+        assert np.array_equal(got[k], ref[k])
+
+
 def test_static_workspace_limits_and_preconditions():
     import torch
     from paper_1503_02852_amd.binding import RnnError
