@@ -49,8 +49,8 @@ int64_t g_layout_skew = 4352;      // bytes, a multiple of 256 (RNNG_LAYOUT_SKEW
 
 // partial_floats: floats per frame of the largest partial-sum tensor any launch of the window needs
 // transposed_copy: a streaming kernel of the window reads matrices transposed
-// twins: the window's stream count is one that the matrix-core kernels serve
-Layout make_layout(const Plan& P, int T, int N, int64_t partial_floats, bool transposed_copy, bool twins) {
+// twins: per buffer id, whether a step launch of the window polls this twin
+Layout make_layout(const Plan& P, int T, int N, int64_t partial_floats, bool transposed_copy, const std::vector<char>& twins) {
     Layout L;
     int n_alloc = 0;
     const int K = (int)P.xnodes.size();
@@ -83,13 +83,12 @@ Layout make_layout(const Plan& P, int T, int N, int64_t partial_floats, bool tra
     for (size_t k = 0; k < P.xnodes.size(); ++k)
         if (P.xnodes[k].kind == NODE_INPUT && P.input_delayed[k]) { L.idx_off[k] = cur; cur = align_up(cur + F * 4, 256); }
     // tile-blocked twins, behind everything else
-    if (twins)
-        for (int b = 0; b < P.n_bufs; ++b)
-            if (P.buf_alloc[b] == 3) {
-                const int64_t at = cur;
-                place(b);
-                if (N % 16 != 0 || P.buf_dim[b] % 16 != 0) L.ragged_twin_bytes += cur - at;
-            }
+    for (int b = 0; b < P.n_bufs; ++b)
+        if (twins[b]) {
+            const int64_t at = cur;
+            place(b);
+            if (N % 16 != 0 || P.buf_dim[b] % 16 != 0) L.ragged_twin_bytes += cur - at;
+        }
     L.total = cur;
     return L;
 }
@@ -323,26 +322,34 @@ struct rnn_graph {
         }
         return false;
     }
-    // true if a step launch of a window with N streams may exchange through tile-blocked twins
-    bool twins_needed(int N) {
-        if (!use_jit) return false;
+    // the tile-blocked twins that step launches of a window with N streams exchange through.  (A member
+    // of a chain runs on its own only in windows that no blocked kernel but the streaming one takes.)
+    std::vector<char> polled_twins(int N) {
+        std::vector<char> polled(plan.n_bufs, 0);
+        if (!use_jit) return polled;
+        auto add = [&](const CompPlan& cp, bool backward) {
+            for (int b : backward ? cp.bwd_shared_bufs : cp.fwd_shared_bufs)
+                if (plan.buf_alloc[plan.twin_base + b] == 3) polled[plan.twin_base + b] = 1;
+        };
         for (size_t c = 0; c < plan.comps.size(); ++c) {
             const CompPlan& cp = plan.comps[c];
             if (!cp.recurrent) continue;
             for (int backward = 0; backward < 2; ++backward) {
                 if (backward ? !cp.has_bwd_program : !cp.has_fwd_program) continue;
-                if (cp.chain >= 0 && chain_choice(cp.chain, backward != 0, N).blocked) return true;
-                if (jit_choice((int)c, backward != 0, N).blocked) return true;
+                const ChainChoice* cc = cp.chain >= 0 ? &chain_choice(cp.chain, backward != 0, N) : nullptr;
+                if (cc && cc->blocked) for (const CompPlan& m : chain_members(plan.chains[cp.chain], *cc)) add(m, backward != 0);
+                const JitChoice& jc = jit_choice((int)c, backward != 0, N);
+                if (jc.blocked && (!cc || cc->source.empty() || jc.stream)) add(cp, backward != 0);
             }
         }
-        return false;
+        return polled;
     }
     // the workspace layout of a window of T frames and N streams (kept for the last shape asked for)
     Layout cached_layout;
     int cached_T = 0, cached_N = 0;
     const Layout& layout_for(int T, int N) {
         if (cached_T != T || cached_N != N) {
-            cached_layout = make_layout(plan, T, N, partial_frame_floats(N), transposed_copy(N), twins_needed(N));
+            cached_layout = make_layout(plan, T, N, partial_frame_floats(N), transposed_copy(N), polled_twins(N));
             cached_T = T; cached_N = N;
         }
         return cached_layout;

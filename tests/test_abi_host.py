@@ -244,3 +244,20 @@ def test_exchange_copies_are_no_larger_than_their_tensors(monkeypatch, layers, N
     # activations and state gradients, each with a history frame and the space between two tensors
     tensors = sum(2 * (4 * (T + 1) * N * n["dim"] + (1 << 16)) for n in spec.nodes if n["kind"] != wl.INPUT and not n["is_output"])
     assert workspace("0") < workspace("1") <= workspace("0") + tensors
+
+
+def test_only_polled_exchange_copies_take_space(monkeypatch):
+    """Two layers on 2 streams, each with a step kernel of its own: the 1,024-wide one runs on the
+    matrix cores, which exchange through tile-blocked copies (h forward, four gates' state gradients
+    backward), the 128-wide one in the register build, which has none."""
+    import workloads as wl
+    from paper_1503_02852_amd import binding
+    monkeypatch.setenv("RNNG_CHAIN", "0")
+    spec, T, N = wl.lstm_net(40, [1024, 128], 61), 1024, 2
+
+    def workspace(blocked):
+        monkeypatch.setenv("RNNG_MSTEP_BLOCKED", blocked)
+        return binding.Graph(spec.node_array(), spec.edge_array()).workspace_bytes(T, N)
+
+    copies, skew = 5 * 4 * (T + 1) * N * 1024, 5 * (1 << 16)
+    assert copies <= workspace("1") - workspace("0") <= copies + skew
