@@ -39,7 +39,7 @@ struct Layout {
     int64_t partial_off = -1;             // partial sums of the two-dimensional matrix-core kernels (one launch at a time)
     std::vector<int64_t> idx_off;         // per exec node id: int32 [(hist + T)][N] copy of a one-hot input's class indices, or -1
     int64_t wt_off = -1;                  // transposed copies of the matrices the streaming kernels read transposed (parameter layout)
-    int64_t flags_off = 0;                // per buffer id: floats per frame of a frame tensor of the workspace (has history frames), else 0
+    int64_t frames_off = 0;               // per buffer id: int64 floats per frame of a frame tensor of the workspace (has history frames), else 0
     int64_t total = 0;
     int64_t ragged_twin_bytes = 0;        // of total: twins that only windows of no whole 16 x 16 tiles need padding for
 };
@@ -56,8 +56,8 @@ Layout make_layout(const Plan& P, int T, int N, int64_t partial_floats, bool tra
     const int K = (int)P.xnodes.size();
     int64_t cur = 0;
     L.table_off = cur; cur += (int64_t)P.n_bufs * 8;
+    L.frames_off = cur; cur += (int64_t)P.n_bufs * 8;
     L.dims_off = cur; cur += (int64_t)P.n_bufs * 4;
-    L.flags_off = cur; cur += (int64_t)P.n_bufs * 4;
     cur = align_up(cur, 16);
     L.words_off = cur; cur += (int64_t)P.words.size() * 4;
     L.blob_bytes = cur;
@@ -1028,8 +1028,8 @@ int rnn_forward_range(rnn_graph* g, const float* d_weights, const float* const* 
     }
     std::memcpy(&g->blob[L.dims_off], P.buf_dim.data(), (size_t)P.n_bufs * 4);
     for (int b = 0; b < P.n_bufs; ++b) {
-        const int32_t flag = ((P.buf_alloc[b] == 1 || P.buf_alloc[b] == 3) && L.buf_off[b] >= 0) ? (int32_t)P.frame_floats(b, N) : 0;
-        std::memcpy(&g->blob[L.flags_off + 4 * (int64_t)b], &flag, 4);
+        const int64_t frame = ((P.buf_alloc[b] == 1 || P.buf_alloc[b] == 3) && L.buf_off[b] >= 0) ? P.frame_floats(b, N) : 0;
+        std::memcpy(&g->blob[L.frames_off + 8 * (int64_t)b], &frame, 8);
     }
     if (!P.words.empty()) std::memcpy(&g->blob[L.words_off], P.words.data(), P.words.size() * 4);
     // (without allocations: as kernel arguments, which need no staging buffer of the runtime's)
@@ -1048,7 +1048,7 @@ int rnn_forward_range(rnn_graph* g, const float* d_weights, const float* const* 
         e = launch_fill(reinterpret_cast<float*>(g->ws + L.sync_off), SYNC_BYTES / 4, 0.0f, s);
         if (e != hipSuccess) return fail_hip(e, "control word reset");
         if (H > 0) {
-            e = launch_zero_history(g->view().buf_ptr, reinterpret_cast<const int32_t*>(g->ws + L.flags_off), P.n_bufs, H, s);
+            e = launch_zero_history(g->view().buf_ptr, reinterpret_cast<const int64_t*>(g->ws + L.frames_off), P.n_bufs, H, s);
             if (e != hipSuccess) return fail_hip(e, "history reset");
         }
     }

@@ -415,7 +415,7 @@ hipError_t launch_upload_words(uint32_t* d_dst, const uint32_t* h_src, int64_t n
 
 namespace {
 // blockIdx.x: the buffer.
-__global__ __launch_bounds__(256) void zero_history_kernel(float* const* __restrict__ buf_ptr, const int32_t* __restrict__ frame_floats, int frames) {
+__global__ __launch_bounds__(256) void zero_history_kernel(float* const* __restrict__ buf_ptr, const int64_t* __restrict__ frame_floats, int frames) {
     const int b = blockIdx.x;
     const long long n = (long long)frames * frame_floats[b];
     if (n <= 0) return;
@@ -424,7 +424,7 @@ __global__ __launch_bounds__(256) void zero_history_kernel(float* const* __restr
 }
 }  // namespace
 
-hipError_t launch_zero_history(float* const* buf_ptr, const int32_t* frame_floats, int n_bufs, int frames, hipStream_t stream) {
+hipError_t launch_zero_history(float* const* buf_ptr, const int64_t* frame_floats, int n_bufs, int frames, hipStream_t stream) {
     if (n_bufs <= 0 || frames <= 0) return hipSuccess;
     hipLaunchKernelGGL(zero_history_kernel, dim3((unsigned)n_bufs, 4), dim3(256), 0, stream, buf_ptr, frame_floats, frames);
     return hipGetLastError();

@@ -63,7 +63,7 @@ hipError_t launch_colsum(const PlanView& pv, int tasks_off, int n_tasks, int max
                          int T, int N, int t0, bool one_writer, hipStream_t stream);
 // Zeroes the history frames in front of a fresh window: `frames` frames of frame_floats[b] floats of
 // every buffer b (0: the buffer keeps none).
-hipError_t launch_zero_history(float* const* buf_ptr, const int32_t* frame_floats, int n_bufs, int frames, hipStream_t stream);
+hipError_t launch_zero_history(float* const* buf_ptr, const int64_t* frame_floats, int n_bufs, int frames, hipStream_t stream);
 hipError_t launch_fill(float* p, int64_t n, float v, hipStream_t stream);
 hipError_t launch_copy(float* dst, const float* src, int64_t n, hipStream_t stream);
 // dst[c][r] = src[r][c] for a row-major rows x cols matrix.

@@ -201,3 +201,28 @@ def test_equally_wide_exchanged_tensors(n_gates, N):
     loss = win.compute_grads(want_loss=True)
     check_against(win, w, ref, f"gates{n_gates}")
     assert abs(loss - ref["loss"]) <= 1e-5 * max(1.0, abs(ref["loss"]))
+
+
+def test_history_of_frames_beyond_2_to_the_31_values_starts_at_zero():
+    """One frame of 65,536 units and 32,768 streams (8 GiB) in a workspace that held NaN: a(t) =
+    W x(t) + d a(t - 1) with the zero history of a fresh window, o = v a."""
+    import torch
+    from paper_1503_02852_amd.runner import Window
+    D, N = 65536, 32768
+    g = wl.GraphSpec()
+    x = g.add_node(wl.INPUT, wl.LINEAR, 1, name="x")
+    a = g.add_node(wl.ADD, wl.LINEAR, D, name="a")
+    o = g.add_node(wl.ADD, wl.LINEAR, 1, is_output=wl.SQUARED_ERROR, name="o")
+    g.add_edge(x, a, wl.FULL, 0); g.add_edge(a, a, wl.DIAG, 1); g.add_edge(a, o, wl.FULL, 0)
+    rng = np.random.default_rng(7)
+    weights = [rng.standard_normal(s).astype(np.float32) for s in ((D, 1), (D,), (1, D))]
+    win = Window(g.node_array(), g.edge_array(), 1, N)
+    win.ws.fill_(0xFF)
+    win.set_params(weights, [None] * 3)
+    win.inputs[x] = torch.linspace(-1.0, 1.0, N, device=win.dev).view(1, N, 1)
+    win.forward()
+    win.check()
+    got = win.node_output(o).reshape(N).astype(np.float64)
+    w, v = weights[0].reshape(D).astype(np.float64), weights[2].reshape(D).astype(np.float64)
+    bound = (D + 3) * 2.0 ** -24 * np.abs(w * v).sum()      # |x| <= 1; one rounding per product and addition
+    assert np.isfinite(got).all() and np.abs(got - win.inputs[x].cpu().numpy().reshape(N).astype(np.float64) * (w * v).sum()).max() <= bound
