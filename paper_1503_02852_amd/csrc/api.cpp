@@ -228,6 +228,7 @@ struct rnn_graph {
             }
         };
         try_wave(force_step_G > 0 ? force_step_G : 32);
+        if (force_step_G <= 0 && register_over_xcds(cp, backward, N)) try_wave(64);
         // 2. matrix-core variants for many streams (weights in LDS or registers, MFMA)
         // 2a. one-dimensional split: stream groups, as many as possible (every group halves the
         //     bytes a workgroup polls per step); unit chunks: as many as the compute units allow
@@ -373,6 +374,24 @@ struct rnn_graph {
         for (int s = 0; s < lay.n_sources; ++s) if (lay.src[s].k_len > 1024) return false;
         return true;
     }
+    // Whether a layer's register build also stays ahead of the matrix-core build on two XCDs' 64 workgroups
+    // (if it fits them): a step polls many columns, each 16 streams wide for the matrix instructions, while the
+    // multiply-adds of at most four streams are few.  Step kernel of 128 frames, register against
+    // matrix-core build: N = 2, LSTM backward (four sources) 544 / 640 / 768 units 0.46 / 0.45 / 0.50 against
+    // 0.81 / 0.82 / 0.96 ms, one source of 544 / 768 / 1,024 units (Elman) 0.28 / 0.28 / 0.27 against 0.26 /
+    // 0.30 / 0.33, of 640 (LSTM forward) 0.33 against 0.35; N = 3 and 4, LSTM backward 288 / 416 units 0.44 /
+    // 0.48 against 0.54 / 0.68, 512 0.47 / 0.47, one source of 288 / 512 / 1,024 units 0.32 / 0.30 / 0.39
+    // against 0.19 / 0.17 / 0.34.  With eight streams' multiply-adds (N >= 5) never (208 units, N = 5,
+    // windows: 0.95 against 0.66), nor with more weights than a lane's registers take well (N = 2, LSTM
+    // backward, 144 / 196 / 256 per lane of 64 workgroups: 0.50 / 0.82 / 1.14 against 0.96 / 0.69 / 0.77).
+    bool register_over_xcds(const CompPlan& cp, bool backward, int N) const {
+        if (N < 2 || N > 4 || cp.step_weight_floats > 160 * 64 * STEP_THREADS) return false;
+        StepLayout lay;
+        compute_step_layout(plan.words.data(), backward ? cp.bwd_desc_off : cp.fwd_desc_off, 256, 1, 1, lay);
+        int columns = 0;
+        for (int s = 0; lay.ok && s < lay.n_sources; ++s) columns += lay.src[s].k_len;
+        return columns >= (N == 2 ? 600 : 1100);
+    }
     // Chains of recurrent components run side by side in one launch: all members in the
     // wave-autonomous build (N <= 8, member g on XCD g), or all in the matrix-core build (the 256
     // workgroups shared among the members).
@@ -429,8 +448,14 @@ struct rnn_graph {
                     c.source = jit_chain_source(plan, members, backward, N, c.G);
             }
             if (c.source.empty()) c.split = false;
-            bool matrix = N > 8;      // (few streams: where a layer on its own would run on the matrix cores)
-            for (int m = ch.first; m <= ch.last && !matrix; ++m) matrix = jit_choice(m, backward, N).mstep;
+            // Few streams: where a layer would need several XCDs.  Side by side on the matrix cores the layers
+            // also beat two register launches one after the other (register_over_xcds): 2 x 768 units, N = 2
+            // 0.56 + 1.02 against 0.67 + 1.00 ms forward + backward, 2 x 320, N = 4 0.37 + 0.58 against 0.89 + 0.95.
+            bool matrix = N > 8;
+            for (int m = ch.first; m <= ch.last && !matrix; ++m) {
+                const JitChoice& jc = jit_choice(m, backward, N);
+                matrix = jc.mstep || (jc.wave && jc.lp.G > 32 && matrix_streams(plan.comps[m], backward, N));
+            }
             if (c.source.empty() && matrix && force_step_J <= 0) {
                 // matrix-core members: each gets an equal share of the 256 workgroups; per member the
                 // most stream groups, then the most unit chunks that fit the share (as for a single

@@ -227,7 +227,7 @@ def test_headers_are_plain_c(tmp_path):
     subprocess.run([gcc, "-std=c99", "-Wall", "-Werror", "-fsyntax-only", "-I", os.path.join(ROOT, "include"), str(src)], check=True)
 
 
-@pytest.mark.parametrize("layers,N", [([1024], 2), ([512], 4), ([256, 256], 8), ([512], 17), ([1020], 3)])
+@pytest.mark.parametrize("layers,N", [([544], 2), ([512], 4), ([256, 256], 8), ([512], 17), ([1020], 3)])
 def test_exchange_copies_are_no_larger_than_their_tensors(monkeypatch, layers, N):
     """Few streams and ragged stream counts: the exchanged tensors' tile-blocked copies hold the
     streams there are, so they take at most what their tensors take (with 16-stream tiles whatever
@@ -261,3 +261,21 @@ def test_only_polled_exchange_copies_take_space(monkeypatch):
 
     copies, skew = 5 * 4 * (T + 1) * N * 1024, 5 * (1 << 16)
     assert copies <= workspace("1") - workspace("0") <= copies + skew
+
+
+@pytest.mark.parametrize("layers,N,copies", [([640], 2, 0), ([768], 2, 0), ([896], 2, 5), ([288], 3, 1), ([512], 4, 1), ([640], 4, 5),
+                                             ([640, 640], 2, 10), ([256], 8, 5)])
+def test_build_of_few_streams(monkeypatch, layers, N, copies):
+    """Which build a direction of an LSTM layer takes at 2 to 8 streams, seen in the workspace: the
+    matrix-core build exchanges through copies of h (forward) and of four state gradients (backward),
+    the register build has none."""
+    import workloads as wl
+    from paper_1503_02852_amd import binding
+    spec, T = wl.lstm_net(40, layers, 61), 2048
+
+    def workspace(blocked):
+        monkeypatch.setenv("RNNG_MSTEP_BLOCKED", blocked)
+        return binding.Graph(spec.node_array(), spec.edge_array()).workspace_bytes(T, N)
+
+    one = 4 * (T + 1) * N * layers[0]
+    assert copies * one <= workspace("1") - workspace("0") <= copies * (one + (1 << 16))
