@@ -332,7 +332,13 @@ hipError_t launch_softmax_rows(float* y, int64_t rows, int dim, hipStream_t stre
 hipError_t launch_softmax_ce_delta(const float* y, const int32_t* targets, float* ds, double* loss, unsigned* flag,
                                    int64_t rows, int dim, hipStream_t stream) {
     if (rows <= 0) return hipSuccess;
-    if (dim > 1024) {
+    // By segments where a wavefront per row is too few of them or walks its row for too long; else a workgroup
+    // has too little to do for its start.  Wavefronts against segments, µs of the backward pass of one layer:
+    // 256 rows of 1,100 / 4,096 columns 12.6 / 18.6 against 11.8 / 12.2; 512 rows of 1,100 / 2,048 / 4,096 12.3 /
+    // 14.8 / 21.2 against 15.0 / 14.4 / 15.2; 1,024 rows of 2,048 / 4,096 16.6 / 23.9 against 21.7 / 22.3; 2,048 rows
+    // of 1,100 / 4,096 / 5,000 / 20,000 17.6 / 32.7 / 39.3 / 163 against 34.1 / 37.9 / 38.0 / 69; 8,192 rows of 1,100 /
+    // 6,000 / 8,192 42 / 113 / 145 against 109 / 117 / 123.
+    if (dim > 1024 && dim > std::min<int64_t>(4 * rows, 4096 + std::min<int64_t>(rows, 8192) / 4)) {
         hipLaunchKernelGGL(softmax_ce_delta_wide_kernel, dim3((unsigned)std::min<int64_t>(rows, 1 << 20), (dim + CE_SEGMENT - 1) / CE_SEGMENT),
                            dim3(256), 0, stream, y, targets, ds, loss, flag, (long long)rows, dim);
         return hipGetLastError();

@@ -41,3 +41,28 @@ def test_softmax_and_delta_at_row_width_edges(O):
     l = -np.log(y[tg >= 0, tg[tg >= 0]].astype(np.float64))
     # the logarithm: |result| times a few roundings, and 2^-21 near 1; a sum of up to four in fp32
     assert abs(loss - l.sum()) <= 2.0 ** -22 * (4 * np.abs(l).sum() + 2 * len(l))
+
+
+@pytest.mark.parametrize("O,T", [(1025, 260), (1027, 601), (2048, 512), (2049, 512), (4097, 1100), (4100, 1024)])
+def test_output_delta_of_many_rows_around_the_change_of_kernels(O, T):
+    """Rows above 1,024 columns are taken whole by a wavefront each, or in segments by workgroups,
+    depending on how many rows and columns there are."""
+    from paper_1503_02852_amd.runner import window_for
+    g = wl.GraphSpec()
+    x = g.add_node(wl.INPUT, wl.LINEAR, 2, name="x")
+    o = g.add_node(wl.ADD, wl.SOFTMAX, O, is_output=wl.CROSS_ENTROPY, name="o")
+    g.add_edge(x, o, wl.FULL, 0)
+    w = wl.make_workload("delta", g, T=T, N=1, seed=O)
+    tg = w.targets[o].reshape(-1)
+    tg[:4] = 0, O - 1, -1, 1024
+    win = window_for(w)
+    win.forward()
+    win.bptt()
+    loss = win.compute_grads(want_loss=True)
+    y = win.node_output(1).reshape(T, O)
+    hot = np.zeros((T, O), np.float32)
+    hot[tg >= 0, tg[tg >= 0]] = 1.0
+    assert (win.node_state_grad(1).reshape(T, O) == np.where(tg[:, None] >= 0, y - hot, np.float32(0.0))).all()
+    l = -np.log(y[tg >= 0, tg[tg >= 0]].astype(np.float64))
+    # a few roundings of each logarithm; sums of up to four in fp32, the rest in double
+    assert abs(loss - l.sum()) <= 2.0 ** -22 * (4 * np.abs(l).sum() + 2 * len(l))
