@@ -97,7 +97,9 @@ __global__ __launch_bounds__(256) void softmax_rows_kernel(float* __restrict__ y
 // per load (which need 4-byte alignment only, so any width will do), columns beyond them are read three times.
 // One wavefront per row leaves 2048 rows two wavefronts per SIMD with one 4-byte load in flight each, three times over:
 // 2048 rows of 20,000, softmax and output delta (below) together 0.30 ms less per window than that (3.03 -> 2.72 ms for a
-// 38,000-512-20,000 LSTM on class indices).  Up to 1024 columns a row fits the registers of one wavefront.
+// 38,000-512-20,000 LSTM on class indices).  Up to 2048 columns a row fits the registers of one wavefront, which
+// then has no barriers: one layer's forward pass, a workgroup / a wavefront per row, 64 rows of 2048 27 / 28 us, 2,048 rows
+// of 1,100 / 2,048 55 / 46 and 71 / 64, 8,192 rows 124 / 93 and 169 / 145 (three reads by a wavefront: 104 and 168).
 typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int SMX_THREADS = 1024, SMX_CHUNK = 4 * SMX_THREADS;
 template <int CHUNKS>
@@ -320,9 +322,14 @@ hipError_t launch_softmax_rows(float* y, int64_t rows, int dim, hipStream_t stre
     if (dim <= 64) hipLaunchKernelGGL((softmax_rows_kernel<1>), grid, block, 0, stream, y, (long long)rows, dim);
     else if (dim <= 256) hipLaunchKernelGGL((softmax_rows_kernel<4>), grid, block, 0, stream, y, (long long)rows, dim);
     else if (dim <= 1024) hipLaunchKernelGGL((softmax_rows_kernel<16>), grid, block, 0, stream, y, (long long)rows, dim);
+    else if (dim <= 2048) hipLaunchKernelGGL((softmax_rows_kernel<32>), grid, block, 0, stream, y, (long long)rows, dim);
     else {
+        // a workgroup's registers hold the row, but no instance more of them than it needs: forward pass of one
+        // layer with one / two / five / ten chunks, 2,048 rows of 4,100 columns 92 / 92 / 107 / 128 us, 8,192 155 / 149 /
+        // 163 / 177, 20,000 346 / 333 / 314 / 325, 40,960 782 / 768 / 770 / 666, 65,536 1,292 / 1,275 / 1,366 / 1,240
         const dim3 wide((unsigned)std::min<int64_t>(rows, 1 << 20)), threads(SMX_THREADS);
         if (dim <= SMX_CHUNK) hipLaunchKernelGGL((softmax_wide_rows_kernel<1>), wide, threads, 0, stream, y, (long long)rows, dim);
+        else if (dim <= 2 * SMX_CHUNK) hipLaunchKernelGGL((softmax_wide_rows_kernel<2>), wide, threads, 0, stream, y, (long long)rows, dim);
         else if (dim <= 5 * SMX_CHUNK) hipLaunchKernelGGL((softmax_wide_rows_kernel<5>), wide, threads, 0, stream, y, (long long)rows, dim);
         else hipLaunchKernelGGL((softmax_wide_rows_kernel<10>), wide, threads, 0, stream, y, (long long)rows, dim);
     }

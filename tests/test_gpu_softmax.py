@@ -7,7 +7,7 @@ import workloads as wl
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("O", [1, 2, 63, 64, 65, 256, 257, 1023, 1024, 1025, 1027, 4096, 4097, 8191, 20480, 20483, 40960, 40963])
+@pytest.mark.parametrize("O", [1, 2, 63, 64, 65, 256, 257, 1023, 1024, 1025, 1027, 2047, 2048, 2049, 4096, 4097, 8191, 8192, 8193, 20480, 20483, 40960, 40963])
 def test_softmax_and_delta_at_row_width_edges(O):
     from paper_1503_02852_amd.runner import window_for
     K, T, N = 3, 5, 3
