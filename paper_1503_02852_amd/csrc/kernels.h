@@ -77,14 +77,17 @@ hipError_t launch_xcc_probe(unsigned* out, int n_blocks, hipStream_t stream);
 // [row0, row0 + rows), and the matching weight gradient G[j][idx[f - shift_rows]] += ds[f][j].
 hipError_t launch_onehot_gather(float* C, const float* W, const int* idx, int n_dst, int n_src, int64_t row0, int64_t rows,
                                 int64_t shift_rows, int64_t total_rows, bool accumulate, hipStream_t stream);
-// ordered: the rows are added one after another in increasing order (one writer per element: the
-// sums are the same bits from run to run), else with float atomics from many workgroups.
 // One-hot weight gradient, G stored whole (no zeros needed in it, nothing is added to what it held).
-// Used where the matrix has at least as many columns as the window has rows: its write, which the scatter's zero fill
-// does as well, then takes longer than the pass over the rows that every row segment makes.
+// Used where the matrix has at least 4,096 columns and at least as many as the window has rows.  Zero fill and scatter
+// against this, us of the gradient call, 512 x 4,096: 64 / 256 / 1,024 / 4,096 rows 27 / 39 / 58 / 132 against 28 / 35 / 38 / 46;
+// 64 x 38,000: 26 / 34 / 38 / 47 against 28 / 35 / 36 / 39; 2,048 x 38,000: 83 / 108 / 180 / 481 against 84 / 98 / 109 / 159.  The line is
+// on the safe side: the scatter's atomics lose beyond it too (512 x 512, 4,096 rows: 135 against 45; 512 x 4,096, 65,536 rows:
+// 1,755 against 353).
 bool onehot_grad_in_rows(int n_dst, int n_src, int64_t rows);
 hipError_t launch_onehot_grad_rows(float* G, const float* ds, const int* idx, int n_dst, int n_src, int64_t shift_rows, int64_t total_rows,
                                    hipStream_t stream);
+// The same added to what G holds.  ordered: the rows are added one after another in increasing order (one
+// writer per element: the sums are the same bits from run to run), else with float atomics from many workgroups.
 hipError_t launch_onehot_scatter(float* G, const float* ds, const int* idx, int n_dst, int n_src, int64_t shift_rows, int64_t total_rows,
                                  bool ordered, hipStream_t stream);
 
