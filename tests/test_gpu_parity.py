@@ -458,9 +458,9 @@ def test_wide_layers_with_the_two_dimensional_split(monkeypatch, kind, N):
 @pytest.mark.parametrize("kind,N", [("elman", 16), ("lstm", 16), ("lstm", 24), ("lstm", 64), ("elman", 48)])
 def test_wide_layers_with_weight_rows_in_registers(kind, N):
     """1024-wide recurrent layers at many streams with the one-dimensional split: the weight rows
-    of a workgroup exceed LDS, so whole sources stay in vector registers.  Stream counts that are
-    multiples of 16 exchange through the tile-blocked twins (one and several stream groups), the
-    others through the row-major tensors; a window computed in two pieces."""
+    of a workgroup exceed LDS, so whole sources stay in vector registers.  Exchange through the
+    tile-blocked twins, in one and several stream groups, with whole and short last blocks of 16
+    streams; a window computed in two pieces."""
     from paper_1503_02852_amd.runner import window_for
     spec = wl.elman_net(12, 1024, 6) if kind == "elman" else wl.lstm_net(12, [1024], 6)
     w = wl.make_workload(f"wide_{kind}", spec, T=5, N=N, seed=43, scale=0.05, bias_scale=0.1, masked_fraction=0.2)
