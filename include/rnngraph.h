@@ -226,8 +226,9 @@ int rnn_specialise(rnn_graph* g, int32_t N);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): rnn_forward with the workspace in a device array that
- * is part of the library image (RNN_STATIC_WORKSPACE_BYTES and room for the second copies below per
- * GPU, 161 MiB, held from the time the library is loaded until the process ends), and the output layers' activations copied to the caller.
+ * is part of the library image (RNN_STATIC_WORKSPACE_BYTES per GPU, 161 MiB more for windows with the
+ * second copies below; each held from the first call that needs it until the process ends), and the
+ * output layers' activations copied to the caller.
  *   d_inputs   as in rnn_forward.
  *   d_outputs  HOST array with one DEVICE pointer per output node, in increasing node id, each a
  *              [T][N][dim] float tensor that receives the node's activations y.
@@ -236,10 +237,9 @@ int rnn_specialise(rnn_graph* g, int32_t N);
  * workspace of the caller's) has done; else RNN_ERR_SEQUENCE.  RNN_ERR_WORKSPACE if the window
  * needs more than RNN_STATIC_WORKSPACE_BYTES (rnn_workspace_bytes tells; the second copies of
  * exchanged tensors that a stream count or a layer width which is no multiple of 16 brings are in
- * that figure, but do not count here), RNN_ERR_SEQUENCE if
- * kernel-class timing is switched on (it creates events).  Afterwards the handle's window lives in
- * the static array: rnn_output, rnn_bptt, rnn_grads work on it as after rnn_forward.  All calls
- * on one GPU share that GPU's array, which keeps the last call's contents (the call clears what
+ * that figure, but do not count here), RNN_ERR_SEQUENCE if kernel-class timing is switched on (it
+ * creates events).  Afterwards the handle's window lives in the static array: rnn_output, rnn_bptt,
+ * rnn_grads work on it as after rnn_forward.  All calls on one GPU share that GPU's array, which keeps the last call's contents (the call clears what
  * must start at zero): calls that overlap on one GPU, from any handle or stream, race. */
 #define RNN_STATIC_WORKSPACE_BYTES (32 * 1024 * 1024)
 int rnn_forward_static(rnn_graph* g, const float* d_weights, const float* const* d_inputs, float* const* d_outputs,

@@ -1124,12 +1124,11 @@ namespace {
 // Part of the library image: every GPU the library runs on holds its own copy of this array, at
 // its own address, until the process ends.  In host code the name is only a handle for
 // hipGetSymbolAddress; all device work goes through the address that call returns.
-// A window may need RNN_STATIC_WORKSPACE_BYTES beside the twins of ragged tiles, which come on top:
-// at most four times as many floats as their tensors (width 1), and the space between tensors.
-constexpr int64_t STATIC_ARRAY_BYTES = 5 * (int64_t)RNN_STATIC_WORKSPACE_BYTES + (1 << 20);
-static __device__ __align__(256) unsigned char scratch[STATIC_ARRAY_BYTES];
+static __device__ __align__(256) unsigned char scratch[RNN_STATIC_WORKSPACE_BYTES];
 constexpr int STATIC_MAX_DEVICES = 64;
-void* g_scratch_ptr[STATIC_MAX_DEVICES];      // per device: address of that GPU's copy (nullptr: not asked yet)
+// per device: address of that GPU's copy (nullptr: not asked yet); [1]: of the large array, for windows that
+// fit RNN_STATIC_WORKSPACE_BYTES but for their twins
+void* g_scratch_ptr[2][STATIC_MAX_DEVICES];
 std::mutex g_scratch_mutex;
 }  // namespace
 
@@ -1142,7 +1141,8 @@ int rnn_forward_static(rnn_graph* g, const float* d_weights, const float* const*
         if (!d_outputs[i]) return fail(RNN_ERR_INVALID_ARGUMENT, "an output tensor pointer is NULL");
     if (T <= 0 || N <= 0) return fail(RNN_ERR_INVALID_ARGUMENT, "T and N must be positive");
     if (g->prof.mask != 0) return fail(RNN_ERR_SEQUENCE, "kernel-class timing creates events: switch it off for rnn_forward_static");
-    const int64_t need = g->layout_for(T, N).total - g->layout_for(T, N).ragged_twin_bytes;
+    const int64_t total = g->layout_for(T, N).total, need = total - g->layout_for(T, N).ragged_twin_bytes;
+    const bool large = total > (int64_t)RNN_STATIC_WORKSPACE_BYTES;
     if (need > (int64_t)RNN_STATIC_WORKSPACE_BYTES)
         return fail(RNN_ERR_WORKSPACE, "the window needs " + std::to_string(need) + " bytes of workspace, the static workspace holds " +
                                            std::to_string((int64_t)RNN_STATIC_WORKSPACE_BYTES));
@@ -1153,17 +1153,17 @@ int rnn_forward_static(rnn_graph* g, const float* d_weights, const float* const*
     void* ws = nullptr;
     {
         std::lock_guard<std::mutex> lock(g_scratch_mutex);
-        if (!g_scratch_ptr[dev]) {
+        if (!g_scratch_ptr[large][dev]) {
             // once per device, with that device current: where this GPU keeps its copy of the array
             void* p = nullptr;
-            e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+            e = large ? static_large_workspace(&p) : hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
             if (e != hipSuccess || !p) return fail_hip(e, "hipGetSymbolAddress(static workspace)");
-            g_scratch_ptr[dev] = p;
+            g_scratch_ptr[large][dev] = p;
         }
-        ws = g_scratch_ptr[dev];
+        ws = g_scratch_ptr[large][dev];
     }
     g->no_alloc = true;
-    const int rc = rnn_forward_range(g, d_weights, d_inputs, T, N, 0, T, ws, STATIC_ARRAY_BYTES, hip_stream);
+    const int rc = rnn_forward_range(g, d_weights, d_inputs, T, N, 0, T, ws, large ? STATIC_LARGE_BYTES : (int64_t)RNN_STATIC_WORKSPACE_BYTES, hip_stream);
     g->no_alloc = false;
     if (rc != RNN_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);

@@ -65,6 +65,10 @@ hipError_t launch_colsum(const PlanView& pv, int tasks_off, int n_tasks, int max
 // every buffer b (0: the buffer keeps none).
 hipError_t launch_zero_history(float* const* buf_ptr, const int64_t* frame_floats, int n_bufs, int frames, hipStream_t stream);
 hipError_t launch_fill(float* p, int64_t n, float v, hipStream_t stream);
+// rnn_forward_static's array for windows that need twins of ragged tiles beside RNN_STATIC_WORKSPACE_BYTES (32 MiB): at most
+// four times as many floats as their tensors (width 1), and the space between tensors.
+constexpr int64_t STATIC_LARGE_BYTES = 161 << 20;
+hipError_t static_large_workspace(void** p);
 hipError_t launch_copy(float* dst, const float* src, int64_t n, hipStream_t stream);
 // dst[c][r] = src[r][c] for a row-major rows x cols matrix.
 hipError_t launch_transpose(float* dst, const float* src, int rows, int cols, hipStream_t stream);
