@@ -133,9 +133,9 @@ int64_t rnn_workspace_bytes(const rnn_graph* g, int32_t T, int32_t N);
  *              window's state between rnn_forward, rnn_bptt and rnn_grads.
  * One graph handle serves one window at a time.  All work is queued on hip_stream; the first
  * forward call of a process on a device also runs a short probe kernel and waits for it (it
- * records on which XCD the workgroups of a launch land: recurrent layers whose workgroups share
- * an XCD then exchange their state through that XCD's L2; RNNG_XCD_LOCAL=0 in the environment
- * switches that off), later calls do not synchronise. */
+ * records whether the workgroups of a launch are dealt to the XCDs in turn: recurrent layers whose
+ * workgroups share an XCD then exchange their state through that XCD's L2; RNNG_XCD_LOCAL=0 in the
+ * environment switches that off), later calls do not synchronise. */
 int rnn_forward(rnn_graph* g, const float* d_weights, const float* const* d_inputs,
                 int32_t T, int32_t N, void* d_workspace, int64_t ws_bytes, void* hip_stream);
 
@@ -207,8 +207,8 @@ int rnn_set_deterministic(rnn_graph* g, int32_t on);
 
 /* Waits for hip_stream and reports what the kernels of the current window have flagged since its
  * rnn_forward (or rnn_forward_range(.., 0, ..)): RNN_ERR_DEVICE if a recurrent step kernel gave up
- * a bounded wait or found itself on another XCD than observed (the window's activations and
- * gradients are then invalid), RNN_ERR_INVALID_ARGUMENT for a target index out of range, else
+ * a bounded wait or had workgroups that share an XCD's L2 on several XCDs (the window's activations
+ * and gradients are then invalid), RNN_ERR_INVALID_ARGUMENT for a target index out of range, else
  * RNN_OK.  The asynchronous calls cannot report these themselves: callers that never pass `loss`
  * to rnn_grads call this once per window, or every so many windows. */
 int rnn_check(rnn_graph* g, void* hip_stream);

@@ -44,6 +44,7 @@ struct Layout {
     int64_t ragged_twin_bytes = 0;        // of total: twins that only windows of no whole 16 x 16 tiles need padding for
 };
 constexpr int64_t SYNC_BYTES = 1024;
+static_assert(16 + 4 * (XCD_WORDS_FIRST + XCD_WORDS) <= SYNC_BYTES, "control words");
 
 int64_t g_layout_skew = 4352;      // bytes, a multiple of 256 (RNNG_LAYOUT_SKEW overrides: tuning aid)
 
@@ -128,12 +129,12 @@ struct Profiler {
     }
 };
 
-// Which XCD the workgroups of a launch land on, observed once per device: xcc[r] is the hardware id
-// of the XCD that ran every workgroup b with b % 8 == r of a probe launch (workgroups are dealt to
-// the XCDs in turn), ok = false if some residue class was spread over several XCDs.  The step
-// kernels that keep a group of workgroups on one residue class then exchange through that XCD's L2
-// with plain stores, and each workgroup checks the id it was given against the one it runs on.
-struct XcdMap { bool known = false, ok = false; int xcc[8] = {0, 0, 0, 0, 0, 0, 0, 0}; };
+// Whether the workgroups of a launch are dealt to the XCDs in turn, observed once per device: ok if every
+// workgroup b of a probe launch with the same b % 8 ran on one XCD.  The step kernels that keep a group of
+// workgroups on one residue class then exchange through that XCD's L2 with plain stores.  Which XCD it is
+// may change between launches (it does once several streams have been used), so each launch leaves
+// the ids it ran on in a control word, and a group on more than one XCD is reported.
+struct XcdMap { bool known = false, ok = false; };
 
 struct rnn_graph {
     Plan plan;
@@ -183,6 +184,7 @@ struct rnn_graph {
     double* loss_ptr() const { return reinterpret_cast<double*>(ws + layout.sync_off); }
     unsigned* ctrl_ptr() const { return reinterpret_cast<unsigned*>(ws + layout.sync_off + 16); }
     int force_step_G = 0;
+    int xcd_words_used = 0;               // of the current window (step_layout.h)
     int spin_limit = 1 << 22;             // bound of every wait inside a step kernel (polling attempts)
     int cu_count = 0;                     // compute units of the device of the current window (0: not asked yet)
     // which build ran the step loop of component c in direction d at its last launch (RNN_BUILD_*, 0: none yet)
@@ -597,13 +599,23 @@ hipError_t ensure_xcd_map(unsigned* scratch, hipStream_t s, const XcdMap** out) 
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) return e;
         m.ok = true;
-        for (int r = 0; r < 8; ++r) {
-            m.xcc[r] = (int)host[r];
-            for (int b = r; b < NB; b += 8) m.ok = m.ok && host[b] == host[r];
-        }
+        for (int b = 8; b < NB; ++b) m.ok = m.ok && host[b] == host[b % 8];
         m.known = true;
     }
     *out = &m;
+    return hipSuccess;
+}
+
+// The control word for the XCDs of the next launch that exchanges through an XCD's L2, or -1.
+hipError_t xcd_word(rnn_graph* g, hipStream_t s, int* word) {
+    *word = -1;
+    if (!g_xcd_local || !g->xcd || !g->xcd->ok) return hipSuccess;
+    if (g->xcd_words_used == XCD_WORDS) {
+        hipError_t e = launch_xcd_words_fold(g->ctrl_ptr(), s);
+        if (e != hipSuccess) return e;
+        g->xcd_words_used = 0;
+    }
+    *word = XCD_WORDS_FIRST + g->xcd_words_used++;
     return hipSuccess;
 }
 
@@ -775,7 +787,10 @@ StepRun run_phases(rnn_graph* g, int comp, bool backward, hipStream_t s, int t0,
                     }
             }
         }
-        if (jc->wave && jc->lp.xcd_stride == 8 && g_xcd_local && g->xcd && g->xcd->ok) a.xcc_expect[0] = g->xcd->xcc[0];
+        if (jc->wave && jc->lp.xcd_stride == 8) {
+            hipError_t we = xcd_word(g, s, &a.xcd_word);
+            if (we != hipSuccess) return step_error(we, "XCD words");
+        }
         StepLaunchPlan lp_all = jc->lp;
         lp_all.G = jc->lp.G * jc->J;       // launch size; a.G stays the number of unit chunks
         if (!launch_fits_device(g, lp_all.G, why)) return step_error(hipSuccess, why);
@@ -856,9 +871,11 @@ StepRun run_chain(rnn_graph* g, int chain, bool backward, hipStream_t s, int t0,
         if (cc.mstep) {
             a.grp_J[i] = cc.J[i];
             a.grp_first[i] = i == 0 ? 0 : a.grp_first[i - 1] + cc.G[i - 1] * cc.J[i - 1];
-        } else if (g_xcd_local && g->xcd && g->xcd->ok) {
-            a.xcc_expect[i] = g->xcd->xcc[i];
         }
+    }
+    if (!cc.mstep) {
+        hipError_t we = xcd_word(g, s, &a.xcd_word);
+        if (we != hipSuccess) return step_error(we, "XCD words");
     }
     int participants = 0;
     for (size_t i = 0; i < cc.G.size(); ++i) participants += cc.G[i] * (cc.mstep ? cc.J[i] : 1);
@@ -961,14 +978,18 @@ namespace {
 // Waits for the stream, then reads the control words of the current window: E_total (to *loss if
 // given) and the flags the kernels raise.  A raised flag means the window's results are invalid.
 int read_control(rnn_graph* g, double* loss, hipStream_t s) {
-    unsigned char back[32];
+    unsigned char back[SYNC_BYTES];
     hipError_t e = hipMemcpyAsync(back, g->loss_ptr(), sizeof(back), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail_hip(e, "control word read-back");
     if (loss) std::memcpy(loss, back, sizeof(double));
     unsigned flag; std::memcpy(&flag, back + 16, 4);
+    for (int i = 0; i < g->xcd_words_used; ++i) {
+        unsigned w; std::memcpy(&w, back + 16 + 4 * (XCD_WORDS_FIRST + i), 4);
+        if (xcd_word_split(w)) flag = 2;
+    }
     if (flag == 3) return fail(RNN_ERR_INVALID_ARGUMENT, "a target class index is not below the output layer's width (that frame was left out)");
-    if (flag == 2) return fail(RNN_ERR_DEVICE, "a recurrent step kernel's workgroup ran on another XCD than the probe launch had shown (results are invalid; RNNG_XCD_LOCAL=0 avoids the assumption)");
+    if (flag == 2) return fail(RNN_ERR_DEVICE, "the workgroups of a recurrent layer ran on several XCDs (results are invalid; RNNG_XCD_LOCAL=0 avoids the assumption)");
     if (flag) return fail(RNN_ERR_DEVICE, "a recurrent step kernel ran into its wait limit (results are invalid)");
     return RNN_OK;
 }
@@ -1072,6 +1093,7 @@ int rnn_forward_range(rnn_graph* g, const float* d_weights, const float* const* 
         // of a window computed later keep the flags an earlier piece has raised.
         e = launch_fill(reinterpret_cast<float*>(g->ws + L.sync_off), SYNC_BYTES / 4, 0.0f, s);
         if (e != hipSuccess) return fail_hip(e, "control word reset");
+        g->xcd_words_used = 0;
         if (H > 0) {
             e = launch_zero_history(g->view().buf_ptr, reinterpret_cast<const int64_t*>(g->ws + L.frames_off), P.n_bufs, H, s);
             if (e != hipSuccess) return fail_hip(e, "history reset");

@@ -77,6 +77,8 @@ hipError_t launch_transpose(float* dst, const float* src, int rows, int cols, hi
 hipError_t launch_upload_words(uint32_t* d_dst, const uint32_t* h_src, int64_t n, hipStream_t stream);
 // Writes the hardware XCD id of workgroup b (256 threads each) to out[b], b < n_blocks.
 hipError_t launch_xcc_probe(unsigned* out, int n_blocks, hipStream_t stream);
+// Folds the words that step launches have left the ids of their XCDs in (step_layout.h) into the flag ctrl[0].
+hipError_t launch_xcd_words_fold(unsigned* ctrl, hipStream_t stream);
 // One-hot sources given as class indices [total_rows]: C[f][j] (+)= W[j][idx[f - shift_rows]] for rows
 // [row0, row0 + rows), and the matching weight gradient G[j][idx[f - shift_rows]] += ds[f][j].
 hipError_t launch_onehot_gather(float* C, const float* W, const int* idx, int n_dst, int n_src, int64_t row0, int64_t rows,

@@ -144,6 +144,17 @@ __global__ __launch_bounds__(STEP_THREADS) void xcc_probe_kernel(unsigned* out) 
 }
 }  // namespace
 
+// ctrl[0] becomes 2 if a launch had a group on more than one XCD; the words are ready for other launches.
+__global__ __launch_bounds__(64) void xcd_words_fold_kernel(unsigned* ctrl) {
+    if (threadIdx.x >= XCD_WORDS) return;
+    unsigned* w = ctrl + XCD_WORDS_FIRST + threadIdx.x;
+    if (xcd_word_split(*w)) atomicMax(ctrl, 2u);
+    *w = 0u;
+}
+hipError_t launch_xcd_words_fold(unsigned* ctrl, hipStream_t stream) {
+    hipLaunchKernelGGL(xcd_words_fold_kernel, dim3(1), dim3(64), 0, stream, ctrl);
+    return hipGetLastError();
+}
 hipError_t launch_xcc_probe(unsigned* out, int n_blocks, hipStream_t stream) {
     hipLaunchKernelGGL(xcc_probe_kernel, dim3(n_blocks), dim3(STEP_THREADS), 0, stream, out);
     return hipGetLastError();
@@ -155,7 +166,8 @@ void fill_step_args(StepArgs& a, const PlanView& pv, const StepLaunchPlan& lp, i
     a.buf_ptr = pv.buf_ptr; a.words = pv.words; a.weights = weights; a.ctrl = ctrl; a.desc_off = desc_off;
     a.T = T; a.N = N; a.backward = backward ? 1 : 0; a.G = lp.G; a.xcd_stride = lp.xcd_stride; a.spin_limit = spin_limit;
     a.n_groups = 0; a.partial = nullptr; a.store_base = nullptr; a.store_bytes = 0; a.weights_t = nullptr; a.weight_bytes = 0; a.twin_base = 0;
-    for (int g = 0; g < STEP_MAX_GROUPS; ++g) { a.grp_desc_off[g] = 0; a.grp_G[g] = 0; a.grp_J[g] = 1; a.grp_first[g] = 0; a.xcc_expect[g] = -1; }
+    for (int g = 0; g < STEP_MAX_GROUPS; ++g) { a.grp_desc_off[g] = 0; a.grp_G[g] = 0; a.grp_J[g] = 1; a.grp_first[g] = 0; }
+    a.xcd_word = -1;
 }
 
 hipError_t launch_recurrent_steps(const PlanView& pv, const StepLaunchPlan& lp, int desc_off, const float* weights,

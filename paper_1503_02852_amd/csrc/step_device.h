@@ -592,9 +592,9 @@ struct WaveRegs {
 //      step's poll, where its acknowledgement overlaps the step's arithmetic.
 template <class MV>
 __device__ __forceinline__ void wave_xcd_setup(WaveRegs<MV>& wv, const StepArgs& a, int group) {
-    const int expect = a.xcc_expect[group];
-    wv.local = suni(expect) >= 0;
-    if (expect >= 0 && step_xcc_id() != expect && threadIdx.x == 0) atomicExch(a.ctrl, 2u);
+    static_assert(STEP_MAX_GROUPS * 8 <= 32, "one byte per group");
+    wv.local = suni(a.xcd_word) >= 0;
+    if (wv.local && threadIdx.x == 0) atomicOr(a.ctrl + suni(a.xcd_word), 1u << (8 * group + (step_xcc_id() & 7)));
 }
 
 // Part index of this workgroup in a single-component launch, or -1 if it has no part.

@@ -68,6 +68,14 @@ struct StepLayout {
 
 constexpr int STEP_MAX_GROUPS = 4;
 
+// Control words behind ctrl that hold the XCDs of one launch each (behind those of the step trace).
+constexpr int XCD_WORDS_FIRST = 192, XCD_WORDS = 60;
+RNNG_HD inline bool xcd_word_split(unsigned w) {      // has a group been on more than one XCD?
+    bool split = false;
+    for (int g = 0; g < STEP_MAX_GROUPS; ++g) { const unsigned b = (w >> (8 * g)) & 0xFF; split = split || (b & (b - 1)) != 0; }
+    return split;
+}
+
 struct StepArgs {
     float* const* buf_ptr;                   // buffer table (read-only for the kernel's lifetime)
     const int32_t* words;                    // plan words (likewise)
@@ -87,12 +95,11 @@ struct StepArgs {
     // Matrix-core build: the streams are split into J groups of N / J; workgroup w owns unit chunk
     // w % G of stream group w / G (G * J workgroups in all).  1 elsewhere.
     int J;
-    // Wave-autonomous builds: hardware id of the XCD on which every workgroup of group g runs
-    // (single-component launch: entry 0), as the host has observed for this launch shape, or -1.
-    // With an id, tensors exchanged inside the group are written with plain stores (the XCD's L2
-    // holds them, and the group's polling loads are served there); a workgroup that finds itself
-    // on another XCD sets ctrl[0] = 2.  With -1 every exchanged tensor is written through.
-    int xcc_expect[STEP_MAX_GROUPS];
+    // Wave-autonomous builds: word (behind ctrl) in which this launch's workgroups leave the XCDs they run
+    // on, bit 8 g + id for group g, or -1.  With a word, tensors exchanged inside a group are written
+    // with plain stores (the XCD's L2 holds them, and the group's polling loads are served there), and
+    // the host reports a group on more than one XCD.  With -1 every exchanged tensor is written through.
+    int xcd_word;
     // Matrix-core build with the two-dimensional split: the partial sums that the workgroups hand
     // to each other, [frame][workgroup][column slice][row][stream] (sentinel-filled by the host).
     float* partial;

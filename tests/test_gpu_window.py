@@ -226,3 +226,22 @@ def test_history_of_frames_beyond_2_to_the_31_values_starts_at_zero():
     w, v = weights[0].reshape(D).astype(np.float64), weights[2].reshape(D).astype(np.float64)
     bound = (D + 3) * 2.0 ** -24 * np.abs(w * v).sum()      # |x| <= 1; one rounding per product and addition
     assert np.isfinite(got).all() and np.abs(got - win.inputs[x].cpu().numpy().reshape(N).astype(np.float64) * (w * v).sum()).max() <= bound
+
+
+def test_layers_on_one_xcd_after_several_streams_have_been_used():
+    """The XCD that a residue class of workgroups lands on changes once several streams have been
+    used: that a group shares one XCD is what counts."""
+    import torch
+    from paper_1503_02852_amd.runner import window_for
+    w = wl.make_workload("streams", wl.lstm_net(9, [40, 33], 6), T=14, N=2, seed=77, scale=0.4, bias_scale=0.3)
+    ref = go.forward_bptt(w.spec.nodes, w.spec.edges, w.weights, w.biases, w.inputs, w.targets, w.T, w.N)
+    win = window_for(w)
+    torch.cuda.synchronize()
+    for s in [torch.cuda.Stream() for _ in range(5)] + [torch.cuda.default_stream()]:
+        with torch.cuda.stream(s):
+            win.forward()
+            for _ in range(70):      # (more launches than there are words for their XCDs)
+                win.bptt()
+            assert abs(win.compute_grads(want_loss=True) - ref["loss"]) <= 1e-5 * max(1.0, abs(ref["loss"]))      # (reports flags too)
+        s.synchronize()
+        check_against(win, w, ref, "streams")

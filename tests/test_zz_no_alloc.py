@@ -72,6 +72,27 @@ def test_static_workspace_does_not_count_the_copies_of_ragged_tiles(spec_fn, T, 
         assert np.array_equal(got[k], ref[k])
 
 
+def test_static_call_under_capture_with_copies_beyond_the_workspace():
+    """A captured rnn_forward_static in the larger array, replayed with other work in between."""
+    import torch
+    spec = wl.lstm_net(8, [512], 4)
+    w = wl.make_workload("static_capture", spec, T=40, N=17, seed=76, scale=0.05)
+    win, ref, _ = outputs_both_ways(w)
+    (o,) = spec.output_nodes()
+    out = torch.zeros((w.T, w.N, 4), dtype=torch.float32, device=win.dev)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        win.g.forward_static(win.weights.data_ptr(), win._input_ptrs(), [out.data_ptr()], w.T, w.N, win._stream())
+    for _ in range(3):
+        out.fill_(float("nan"))
+        win.forward()                  # eager, on the caller's workspace
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy(), ref[o])
+
+
 def test_static_workspace_limits_and_preconditions():
     import torch
     from paper_1503_02852_amd.binding import RnnError
