@@ -511,51 +511,56 @@ hipError_t run_gemms(rnn_graph* g, const std::vector<GemmProblemPlan>& probs, bo
     if (probs.empty() || rows <= 0) return hipSuccess;
     const int prof = g->prof.begin(backward ? RNN_PROF_GEMM_BWD : RNN_PROF_GEMM_FWD, s);
     int64_t n_launch = 0;
-    size_t max_pairs = 0;
-    for (const auto& p : probs) max_pairs = p.pairs.size() > max_pairs ? p.pairs.size() : max_pairs;
-    for (size_t round = 0; round * GEMM_MAX_PAIRS < max_pairs; ++round) {
-        GemmGroup grp; std::memset(&grp, 0, sizeof(grp));
-        grp.split_k = 1; grp.accumulate = round > 0;
-        auto flush = [&]() -> hipError_t {
-            if (grp.n_problems == 0) return hipSuccess;
-            // Few output tiles and a long contraction (huge input layers): split the contraction over
-            // more workgroups, which add their parts atomically into the zeroed destination.
-            int64_t tiles = 0; int kmax = 0;
-            for (int i = 0; i < grp.n_problems; ++i) {
-                tiles += (int64_t)((grp.p[i].M + 127) / 128) * ((grp.p[i].N + 127) / 128);
-                for (int q = 0; q < grp.p[i].n_pairs; ++q) kmax = std::max(kmax, grp.p[i].pairs[q].K);
-            }
-            int split = 1;
-            if (tiles < 256 && !g->deterministic) split = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(16, kmax / 512), (512 + tiles - 1) / tiles));
-            grp.split_k = split;
-            if (split > 1 && !grp.accumulate)
-                for (int i = 0; i < grp.n_problems; ++i) {
-                    hipError_t e = launch_fill(grp.p[i].C, (int64_t)grp.p[i].M * grp.p[i].ldc, 0.0f, s);
-                    if (e != hipSuccess) return e;
-                    ++n_launch;
-                }
-            hipError_t e = launch_gemm_group(backward ? GEMM_NN : GEMM_NT, grp, s);
-            grp.n_problems = 0; ++n_launch;
-            return e;
-        };
-        for (const auto& pp0 : probs) {
-            // products with a one-hot source are column gathers, done after the GEMMs (below)
-            GemmProblemPlan pp; pp.c_buf = pp0.c_buf; pp.n = pp0.n;
-            for (const GemmPairPlan& pr : pp0.pairs) if (!g->is_onehot(pr.a_buf)) pp.pairs.push_back(pr);
-            if (pp.pairs.size() <= round * GEMM_MAX_PAIRS) continue;
-            GemmProblem& gp = grp.p[grp.n_problems];
-            gp.C = g->buf(pp.c_buf) + r0 * pp.n; gp.ldc = pp.n; gp.M = (int)rows; gp.N = pp.n; gp.n_pairs = 0;
-            for (size_t q = round * GEMM_MAX_PAIRS; q < pp.pairs.size() && gp.n_pairs < GEMM_MAX_PAIRS; ++q) {
-                const GemmPairPlan& pr = pp.pairs[q];
-                GemmPair& o = gp.pairs[gp.n_pairs++];
-                o.A = g->buf(pr.a_buf); o.B = g->weights + pr.b_w_off; o.K = pr.k_len; o.lda = pr.k_len;
-                o.ldb = backward ? pp.n : pr.k_len;
-                o.a_row_off = (int)r0 + (backward ? pr.delay : -pr.delay) * g->N; o.a_rows = (int)F;
-                // an input read in place has the window's frames only: its row 0 is internal row HN
-                if (g->caller_input(pr.a_buf)) { o.a_row_off -= (int)HN; o.a_rows = (int)(F - HN); }
-            }
-            if (++grp.n_problems == GEMM_MAX_PROBLEMS) { hipError_t e = flush(); if (e != hipSuccess) return e; }
+    GemmGroup grp;
+    grp.n_problems = grp.n_pairs = 0;
+    auto flush = [&]() -> hipError_t {
+        if (grp.n_problems == 0) return hipSuccess;
+        // Few output tiles and a long contraction (huge input layers): split the contraction over
+        // more workgroups, which add their parts atomically into the zeroed destination.
+        int64_t tiles = 0; int kmax = 0;
+        for (int i = 0; i < grp.n_problems; ++i) tiles += (int64_t)((grp.p[i].M + 127) / 128) * ((grp.p[i].N + 127) / 128);
+        for (int q = 0; q < grp.n_pairs; ++q) kmax = std::max(kmax, grp.pair[q].K);
+        int split = 1;
+        if (tiles < 256) split = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(16, kmax / 512), (512 + tiles - 1) / tiles));
+        for (int i = 0; i < grp.n_problems; ++i) grp.p[i].min_split = split;
+        plan_gemm_group(backward ? GEMM_NN : GEMM_NT, grp, g->deterministic);
+        for (int i = 0; i < grp.n_problems; ++i) {
+            if (grp.p[i].split == 1 || grp.p[i].accumulate) continue;
+            hipError_t e = launch_fill(grp.p[i].C, (int64_t)grp.p[i].M * grp.p[i].ldc, 0.0f, s);
+            if (e != hipSuccess) return e;
+            ++n_launch;
         }
+        hipError_t e = launch_gemm_group(backward ? GEMM_NN : GEMM_NT, grp, s);
+        grp.n_problems = grp.n_pairs = 0; ++n_launch;
+        return e;
+    };
+    for (const auto& pp : probs) {
+        GemmProblem* gp = nullptr;
+        bool first = true;
+        for (const GemmPairPlan& pr : pp.pairs) {
+            if (g->is_onehot(pr.a_buf)) continue;      // products with a one-hot source are column gathers, done after the GEMMs (below)
+            if (grp.n_pairs == GEMM_MAX_PAIRS || (!gp && grp.n_problems == GEMM_MAX_PROBLEMS)) {
+                hipError_t e = flush();
+                if (e != hipSuccess) return e;
+                gp = nullptr;
+            }
+            if (!gp) {
+                gp = &grp.p[grp.n_problems++];
+                std::memset(gp, 0, sizeof(*gp));
+                gp->C = g->buf(pp.c_buf) + r0 * pp.n; gp->ldc = pp.n; gp->M = (int)rows; gp->N = pp.n;
+                gp->first_pair = grp.n_pairs; gp->accumulate = first ? 0 : 1;      // (more pairs than one launch takes: the next one adds)
+                first = false;
+            }
+            GemmPair& o = grp.pair[grp.n_pairs++];
+            ++gp->n_pairs;
+            o.A = g->buf(pr.a_buf); o.B = g->weights + pr.b_w_off; o.K = pr.k_len; o.lda = pr.k_len;
+            o.ldb = backward ? pp.n : pr.k_len;
+            o.a_row_off = (int)r0 + (backward ? pr.delay : -pr.delay) * g->N; o.a_rows = (int)F;
+            // an input read in place has the window's frames only: its row 0 is internal row HN
+            if (g->caller_input(pr.a_buf)) { o.a_row_off -= (int)HN; o.a_rows = (int)(F - HN); }
+        }
+    }
+    {
         hipError_t e = flush();
         if (e != hipSuccess) return e;
     }
@@ -1370,40 +1375,42 @@ int rnn_grads(rnn_graph* g, float* d_grads, double* loss, void* hip_stream) {
     };
     std::vector<GemmGroup>& groups = g->grad_groups;
     groups.clear();
-    GemmGroup grp; std::memset(&grp, 0, sizeof(grp));
     int64_t tiles = 0, n_launch = 0;
-    bool sole = true;
-    auto flush = [&]() {
-        if (grp.n_problems == 0) return;
-        int split = (int)((1024 + tiles - 1) / tiles);
-        const int max_split = (int)((F + 127) / 128);
-        if (split > max_split) split = max_split;
-        if (split < 1 || g->deterministic) split = 1;
-        // split_k > 1 adds atomically into the zeroed buffer; split_k == 1 must add too (accumulate) where
-        // several connections share a block
-        grp.split_k = split; grp.accumulate = !sole;
-        if (split == 1 && sole)
-            for (int i = 0; i < grp.n_problems; ++i) own(grp.p[i].C - d_grads, (int64_t)grp.p[i].M * grp.p[i].N);
-        groups.push_back(grp);
-        grp.n_problems = 0; tiles = 0; sole = true;
+    int since = 0;      // first problem of the current eight
+    // Eight products together have at least as many parts as make 1,024 workgroups of 128 x 128 (and 128 frames each).
+    auto eight = [&]() {
+        GemmGroup& grp = groups.back();
+        for (int i = since; i < grp.n_problems; ++i)
+            grp.p[i].min_split = (int)std::max<int64_t>(1, std::min<int64_t>((1024 + tiles - 1) / tiles, (F + 127) / 128));
+        since = grp.n_problems; tiles = 0;
     };
     for (const GradGemmPlan& gg : P.grad_gemms) {
         if (g->is_onehot(gg.src_buf)) {
             if (in_rows(gg)) own(gg.w_off, (int64_t)gg.n_dst * gg.n_src);
             continue;
         }
-        GemmProblem& gp = grp.p[grp.n_problems];
-        gp.C = d_grads + gg.w_off; gp.ldc = gg.n_src; gp.M = gg.n_dst; gp.N = gg.n_src; gp.n_pairs = 1;
-        GemmPair& o = gp.pairs[0];
+        if (groups.empty() || groups.back().n_problems == GEMM_MAX_PROBLEMS) {
+            groups.emplace_back();
+            groups.back().n_problems = groups.back().n_pairs = since = 0;
+        }
+        GemmGroup& grp = groups.back();
+        GemmProblem& gp = grp.p[grp.n_problems++];
+        gp.C = d_grads + gg.w_off; gp.ldc = gg.n_src; gp.M = gg.n_dst; gp.N = gg.n_src;
+        gp.first_pair = grp.n_pairs; gp.n_pairs = 1; gp.accumulate = gg.sole ? 0 : 1;      // where several connections share a block all add
+        GemmPair& o = grp.pair[grp.n_pairs++];
         // eps_m(t) of every frame of the window against y_src(t - d); for the window's first d
         // frames that is a history frame (the real activation of a frame before the window)
         o.A = g->frame0(gg.dst_buf); o.lda = gg.n_dst;
         o.B = g->frame0(gg.src_buf) - (int64_t)gg.delay * N * gg.n_src; o.ldb = gg.n_src; o.K = (int)F; o.a_row_off = 0; o.a_rows = (int)F;
         tiles += (int64_t)((gg.n_dst + 127) / 128) * ((gg.n_src + 127) / 128);
-        sole = sole && gg.sole;
-        if (++grp.n_problems == GEMM_MAX_PROBLEMS) flush();
+        if (grp.n_problems - since == 8) eight();
     }
-    flush();
+    for (GemmGroup& grp : groups) {
+        if (&grp == &groups.back() && tiles > 0) eight();
+        plan_gemm_group(GEMM_TN, grp, g->deterministic);
+        for (int i = 0; i < grp.n_problems; ++i)
+            if (grp.p[i].split == 1 && !grp.p[i].accumulate) own(grp.p[i].C - d_grads, (int64_t)grp.p[i].M * grp.p[i].N);
+    }
 
     hipError_t e = hipSuccess;
     std::sort(owned.begin(), owned.end());

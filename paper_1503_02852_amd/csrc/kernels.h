@@ -11,31 +11,39 @@ namespace rnng {
 // ---------------------------------------------------------------------------------------
 // Grouped fp32 MFMA GEMM:  C[M][N] (+)= sum over pairs  A_p(M x K_p) * B_p(K_p x N)
 // ---------------------------------------------------------------------------------------
-constexpr int GEMM_MAX_PAIRS = 4;
-constexpr int GEMM_MAX_PROBLEMS = 8;
+constexpr int GEMM_MAX_PAIRS = 40;         // of a launch, all problems together
+constexpr int GEMM_MAX_PROBLEMS = 24;
+constexpr int GEMM_WIDE_ROW = 1 << 22;     // rows of so many floats and more: 128 of them are beyond a 32-bit byte offset
 
 struct GemmPair {
     const float* A;   // K-contiguous modes: element (m, k) at A[(m + a_row_off) * lda + k], zero if the
                       // shifted row falls outside [0, a_rows);  M-contiguous mode: element (m, k) at A[k * lda + m]
     const float* B;   // K-contiguous mode: element (k, n) at B[n * ldb + k];  N-contiguous: B[k * ldb + n]
-    int K, lda, ldb, a_row_off, a_rows;
+    int K, lda, ldb, a_row_off, a_rows;      // (a row ends after K, M or N floats: lda, ldb are exactly that)
 };
 struct GemmProblem {
-    float* C; int ldc, M, N, n_pairs;
-    GemmPair pairs[GEMM_MAX_PAIRS];
+    float* C; int ldc, M, N, first_pair, n_pairs;
+    int accumulate;         // 1: C += result instead of C = result
+    int min_split;          // the contraction is split into no fewer parts than this (their sums round no less than these)
+    // by plan_gemm_group:
+    int split;              // > 1: that many workgroups share the contraction of a tile and add to C, which must be zero
+    int kind;               // 0, 1, 2: tiles of 32, 64, 128; 3: of 32, with rows of GEMM_WIDE_ROW floats or more
+    int chunks, narrow;
 };
 struct GemmGroup {
     GemmProblem p[GEMM_MAX_PROBLEMS];
-    int n_problems;
-    int split_k;      // >1: K is split over blockIdx.z and results are added atomically (C must be pre-zeroed)
-    int accumulate;   // 1: C += result instead of C = result (ignored when split_k > 1)
-    int group_m;      // set by launch_gemm_group: tile order (see the kernel); 0: row by row, no XCD ranges
+    GemmPair pair[GEMM_MAX_PAIRS];
+    int first_block[GEMM_MAX_PROBLEMS];      // from here on set by launch_gemm_group
+    int n_blocks, group_m;
+    int n_problems, n_pairs;
 };
 enum GemmMode {
     GEMM_NT = 0,   // A K-contiguous, B K-contiguous      (forward:  Y_dst = Y_src W^T)
     GEMM_NN = 1,   // A K-contiguous, B N-contiguous      (backward: dY_src = dS_dst W)
     GEMM_TN = 2    // A M-contiguous, B N-contiguous      (gradient: G = dS_dst^T Y_src)
 };
+// Chooses tiles and splits by estimated time; one_writer: no splits.
+void plan_gemm_group(GemmMode mode, GemmGroup& g, bool one_writer);
 hipError_t launch_gemm_group(GemmMode mode, const GemmGroup& g, hipStream_t stream);
 
 // ---------------------------------------------------------------------------------------

@@ -70,3 +70,41 @@ def test_infinities_nan_and_the_ends_of_the_range():
     # K products and K additions: 2^-24 of the sum of magnitudes each, or half of the subnormal spacing 2^-149
     ok = np.isfinite(ref)
     assert (np.abs(a[ok].astype(np.float64) - exact[ok]) <= (K + 6) * 2.0 ** -24 * size[ok] + K * 2.0 ** -149).all()
+
+
+@pytest.mark.parametrize("K,H,O,T,N,delay", [(40, 256, 61, 96, 8, 1),          # one kind of tile per direction: of 64, 32 and 32
+                                             (130, 1030, 260, 700, 5, 1),      # tiles of 128 with a remainder, gradients in parts
+                                             (250, 250, 250, 1000, 3, 2),
+                                             (520, 2050, 24, 1030, 2, 0),      # narrow gradients beside a wide one: two launches
+                                             (5000, 520, 16, 200, 3, 0)])      # a long contraction added up over workgroups
+def test_products_in_every_kind_of_tile(K, H, O, T, N, delay):
+    test_products_at_tile_and_chunk_edges(K, H, O, T, N, delay)
+
+
+@pytest.mark.parametrize("K,H,O,T,delay", [(2 ** 22 + 5, 3, 2, 3, 1), (2, 2 ** 22 + 3, 2, 2, 0)])
+def test_rows_beyond_a_32_bit_tile(K, H, O, T, delay):
+    test_products_at_tile_and_chunk_edges(K, H, O, T, 1, delay)
+
+
+def test_more_products_than_one_launch_takes():
+    """45 sources of one node (a launch takes 40 products) and 91 weight matrices (24)."""
+    from oracle import graph_oracle as go
+    from paper_1503_02852_amd.runner import window_for
+    g = wl.GraphSpec()
+    x = g.add_node(wl.INPUT, wl.LINEAR, 7, name="x")
+    hs = [g.add_node(wl.ADD, wl.TANH, 3 + i % 40, name=f"h{i}") for i in range(45)]
+    a = g.add_node(wl.ADD, wl.LINEAR, 33, name="a")
+    o = g.add_node(wl.ADD, wl.LINEAR, 5, is_output=wl.SQUARED_ERROR, name="o")
+    for i, h in enumerate(hs):
+        g.add_edge(x, h, wl.FULL, 0)
+        g.add_edge(h, a, wl.FULL, i % 3)
+    g.add_edge(a, o, wl.FULL, 0)
+    w = wl.make_workload("many", g, T=20, N=3, seed=9, scale=0.3)
+    win = window_for(w)
+    win.step()
+    win.check()
+    ref = go.forward_bptt(w.spec.nodes, w.spec.edges, w.weights, w.biases, w.inputs, w.targets, w.T, w.N)
+    gw, _ = win.grads_unpacked()
+    # at most 45 x 42 terms per sum, three products in a row: 2^-24 times the root of the terms, times 100 for cancellation
+    for got, want in [(win.node_output(a), ref["y"][a]), (win.node_output(o), ref["y"][o])] + list(zip(gw, ref["grad_w"])):
+        assert np.abs(got - want).max() <= 3e-4 * np.abs(want).max()
