@@ -924,6 +924,15 @@ std::string jit_smstep_source(const Plan& P, const CompPlan& cp, bool backward, 
         }
         ngr.push_back({sidx, ((lay.src[sidx].k_len + CW - 1) / CW + D - 1) / D});
     }
+    bool symmetric = true;      // sources of one width that feed the same row tiles
+    for (int sidx = 0; sidx < lay.n_sources; ++sidx) {
+        symmetric = symmetric && ks[sidx].second == ks[0].second;
+        for (int nt = 0; nt < NTU; ++nt) {
+            auto feeds = [&](int s2) { return std::find(used.begin(), used.end(), std::make_pair(s2 * 16 + nt, 1)) != used.end(); };
+            symmetric = symmetric && feeds(sidx) == feeds(0);
+        }
+    }
+    o << "    static constexpr bool SYMMETRIC = " << (symmetric ? "true" : "false") << ";\n";
     emit_switch("K", "s", ks, 0); emit_switch("edge_", "key", edge_of, -1); emit_switch("used_", "key", used, 0); emit_switch("ngr", "s", ngr, 0);
     o << "    static __device__ __forceinline__ constexpr int edge(int s, int task) { return edge_(s * " << STEP_MAX_TASKS << " + task); }\n";
     o << "    static __device__ __forceinline__ constexpr bool used(int s, int nt) { return used_(s * 16 + nt) != 0; }\n};\n";
