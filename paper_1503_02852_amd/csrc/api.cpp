@@ -1096,13 +1096,10 @@ int rnn_forward_range(rnn_graph* g, const float* d_weights, const float* const* 
         // A new window: the control words (loss, error flags) start at zero, and so do the history
         // frames in front of every frame tensor (the state before a fresh window is zero).  Pieces
         // of a window computed later keep the flags an earlier piece has raised.
-        e = launch_fill(reinterpret_cast<float*>(g->ws + L.sync_off), SYNC_BYTES / 4, 0.0f, s);
-        if (e != hipSuccess) return fail_hip(e, "control word reset");
         g->xcd_words_used = 0;
-        if (H > 0) {
-            e = launch_zero_history(g->view().buf_ptr, reinterpret_cast<const int64_t*>(g->ws + L.frames_off), P.n_bufs, H, s);
-            if (e != hipSuccess) return fail_hip(e, "history reset");
-        }
+        e = launch_zero_history(g->view().buf_ptr, reinterpret_cast<const int64_t*>(g->ws + L.frames_off), P.n_bufs, H,
+                                reinterpret_cast<unsigned*>(g->ws + L.sync_off), (int)(SYNC_BYTES / 4), s);
+        if (e != hipSuccess) return fail_hip(e, "window reset");
     }
     // one-hot inputs with delayed connections: their class indices likewise (-1, the zero vector, in a fresh window's history)
     for (size_t i = 0; i < P.input_nodes.size(); ++i) {
@@ -1225,44 +1222,33 @@ int rnn_shift_window(rnn_graph* g, int32_t frames, void* hip_stream) {
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const int Ti = g->Ti();
     // y(t) <- y(t + frames) for every stored frame, the history frames in front of the window
-    // included: they then hold the frames right before the new window start.  Block by block in
-    // stream order, so that source and destination of one copy never overlap.
-    auto shift = [&](int b) -> hipError_t {
-        const int64_t fr = P.frame_floats(b, g->N);
-        float* y = g->buf(b);
-        for (int t = 0; t + frames < Ti; t += frames) {
-            const int n = std::min(frames, Ti - frames - t);
-            hipError_t e = hipMemcpyAsync(y + t * fr, y + (t + frames) * fr, (size_t)n * fr * sizeof(float), hipMemcpyDeviceToDevice, s);
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
+    // included: they then hold the frames right before the new window start.
+    ShiftTensors st;
+    st.count = 0;
+    auto shift = [&](void* p, int64_t frame_words) -> hipError_t {
+        st.p[st.count] = p; st.frame_words[st.count] = frame_words;
+        if (++st.count < SHIFT_MAX_TENSORS) return hipSuccess;
+        const hipError_t e = launch_shift_frames(st, frames, Ti, s);
+        st.count = 0;
+        return e;
     };
-    for (size_t k = 0; k < P.xnodes.size(); ++k) {
+    hipError_t e = hipSuccess;
+    for (size_t k = 0; k < P.xnodes.size() && e == hipSuccess; ++k) {
         const int b = P.ybuf((int)k);
         if (g->layout.buf_off[b] < 0) continue;      // an input read in place: the caller shifts it
-        hipError_t e = shift(b);
-        if (e != hipSuccess) return fail_hip(e, "window shift");
-        if (P.twin_base >= 0 && g->layout.buf_off[P.twin_base + b] >= 0) {      // its tile-blocked twin
-            e = shift(P.twin_base + b);
-            if (e != hipSuccess) return fail_hip(e, "window shift");
-        }
+        e = shift(g->buf(b), P.frame_floats(b, g->N));
+        const int twin = P.twin_base + b;      // its tile-blocked twin
+        if (e == hipSuccess && P.twin_base >= 0 && g->layout.buf_off[twin] >= 0) e = shift(g->buf(twin), P.frame_floats(twin, g->N));
     }
-    for (size_t k = 0; k < P.xnodes.size(); ++k) {
+    for (size_t k = 0; k < P.xnodes.size() && e == hipSuccess; ++k) {
         int32_t* hist_idx = g->is_onehot((int)k) ? g->onehot_history((int)k) : nullptr;
-        if (!hist_idx) continue;
-        const int64_t fr = g->N;
-        for (int t = 0; t + frames < Ti; t += frames) {
-            const int n = std::min(frames, Ti - frames - t);
-            hipError_t e = hipMemcpyAsync(hist_idx + t * fr, hist_idx + (t + frames) * fr, (size_t)n * fr * sizeof(int32_t), hipMemcpyDeviceToDevice, s);
-            if (e != hipSuccess) return fail_hip(e, "window shift");
-        }
+        if (hist_idx) e = shift(hist_idx, g->N);
     }
     // interleaved exchange tensors of forward activations move along with their members
-    for (const BundlePlan& bp : P.bundles) {
-        if (bp.members[0] >= (int)P.xnodes.size() || g->layout.buf_off[bp.ebuf] < 0) continue;
-        hipError_t e = shift(bp.ebuf);
-        if (e != hipSuccess) return fail_hip(e, "window shift");
-    }
+    for (const BundlePlan& bp : P.bundles)
+        if (e == hipSuccess && bp.members[0] < (int)P.xnodes.size() && g->layout.buf_off[bp.ebuf] >= 0) e = shift(g->buf(bp.ebuf), P.frame_floats(bp.ebuf, g->N));
+    if (e == hipSuccess) e = launch_shift_frames(st, frames, Ti, s);
+    if (e != hipSuccess) return fail_hip(e, "window shift");
     g->fwd_upto = g->T - frames;
     g->fwd_done = g->bptt_done = false;
     return RNN_OK;

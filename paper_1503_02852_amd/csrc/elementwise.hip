@@ -427,19 +427,57 @@ hipError_t launch_upload_words(uint32_t* d_dst, const uint32_t* h_src, int64_t n
 }
 
 namespace {
-// blockIdx.x: the buffer.
-__global__ __launch_bounds__(256) void zero_history_kernel(float* const* __restrict__ buf_ptr, const int64_t* __restrict__ frame_floats, int frames) {
+// blockIdx.x: the buffer; behind the last one the control words.
+__global__ __launch_bounds__(256) void zero_history_kernel(float* const* __restrict__ buf_ptr, const int64_t* __restrict__ frame_floats, int n_bufs, int frames,
+                                                           unsigned* __restrict__ ctrl, int ctrl_words) {
     const int b = blockIdx.x;
+    if (b == n_bufs) {
+        if (blockIdx.y == 0) for (int i = threadIdx.x; i < ctrl_words; i += 256) ctrl[i] = 0u;
+        return;
+    }
     const long long n = (long long)frames * frame_floats[b];
     if (n <= 0) return;
     float* p = buf_ptr[b];
     for (long long i = blockIdx.y * 256 + threadIdx.x; i < n; i += 256LL * gridDim.y) p[i] = 0.0f;
 }
+
+// y(t) <- y(t + frames) for all stored frames of up to SHIFT_MAX_TENSORS tensors.  A thread walks a chain of its own, the elements
+// that lie whole shifts apart (of one or four floats), so that source and destination may overlap; eight of
+// a chain's elements are in flight.  One copy per tensor and piece before: 2 x 512 LSTM, 256 of 512 frames 121 -> 8 us, one of 2 frames 59 -> 3 us.
+template <class V>
+__device__ __forceinline__ void shift_tensor(V* y, long long frame, int frames, int stored) {
+    const long long step = frame * frames, last = frame * (stored - frames);
+    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < step && i < last; i += 256LL * gridDim.x) {
+        long long at = i;
+        for (; at + 7 * step < last; at += 8 * step) {
+            V v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = y[at + (j + 1) * step];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) y[at + j * step] = v[j];
+        }
+        for (; at < last; at += step) y[at] = y[at + step];
+    }
+}
+__global__ __launch_bounds__(256) void shift_frames_kernel(const ShiftTensors s, int frames, int stored) {
+    const int b = blockIdx.y;
+    void* p = s.p[b];
+    if (s.frame_words[b] % 4 == 0 && ((uintptr_t)p & 15) == 0) shift_tensor(static_cast<uint4*>(p), s.frame_words[b] / 4, frames, stored);
+    else shift_tensor(static_cast<uint32_t*>(p), s.frame_words[b], frames, stored);
+}
 }  // namespace
 
-hipError_t launch_zero_history(float* const* buf_ptr, const int64_t* frame_floats, int n_bufs, int frames, hipStream_t stream) {
-    if (n_bufs <= 0 || frames <= 0) return hipSuccess;
-    hipLaunchKernelGGL(zero_history_kernel, dim3((unsigned)n_bufs, 4), dim3(256), 0, stream, buf_ptr, frame_floats, frames);
+hipError_t launch_zero_history(float* const* buf_ptr, const int64_t* frame_floats, int n_bufs, int frames, unsigned* ctrl, int ctrl_words, hipStream_t stream) {
+    hipLaunchKernelGGL(zero_history_kernel, dim3((unsigned)n_bufs + 1, frames > 0 ? 4 : 1), dim3(256), 0, stream, buf_ptr, frame_floats, n_bufs, frames, ctrl, ctrl_words);
+    return hipGetLastError();
+}
+
+hipError_t launch_shift_frames(const ShiftTensors& s, int frames, int stored, hipStream_t stream) {
+    if (s.count <= 0) return hipSuccess;
+    int64_t most = 0;
+    for (int i = 0; i < s.count; ++i) most = std::max(most, s.frame_words[i] * std::min(frames, stored - frames));
+    const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>((most / 4 + 255) / 256, 1024)), (unsigned)s.count);
+    hipLaunchKernelGGL(shift_frames_kernel, grid, dim3(256), 0, stream, s, frames, stored);
     return hipGetLastError();
 }
 

@@ -69,9 +69,13 @@ hipError_t launch_squared_error_delta(const float* y, const float* d, float* ds,
 // The sums run over frames [t0, T); factors may reach back to frames before t0.
 hipError_t launch_colsum(const PlanView& pv, int tasks_off, int n_tasks, int max_dim, const float* weights, float* grads,
                          int T, int N, int t0, bool one_writer, hipStream_t stream);
-// Zeroes the history frames in front of a fresh window: `frames` frames of frame_floats[b] floats of
-// every buffer b (0: the buffer keeps none).
-hipError_t launch_zero_history(float* const* buf_ptr, const int64_t* frame_floats, int n_bufs, int frames, hipStream_t stream);
+// A fresh window: zeroes its control words and the history frames in front of it, `frames` frames of
+// frame_floats[b] floats of every buffer b (0: the buffer keeps none).
+hipError_t launch_zero_history(float* const* buf_ptr, const int64_t* frame_floats, int n_bufs, int frames, unsigned* ctrl, int ctrl_words, hipStream_t stream);
+// Moves `stored` frames of up to SHIFT_MAX_TENSORS tensors `frames` frames ahead, in place (the last `frames` keep what they held).
+constexpr int SHIFT_MAX_TENSORS = 96;
+struct ShiftTensors { void* p[SHIFT_MAX_TENSORS]; int64_t frame_words[SHIFT_MAX_TENSORS]; int count; };      // 32-bit words per frame
+hipError_t launch_shift_frames(const ShiftTensors& s, int frames, int stored, hipStream_t stream);
 hipError_t launch_fill(float* p, int64_t n, float v, hipStream_t stream);
 // rnn_forward_static's array for windows that need twins of ragged tiles beside RNN_STATIC_WORKSPACE_BYTES (32 MiB): at most
 // four times as many floats as their tensors (width 1), and the space between tensors.

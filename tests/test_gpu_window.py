@@ -245,3 +245,22 @@ def test_layers_on_one_xcd_after_several_streams_have_been_used():
             assert abs(win.compute_grads(want_loss=True) - ref["loss"]) <= 1e-5 * max(1.0, abs(ref["loss"]))      # (reports flags too)
         s.synchronize()
         check_against(win, w, ref, "streams")
+
+
+@pytest.mark.parametrize("T,N,hidden,frames", [(2, 1, 16, 1), (23, 1, 5, 1), (23, 3, 7, 2), (40, 16, 32, 3), (23, 5, 16, 22), (12, 20, 33, 6)])
+def test_shift_moves_every_frame(T, N, hidden, frames):
+    """Chains of every length (T / frames around eight and its multiples), tensors of whole and of ragged
+    groups of four floats, twins: the frames that stay are the same bits, moved."""
+    from paper_1503_02852_amd.runner import window_for
+    spec = wl.lstm_net(6, [hidden, hidden], 5)
+    w = wl.make_workload("shift", spec, T=T, N=N, seed=T + N, scale=0.4)
+    win = window_for(w)
+    win.forward()
+    nodes = [k for k, n in enumerate(spec.nodes) if n["kind"] != wl.INPUT]
+    before = {k: win.node_output(k).copy() for k in nodes}
+    rng = np.random.default_rng(1)
+    x, o = spec.input_nodes()[0], spec.output_nodes()[0]
+    win.advance({x: rng.standard_normal((frames, N, 6)).astype(np.float32)}, {o: np.zeros((frames, N), np.int32)})
+    win.check()
+    for k in nodes:
+        assert np.array_equal(win.node_output(k)[:T - frames], before[k][frames:]), spec.nodes[k]["name"]
