@@ -504,7 +504,9 @@ namespace {
 // Launches the GEMM problems of one component and direction, grouped by up to
 // GEMM_MAX_PROBLEMS destinations per launch and GEMM_MAX_PAIRS products per destination.
 // Rows of frames [t0, t1) only.
-hipError_t run_gemms(rnn_graph* g, const std::vector<GemmProblemPlan>& probs, bool backward, hipStream_t s, int t0, int t1) {
+// finish: the component whose program these products can finish (CompPlan::in_products), or NULL; *finished is set if they did.
+hipError_t run_gemms(rnn_graph* g, const std::vector<GemmProblemPlan>& probs, bool backward, hipStream_t s, int t0, int t1,
+                     const CompPlan* finish = nullptr, bool* finished = nullptr) {
     // t0, t1: internal frames
     const int64_t F = (int64_t)g->Ti() * g->N, HN = (int64_t)g->hist() * g->N;
     const int64_t r0 = (int64_t)t0 * g->N, rows = (int64_t)(t1 - t0) * g->N;
@@ -524,6 +526,13 @@ hipError_t run_gemms(rnn_graph* g, const std::vector<GemmProblemPlan>& probs, bo
         if (tiles < 256) split = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(16, kmax / 512), (512 + tiles - 1) / tiles));
         for (int i = 0; i < grp.n_problems; ++i) grp.p[i].min_split = split;
         plan_gemm_group(backward ? GEMM_NN : GEMM_NT, grp, g->deterministic);
+        // one unsplit product, all of its pairs in this launch and none of them a gather (below): the node's program is done where it is
+        // stored.  (2048 rows of 20,000 columns: the program's launch took 210 us, two passes over 164 MB.)
+        if (finish && finish->in_products && grp.n_problems == 1 && grp.n_pairs == (int)probs[0].pairs.size() && grp.p[0].split == 1 && !grp.p[0].accumulate) {
+            grp.p[0].bias = finish->products_bias >= 0 ? g->weights + finish->products_bias : nullptr;
+            grp.p[0].act = finish->products_act;
+            *finished = true;
+        }
         for (int i = 0; i < grp.n_problems; ++i) {
             if (grp.p[i].split == 1 || grp.p[i].accumulate) continue;
             hipError_t e = launch_fill(grp.p[i].C, (int64_t)grp.p[i].M * grp.p[i].ldc, 0.0f, s);
@@ -1019,10 +1028,13 @@ int forward_frames(rnn_graph* g, int t0, int t1, hipStream_t s) {
             if (r.error) return fail(r.code, "forward: " + r.err);
             if (r.e == hipSuccess) { chain_done_to = ch.last; continue; }
         }
-        e = run_gemms(g, cp.fwd_gemms, false, s, t0, t1);
+        bool finished = false;
+        e = run_gemms(g, cp.fwd_gemms, false, s, t0, t1, &cp, &finished);
         if (e != hipSuccess) return fail_hip(e, "forward GEMM");
-        const StepRun r = run_phases(g, c, false, s, t0, t1);
-        if (r.error) return fail(r.code, "forward: " + r.err);
+        if (!finished) {
+            const StepRun r = run_phases(g, c, false, s, t0, t1);
+            if (r.error) return fail(r.code, "forward: " + r.err);
+        }
         if (cp.softmax_node >= 0) {
             const int dim = P.xnodes[cp.softmax_node].dim;
             e = launch_softmax_rows(g->buf(P.ybuf(cp.softmax_node)) + (int64_t)t0 * N * dim, (int64_t)(t1 - t0) * N, dim, s);

@@ -27,6 +27,8 @@
 #include <cstdlib>
 #include <type_traits>
 
+#include "graph.h"
+#include "interp.h"
 #include "kernels.h"
 
 namespace rnng {
@@ -121,6 +123,12 @@ template <bool KC, int T> struct Operand {
             for (int t = 0; t < T; ++t) f[i][t] = at[(4 * q + 2 * i) * R + 64 * t];
     }
 };
+
+// What a node's program does to its products (interp.h), in the order it does it.
+__device__ __forceinline__ float finish(float v, bool has_bias, float bias, int act) {
+    if (has_bias) v += bias;
+    return act == ACT_SIGMOID ? sigmoid_f(v) : act == ACT_TANH ? tanh_f(v) : act == ACT_RELU ? fmaxf(v, 0.0f) : v;
+}
 
 template <bool A_KC, bool B_KC, int T>
 __global__ __launch_bounds__(NTHREADS, T == 2 ? 4 : 6) void gemm_kernel(const GemmGroup g) {
@@ -244,6 +252,17 @@ __global__ __launch_bounds__(NTHREADS, T == 2 ? 4 : 6) void gemm_kernel(const Ge
     }
     const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(P.C + (long long)m0 * P.ldc + n0, 0, rsrc_bytes((long long)(P.M - m0) * P.ldc - n0), RSRC_FLAGS);
     const int row_bytes = 4 * P.ldc;
+    if (P.bias != nullptr || P.act != ACT_LINEAR) {
+#pragma unroll
+        for (int y = 0; y < T; ++y) {
+            const int col = n0 + brow + 64 * y;
+            const float bias = P.bias != nullptr && col < P.N ? P.bias[col] : 0.0f;
+#pragma unroll
+            for (int x = 0; x < T; ++x)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[x][y][e] = finish(acc[x][y][e], P.bias != nullptr, bias, P.act);
+        }
+    }
 #pragma unroll
     for (int y = 0; y < T; ++y) {
         const int at = n0 + brow + 64 * y < P.N ? (row0 - m0) * row_bytes + 4 * (brow + 64 * y) : OUTSIDE;
@@ -359,7 +378,7 @@ __global__ __launch_bounds__(64 * SMALL_WAVES, 4) void gemm_small_kernel(const G
         if (row < P.M && col < P.N) {
             float* dst = P.C + (size_t)row * P.ldc + col;
             if (P.split > 1 || P.accumulate) unsafeAtomicAdd(dst, s);
-            else *dst = s;
+            else *dst = finish(s, P.bias != nullptr, P.bias != nullptr ? P.bias[col] : 0.0f, P.act);
         }
     }
 }

@@ -24,6 +24,8 @@ struct GemmPair {
 struct GemmProblem {
     float* C; int ldc, M, N, first_pair, n_pairs;
     int accumulate;         // 1: C += result instead of C = result
+    const float* bias;      // stored is f(result + bias[column]) (NULL: none), f by act (ACT_*); only where the result is stored by
+    int act;                // one workgroup (split == 1, no accumulate)
     int min_split;          // the contraction is split into no fewer parts than this (their sums round no less than these)
     // by plan_gemm_group:
     int split;              // > 1: that many workgroups share the contraction of a tile and add to C, which must be zero

@@ -452,6 +452,13 @@ bool build_plan(const std::vector<GNode>& nodes, const std::vector<GEdge>& edges
             if (!emit_phase(P, cp.fwd_phases, tasks, ops, part_bufs, written, shared, cp.recurrent ? -1 : 0, err)) return false;
         }
         cp.has_fwd_program = true;
+        if (!cp.recurrent && members.size() == 1 && xn[members[0]].kind == NODE_ADD && cp.fwd_gemms.size() == 1) {
+            const int k = members[0];
+            cp.in_products = cp.fwd_gemms[0].c_buf == P.ybuf(k);
+            for (int m : in_e[k]) cp.in_products = cp.in_products && xe[m].wkind == W_FULL && batched(m);
+            cp.products_act = xn[k].act == ACT_SIGMOID || xn[k].act == ACT_TANH || xn[k].act == ACT_RELU ? xn[k].act : ACT_LINEAR;
+            cp.products_bias = xn[k].has_bias ? (int)P.bias_off[k] : -1;
+        }
         auto emit_desc = [&](const std::vector<PhasePlan>& phs) {
             const int off = (int)P.words.size();
             P.words.push_back((int)phs.size());

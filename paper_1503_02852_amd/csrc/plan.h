@@ -52,6 +52,9 @@ struct CompPlan {
     // buffers that workgroups of the persistent step kernel read from each other (sources of
     // full connections inside the recurrent node); they are pre-filled with a sentinel
     std::vector<int> fwd_shared_bufs, bwd_shared_bufs;
+    // an ordinary additive node that only batched products lead into: its program is y = f(products + bias), which the products'
+    // kernel can finish where it stores them (act: ACT_*; bias_off -1: none)
+    bool in_products = false; int products_act = 0, products_bias = -1;
     int64_t step_weight_floats = 0;         // weights of all full connections inside the component
     int chain = -1;                         // index into Plan::chains if the component is a chain member
     bool helper = false;                    // a helper member of a chain launch (ChainPlan::fwd_split / bwd_split)

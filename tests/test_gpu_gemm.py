@@ -108,3 +108,27 @@ def test_more_products_than_one_launch_takes():
     # at most 45 x 42 terms per sum, three products in a row: 2^-24 times the root of the terms, times 100 for cancellation
     for got, want in [(win.node_output(a), ref["y"][a]), (win.node_output(o), ref["y"][o])] + list(zip(gw, ref["grad_w"])):
         assert np.abs(got - want).max() <= 3e-4 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("act", [wl.LINEAR, wl.SIGMOID, wl.TANH, wl.RELU])
+@pytest.mark.parametrize("K,H,O,T,N", [(5, 7, 3, 6, 1), (70, 130, 65, 130, 1), (90, 520, 300, 1100, 3), (4500, 40, 30, 9, 2)])
+def test_nodes_finished_where_their_products_are_stored(K, H, O, T, N, act):
+    """y = f(W x + b) of nodes that only products lead into, in every kind of tile, and where the products are split
+    (the last case) by a program of its own; a second source, delayed, feeds the output node."""
+    from oracle import graph_oracle as go
+    from paper_1503_02852_amd.runner import window_for
+    g = wl.GraphSpec()
+    x = g.add_node(wl.INPUT, wl.LINEAR, K, name="x")
+    a = g.add_node(wl.ADD, act, H, has_bias=True, name="a")
+    o = g.add_node(wl.ADD, wl.SOFTMAX, O, has_bias=True, is_output=1, name="o")
+    g.add_edge(x, a, wl.FULL, 0)
+    g.add_edge(a, o, wl.FULL, 0)
+    g.add_edge(a, o, wl.FULL, 1)
+    w = wl.make_workload("finish", g, T=T, N=N, seed=K + O, scale=0.6 / np.sqrt(K), bias_scale=0.5)
+    win = window_for(w)
+    win.step()
+    win.check()
+    ref = go.forward_bptt(w.spec.nodes, w.spec.edges, w.weights, w.biases, w.inputs, w.targets, w.T, w.N)
+    # sums of K and 2 H products, rounded by 2^-24 of their size each, through functions of slope 1 and below
+    for k in (a, o):
+        assert np.abs(win.node_output(k) - ref["y"][k]).max() <= (K + 2 * H + 20) * 2.0 ** -24 * max(1.0, np.abs(ref["y"][k]).max())
