@@ -162,24 +162,25 @@ __global__ __launch_bounds__(SMX_THREADS) void softmax_wide_rows_kernel(float* _
     }
 }
 
+// One wavefront per row.  The workgroups' losses meet in one address, about 13 ns each: a workgroup takes several rows where
+// rows are short, so that the additions don't outlast the rows (8,192 rows of 30 / 256 columns 27 / 29 -> 11 / 14 us).
 __global__ __launch_bounds__(256) void softmax_ce_delta_kernel(const float* __restrict__ y, const int32_t* __restrict__ targets,
                                                                float* __restrict__ ds, double* loss, unsigned* flag, long long rows, int dim) {
-    __shared__ float wl[4];
-    const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    __shared__ double wl[4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float l = 0.0f;
-    if (row < rows) {
+    double l = 0.0;
+    for (long long row = (long long)blockIdx.x * 4 + wave; row < rows; row += 4LL * gridDim.x) {
         int tg = targets[row];
         if (tg >= dim) { if (lane == 0) atomicMax(flag, 3u); tg = -1; }      // not a class of this layer: the frame is left out
         const float* p = y + row * dim;
         float* d = ds + row * dim;
         for (int i = lane; i < dim; i += 64) d[i] = tg >= 0 ? p[i] - (i == tg ? 1.0f : 0.0f) : 0.0f;
-        if (tg >= 0 && lane == 0) l = -__logf(p[tg]);
+        if (tg >= 0 && lane == 0) l += (double)-__logf(p[tg]);
     }
     if (lane == 0) wl[wave] = l;
     __syncthreads();
     if (threadIdx.x == 0) {
-        const double s = (double)wl[0] + (double)wl[1] + (double)wl[2] + (double)wl[3];
+        const double s = wl[0] + wl[1] + wl[2] + wl[3];
         if (s != 0.0) atomicAdd(loss, s);
     }
 }
@@ -251,6 +252,51 @@ __global__ __launch_bounds__(256) void squared_error_delta_kernel(const float* _
     }
 }
 
+// The sum over rows of the product of NF factors without comparisons, for one unit.  Bound by memory: the factors' addresses are
+// worked out once and eight rows' loads are in flight.  One row at a time, each behind the reads of its descriptor, before: three layers of
+// 1,024 units at 64 x 128 frames 407 -> 150 us, 2 x 512 at 32 x 256 119 -> 44, 2 x 256 at 1,024 frames 19 -> 7.
+template <int NF>
+__device__ __forceinline__ float colsum_products(const PlanView& pv, const int32_t* w, const float* __restrict__ weights, int i, int dim, long long N,
+                                                 long long rows, long long r, long long step) {
+    const float* q[NF];
+    long long shift[NF];
+    float wf[NF];
+    bool weighted[NF];
+#pragma unroll
+    for (int j = 0; j < NF; ++j) {
+        const int32_t* f = w + CS_HEADER_WORDS + j * CF_WORDS;
+        shift[j] = f[CF_FRAME_OFF] * N;
+        q[j] = pv.buf_ptr[f[CF_BUF]] + i;
+        weighted[j] = f[CF_W_OFF] >= 0;
+        wf[j] = weighted[j] ? weights[f[CF_W_OFF] + i] : 1.0f;
+    }
+    constexpr int U = 8;
+    float s = 0.0f;
+    for (; r < rows; r += U * step) {
+        float v[NF][U];
+        bool ok[NF][U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < NF; ++j) {
+                const long long at = r + u * step + shift[j];
+                ok[j][u] = at >= 0 && at < rows && r + u * step < rows;
+                v[j][u] = q[j][(ok[j][u] ? at : 0) * dim];
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            float prod = 1.0f;
+#pragma unroll
+            for (int j = 0; j < NF; ++j) {
+                const float x = ok[j][u] ? v[j][u] : 0.0f;
+                prod *= weighted[j] ? x * wf[j] : x;
+            }
+            s += r + u * step < rows ? prod : 0.0f;
+        }
+    }
+    return s;
+}
+
 // grid: (ceil(dim / 64), n_tasks, row splits); block (64, 4).
 __global__ __launch_bounds__(256) void colsum_kernel(PlanView pv, int tasks_off, const float* __restrict__ weights,
                                                      float* __restrict__ grads, int T, int N, int t0) {
@@ -258,11 +304,16 @@ __global__ __launch_bounds__(256) void colsum_kernel(PlanView pv, int tasks_off,
     const int32_t* w = pv.words + tasks_off;
     for (int task = 0; task < (int)blockIdx.y; ++task) w += CS_HEADER_WORDS + w[CS_NFACTORS] * CF_WORDS;
     const int dim = w[CS_DIM], nf = w[CS_NFACTORS];
+    if ((int)blockIdx.x * 64 >= dim) return;
     const int i = blockIdx.x * 64 + threadIdx.x;
-    const long long rows = (long long)T * N;
+    const long long rows = (long long)T * N, first = (long long)t0 * N + (long long)blockIdx.z * 4 + threadIdx.y, step = 4LL * gridDim.z;
+    bool plain = nf <= 2;
+    for (int j = 0; j < nf && plain; ++j) plain = w[CS_HEADER_WORDS + j * CF_WORDS + CF_CMP] == 0;
     float s = 0.0f;
-    if (i < dim) {
-        for (long long r = (long long)t0 * N + (long long)blockIdx.z * 4 + threadIdx.y; r < rows; r += 4LL * gridDim.z) {
+    if (i < dim && plain && nf == 1) s = colsum_products<1>(pv, w, weights, i, dim, N, rows, first, step);
+    else if (i < dim && plain && nf == 2) s = colsum_products<2>(pv, w, weights, i, dim, N, rows, first, step);
+    else if (i < dim) {
+        for (long long r = first; r < rows; r += step) {
             const int t = (int)(r / N), n = (int)(r % N);
             float prod = 1.0f;
             auto value = [&](int j) {
@@ -350,8 +401,8 @@ hipError_t launch_softmax_ce_delta(const float* y, const int32_t* targets, float
                            dim3(256), 0, stream, y, targets, ds, loss, flag, (long long)rows, dim);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(softmax_ce_delta_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, y, targets, ds, loss, flag,
-                       (long long)rows, dim);
+    const int64_t blocks = std::min<int64_t>((rows + 3) / 4, dim <= 256 ? 512 : 2048);
+    hipLaunchKernelGGL(softmax_ce_delta_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, y, targets, ds, loss, flag, (long long)rows, dim);
     return hipGetLastError();
 }
 
@@ -359,7 +410,7 @@ hipError_t launch_squared_error_delta(const float* y, const float* d, float* ds,
                                       hipStream_t stream) {
     if (n <= 0) return hipSuccess;
     long long blocks = (n + 255) / 256;
-    if (blocks > 2048) blocks = 2048;
+    if (blocks > 512) blocks = n > (1 << 22) ? 2048 : 512;      // (their losses meet in one address, 13 ns each: 3,000 x 61 10.3 -> 7.8 us)
     hipLaunchKernelGGL(squared_error_delta_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, y, d, ds, loss, (long long)n, act);
     return hipGetLastError();
 }

@@ -66,3 +66,41 @@ def test_output_delta_of_many_rows_around_the_change_of_kernels(O, T):
     l = -np.log(y[tg >= 0, tg[tg >= 0]].astype(np.float64))
     # a few roundings of each logarithm; sums of up to four in fp32, the rest in double
     assert abs(loss - l.sum()) <= 2.0 ** -22 * (4 * np.abs(l).sum() + 2 * len(l))
+
+
+@pytest.mark.parametrize("T,N", [(1, 1), (9, 1), (65, 1), (130, 5), (700, 3), (300, 20)])
+def test_sums_over_frames(T, N):
+    """Bias and peephole gradients (sums over all frames of one and of two factors, one of them a frame back) and the
+    loss, at row counts around the groups that a thread takes at once, against float64 on the GPU's own factors."""
+    from paper_1503_02852_amd.runner import window_for
+    spec = wl.lstm_net(4, [70], 9)
+    w = wl.make_workload("sums", spec, T=T, N=N, seed=T + N, scale=0.4, bias_scale=0.3, masked_fraction=0.2)
+    win = window_for(w)
+    win.forward()
+    win.bptt()
+    loss = win.compute_grads(want_loss=True)
+    gw, gb = win.grads_unpacked()
+
+    def check(got, a, b):
+        # a product and a sum over T N frames, each rounded by 2^-24 of the magnitudes' sum
+        want, size = (a * b).sum(axis=(0, 1)), np.abs(a * b).sum(axis=(0, 1))
+        assert (np.abs(got - want) <= (T * N + 4) * 2.0 ** -24 * size + 1e-37).all()
+
+    sums = 0
+    for k, node in enumerate(spec.nodes):
+        if node["has_bias"]:
+            check(gb[k], win.node_state_grad(k).astype(np.float64), 1.0)
+            sums += 1
+    for m, e in enumerate(spec.edges):
+        if e["wkind"] == wl.DIAG and spec.nodes[e["dst"]]["kind"] == wl.ADD:
+            y = np.zeros((T, N, 70))
+            y[e["delay"]:] = win.node_output(e["src"])[:T - e["delay"]]
+            check(gw[m], win.node_state_grad(e["dst"]).astype(np.float64), y)
+            sums += 1
+    assert sums >= 8
+    (o,) = spec.output_nodes()
+    tg = w.targets[o].reshape(-1)
+    p = win.node_output(o).astype(np.float64).reshape(T * N, -1)[np.arange(T * N), np.maximum(tg, 0)]
+    want = -np.log(p[tg >= 0]).sum()
+    # the hardware logarithm's error (2 ulp of log2 near 1: 2^-22 absolute) per frame
+    assert abs(loss - want) <= 2.0 ** -21 * max(1.0, T * N) + 1e-6 * want
