@@ -739,7 +739,7 @@ StepRun run_phases(rnn_graph* g, int comp, bool backward, hipStream_t s, int t0,
     if (!cp.recurrent) {
         const int prof = g->prof.begin(RNN_PROF_OTHER, s);
         for (const PhasePlan& ph : phases) {
-            hipError_t e = launch_node_program(pv, ph.prog_off, ph.max_dim, g->weights, T, N, t0, t1, s);
+            hipError_t e = launch_node_program(pv, ph.prog_off, ph.max_dim, ph.quads, g->weights, T, N, t0, t1, s);
             if (e != hipSuccess) return step_error(e, "node program launch");
         }
         g->prof.end(prof, (int64_t)phases.size(), s);
@@ -833,7 +833,7 @@ StepRun run_phases(rnn_graph* g, int comp, bool backward, hipStream_t s, int t0,
                 if (e != hipSuccess) return step_error(e, "per-frame matrix-vector launch");
                 ++n_launch;
             }
-            hipError_t e = launch_node_program(pv, ph.prog_off, ph.max_dim, g->weights, T, N, t, t + 1, s);
+            hipError_t e = launch_node_program(pv, ph.prog_off, ph.max_dim, ph.quads, g->weights, T, N, t, t + 1, s);
             if (e != hipSuccess) return step_error(e, "per-frame node program launch");
             ++n_launch;
         }

@@ -51,8 +51,8 @@ hipError_t launch_gemm_group(GemmMode mode, const GemmGroup& g, hipStream_t stre
 // ---------------------------------------------------------------------------------------
 // Element-wise node programs, step matrix-vector products, softmax, reductions
 // ---------------------------------------------------------------------------------------
-// Runs a node program for frames [t0, t1) and all streams.
-hipError_t launch_node_program(const PlanView& pv, int prog_off, int max_dim, const float* weights,
+// Runs a node program for frames [t0, t1) and all streams.  quads: all of its vectors are max_dim wide, a multiple of 4.
+hipError_t launch_node_program(const PlanView& pv, int prog_off, int max_dim, bool quads, const float* weights,
                                int T, int N, int t0, int t1, hipStream_t stream);
 // Matrix-vector task list for frame t (per-step launch).
 hipError_t launch_step_matvec(const PlanView& pv, int mv_off, int n_tasks, int max_out, const float* weights,

@@ -61,6 +61,18 @@ struct Lowering {
     }
 };
 
+// (see PhasePlan::quads)
+bool program_in_quads(const int32_t* p) {
+    const int dim = p[PG_MAXDIM];
+    bool ok = dim % 4 == 0 && p[PG_NSLOTS] <= QUAD_SLOTS;
+    const int32_t* e = p + PG_HEADER_WORDS;
+    for (int g = 0; g < p[PG_NGATHER]; ++g, e += GA_WORDS) ok = ok && e[GA_DIM] == dim && e[GA_KIND] != GA_KIND_ACC;
+    for (int v = 0; v < p[PG_NINV]; ++v, e += IV_WORDS) ok = ok && e[IV_DIM] == dim;
+    e += p[PG_NOPS] * MO_WORDS;
+    for (int q = 0; q < p[PG_NSTORES]; ++q, e += ST_WORDS) ok = ok && e[ST_DIM] == dim;
+    return ok;
+}
+
 // Returns the word offset of the program, or -1 (with err set) if it needs too many slots.
 int emit_program(std::vector<int32_t>& w, const std::vector<OpH>& all_ops, int first, int last,
                  const std::vector<int>& buf_dim, int& max_dim, bool dry_run, const EmitCtx* ctx = nullptr) {
@@ -273,6 +285,7 @@ bool emit_phase(Plan& P, std::vector<PhasePlan>& out, const std::vector<MvTaskH>
         PhasePlan ph;
         if (first_part && !tasks.empty()) { ph.mv_off = emit_matvecs(P.words, tasks, ph.mv_max_out); ph.n_mv_tasks = (int)tasks.size(); }
         ph.prog_off = emit_program(P.words, ops, first, last, P.buf_dim, ph.max_dim, false, &ctx);
+        ph.quads = ph.prog_off >= 0 && program_in_quads(P.words.data() + ph.prog_off);
         out.push_back(ph);
         first = last; first_part = false;
     }

@@ -37,6 +37,7 @@ struct PhasePlan {
     int mv_off = -1;     // word offset of the matrix-vector task list (-1: none)
     int prog_off = -1;   // word offset of the node program
     int max_dim = 0;
+    bool quads = false;  // the program takes at most QUAD_SLOTS, all of its vectors are max_dim wide, a multiple of 4, and none is a matrix-vector accumulator
     int mv_max_out = 0;  // largest n_out over the tasks
     int n_mv_tasks = 0;
 };

@@ -64,6 +64,8 @@ enum { ST_BUF = 0, ST_SLOT, ST_DIM, ST_FLAGS, ST_WORDS };         // flags bit 0
 
 constexpr int MAX_SLOTS = 32;     // a 32-float slot file stays in vector registers (indexed with uniform indices)
 
+constexpr int QUAD_SLOTS = 12;    // of a program that runs on four units per thread (PhasePlan::quads)
+
 inline int program_words(const int32_t* p) {
     return PG_HEADER_WORDS + p[PG_NGATHER] * GA_WORDS + p[PG_NINV] * IV_WORDS + p[PG_NOPS] * MO_WORDS +
            p[PG_NSTORES] * ST_WORDS;

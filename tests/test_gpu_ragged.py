@@ -63,3 +63,22 @@ def test_ragged_windows_in_pieces_and_moved_ahead(monkeypatch, layers, N):
         monkeypatch.setattr(wl, "make_workload", lambda *a, **k: make(*a, **{**k, "scale": 1.5 / max(layers) ** 0.5}))
     tw.test_window_computed_in_pieces_equals_the_window_at_once("ragged")
     tw.test_window_moved_ahead_with_carried_state("ragged")
+
+
+@pytest.mark.parametrize("dim,T,N", [(4, 5, 1), (8, 9, 3), (36, 30, 7), (128, 3, 40), (6, 9, 3), (33, 9, 2)])
+def test_element_wise_programs_of_ordinary_nodes(dim, T, N):
+    """Programs over whole groups of four units and over others: products, maxima, every activation, biases, diagonal and
+    identity connections, one of them delayed, against the oracle (bars of the parity tests)."""
+    from tests.test_gpu_parity import run_both
+    g = wl.GraphSpec()
+    x = g.add_node(wl.INPUT, wl.LINEAR, dim, name="x")
+    a = g.add_node(wl.ADD, wl.TANH, dim, has_bias=True, name="a")
+    b = g.add_node(wl.ADD, wl.SIGMOID, dim, has_bias=True, name="b")
+    m = g.add_node(wl.MUL, wl.LINEAR, dim, name="m")
+    mx = g.add_node(wl.MAX, wl.LINEAR, dim, name="mx")
+    r = g.add_node(wl.ADD, wl.RELU, dim, has_bias=True, name="r")
+    o = g.add_node(wl.ADD, wl.SOFTMAX, 5, has_bias=True, is_output=wl.CROSS_ENTROPY, name="o")
+    for src, dst, kind, delay in [(x, a, wl.FULL, 0), (x, b, wl.FULL, 0), (x, a, wl.DIAG, 1), (a, m, wl.IDENTITY, 0), (b, m, wl.DIAG, 0), (a, mx, wl.DIAG, 0),
+                                  (b, mx, wl.IDENTITY, 1), (m, r, wl.DIAG, 0), (mx, r, wl.IDENTITY, 0), (a, r, wl.FULL, 0), (r, o, wl.FULL, 0)]:
+        g.add_edge(src, dst, kind, delay)
+    run_both(wl.make_workload("programs", g, T=T, N=N, seed=dim + T, scale=0.5, bias_scale=0.3), label=f"programs {dim}")
