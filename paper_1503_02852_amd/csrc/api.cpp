@@ -34,6 +34,7 @@ int64_t align_up(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
 
 struct Layout {
     int64_t table_off = 0, dims_off = 0, words_off = 0, blob_bytes = 0;
+    int64_t lay_off = 0;                  // behind the plan words, inside the blob: layouts of the step launches (rnn_graph::step_layouts), blob_bytes: with all there can be
     int64_t sync_off = 0;                 // 1 KiB of zero-initialised control words; the loss (double) sits at its start
     std::vector<int64_t> buf_off;         // per buffer id, bytes; -1 = not in the workspace
     int64_t partial_off = -1;             // partial sums of the two-dimensional matrix-core kernels (one launch at a time)
@@ -51,7 +52,8 @@ int64_t g_layout_skew = 4352;      // bytes, a multiple of 256 (RNNG_LAYOUT_SKEW
 // partial_floats: floats per frame of the largest partial-sum tensor any launch of the window needs
 // transposed_copy: a streaming kernel of the window reads matrices transposed
 // twins: per buffer id, whether a step launch of the window polls this twin
-Layout make_layout(const Plan& P, int T, int N, int64_t partial_floats, bool transposed_copy, const std::vector<char>& twins) {
+// layouts: most layouts of step launches that the window's plan tables carry
+Layout make_layout(const Plan& P, int T, int N, int64_t partial_floats, bool transposed_copy, const std::vector<char>& twins, int layouts) {
     Layout L;
     int n_alloc = 0;
     const int K = (int)P.xnodes.size();
@@ -61,6 +63,8 @@ Layout make_layout(const Plan& P, int T, int N, int64_t partial_floats, bool tra
     L.dims_off = cur; cur += (int64_t)P.n_bufs * 4;
     cur = align_up(cur, 16);
     L.words_off = cur; cur += (int64_t)P.words.size() * 4;
+    L.lay_off = cur;
+    cur += layouts * STEP_LAYOUT_WORDS * 4;
     L.blob_bytes = cur;
     cur = align_up(cur, 256);
     L.sync_off = cur; cur += SYNC_BYTES;
@@ -91,6 +95,7 @@ Layout make_layout(const Plan& P, int T, int N, int64_t partial_floats, bool tra
             if (N % 16 != 0 || P.buf_dim[b] % 16 != 0) L.ragged_twin_bytes += cur - at;
         }
     L.total = cur;
+    L.ragged_twin_bytes += L.blob_bytes - L.lay_off;      // (the static workspace's limit counts the layouts no more than those twins)
     return L;
 }
 
@@ -135,6 +140,9 @@ struct Profiler {
 // may change between launches (it does once several streams have been used), so each launch leaves
 // the ids it ran on in a control word, and a group on more than one XCD is reported.
 struct XcdMap { bool known = false, ok = false; };
+
+struct rnn_graph;
+namespace { bool wave_tensor_sizes_ok(const rnn_graph* g); }
 
 struct rnn_graph {
     Plan plan;
@@ -352,12 +360,63 @@ struct rnn_graph {
     int cached_T = 0, cached_N = 0;
     const Layout& layout_for(int T, int N) {
         if (cached_T != T || cached_N != N) {
-            cached_layout = make_layout(plan, T, N, partial_frame_floats(N), transposed_copy(N), polled_twins(N));
+            const int64_t partial = partial_frame_floats(N);
+            const bool copy = transposed_copy(N);
+            const std::vector<char> twins = polled_twins(N);
+            int layouts = 0;
+            for (const bool sizes_ok : {true, false})      // (whether the chain launches can run is known with the layout only)
+                layouts = std::max(layouts, (int)(step_layouts(N, sizes_ok).words.size() / STEP_LAYOUT_WORDS));
+            cached_layout = make_layout(plan, T, N, partial, copy, twins, layouts);
             cached_T = T; cached_N = N;
         }
         return cached_layout;
     }
-    void drop_choices() { jit_choices.clear(); chain_choices.clear(); cached_T = cached_N = 0; }
+    void drop_choices() { jit_choices.clear(); chain_choices.clear(); cached_T = cached_N = 0; lay = StepLayouts(); }
+    // The layouts (step_layout.h) of the weights-in-registers launches of a window with N streams, one after the other as the kernels
+    // load them, and where the first one of a component's or chain's launch lies (direction: 2 c + d; -1: none).  sizes_ok: wave_tensor_sizes_ok.
+    struct StepLayouts { std::vector<int32_t> words; std::vector<int> comp, chain; int N = 0; bool sizes_ok = false; };
+    StepLayouts lay;      // of the current window
+    StepLayouts step_layouts(int N, bool sizes_ok) {
+        StepLayouts r;
+        r.comp.assign(2 * plan.comps.size(), -1); r.chain.assign(2 * plan.chains.size(), -1);
+        r.N = N; r.sizes_ok = sizes_ok;
+        if (!use_jit || framewise) return r;
+        auto add = [&](const CompPlan& cp, bool backward, int G) {
+            const int at = (int)(r.words.size() / STEP_LAYOUT_WORDS);
+            StepLayout l;
+            std::memset(&l, 0, sizeof(l));
+            compute_step_layout(plan.words.data(), backward ? cp.bwd_desc_off : cp.fwd_desc_off, G, step_nb_for(N), N, l);
+            r.words.resize((size_t)(at + 1) * STEP_LAYOUT_WORDS);
+            std::memcpy(&r.words[(size_t)at * STEP_LAYOUT_WORDS], &l, STEP_LAYOUT_HEAD * 4);
+            std::memcpy(&r.words[(size_t)at * STEP_LAYOUT_WORDS + STEP_LAYOUT_HEAD], l.src, sizeof(l.src));
+            return at;
+        };
+        for (size_t c = 0; c < plan.comps.size(); ++c) {
+            const CompPlan& cp = plan.comps[c];
+            if (!cp.recurrent) continue;
+            for (int d = 0; d < 2; ++d) {
+                if (d ? !cp.has_bwd_program : !cp.has_fwd_program) continue;
+                if (cp.chain >= 0 && sizes_ok) {
+                    const ChainPlan& ch = plan.chains[cp.chain];
+                    const ChainChoice& cc = chain_choice(cp.chain, d != 0, N);
+                    if (!cc.source.empty()) {
+                        if ((int)c != ch.first || cc.mstep) continue;
+                        const std::vector<CompPlan>& members = chain_members(ch, cc);
+                        for (size_t i = 0; i < members.size(); ++i) {
+                            const int at = add(members[i], d != 0, cc.G[i]);
+                            if (i == 0) r.chain[2 * cp.chain + d] = at;
+                        }
+                        continue;
+                    }
+                }
+                const JitChoice& jc = jit_choice((int)c, d != 0, N);
+                if (!jc.source.empty() && jc.wave) r.comp[2 * c + d] = add(cp, d != 0, jc.lp.G);
+            }
+        }
+        return r;
+    }
+    int table_bytes() const { return (int)std::min<int64_t>(layout.lay_off + (int64_t)lay.words.size() * 4, 1 << 30); }
+    const int32_t* layout_at(int at) const { return at < 0 ? nullptr : reinterpret_cast<const int32_t*>(ws + layout.lay_off) + (int64_t)at * STEP_LAYOUT_WORDS; }
     // Whether the matrix-core kernels take a component at N streams.  From 9 streams on the
     // weights-in-registers kernels do not exist.  From 2 streams on they lose where they need more
     // workgroups than one XCD has (their exchange then crosses the XCDs and every lane multiplies for
@@ -774,6 +833,7 @@ StepRun run_phases(rnn_graph* g, int comp, bool backward, hipStream_t s, int t0,
         if (window) { a.store_base = reinterpret_cast<float*>(g->ws); a.store_bytes = (unsigned)g->layout.total; }
         a.J = jc->J;
         a.twin_base = g->plan.twin_base;
+        a.lay = g->layout_at(g->lay.comp[2 * comp + (backward ? 1 : 0)]); a.table_bytes = g->table_bytes();
         if (jc->two_d) {
             if (g->layout.partial_off < 0) return step_error(hipErrorInvalidValue, "partial-sum tensor missing from the workspace");
             a.partial = reinterpret_cast<float*>(g->ws + g->layout.partial_off);
@@ -879,9 +939,12 @@ StepRun run_chain(rnn_graph* g, int chain, bool backward, hipStream_t s, int t0,
     if (window) { a.store_base = reinterpret_cast<float*>(g->ws); a.store_bytes = (unsigned)g->layout.total; }
     a.n_groups = (int)members.size();
     a.twin_base = g->plan.twin_base;
+    a.table_bytes = g->table_bytes();
+    const int first_lay = g->lay.chain[2 * chain + (backward ? 1 : 0)];
     for (int i = 0; i < a.n_groups; ++i) {
         a.grp_desc_off[i] = backward ? members[i].bwd_desc_off : members[i].fwd_desc_off;
         a.grp_G[i] = cc.G[i];
+        a.grp_lay[i] = g->layout_at(first_lay < 0 ? -1 : first_lay + i);
         if (cc.mstep) {
             a.grp_J[i] = cc.J[i];
             a.grp_first[i] = i == 0 ? 0 : a.grp_first[i - 1] + cc.G[i - 1] * cc.J[i - 1];
@@ -1083,8 +1146,12 @@ int rnn_forward_range(rnn_graph* g, const float* d_weights, const float* const* 
     g->inputs.assign(P.xnodes.size(), nullptr);
     for (size_t i = 0; i < P.input_nodes.size(); ++i) g->inputs[P.input_nodes[i]] = d_inputs[i];
 
-    // plan tables: buffer pointers, widths, program words
-    g->blob.assign(L.blob_bytes, 0);
+    // plan tables: buffer pointers, widths, program words, layouts of the step launches
+    const bool sizes_ok = wave_tensor_sizes_ok(g);
+    if (g->lay.N != N || g->lay.sizes_ok != sizes_ok) g->lay = g->step_layouts(N, sizes_ok);
+    const int64_t blob_bytes = L.lay_off + (int64_t)g->lay.words.size() * 4;
+    g->blob.assign(blob_bytes, 0);
+    if (!g->lay.words.empty()) std::memcpy(&g->blob[L.lay_off], g->lay.words.data(), g->lay.words.size() * 4);
     for (int b = 0; b < P.n_bufs; ++b) {
         float* p = g->buf(b);
         std::memcpy(&g->blob[L.table_off + 8 * (int64_t)b], &p, 8);
@@ -1096,8 +1163,8 @@ int rnn_forward_range(rnn_graph* g, const float* d_weights, const float* const* 
     }
     if (!P.words.empty()) std::memcpy(&g->blob[L.words_off], P.words.data(), P.words.size() * 4);
     // (without allocations: as kernel arguments, which need no staging buffer of the runtime's)
-    hipError_t e = g->no_alloc ? launch_upload_words(reinterpret_cast<uint32_t*>(g->ws), reinterpret_cast<const uint32_t*>(g->blob.data()), L.blob_bytes / 4, s)
-                               : hipMemcpyAsync(g->ws, g->blob.data(), (size_t)L.blob_bytes, hipMemcpyHostToDevice, s);
+    hipError_t e = g->no_alloc ? launch_upload_words(reinterpret_cast<uint32_t*>(g->ws), reinterpret_cast<const uint32_t*>(g->blob.data()), blob_bytes / 4, s)
+                               : hipMemcpyAsync(g->ws, g->blob.data(), (size_t)blob_bytes, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return fail_hip(e, "plan table upload");
     if (!g->xcd) {
         e = ensure_xcd_map(reinterpret_cast<unsigned*>(g->ws + L.sync_off), s, &g->xcd);

@@ -353,6 +353,16 @@ bool emit_wave_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, b
         o << "    static __device__ __forceinline__ constexpr int bs_q(int b, int j) { return bs_q_(b * 4 + j); }\n";
     }
     o << "    static __device__ __forceinline__ constexpr int esrc(int task, int e) { return esrc_(task * " << STEP_MAX_EDGES << " + e); }\n";
+    // how an edge's weights are read: transposed, rows of whole groups of four
+    std::vector<std::pair<int, int>> etr, ek4;
+    for (int t = 0; t < ph.n_tasks; ++t)
+        for (int e = 0; e < ph.task[t].n_edges; ++e) {
+            etr.push_back({t * STEP_MAX_EDGES + e, ph.task[t].e[e].transposed});
+            ek4.push_back({t * STEP_MAX_EDGES + e, ph.task[t].e[e].k_len % 4 == 0 ? 1 : 0});
+        }
+    emit_switch("etr_", "key", etr); emit_switch("ek4_", "key", ek4);
+    o << "    static __device__ __forceinline__ constexpr bool etr(int task, int e) { return etr_(task * " << STEP_MAX_EDGES << " + e) != 0; }\n";
+    o << "    static __device__ __forceinline__ constexpr bool ek4(int task, int e) { return ek4_(task * " << STEP_MAX_EDGES << " + e) != 0; }\n";
     o << "    static __device__ __forceinline__ constexpr int woff(int ul, int task, int e) { return woff_((ul * "
       << (ph.n_tasks > 0 ? ph.n_tasks : 1) << " + task) * " << STEP_MAX_EDGES << " + e); }\n};\n";
     // (the group's LDS as one struct: a chain launch overlays those of its groups, of which a
@@ -449,7 +459,7 @@ std::string jit_chain_source(const Plan& P, const std::vector<CompPlan>& members
          "    const int grp = blockIdx.x & 7, w = blockIdx.x >> 3;\n"
          "    if (grp >= a.n_groups || w >= a.grp_G[grp]) return;\n"
          "    StepArgs b = a;\n"
-         "    b.desc_off = a.grp_desc_off[grp]; b.G = a.grp_G[grp];\n"
+         "    b.desc_off = a.grp_desc_off[grp]; b.lay = a.grp_lay[grp]; b.G = a.grp_G[grp];\n"
          "    switch (grp) {\n";
     for (int g = 0; g < n; ++g) o << "        case " << g << ": grp" << g << "::body(b, w, lds.l" << g << "); break;\n";
     o << "        default: break;\n    }\n}\n";

@@ -607,10 +607,28 @@ __device__ __forceinline__ int step_part_index(const StepArgs& a) {
     return w < a.G ? w : -1;
 }
 
+// The component's layout into LDS (the caller's barrier follows), and the plan tables on their way into the L2.  Worked out by one
+// thread, a dependent read and a division after the other, the layout took 5 of the 13 to 18 us before a launch's first step.
+__device__ __forceinline__ void load_step_layout(const StepArgs& a, int NB, int N, StepLayout& lay, int tid, int threads) {
+    int ahead = 0;
+    const int line = tid * 128;
+    if (line < a.table_bytes) ahead = *reinterpret_cast<const int*>(reinterpret_cast<const char*>(a.buf_ptr) + line);
+    if (a.lay != nullptr) {
+        int* head = reinterpret_cast<int*>(&lay);
+        int* src = reinterpret_cast<int*>(lay.src);
+        for (int i = tid; i < STEP_LAYOUT_WORDS; i += threads) {
+            const int v = a.lay[i];
+            if (i < STEP_LAYOUT_HEAD) head[i] = v;
+            else src[i - STEP_LAYOUT_HEAD] = v;
+        }
+    } else if (tid == 0) compute_step_layout(a.words, a.desc_off, a.G, NB, N, lay);
+    asm volatile("" :: "v"(ahead));
+}
+
 template <class MV, int NB>
 __device__ __forceinline__ void wave_prologue(const StepArgs& a, StepShared& sh) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (tid == 0) compute_step_layout(a.words, a.desc_off, a.G, NB, a.N, sh.lay);
+    load_step_layout(a, NB, a.N, sh.lay, tid, STEP_THREADS);
     const int ul = lane % MV::UW, n = lane / MV::UW;
     sh.iteminfo[0][tid] = (unsigned)(wave * MV::UW + ul) | ((unsigned)(n < a.N ? n : 0xFFFF) << 16);
     __syncthreads();
@@ -625,27 +643,59 @@ __device__ __forceinline__ void wave_setup(WaveRegs<MV>& wv, const StepArgs& a, 
         wv.xfoff[r] = MV::rfoff(r); wv.xstride[r] = (long long)MV::N * MV::RK(r);
         wv.xsrc[r] = ((cbufs_t)a.buf_ptr)[MV::rbuf(r)];
     }
+    // Loads of several words where a row's columns (transposed: the wavefront's units) lie side by side, none behind a lane's branch, so
+    // that all are in flight together: a lane without an element reads the matrix's first one and takes zero.
+    typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+    const int ul0 = wave * MV::UW;
 #pragma unroll
-    for (int ul = 0; ul < MV::UW; ++ul) {
+    for (int task = 0; task < MV::NT; ++task) {
+        const StepTask& tk = ph.task[task];
+        const int chunk = suni(tk.chunk), n_out = suni(tk.n_out), u0 = w * chunk + ul0;
+        const int mine = suni(min(min(chunk - ul0, n_out - u0), MV::UW));      // units of this wavefront
 #pragma unroll
-        for (int task = 0; task < MV::NT; ++task) {
-            const StepTask& tk = ph.task[task];
-            const int chunk = suni(tk.chunk), n_out = suni(tk.n_out);
-            const int ulw = wave * MV::UW + ul, u = w * chunk + ulw;
-            const bool uok = ulw < chunk && u < n_out;
+        for (int e = 0; e < STEP_MAX_EDGES; ++e) {
+            if (e >= MV::nedges(task)) continue;
+            const int K = suni(tk.e[e].k_len);
+            const float* W = a.weights + suni(tk.e[e].w_off);
+            constexpr int FM = WAVE_FMAX;
+            const int F = MV::F(MV::esrc(task, e)), k0 = F * lane;
+            if (MV::etr(task, e)) {
 #pragma unroll
-            for (int e = 0; e < STEP_MAX_EDGES; ++e) {
-                if (e < MV::nedges(task)) {
-                    const int K = suni(tk.e[e].k_len), transposed = suni(tk.e[e].transposed);
-                    const float* W = a.weights + suni(tk.e[e].w_off);
-                    const int F = MV::F(MV::esrc(task, e));
+                for (int f = 0; f < FM; ++f) {
+                    if (f >= F) continue;
+                    const bool in = k0 + f < K;
+                    const float* p = W + (in && mine > 0 ? (size_t)(k0 + f) * n_out + u0 : 0);
+                    float x[MV::UW];
+                    if (mine == MV::UW) {
 #pragma unroll
-                    for (int f = 0; f < WAVE_FMAX; ++f) {
-                        if (f < F) {
-                            const int k = F * lane + f;
-                            float v = 0.0f;
-                            if (uok && k < K) v = transposed ? W[(size_t)k * n_out + u] : W[(size_t)u * K + k];
-                            wv.wr[MV::woff(ul, task, e) + f] = v;
+                        for (int ul = 0; ul < MV::UW; ++ul) x[ul] = p[ul];
+                    } else {
+#pragma unroll
+                        for (int ul = 0; ul < MV::UW; ++ul) x[ul] = ul < mine ? p[ul] : 0.0f;
+                    }
+#pragma unroll
+                    for (int ul = 0; ul < MV::UW; ++ul) wv.wr[MV::woff(ul, task, e) + f] = in ? x[ul] : 0.0f;
+                }
+            } else {
+#pragma unroll
+                for (int ul = 0; ul < MV::UW; ++ul) {
+                    const float* row = W + (ul < mine ? (size_t)(u0 + ul) * K : 0);
+                    if (F % 4 == 0 && MV::ek4(task, e)) {
+#pragma unroll
+                        for (int f = 0; f < FM; f += 4) {
+                            if (f >= F) continue;
+                            const bool in = ul < mine && k0 + f < K;
+                            const float4u x = *reinterpret_cast<const float4u*>(row + (in ? k0 + f : 0));
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) if (f + j < F) wv.wr[MV::woff(ul, task, e) + f + j] = in ? x[j] : 0.0f;
+                        }
+                    } else {
+#pragma unroll
+                        for (int f = 0; f < FM; ++f) {
+                            if (f >= F) continue;
+                            const bool in = ul < mine && k0 + f < K;
+                            const float x = row[in ? k0 + f : 0];
+                            wv.wr[MV::woff(ul, task, e) + f] = in ? x : 0.0f;
                         }
                     }
                 }

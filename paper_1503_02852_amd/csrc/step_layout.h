@@ -66,6 +66,9 @@ struct StepLayout {
     StepSource src[STEP_MAX_SOURCES];
 };
 
+// A single-phase component's layout as the plan tables carry it: StepLayout up to its first phase, then the sources.
+constexpr int STEP_LAYOUT_HEAD = 5 + (int)(sizeof(StepPhase) / 4), STEP_LAYOUT_WORDS = STEP_LAYOUT_HEAD + (int)(sizeof(StepSource) * STEP_MAX_SOURCES / 4);
+
 constexpr int STEP_MAX_GROUPS = 4;
 
 // Control words behind ctrl that hold the XCDs of one launch each (behind those of the step trace).
@@ -82,10 +85,13 @@ struct StepArgs {
     const float* weights;
     unsigned* ctrl;                          // [0]: set to 1 when a wait ran into the spin limit
     int desc_off, T, N, backward, G, xcd_stride, spin_limit;
+    const int32_t* lay;                      // the component's layout (STEP_LAYOUT_WORDS words), or NULL: the kernel works it out
+    int table_bytes;                         // of the plan tables from buf_ptr on
     // Chain launches (several recurrent components side by side): group g runs descriptor
     // grp_desc_off[g] on grp_G[g] workgroups; block b belongs to group b % 8, part b / 8, which
     // puts each group on one XCD.  n_groups == 0: a single component (desc_off, G, xcd_stride).
     int n_groups, grp_desc_off[STEP_MAX_GROUPS], grp_G[STEP_MAX_GROUPS];
+    const int32_t* grp_lay[STEP_MAX_GROUPS];
     // Chains of the matrix-core build: group g takes the blocks [grp_first[g], grp_first[g] +
     // grp_G[g] * grp_J[g]) (all groups use all XCDs).
     int grp_J[STEP_MAX_GROUPS], grp_first[STEP_MAX_GROUPS];

@@ -264,3 +264,23 @@ def test_shift_moves_every_frame(T, N, hidden, frames):
     win.check()
     for k in nodes:
         assert np.array_equal(win.node_output(k)[:T - frames], before[k][frames:]), spec.nodes[k]["name"]
+
+
+def test_another_windows_workspace_is_asked_for_between_the_passes():
+    """The layouts that the step launches load belong to the window of the last forward pass, whatever shapes are asked about since."""
+    from paper_1503_02852_amd.runner import window_for
+    spec = wl.lstm_net(6, [24, 24], 5)
+    w = wl.make_workload("between", spec, T=11, N=1, seed=4, scale=0.4)
+    grads = []
+    for ask in (False, True):
+        win = window_for(w)
+        win.forward()
+        if ask:
+            for T, N in [(7, 4), (30, 2), (5, 16)]:
+                assert win.g.workspace_bytes(T, N) > 0
+        win.bptt()
+        win.compute_grads()
+        win.check()
+        grads.append(win.grads.cpu().numpy())
+    # the same sums but for the order in which parts are added
+    assert np.abs(grads[0] - grads[1]).max() <= 1e-5 * np.abs(grads[0]).max()
