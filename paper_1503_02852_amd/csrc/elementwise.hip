@@ -29,8 +29,7 @@ void node_program_kernel(PlanView pv, int prog_off, int max_dim,
 }
 
 // The same for short programs all of whose vectors have one width, a multiple of 4: four units per thread, so that a program word is
-// read and decoded once for four of them (it was bound by that: three gated layers of 1,024 units at 64 x 128 frames, seven such launches,
-// 12.70 -> 12.53 ms per window).
+// read and decoded once for four of them (it was bound by that: products and sums of 8,192 x 1,024 elements 42.5 -> 22.6 us).
 typedef float program_float4 __attribute__((ext_vector_type(4), aligned(4)));
 __global__ __launch_bounds__(256) void node_program4_kernel(PlanView pv, int prog_off, int dim, const float* __restrict__ weights,
                                                             int T, int N, int t0, long long total) {

@@ -644,58 +644,67 @@ __device__ __forceinline__ void wave_setup(WaveRegs<MV>& wv, const StepArgs& a, 
         wv.xsrc[r] = ((cbufs_t)a.buf_ptr)[MV::rbuf(r)];
     }
     // Loads of several words where a row's columns (transposed: the wavefront's units) lie side by side, none behind a lane's branch, so
-    // that all are in flight together: a lane without an element reads the matrix's first one and takes zero.
-    typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+    // that all are in flight together.  They go through a descriptor over the matrix, outside of which a lane without an element
+    // reads zero: as selects behind the loads, the lanes' masks filled the scalar registers (72 -> 128 spilled ones at 1,024 units).
+    constexpr int NONE = (int)0xC0000000u;
     const int ul0 = wave * MV::UW;
 #pragma unroll
     for (int task = 0; task < MV::NT; ++task) {
         const StepTask& tk = ph.task[task];
-        const int chunk = suni(tk.chunk), n_out = suni(tk.n_out), u0 = w * chunk + ul0;
+        const int chunk = suni(tk.chunk), n_out = suni(tk.n_out), u0 = w * chunk + suni(ul0);
         const int mine = suni(min(min(chunk - ul0, n_out - u0), MV::UW));      // units of this wavefront
 #pragma unroll
         for (int e = 0; e < STEP_MAX_EDGES; ++e) {
             if (e >= MV::nedges(task)) continue;
             const int K = suni(tk.e[e].k_len);
-            const float* W = a.weights + suni(tk.e[e].w_off);
-            constexpr int FM = WAVE_FMAX;
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.weights) + suni(tk.e[e].w_off), 0, n_out * K * 4, STEP_RSRC_FLAGS);
             const int F = MV::F(MV::esrc(task, e)), k0 = F * lane;
             if (MV::etr(task, e)) {
+                const int at = (k0 * n_out + u0) * 4;      // (columns beyond K lie beyond the matrix)
 #pragma unroll
-                for (int f = 0; f < FM; ++f) {
+                for (int f = 0; f < WAVE_FMAX; ++f) {
                     if (f >= F) continue;
-                    const bool in = k0 + f < K;
-                    const float* p = W + (in && mine > 0 ? (size_t)(k0 + f) * n_out + u0 : 0);
-                    float x[MV::UW];
+                    const int off = at + f * n_out * 4;
+                    unsigned x[MV::UW];
                     if (mine == MV::UW) {
+                        constexpr int V = MV::UW % 4 == 0 ? 4 : MV::UW % 2 == 0 ? 2 : 1;
 #pragma unroll
-                        for (int ul = 0; ul < MV::UW; ++ul) x[ul] = p[ul];
+                        for (int ul = 0; ul < MV::UW; ul += V) {
+                            if constexpr (V == 4) {
+                                const muintx4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 4 * ul, 0, 0);
+                                x[ul] = v.x; x[ul + 1] = v.y; x[ul + 2] = v.z; x[ul + 3] = v.w;
+                            } else if constexpr (V == 2) {
+                                const suintx2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, off + 4 * ul, 0, 0);
+                                x[ul] = v.x; x[ul + 1] = v.y;
+                            } else {
+                                x[ul] = __builtin_amdgcn_raw_buffer_load_b32(rs, off + 4 * ul, 0, 0);
+                            }
+                        }
                     } else {
 #pragma unroll
-                        for (int ul = 0; ul < MV::UW; ++ul) x[ul] = ul < mine ? p[ul] : 0.0f;
+                        for (int ul = 0; ul < MV::UW; ++ul) x[ul] = __builtin_amdgcn_raw_buffer_load_b32(rs, ul < mine ? off + 4 * ul : NONE, 0, 0);
                     }
 #pragma unroll
-                    for (int ul = 0; ul < MV::UW; ++ul) wv.wr[MV::woff(ul, task, e) + f] = in ? x[ul] : 0.0f;
+                    for (int ul = 0; ul < MV::UW; ++ul) wv.wr[MV::woff(ul, task, e) + f] = __uint_as_float(x[ul]);
                 }
             } else {
 #pragma unroll
                 for (int ul = 0; ul < MV::UW; ++ul) {
-                    const float* row = W + (ul < mine ? (size_t)(u0 + ul) * K : 0);
+                    const int at = ((u0 + ul) * K + k0) * 4;
+                    // (a lane's columns beyond K: the next row's)
                     if (F % 4 == 0 && MV::ek4(task, e)) {
 #pragma unroll
-                        for (int f = 0; f < FM; f += 4) {
+                        for (int f = 0; f < WAVE_FMAX; f += 4) {
                             if (f >= F) continue;
-                            const bool in = ul < mine && k0 + f < K;
-                            const float4u x = *reinterpret_cast<const float4u*>(row + (in ? k0 + f : 0));
+                            const muintx4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, ul < mine && k0 + f < K ? at + 4 * f : NONE, 0, 0);
 #pragma unroll
-                            for (int j = 0; j < 4; ++j) if (f + j < F) wv.wr[MV::woff(ul, task, e) + f + j] = in ? x[j] : 0.0f;
+                            for (int j = 0; j < 4; ++j) if (f + j < F) wv.wr[MV::woff(ul, task, e) + f + j] = __uint_as_float(v[j]);
                         }
                     } else {
 #pragma unroll
-                        for (int f = 0; f < FM; ++f) {
+                        for (int f = 0; f < WAVE_FMAX; ++f) {
                             if (f >= F) continue;
-                            const bool in = ul < mine && k0 + f < K;
-                            const float x = row[in ? k0 + f : 0];
-                            wv.wr[MV::woff(ul, task, e) + f] = in ? x : 0.0f;
+                            wv.wr[MV::woff(ul, task, e) + f] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, ul < mine && k0 + f < K ? at + 4 * f : NONE, 0, 0));
                         }
                     }
                 }
