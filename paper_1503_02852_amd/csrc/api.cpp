@@ -616,6 +616,7 @@ hipError_t run_gemms(rnn_graph* g, const std::vector<GemmProblemPlan>& probs, bo
                 gp = &grp.p[grp.n_problems++];
                 std::memset(gp, 0, sizeof(*gp));
                 gp->C = g->buf(pp.c_buf) + r0 * pp.n; gp->ldc = pp.n; gp->M = (int)rows; gp->N = pp.n;
+                gp->window_M = g->T * g->N;
                 gp->first_pair = grp.n_pairs; gp->accumulate = first ? 0 : 1;      // (more pairs than one launch takes: the next one adds)
                 first = false;
             }
@@ -1460,7 +1461,7 @@ int rnn_grads(rnn_graph* g, float* d_grads, double* loss, void* hip_stream) {
         }
         GemmGroup& grp = groups.back();
         GemmProblem& gp = grp.p[grp.n_problems++];
-        gp.C = d_grads + gg.w_off; gp.ldc = gg.n_src; gp.M = gg.n_dst; gp.N = gg.n_src;
+        gp.C = d_grads + gg.w_off; gp.ldc = gg.n_src; gp.M = gp.window_M = gg.n_dst; gp.N = gg.n_src;
         gp.first_pair = grp.n_pairs; gp.n_pairs = 1; gp.accumulate = gg.sole ? 0 : 1;      // where several connections share a block all add
         GemmPair& o = grp.pair[grp.n_pairs++];
         // eps_m(t) of every frame of the window against y_src(t - d); for the window's first d

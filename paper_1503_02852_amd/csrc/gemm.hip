@@ -423,6 +423,7 @@ double estimate(GemmMode mode, const GemmGroup& g, int mask, int kind, int facto
 }  // namespace
 
 void plan_gemm_group(GemmMode mode, GemmGroup& g, bool one_writer) {
+    bool pieces = false;
     for (int i = 0; i < g.n_problems; ++i) {
         GemmProblem& p = g.p[i];
         p.chunks = 0;
@@ -432,36 +433,51 @@ void plan_gemm_group(GemmMode mode, GemmGroup& g, bool one_writer) {
             p.chunks = (int)std::min<int64_t>((int64_t)p.chunks + c, 1 << 30);
             ld = std::max(ld, std::max(g.pair[q].lda, g.pair[q].ldb));
         }
-        p.narrow = std::min(p.M, p.N) < 96;
+        p.narrow = std::min(p.window_M, p.N) < 96;
         p.kind = ld >= GEMM_WIDE_ROW ? 3 : 0;
+        pieces = pieces || p.M != p.window_M;
     }
-    // every problem in tiles of one size, or the narrow ones in smaller tiles and a launch of their own
-    int kind[2] = {0, 0}, factor[2] = {1, 1}, part_factor[2][3];
-    double best = 1e30, part[2][3];
     // Weight gradients are added to zeros that the caller has stored; other products are split only where they have to be, since the
     // order in which the parts are added changes from run to run.
     int most = mode == GEMM_TN ? 64 : 1;
     for (int i = 0; i < g.n_problems; ++i) most = std::max(most, g.p[i].min_split);
-    auto cheapest = [&](int mask, int k, int& f) {
-        double t = 1e30;
-        for (int s = 1; s <= (one_writer ? 1 : most); s *= 2) {
-            const double e = estimate(mode, g, mask, k, s, one_writer);
-            if (e < t) { t = e; f = s; }
-        }
-        return t;
-    };
-    for (int k = 0; k < 3; ++k) {
-        int f = 1;
-        const double t = cheapest(3, k, f);
-        if (t < best) { best = t; kind[0] = kind[1] = k; factor[0] = factor[1] = f; }
-        for (int m = 0; m < 2; ++m) part[m][k] = cheapest(1 << m, k, part_factor[m][k]);
-    }
-    for (int a = 0; a < 2; ++a)
-        for (int b = a + 1; b < 3; ++b)
-            if (part[0][a] > 0.0 && part[1][b] > 0.0 && part[0][a] + part[1][b] < best) {
-                best = part[0][a] + part[1][b];
-                kind[0] = a; kind[1] = b; factor[0] = part_factor[0][a]; factor[1] = part_factor[1][b];
+    // every problem in tiles of one size, or the narrow ones in smaller tiles and a launch of their own; kinds lo[m] .. hi[m] for
+    // the narrow ones (m = 0) and the others
+    int lo[2] = {0, 0}, hi[2] = {2, 2}, kind[2] = {0, 0}, factor[2] = {1, 1};
+    auto choose = [&]() {
+        auto cheapest = [&](int mask, int k, int& f) {
+            double t = 1e30;
+            for (int s = 1; s <= (one_writer ? 1 : most); s *= 2) {
+                const double e = estimate(mode, g, mask, k, s, one_writer);
+                if (e < t) { t = e; f = s; }
             }
+            return t;
+        };
+        double best = 1e30, part[2][3];
+        int part_factor[2][3];
+        for (int k = 0; k < 3; ++k) {
+            int f = 1;
+            const double t = cheapest(3, k, f);
+            if (t < best && k >= lo[0] && k >= lo[1] && k <= hi[0] && k <= hi[1]) { best = t; kind[0] = kind[1] = k; factor[0] = factor[1] = f; }
+            for (int m = 0; m < 2; ++m) part[m][k] = cheapest(1 << m, k, part_factor[m][k]);
+        }
+        for (int a = lo[0]; a <= hi[0]; ++a)
+            for (int b = std::max(a + 1, lo[1]); b <= hi[1]; ++b)
+                if (part[0][a] > 0.0 && part[1][b] > 0.0 && part[0][a] + part[1][b] < best) {
+                    best = part[0][a] + part[1][b];
+                    kind[0] = a; kind[1] = b; factor[0] = part_factor[0][a]; factor[1] = part_factor[1][b];
+                }
+    };
+    if (pieces) {
+        // Tiles of 32 add in another order than those of 64 and 128 (which add alike): the whole window's rows say which of
+        // the two a problem takes, so that a frame's result does not depend on how many frames share a call.
+        int rows[GEMM_MAX_PROBLEMS];
+        for (int i = 0; i < g.n_problems; ++i) { rows[i] = g.p[i].M; g.p[i].M = g.p[i].window_M; }
+        choose();
+        for (int i = 0; i < g.n_problems; ++i) g.p[i].M = rows[i];
+        for (int m = 0; m < 2; ++m) { lo[m] = kind[m] == 0 ? 0 : 1; hi[m] = kind[m] == 0 ? 0 : 2; }
+    }
+    choose();
     for (int i = 0; i < g.n_problems; ++i) {
         GemmProblem& p = g.p[i];
         const int m = p.narrow ? 0 : 1;

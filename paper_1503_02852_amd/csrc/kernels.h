@@ -23,6 +23,7 @@ struct GemmPair {
 };
 struct GemmProblem {
     float* C; int ldc, M, N, first_pair, n_pairs;
+    int window_M;           // M if all frames of the window were in this call (M where that is so, and where M is no frames)
     int accumulate;         // 1: C += result instead of C = result
     const float* bias;      // stored is f(result + bias[column]) (NULL: none), f by act (ACT_*); only where the result is stored by
     int act;                // one workgroup (split == 1, no accumulate)

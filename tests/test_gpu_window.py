@@ -284,3 +284,46 @@ def test_another_windows_workspace_is_asked_for_between_the_passes():
         grads.append(win.grads.cpu().numpy())
     # the same sums but for the order in which parts are added
     assert np.abs(grads[0] - grads[1]).max() <= 1e-5 * np.abs(grads[0]).max()
+
+
+def deep_net(widths, acts):
+    """Layers one after the other, no recurrent one, squared error at the last."""
+    g = wl.GraphSpec()
+    at = g.add_node(wl.INPUT, wl.LINEAR, widths[0], name="x")
+    for i, (n, act) in enumerate(zip(widths[1:], acts)):
+        last = i == len(acts) - 1
+        node = g.add_node(wl.ADD, act, n, has_bias=True, is_output=wl.SQUARED_ERROR if last else False, name=f"h{i}")
+        g.add_edge(at, node, wl.FULL, 0)
+        at = node
+    return g
+
+
+# (products of at most 1,000 columns are not split over workgroups: their additions have one order)
+BIT_NETS = {
+    "wide and narrow products": lambda: (deep_net([200, 1030, 61, 520], [wl.TANH, wl.LINEAR, wl.SIGMOID]), 160, 8, None),
+    "many frames": lambda: (deep_net([40, 130, 257], [wl.RELU, wl.LINEAR]), 4000, 1, None),
+    "stacked layers": lambda: (wl.lstm_net(40, [64, 64], 61), 96, 9, None),
+}
+
+
+@pytest.mark.parametrize("deterministic", [False, True])
+@pytest.mark.parametrize("name", sorted(BIT_NETS))
+def test_pieces_give_the_same_bits_as_the_window_at_once(name, deterministic):
+    from paper_1503_02852_amd.runner import window_for
+    spec, T, N, build = BIT_NETS[name]()
+    with pytest.MonkeyPatch.context() as env:
+        if build:
+            env.setenv("RNNG_STEP_BUILD", build)
+        w = wl.make_workload(name, spec, T=T, N=N, seed=12, scale=0.2, bias_scale=0.3)
+        win = window_for(w)
+        win.g.set_deterministic(deterministic)
+    win.forward()
+    nodes = [k for k, n in enumerate(spec.nodes) if n["kind"] != wl.INPUT]
+    at_once = {k: win.node_output(k).copy() for k in nodes}
+    for cuts in ([0, 1, 2, 3, T // 3, T // 2 + 1, T - 1, T], [0, *range(5, T, max(4, T // 24)), T]):
+        win.ws.fill_(0xFF)
+        for a, b in zip(cuts, cuts[1:]):
+            win.forward_range(a, b)
+        win.check()
+        for k in nodes:
+            assert np.array_equal(win.node_output(k), at_once[k]), (spec.nodes[k]["name"], cuts)
