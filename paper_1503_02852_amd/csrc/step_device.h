@@ -2664,8 +2664,8 @@ __device__ __forceinline__ void smstep_kernel_body(const StepArgs& a, SShared& m
         // Every second step goes through the columns, and the sources where they are alike, backwards: what it reads first is
         // what the step before read last and what the 256 MiB memory-side cache still holds; in the same order each step would find
         // the lines gone that it is about to read.  (256 MiB of weights per step, forward / backward: 16 streams 46.9 / 59.6 -> 44.8 / 56.6 us,
-        // 64 streams 82 / 116 -> 81 / 111.)
-        const bool rev = MSTREAM_SERPENTINE && (step & 1) != 0;
+        // 64 streams 82 / 116 -> 81 / 111.)  By the frame's parity, not the launch's step: a frame adds up alike wherever its call begins.
+        const bool rev = MSTREAM_SERPENTINE && (t & 1) != 0;
         __amdgpu_buffer_rsrc_t rs[SM::NSRC];
 #pragma unroll
         for (int sidx = 0; sidx < SM::NSRC; ++sidx) {

@@ -303,6 +303,9 @@ BIT_NETS = {
     "wide and narrow products": lambda: (deep_net([200, 1030, 61, 520], [wl.TANH, wl.LINEAR, wl.SIGMOID]), 160, 8, None),
     "many frames": lambda: (deep_net([40, 130, 257], [wl.RELU, wl.LINEAR]), 4000, 1, None),
     "stacked layers": lambda: (wl.lstm_net(40, [64, 64], 61), 96, 9, None),
+    # weights read from memory every step, in turn forwards and backwards
+    "streamed weights": lambda: (wl.elman_net(40, 520, 61), 24, 17, "stream"),
+    "streamed weights, few streams": lambda: (wl.elman_net(40, 260, 61), 24, 3, "stream"),
 }
 
 
@@ -320,6 +323,7 @@ def test_pieces_give_the_same_bits_as_the_window_at_once(name, deterministic):
     win.forward()
     nodes = [k for k, n in enumerate(spec.nodes) if n["kind"] != wl.INPUT]
     at_once = {k: win.node_output(k).copy() for k in nodes}
+    assert build is None or win.g.step_build(nodes[0])[0] == "streaming"
     for cuts in ([0, 1, 2, 3, T // 3, T // 2 + 1, T - 1, T], [0, *range(5, T, max(4, T // 24)), T]):
         win.ws.fill_(0xFF)
         for a, b in zip(cuts, cuts[1:]):
