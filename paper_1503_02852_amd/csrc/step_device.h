@@ -1263,6 +1263,11 @@ __device__ __forceinline__ void wave_step(PhaseRegs<PH>& r, const WaveRegs<MV>& 
 #pragma unroll
                 for (int f = 0; f < WAVE_FMAX; ++f)
                     if (f < MV::F(sidx)) xr[n][MV::xoff(sidx) + f] = xs[GX::lane_pos(sidx, n, lane, f)];
+        // All of them under way before the ring row's address is worked out and loaded: left to itself the compiler
+        // put one of Elman's two reads behind that, a wait of its own in every step (512 units, 1 stream, forward /
+        // backward 1.32 / 1.30 -> 1.26 / 1.23 ms per 2,048 steps; 128 units, 8 streams 470 / 462 -> 471 / 449 us per 512).  Up to 16
+        // values: with more the reads are many and better spread over the products (2 x 32 values, 512 units, backward 996 -> 1,012 us).
+        if (NB * MV::XF <= 16) __builtin_amdgcn_sched_barrier(1);      // (arithmetic may cross)
     } else if (!has_units) {
         return;
     }
