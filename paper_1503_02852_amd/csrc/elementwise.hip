@@ -550,7 +550,9 @@ __global__ __launch_bounds__(256) void zero_history_kernel(float* const* __restr
 
 // y(t) <- y(t + frames) for all stored frames of up to SHIFT_MAX_TENSORS tensors.  A thread walks a chain of its own, the elements
 // that lie whole shifts apart (of one or four floats), so that source and destination may overlap; eight of
-// a chain's elements are in flight.  One copy per tensor and piece before: 2 x 512 LSTM, 256 of 512 frames 121 -> 8 us, one of 2 frames 59 -> 3 us.
+// a chain's elements are in flight, in registers (with HIP's own uint4 they lay in scratch between load and store: 2 x 512
+// LSTM on 32 streams, 16 of 256 frames 137 -> 97 us).  One copy per tensor and piece before: 2 x 512 LSTM, 256 of 512 frames 121 -> 8 us, one of 2 frames 59 -> 3 us.
+typedef unsigned int shift_uint4 __attribute__((ext_vector_type(4)));
 template <class V>
 __device__ __forceinline__ void shift_tensor(V* y, long long frame, int frames, int stored) {
     const long long step = frame * frames, last = frame * (stored - frames);
@@ -569,7 +571,7 @@ __device__ __forceinline__ void shift_tensor(V* y, long long frame, int frames, 
 __global__ __launch_bounds__(256) void shift_frames_kernel(const ShiftTensors s, int frames, int stored) {
     const int b = blockIdx.y;
     void* p = s.p[b];
-    if (s.frame_words[b] % 4 == 0 && ((uintptr_t)p & 15) == 0) shift_tensor(static_cast<uint4*>(p), s.frame_words[b] / 4, frames, stored);
+    if (s.frame_words[b] % 4 == 0 && ((uintptr_t)p & 15) == 0) shift_tensor(static_cast<shift_uint4*>(p), s.frame_words[b] / 4, frames, stored);
     else shift_tensor(static_cast<uint32_t*>(p), s.frame_words[b], frames, stored);
 }
 }  // namespace

@@ -4,6 +4,7 @@ compute call is made here."""
 import ctypes
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -279,3 +280,21 @@ def test_build_of_few_streams(monkeypatch, layers, N, copies):
 
     one = 4 * (T + 1) * N * layers[0]
     assert copies * one <= workspace("1") - workspace("0") <= copies * (one + (1 << 16))
+
+
+def _kernel_resources(source):
+    """name -> bytes of scratch per lane of every kernel of one source file, from the compiler's own listing."""
+    from paper_1503_02852_amd import build
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    build_dir = os.path.join(build.HERE, "_build")
+    cmd = [hipcc, *build.FLAGS, "-I", build_dir, "--cuda-device-only", "-S", os.path.join(build.CSRC, source), "-o", "-"]
+    text = subprocess.run(cmd, check=True, capture_output=True, text=True).stdout
+    meta = re.findall(r"\.name:\s+(\S+)\n(.*?)\.wavefront_size", text, re.S)
+    assert meta
+    return {name: int(re.search(r"private_segment_fixed_size:\s+(\d+)", rest)[1]) for name, rest in meta}
+
+
+@pytest.mark.parametrize("source,kernel", [("elementwise.hip", "shift_frames_kernel")])
+def test_kernels_hold_what_is_in_flight_in_registers(source, kernel):
+    scratch = {name: n for name, n in _kernel_resources(source).items() if kernel in name}
+    assert scratch and not any(scratch.values()), scratch
