@@ -285,21 +285,22 @@ __global__ __launch_bounds__(256) void softmax_ce_delta_wide_kernel(const float*
 // follows the error criterion and the layer's activation): dE/ds = (y - d) f'(s).
 __global__ __launch_bounds__(256) void squared_error_delta_kernel(const float* __restrict__ y, const float* __restrict__ d,
                                                                   float* __restrict__ ds, double* loss, long long n, int act) {
-    __shared__ float wl[4];
+    __shared__ double wl[4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float l = 0.0f;
+    double l = 0.0;
     for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += 256LL * gridDim.x) {
         const float yi = y[i], di = d[i];
         const float err = di != di ? 0.0f : yi - di;      // a NaN target element carries no error
         const float fp = act == 1 ? yi * (1.0f - yi) : act == 2 ? 1.0f - yi * yi : act == 4 ? (yi > 0.0f ? 1.0f : 0.0f) : 1.0f;
         ds[i] = err * fp;
-        l += 0.5f * err * err;
+        l += (double)(0.5f * err * err);
     }
-    l = wave_sum(l);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
     if (lane == 0) wl[wave] = l;
     __syncthreads();
     if (threadIdx.x == 0) {
-        const double s = (double)wl[0] + (double)wl[1] + (double)wl[2] + (double)wl[3];
+        const double s = wl[0] + wl[1] + wl[2] + wl[3];
         if (s != 0.0) atomicAdd(loss, s);
     }
 }

@@ -104,3 +104,22 @@ def test_sums_over_frames(T, N):
     want = -np.log(p[tg >= 0]).sum()
     # the hardware logarithm's error (2 ulp of log2 near 1: 2^-22 absolute) per frame
     assert abs(loss - want) <= 2.0 ** -21 * max(1.0, T * N) + 1e-6 * want
+
+
+@pytest.mark.parametrize("T,O", [(1, 3), (37, 130), (513, 256), (1023, 4096), (1100, 4096)])
+def test_squared_error_sums_in_double(T, O):
+    """The loss of up to several million elements against a double sum of the terms, each rounded to fp32 like the kernel's."""
+    from paper_1503_02852_amd.runner import window_for
+    spec = wl.GraphSpec()
+    x = spec.add_node(wl.INPUT, wl.LINEAR, 4, name="x")
+    o = spec.add_node(wl.ADD, wl.LINEAR, O, has_bias=True, is_output=wl.SQUARED_ERROR, name="y")
+    spec.add_edge(x, o, wl.FULL, 0)
+    w = wl.make_workload("squared", spec, T=T, N=1, seed=T, scale=0.4, bias_scale=0.3)
+    win = window_for(w)
+    win.forward()
+    win.bptt()
+    loss = win.compute_grads(want_loss=True)
+    err = win.node_output(o) - w.targets[o].astype(np.float32)
+    terms = (np.float32(0.5) * err * err).astype(np.float64)
+    # every addition of the longest chain (a thread's terms, a wavefront, a workgroup, up to 2,048 workgroups) rounds by 2^-53
+    assert abs(loss - terms.sum()) <= 2.0 ** -53 * (T * O / (512 * 256) + 2048 + 16 + 64) * terms.sum()
