@@ -252,26 +252,27 @@ __global__ __launch_bounds__(NTHREADS, T == 2 ? 4 : 6) void gemm_kernel(const Ge
     }
     const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(P.C + (long long)m0 * P.ldc + n0, 0, rsrc_bytes((long long)(P.M - m0) * P.ldc - n0), RSRC_FLAGS);
     const int row_bytes = 4 * P.ldc;
-    if (P.bias != nullptr || P.act != ACT_LINEAR) {
+    // What finish() does, f chosen outside the unrolled elements and their values stored sixteen at a time: chosen per element, all of
+    // them at once, it took 48 registers more than there are.
+    auto store = [&](auto f) {
 #pragma unroll
         for (int y = 0; y < T; ++y) {
             const int col = n0 + brow + 64 * y;
-            const float bias = P.bias != nullptr && col < P.N ? P.bias[col] : 0.0f;
+            const int at = col < P.N ? (row0 - m0) * row_bytes + 4 * (brow + 64 * y) : OUTSIDE;
+            const float bias = P.bias != nullptr && col < P.N ? P.bias[col] : -0.0f;      // (v + -0 is v, -0 too)
 #pragma unroll
-            for (int x = 0; x < T; ++x)
+            for (int x = 0; x < T; ++x) {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[x][y][e] = finish(acc[x][y][e], P.bias != nullptr, bias, P.act);
+                for (int e = 0; e < 16; ++e)
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(f(acc[x][y][e] + bias)), rc, at + (64 * x + 8 * (e >> 2) + (e & 3)) * row_bytes, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
-    }
-#pragma unroll
-    for (int y = 0; y < T; ++y) {
-        const int at = n0 + brow + 64 * y < P.N ? (row0 - m0) * row_bytes + 4 * (brow + 64 * y) : OUTSIDE;
-#pragma unroll
-        for (int x = 0; x < T; ++x)
-#pragma unroll
-            for (int e = 0; e < 16; ++e)
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[x][y][e]), rc, at + (64 * x + 8 * (e >> 2) + (e & 3)) * row_bytes, 0, 0);
-    }
+    };
+    if (P.act == ACT_SIGMOID) store([](float v) { return sigmoid_f(v); });
+    else if (P.act == ACT_TANH) store([](float v) { return tanh_f(v); });
+    else if (P.act == ACT_RELU) store([](float v) { return fmaxf(v, 0.0f); });
+    else store([](float v) { return v; });
 }
 
 constexpr int SMALL_WAVES = 8, SMALL_DEPTH = 4, SMALL_TILE = 32;

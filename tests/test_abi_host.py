@@ -294,7 +294,7 @@ def _kernel_resources(source):
     return {name: int(re.search(r"private_segment_fixed_size:\s+(\d+)", rest)[1]) for name, rest in meta}
 
 
-@pytest.mark.parametrize("source,kernel", [("elementwise.hip", "shift_frames_kernel")])
+@pytest.mark.parametrize("source,kernel", [("elementwise.hip", "shift_frames_kernel"), ("gemm.hip", "11gemm_kernel")])
 def test_kernels_hold_what_is_in_flight_in_registers(source, kernel):
     scratch = {name: n for name, n in _kernel_resources(source).items() if kernel in name}
     assert scratch and not any(scratch.values()), scratch
