@@ -226,9 +226,9 @@ int rnn_specialise(rnn_graph* g, int32_t N);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): rnn_forward with the workspace in a device array that
- * is part of the library image (RNN_STATIC_WORKSPACE_BYTES per GPU, 161 MiB more for windows with the
- * second copies below; each held from the first call that needs it until the process ends), and the
- * output layers' activations copied to the caller.
+ * is part of the library image (RNN_STATIC_WORKSPACE_BYTES per GPU, 161 MiB more for windows that fit it
+ * but for what does not count, see below; each held from the first call that needs it until the process
+ * ends), and the output layers' activations copied to the caller.
  *   d_inputs   as in rnn_forward.
  *   d_outputs  HOST array with one DEVICE pointer per output node, in increasing node id, each a
  *              [T][N][dim] float tensor that receives the node's activations y.
@@ -236,8 +236,8 @@ int rnn_specialise(rnn_graph* g, int32_t N);
  * be loaded, which one earlier rnn_forward of the same graph handle and N on this device (on a
  * workspace of the caller's) has done; else RNN_ERR_SEQUENCE.  RNN_ERR_WORKSPACE if the window
  * needs more than RNN_STATIC_WORKSPACE_BYTES (rnn_workspace_bytes tells; the second copies of
- * exchanged tensors that a stream count or a layer width which is no multiple of 16 brings are in
- * that figure, but do not count here), RNN_ERR_SEQUENCE if kernel-class timing is switched on (it
+ * exchanged tensors that a stream count or a layer width which is no multiple of 16 brings and the
+ * few KiB that step launches read their layout from are in that figure, but do not count here), RNN_ERR_SEQUENCE if kernel-class timing is switched on (it
  * creates events).  Afterwards the handle's window lives in the static array: rnn_output, rnn_bptt,
  * rnn_grads work on it as after rnn_forward.  All calls on one GPU share that GPU's array, which keeps the last call's contents (the call clears what
  * must start at zero): calls that overlap on one GPU, from any handle or stream, race. */

@@ -42,7 +42,8 @@ struct Layout {
     int64_t wt_off = -1;                  // transposed copies of the matrices the streaming kernels read transposed (parameter layout)
     int64_t frames_off = 0;               // per buffer id: int64 floats per frame of a frame tensor of the workspace (has history frames), else 0
     int64_t total = 0;
-    int64_t ragged_twin_bytes = 0;        // of total: twins that only windows of no whole 16 x 16 tiles need padding for
+    int64_t uncounted_bytes = 0;          // of total, what the static workspace's limit leaves out: twins that only windows of no whole
+                                          // 16 x 16 tiles need padding for, the layouts of step launches
 };
 constexpr int64_t SYNC_BYTES = 1024;
 static_assert(16 + 4 * (XCD_WORDS_FIRST + XCD_WORDS) <= SYNC_BYTES, "control words");
@@ -92,10 +93,10 @@ Layout make_layout(const Plan& P, int T, int N, int64_t partial_floats, bool tra
         if (twins[b]) {
             const int64_t at = cur;
             place(b);
-            if (N % 16 != 0 || P.buf_dim[b] % 16 != 0) L.ragged_twin_bytes += cur - at;
+            if (N % 16 != 0 || P.buf_dim[b] % 16 != 0) L.uncounted_bytes += cur - at;
         }
     L.total = cur;
-    L.ragged_twin_bytes += L.blob_bytes - L.lay_off;      // (the static workspace's limit counts the layouts no more than those twins)
+    L.uncounted_bytes += align_up(L.blob_bytes, 256) - align_up(L.lay_off, 256);      // (all that the layouts moved the rest by)
     return L;
 }
 
@@ -1231,7 +1232,7 @@ namespace {
 static __device__ __align__(256) unsigned char scratch[RNN_STATIC_WORKSPACE_BYTES];
 constexpr int STATIC_MAX_DEVICES = 64;
 // per device: address of that GPU's copy (nullptr: not asked yet); [1]: of the large array, for windows that
-// fit RNN_STATIC_WORKSPACE_BYTES but for their twins
+// fit RNN_STATIC_WORKSPACE_BYTES but for what its limit leaves out
 void* g_scratch_ptr[2][STATIC_MAX_DEVICES];
 std::mutex g_scratch_mutex;
 }  // namespace
@@ -1245,7 +1246,7 @@ int rnn_forward_static(rnn_graph* g, const float* d_weights, const float* const*
         if (!d_outputs[i]) return fail(RNN_ERR_INVALID_ARGUMENT, "an output tensor pointer is NULL");
     if (T <= 0 || N <= 0) return fail(RNN_ERR_INVALID_ARGUMENT, "T and N must be positive");
     if (g->prof.mask != 0) return fail(RNN_ERR_SEQUENCE, "kernel-class timing creates events: switch it off for rnn_forward_static");
-    const int64_t total = g->layout_for(T, N).total, need = total - g->layout_for(T, N).ragged_twin_bytes;
+    const int64_t total = g->layout_for(T, N).total, need = total - g->layout_for(T, N).uncounted_bytes;
     const bool large = total > (int64_t)RNN_STATIC_WORKSPACE_BYTES;
     if (need > (int64_t)RNN_STATIC_WORKSPACE_BYTES)
         return fail(RNN_ERR_WORKSPACE, "the window needs " + std::to_string(need) + " bytes of workspace, the static workspace holds " +

@@ -282,6 +282,36 @@ def test_build_of_few_streams(monkeypatch, layers, N, copies):
     assert copies * one <= workspace("1") - workspace("0") <= copies * (one + (1 << 16))
 
 
+@pytest.mark.parametrize("nodes", [2, 7, 23, 40])
+def test_static_workspace_does_not_count_the_layouts_of_step_launches(monkeypatch, nodes):
+    """What rnn_forward_static says a window needs, where that is too much (the call ends there), with and without
+    step kernels of the run-time compiler, whose register launches bring layouts into the plan tables."""
+    import workloads as wl
+    from paper_1503_02852_amd import binding
+    spec = wl.GraphSpec()
+    at = spec.add_node(wl.INPUT, wl.LINEAR, 8, name="x")
+    h = spec.add_node(wl.ADD, wl.TANH, 16, has_bias=True, name="h")
+    spec.add_edge(at, h, wl.FULL, 0)
+    spec.add_edge(h, h, wl.FULL, 1)
+    for i in range(nodes):
+        k = spec.add_node(wl.ADD, wl.TANH, 16, has_bias=True, name=f"a{i}")
+        spec.add_edge(h, k, wl.FULL, 0)
+        h = k
+    o = spec.add_node(wl.ADD, wl.SOFTMAX, 4, has_bias=True, is_output=True, name="y")
+    spec.add_edge(h, o, wl.FULL, 0)
+
+    def sizes(jit):
+        monkeypatch.setenv("RNNG_JIT", jit)
+        g = binding.Graph(spec.node_array(), spec.edge_array())
+        with pytest.raises(binding.RnnError) as ei:
+            g.forward_static(256, [256], [256], 1 << 20, 1, 0)
+        assert ei.value.code == -3
+        return g.workspace_bytes(1 << 20, 1), int(re.search(r"needs (\d+) bytes", str(ei.value))[1])
+
+    (all_with, with_layouts), (all_without, without) = sizes("1"), sizes("0")
+    assert all_with > all_without and with_layouts == without
+
+
 def _kernel_resources(source):
     """name -> bytes of scratch per lane of every kernel of one source file, from the compiler's own listing."""
     from paper_1503_02852_amd import build
