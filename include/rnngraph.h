@@ -143,7 +143,9 @@ int rnn_forward(rnn_graph* g, const float* d_weights, const float* const* d_inpu
  * the forward pass advances by h' new frames while the backward pass covers the last h frames).
  * Frames [0, t_begin) must already hold the results of earlier calls on the same workspace with
  * the same T and N (RNN_ERR_SEQUENCE otherwise): delayed connections read them as y(t - d), so a
- * window computed in pieces equals the window computed at once.  Arguments as in rnn_forward,
+ * window computed in pieces equals the window computed at once (to the last bit, but where products of
+ * 1,024 columns and more over few rows are shared by several workgroups, whose parts are added in any
+ * order; rnn_set_deterministic keeps to one).  Arguments as in rnn_forward,
  * which is rnn_forward_range(.., 0, T, ..).  A call with t_begin = 0 starts a fresh window: zero
  * state in front of it, control words cleared.  rnn_bptt needs the whole window computed. */
 int rnn_forward_range(rnn_graph* g, const float* d_weights, const float* const* d_inputs,

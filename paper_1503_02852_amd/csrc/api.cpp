@@ -1425,7 +1425,7 @@ int rnn_grads(rnn_graph* g, float* d_grads, double* loss, void* hip_stream) {
     const int T = g->T, N = g->N, H = g->hist();
     const int64_t F = (int64_t)T * N;      // the window's own frames: the sums run over t0' < t <= t1
 
-    // Weight-gradient GEMMs: the contraction runs over frames, split over blockIdx.z.  A block that one
+    // Weight-gradient GEMMs: the contraction runs over frames, its parts x tiles in one row of workgroups.  A block that one
     // unsplit product writes is stored, not added to zeros: blocks of at least OWN_MIN floats are
     // left out of the zero fill (smaller ones are not worth another fill launch for what lies between them).
     // Filling and adding moved each such block twice more.  This call with blocks from 1 / 2^18 / 2^20 / 2^22 / 2^24 floats

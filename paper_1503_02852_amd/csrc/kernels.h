@@ -27,7 +27,8 @@ struct GemmProblem {
     int accumulate;         // 1: C += result instead of C = result
     const float* bias;      // stored is f(result + bias[column]) (NULL: none), f by act (ACT_*); only where the result is stored by
     int act;                // one workgroup (split == 1, no accumulate)
-    int min_split;          // the contraction is split into no fewer parts than this (their sums round no less than these)
+    int min_split;          // tiles of 64 and 128 split the contraction into no fewer parts than this, if several workgroups may add to
+                            // a result (their sums round no less than these; tiles of 32 add sums of 64 columns by themselves)
     // by plan_gemm_group:
     int split;              // > 1: that many workgroups share the contraction of a tile and add to C, which must be zero
     int kind;               // 0, 1, 2: tiles of 32, 64, 128; 3: of 32, with rows of GEMM_WIDE_ROW floats or more

@@ -2333,9 +2333,6 @@ __device__ __forceinline__ void mstep2_kernel_body(const StepArgs& a, M2Shared& 
 //   constexpr seg_ul(i), seg_task(i), seg_edge(i), seg_src(i), seg_tr(i) (reads the transposed copy), K(s), KP(s) (padded to 256),
 //   xoff(s), pq0(s) / pqn(s) (first polling register and count of source s).
 // =============================================================================================
-#ifndef MSTREAM_SERPENTINE
-#define MSTREAM_SERPENTINE 1
-#endif
 struct SShared { StepShared sh; };
 
 template <class PH, class SS>
@@ -2670,7 +2667,7 @@ __device__ __forceinline__ void smstep_kernel_body(const StepArgs& a, SShared& m
         // what the step before read last and what the 256 MiB memory-side cache still holds; in the same order each step would find
         // the lines gone that it is about to read.  (256 MiB of weights per step, forward / backward: 16 streams 46.9 / 59.6 -> 44.8 / 56.6 us,
         // 64 streams 82 / 116 -> 81 / 111.)  By the frame's parity, not the launch's step: a frame adds up alike wherever its call begins.
-        const bool rev = MSTREAM_SERPENTINE && (t & 1) != 0;
+        const bool rev = (t & 1) != 0;
         __amdgpu_buffer_rsrc_t rs[SM::NSRC];
 #pragma unroll
         for (int sidx = 0; sidx < SM::NSRC; ++sidx) {
