@@ -215,7 +215,7 @@ __global__ __launch_bounds__(SMX_THREADS) void softmax_wide_rows_kernel(float* _
 }
 
 // One wavefront per row.  The workgroups' losses meet in one address, about 13 ns each: a workgroup takes several rows where
-// rows are short, so that the additions don't outlast the rows (8,192 rows of 30 / 256 columns 27 / 29 -> 11 / 14 us).
+// there are few values, so that the additions don't outlast the rows (the launch's rule below).
 __global__ __launch_bounds__(256) void softmax_ce_delta_kernel(const float* __restrict__ y, const int32_t* __restrict__ targets,
                                                                float* __restrict__ ds, double* loss, unsigned* flag, long long rows, int dim) {
     __shared__ double wl[4];
@@ -458,7 +458,12 @@ hipError_t launch_softmax_ce_delta(const float* y, const int32_t* targets, float
                            dim3(256), 0, stream, y, targets, ds, loss, flag, (long long)rows, dim);
         return hipGetLastError();
     }
-    const int64_t blocks = std::min<int64_t>((rows + 3) / 4, dim <= 256 ? 512 : 2048);
+    // Additions to the loss against rows that a wavefront walks one after the other, each of which costs about as much as 128
+    // values beside its own.  512 / 2,048 workgroups, us of the backward pass of one layer: 8,192 rows of 30 / 256 / 600 / 1,000
+    // columns 17 / 34, 19 / 35, 28 / 39, 37 / 42; 32,768 of 30 / 128 / 256 / 400 / 1,000 24 / 36, 28 / 38, 43 / 43, 58 / 49, 108 / 68;
+    // 65,536 of 128 51 / 45; 131,072 of 30 67 / 46; 400,000 of 30 183 / 78.  Beyond 1,024 columns there is no such side (2,048 rows of 1,500 /
+    // 2,000 20.5 / 21.4 and 24.4 / 23.2, 4,096 32.9 / 31.1 and 37.2 / 32.3).
+    const int64_t blocks = std::min<int64_t>((rows + 3) / 4, dim <= 1024 && rows * (dim + 128) <= 12 << 20 ? 512 : 2048);
     hipLaunchKernelGGL(softmax_ce_delta_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, y, targets, ds, loss, flag, (long long)rows, dim);
     return hipGetLastError();
 }
@@ -467,7 +472,9 @@ hipError_t launch_squared_error_delta(const float* y, const float* d, float* ds,
                                       hipStream_t stream) {
     if (n <= 0) return hipSuccess;
     long long blocks = (n + 255) / 256;
-    if (blocks > 512) blocks = n > (1 << 22) ? 2048 : 512;      // (their losses meet in one address, 13 ns each: 3,000 x 61 10.3 -> 7.8 us)
+    // (their losses meet in one address, 13 ns each.  512 / 2,048 workgroups, us of the backward pass of one layer: 2^18 values 15 / 21, 2^20 17 / 34,
+    // 2^22 26 / 39, 2^23 37 / 45, 2^24 60 / 56, 2^26 322 / 158)
+    if (blocks > 512) blocks = n > (1 << 23) ? std::min<long long>(blocks, 2048) : 512;
     hipLaunchKernelGGL(squared_error_delta_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, y, d, ds, loss, (long long)n, act);
     return hipGetLastError();
 }

@@ -123,3 +123,27 @@ def test_squared_error_sums_in_double(T, O):
     terms = (np.float32(0.5) * err * err).astype(np.float64)
     # every addition of the longest chain (a thread's terms, a wavefront, a workgroup, up to 2,048 workgroups) rounds by 2^-53
     assert abs(loss - terms.sum()) <= 2.0 ** -53 * (T * O / (512 * 256) + 2048 + 16 + 64) * terms.sum()
+
+
+@pytest.mark.parametrize("T", [66576, 66577])
+def test_output_delta_of_many_short_rows(T):
+    """61 classes, as many rows as 512 workgroups take and one more: every row's delta and the loss."""
+    from paper_1503_02852_amd.runner import window_for
+    spec = wl.GraphSpec()
+    x = spec.add_node(wl.INPUT, wl.LINEAR, 4, name="x")
+    o = spec.add_node(wl.ADD, wl.SOFTMAX, 61, has_bias=True, is_output=True, name="y")
+    spec.add_edge(x, o, wl.FULL, 0)
+    w = wl.make_workload("rows", spec, T=T, N=1, seed=T, scale=0.4, bias_scale=0.3)
+    w.targets[o][::7] = -1
+    win = window_for(w)
+    win.forward()
+    win.bptt()
+    loss = win.compute_grads(want_loss=True)
+    y, tg = win.node_output(o).reshape(T, 61), w.targets[o].reshape(-1)
+    used = tg >= 0
+    want = np.where(used[:, None], y, np.float32(0.0))
+    want[used, tg[used]] -= np.float32(1.0)
+    assert np.array_equal(win.node_state_grad(o).reshape(T, 61), want)
+    # the hardware logarithm's error (2 ulp of log2 near 1: 2^-22 absolute) per frame
+    sum_ = -np.log(y[used, tg[used]].astype(np.float64)).sum()
+    assert abs(loss - sum_) <= 2.0 ** -21 * T + 1e-6 * sum_
