@@ -434,12 +434,16 @@ void plan_gemm_group(GemmMode mode, GemmGroup& g, bool one_writer) {
             p.chunks = (int)std::min<int64_t>((int64_t)p.chunks + c, 1 << 30);
             ld = std::max(ld, std::max(g.pair[q].lda, g.pair[q].ldb));
         }
-        p.narrow = std::min(p.window_M, p.N) < 96;
+        // One tile of the largest kind across.  Counted as narrow up to 64 / 95 / 128 rows or columns, us of the gradient products: 128 outputs
+        // of 1,024 units, 8,192 frames 212 / 212 / 196, of 2,048 units, 4,096 frames 322 / 322 / 297; forward products and up to 119 outputs alike.
+        // (Up to 191: 160 outputs, 4,096 frames 111 -> 126.)
+        p.narrow = std::min(p.window_M, p.N) <= 128;
         p.kind = ld >= GEMM_WIDE_ROW ? 3 : 0;
         pieces = pieces || p.M != p.window_M;
     }
     // Weight gradients are added to zeros that the caller has stored; other products are split only where they have to be, since the
-    // order in which the parts are added changes from run to run.
+    // order in which the parts are added changes from run to run.  (Three products of 512 x 512, 8,192 frames in up to 1 / 4 / 8 / 64 / 256 parts 143 /
+    // 133 / 130 / 130 / 130 us; with fewer frames or units alike from 1 on: what they cannot do without, min_split, makes enough workgroups.)
     int most = mode == GEMM_TN ? 64 : 1;
     for (int i = 0; i < g.n_problems; ++i) most = std::max(most, g.p[i].min_split);
     // every problem in tiles of one size, or the narrow ones in smaller tiles and a launch of their own; kinds lo[m] .. hi[m] for

@@ -64,7 +64,10 @@ enum { ST_BUF = 0, ST_SLOT, ST_DIM, ST_FLAGS, ST_WORDS };         // flags bit 0
 
 constexpr int MAX_SLOTS = 32;     // a 32-float slot file stays in vector registers (indexed with uniform indices)
 
-constexpr int QUAD_SLOTS = 12;    // of a program that runs on four units per thread (PhasePlan::quads)
+// Of a program that runs on four units per thread (PhasePlan::quads).  Sums of k products, 1,024 units, 8,192 frames, programs of up to 0 / 12 / 24
+// slots on four units, us of a window's node programs: k = 2 177 / 151 / 152, 7 422 / 362 / 362, 12 685 / 589 / 611, 20 1,088 / 939 / 980; 256 frames
+// and fewer alike within 5 %.
+constexpr int QUAD_SLOTS = 12;
 
 inline int program_words(const int32_t* p) {
     return PG_HEADER_WORDS + p[PG_NGATHER] * GA_WORDS + p[PG_NINV] * IV_WORDS + p[PG_NOPS] * MO_WORDS +
