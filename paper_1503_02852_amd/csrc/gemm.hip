@@ -434,10 +434,10 @@ void plan_gemm_group(GemmMode mode, GemmGroup& g, bool one_writer) {
             p.chunks = (int)std::min<int64_t>((int64_t)p.chunks + c, 1 << 30);
             ld = std::max(ld, std::max(g.pair[q].lda, g.pair[q].ldb));
         }
-        // One tile of the largest kind across.  Counted as narrow up to 64 / 95 / 128 rows or columns, us of the gradient products: 128 outputs
-        // of 1,024 units, 8,192 frames 212 / 212 / 196, of 2,048 units, 4,096 frames 322 / 322 / 297; forward products and up to 119 outputs alike.
-        // (Up to 191: 160 outputs, 4,096 frames 111 -> 126.)
-        p.narrow = std::min(p.window_M, p.N) <= 128;
+        // Not quite one tile of the largest kind across.  Counted as narrow up to 63 / 95 / 128 / 191 rows or columns, us of the gradient products: 100
+        // outputs of 1,024 units, 4,096 frames 133 / 132 / 132 / 131, 128 outputs, 8,192 frames 212 / 212 / 196 / 196, but three gated layers
+        // of 1,024 on 128 inputs, 8,192 frames 3,315 / 3,315 / 3,380, and 160 outputs 111 / 111 / 111 / 126.
+        p.narrow = std::min(p.window_M, p.N) < 96;
         p.kind = ld >= GEMM_WIDE_ROW ? 3 : 0;
         pieces = pieces || p.M != p.window_M;
     }
