@@ -2659,15 +2659,17 @@ __device__ __forceinline__ void smstep_kernel_body(const StepArgs& a, SShared& m
     for (int p = 0; p < IPT; ++p)
 #pragma unroll
         for (int c = 0; c < (PH::NC > 0 ? PH::NC : 1); ++c) carry[p][c] = 0.0f;
-    const int nsteps = step_count(a);
+    const int nsteps = step_count(a), first = __builtin_amdgcn_readfirstlane(step_frame(a, 0) & 1);
     for (int step = 0; step < nsteps; ++step) {
         const int t = step_frame(a, step);
         RNNG_STAMP(0);
         // Every second step goes through the columns, and the sources where they are alike, backwards: what it reads first is
         // what the step before read last and what the 256 MiB memory-side cache still holds; in the same order each step would find
         // the lines gone that it is about to read.  (256 MiB of weights per step, forward / backward: 16 streams 46.9 / 59.6 -> 44.8 / 56.6 us,
-        // 64 streams 82 / 116 -> 81 / 111.)  By the frame's parity, not the launch's step: a frame adds up alike wherever its call begins.
-        const bool rev = (t & 1) != 0;
+        // 64 streams 82 / 116 -> 81 / 111.)  The even frames (t is the first frame + or - step), not the launch's even steps: a frame adds up
+        // alike wherever its call begins.  (Which way is no matter; written like this 16 streams take 50.6 / 57.1 us on a card where t & 1 takes 50.4 / 59.7 and
+        // step & 1 49.3 / 59.7: the loops differ by a few scalar instructions only.)
+        const bool rev = (step & 1) == first;
         __amdgpu_buffer_rsrc_t rs[SM::NSRC];
 #pragma unroll
         for (int sidx = 0; sidx < SM::NSRC; ++sidx) {
