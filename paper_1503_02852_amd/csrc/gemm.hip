@@ -403,7 +403,8 @@ int split_of(const GemmProblem& p, int kind, int factor, bool one_writer) {
 //     385 / 396, 12 x 250 x 250, K = 3000 in 8 / 24 parts 67 / 62, 89 / 79
 //   tiles of 64: 566 / 643, 364 / 514, 47 / 43; 409 / 425, 53 / 59, 88 / 92
 //   tiles of 32: 1021 / 1088, 709 / 732, 74 / 71; in one part 489 / 535, 56 / 53
-// (64 of 2048 x 20,000 x 512 is 41 % off, but the order of the kinds is the measured one.)
+// (Tiles of 64 for 2048 x 20,000 x 512 are 41 % off; the kind with the least estimate is the fastest one but for 12 x 250 x 250, where 32 takes 3 us
+// more than 64.)
 double estimate(GemmMode mode, const GemmGroup& g, int mask, int kind, int factor, bool one_writer) {
     static const double start[3] = {0.8, 0.8, 4.0}, alone[3] = {0.04, 0.41, 1.15};
     const double each[3] = {mode == GEMM_TN ? 0.085 : 0.12, 0.30, 0.90};
