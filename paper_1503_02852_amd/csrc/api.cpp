@@ -201,8 +201,8 @@ struct rnn_graph {
     bool use_jit = true;
     bool use_store_window = true;
     // Run-time specialised step kernels, chosen once per (component, direction, stream count).
-    struct JitChoice { bool wave = false, mstep = false, stream = false, needs_t = false, blocked = false; int J = 1; StepLaunchPlan lp; std::string source, source_window; bool two_d = false; int64_t partial_floats = 0; };
-    int force_step_J = 0;
+    struct JitChoice { bool wave = false, mstep = false, stream = false, needs_t = false, blocked = false, local = false; int J = 1; StepLaunchPlan lp; std::string source, source_window; bool two_d = false; int64_t partial_floats = 0; };
+    int force_step_J = 0, local_env = -1;      // RNNG_MSTEP_LOCAL: 0 never, 1 wherever it can run
     bool prefer_streaming = false;        // RNNG_STEP_BUILD=stream
     // the workgroups of a step launch wait for each other, so all of them must be resident at once:
     // one per compute unit (256 on a whole MI355X, fewer on a partition)
@@ -238,8 +238,17 @@ struct rnn_graph {
                 c.lp.xcd_stride = G <= 32 ? 8 : 1;
             }
         };
+        auto try_local = [&]() {
+            if (!c.source.empty() || c.stream || force_step_G > 0 || force_step_J > 0 || !local_streams(cp, backward, N)) return;
+            const int J = (N + 15) / 16;
+            const MstepPick p = pick_mstep(cp, backward, N, J, 32, true);
+            if (p.G && J <= 8 * (32 / p.G) && p.G * J <= max_workgroups() && (local_env == 1 || p.rows <= (N >= 16 ? 48 : 32))) take_mstep(c, cp, backward, N, p, true);
+        };
+        if (N >= 5 || local_env == 1) try_local();
         try_wave(force_step_G > 0 ? force_step_G : 32);
+        if (N >= 4) try_local();
         if (force_step_G <= 0 && register_over_xcds(cp, backward, N)) try_wave(64);
+        try_local();
         // 2. matrix-core variants for many streams (weights in LDS or registers, MFMA)
         // 2a. one-dimensional split: stream groups, as many as possible (every group halves the
         //     bytes a workgroup polls per step); unit chunks: as many as the compute units allow
@@ -250,22 +259,11 @@ struct rnn_graph {
         if (c.source.empty() && !c.stream && matrix_streams(cp, backward, N)) {
             for (int J : {4, 3, 2, 1}) {
                 if (force_step_J > 0 && J != force_step_J) continue;
-                JitChoice best; int best_rows = -1;
-                for (int G : {256, 128, 64, 32, 16}) {
-                    if (force_step_G > 0 && G != force_step_G) continue;
-                    if (G * J > max_workgroups()) continue;
-                    size_t lds = 0; int rows = 0, threads = 256; bool blocked = false;
-                    std::string src = jit_mstep_source(plan, cp, backward, N, G, J, &lds, &rows, &threads, &blocked);
-                    if (src.empty()) continue;
-                    if (best_rows < 0 || (best_rows < 16 && rows > best_rows)) {      // first hit = most workgroups; move to fewer only to fill a tile
-                        best.source = src; best.mstep = true; best.lp.ok = true; best.lp.G = G; best.lp.NB = 1; best.lp.lds_bytes = lds; best.J = J;
-                        best.lp.threads = threads; best.blocked = blocked;
-                        best.lp.xcd_stride = G * J <= 32 ? 8 : 1;
-                        best_rows = rows;
-                    }
-                    if (best_rows >= 16) break;
-                }
-                if (!best.source.empty()) { one_d = best; one_d_rows = best_rows; break; }
+                const MstepPick p = pick_mstep(cp, backward, N, J, max_workgroups() / J, false);
+                if (!p.G) continue;
+                take_mstep(one_d, cp, backward, N, p, false);
+                one_d_rows = p.rows;
+                break;
             }
         }
         // 2b. the two-dimensional split, where a workgroup polls a sixteenth (or a quarter) of every
@@ -275,7 +273,7 @@ struct rnn_graph {
         const char* env2d = std::getenv("RNNG_MSTEP_2D");
         const bool forced_2d = env2d && std::atoi(env2d) != 0, no_2d = env2d && std::atoi(env2d) == 0;
         if (c.source.empty() && N > 8 && force_step_G <= 0 && force_step_J <= 0 && max_workgroups() >= 256 && !no_2d &&
-            (forced_2d || one_d_rows < 16)) {
+            (forced_2d || one_d_rows < MSTEP_MIN_ROWS)) {
             StepLayout lay;
             compute_step_layout(plan.words.data(), backward ? cp.bwd_desc_off : cp.fwd_desc_off, 256, 1, N, lay);
             int64_t polled = 0;
@@ -436,6 +434,63 @@ struct rnn_graph {
         for (int s = 0; s < lay.n_sources; ++s) if (lay.src[s].k_len > 1024) return false;
         return true;
     }
+    // The unit chunks of a component in the matrix-core build with J stream groups, at most `limit` of them: as many as fill one 16-row
+    // tile of the matrix instructions each, if need be two and more: a tile takes as long half empty (us a step: 2 x 192 LSTM units, 20
+    // streams, forward 32 chunks of 24 rows 2.24, 48 of 16 1.54; 2 x 448, 8 streams, backward 16 of 28 5.47, 28 of 16 3.49).  Rather a
+    // third of a tile empty than weight rows in registers.
+    struct MstepPick { int G = 0, J = 0, rows = 0, columns = 0; };      // columns: contracted by a workgroup per step, once per 16 x 16 tile; G = 0: does not fit
+    static constexpr int MSTEP_MIN_ROWS = 11;
+    MstepPick pick_mstep(const CompPlan& cp, bool backward, int N, int J, int limit, bool local) const {
+        MstepPick best;
+        StepLayout lay;
+        compute_step_layout(plan.words.data(), backward ? cp.bwd_desc_off : cp.fwd_desc_off, 256, 1, 1, lay);
+        if (!lay.ok || lay.n_phases != 1 || lay.ph[0].n_tasks < 1) return best;
+        const int nt = lay.ph[0].n_tasks;
+        int dim = plan.words[lay.ph[0].prog_off + PG_MAXDIM], k = 0;
+        for (int t = 0; t < nt; ++t) dim = std::max(dim, lay.ph[0].task[t].n_out);
+        for (int s = 0; s < lay.n_sources; ++s) k += lay.src[s].k_len;
+        for (int tiles = 1; tiles <= 16 && !best.G; ++tiles) {
+            const int most = 16 * tiles / nt;
+            for (int chunk = most; chunk >= 1 && chunk * nt > 16 * (tiles - 1); --chunk) {
+                if (chunk * 3 < most * 2 && best.G) break;
+                MstepPick p;
+                p.G = force_step_G > 0 ? force_step_G : (dim + chunk - 1) / chunk; p.J = J;
+                if (p.G > limit) break;
+                bool regs = false;
+                const bool fits = jit_mstep_fits(plan, cp, backward, N, p.G, J, local, &p.rows, &regs);
+                p.columns = k * ((p.rows + 15) / 16) * (((N + 15) / 16 + J - 1) / J);
+                if (force_step_G > 0) return fits ? p : best;
+                if (!fits || (regs && best.G)) continue;
+                best = p;
+                if (!regs) break;
+            }
+        }
+        return best;
+    }
+    void take_mstep(JitChoice& c, const CompPlan& cp, bool backward, int N, const MstepPick& p, bool local) const {
+        c.source = jit_mstep_source(plan, cp, backward, N, p.G, p.J, &c.lp.lds_bytes, &c.lp.threads, &c.blocked, local);
+        if (c.source.empty()) return;
+        c.mstep = true; c.local = local; c.J = p.J;
+        c.lp.ok = true; c.lp.G = p.G; c.lp.NB = 1;
+        c.lp.xcd_stride = !local && p.G * p.J <= 32 ? 8 : 1;
+    }
+    // Whether a layer of its own exchanges inside one XCD (stream groups of 16, each on the 32 workgroups of an XCD at most) where it fits:
+    // its exchanged values are stored plainly, and nothing is held back.  us a step, inside one XCD against across: LSTM forward 64 units, N = 64 1.07 / 1.42, 256 1.61 / 1.99; backward 256 2.23 / 2.54, 384, N = 8 2.76 / 4.46; one source
+    // of 128 to 512 units (Elman), N = 16 to 64 0.81 to 1.45 / 0.92 to 1.64.  With three tiles a workgroup only while 16 streams fill them
+    // (LSTM forward 384 units, N = 8 2.24 / 1.97, N = 16 2.31 / 2.41), never with four (512 units, N = 16 3.30 / 1.89).
+    // Up to 8 streams against the weights-in-registers build on one XCD: one source from N = 5 on (LSTM forward 16 / 100 units, N = 5
+    // 1.00 / 1.03 against 1.11 / 1.41, N = 4 1.00 / 1.05 against 0.89 / 0.98); several from 400 columns on (LSTM backward, N = 8, 48 / 100 / 128 units 1.64 / 1.66 / 1.76
+    // against 1.18 / 1.77 / 1.92).  N = 2 to 4: after that build on one XCD;
+    // before it on two at N = 4 (LSTM backward, 384 units 2.7 / 3.7).
+    bool local_streams(const CompPlan& cp, bool backward, int N, int several_from = 400, int one_from = 0) const {
+        if (local_env == 0 || N < 2 || !matrix_streams(cp, backward, N)) return false;
+        if (N > 8 || local_env == 1) return true;
+        StepLayout lay;
+        compute_step_layout(plan.words.data(), backward ? cp.bwd_desc_off : cp.fwd_desc_off, 256, 1, 1, lay);
+        int columns = 0;
+        for (int s = 0; lay.ok && s < lay.n_sources; ++s) columns += lay.src[s].k_len;
+        return columns > (lay.n_sources == 1 ? one_from : several_from);
+    }
     // Whether a layer's register build also stays ahead of the matrix-core build on two XCDs' 64 workgroups
     // (if it fits them): a step polls many columns, each 16 streams wide for the matrix instructions, while the
     // multiply-adds of at most four streams are few.  Step kernel of 128 frames, register against
@@ -493,7 +548,7 @@ struct rnn_graph {
         // multiply-adds per lane and step on, else from 24 backward / 100 forward)
         const char* envh = std::getenv("RNNG_CHAIN_HELPERS");
         const bool helpers_off = envh && std::atoi(envh) == 0, helpers_all = envh && std::atoi(envh) == 1;
-        if (use_jit && use_chains && force_step_G <= 0 && !prefer_streaming) {
+        auto registers = [&]() {
             for (int attempt = 0; attempt < 2 && c.source.empty(); ++attempt) {
                 c.split = attempt == 0 && !helpers_off && !(backward ? ch.bwd_split : ch.fwd_split).empty();
                 if (attempt == 0 && !c.split) continue;
@@ -510,10 +565,11 @@ struct rnn_graph {
                     c.source = jit_chain_source(plan, members, backward, N, c.G);
             }
             if (c.source.empty()) c.split = false;
+        };
+        auto matrix_cores = [&](bool matrix) {
             // Few streams: where a layer would need several XCDs.  Side by side on the matrix cores the layers
             // also beat two register launches one after the other (register_over_xcds): 2 x 768 units, N = 2
             // 0.56 + 1.02 against 0.67 + 1.00 ms forward + backward, 2 x 320, N = 4 0.37 + 0.58 against 0.89 + 0.95.
-            bool matrix = N > 8;
             for (int m = ch.first; m <= ch.last && !matrix; ++m) {
                 const JitChoice& jc = jit_choice(m, backward, N);
                 matrix = jc.mstep || (jc.wave && jc.lp.G > 32 && matrix_streams(plan.comps[m], backward, N));
@@ -525,28 +581,31 @@ struct rnn_graph {
                 // Backward launches of a stack are bound by the matrix instructions of the members that
                 // also contract the later member's error terms, while compute units idle: helper members
                 // take those products (RNNG_CHAIN_HELPERS = 0: never).
+                // Apart, each layer has all compute units: side by side pays while the slowest member's step (its matrix instructions, the
+                // exchange counted as STEP_COLUMNS) is no longer than theirs together.  2 x 700 units, N = 40, backward: 28 us a step side
+                // by side (groups of 40 streams on 6 rows), 12.6 apart; 2 x 512, N = 64, forward 5.6 against 6.0.
+                constexpr int STEP_COLUMNS = 2200;
+                int apart = 0;
+                for (int m = ch.first; m <= ch.last; ++m) {
+                    MstepPick p;
+                    for (int J = 4; J >= 1 && !p.G; --J) p = pick_mstep(plan.comps[m], backward, N, J, max_workgroups() / J, false);
+                    apart = p.G && apart < (1 << 29) ? apart + p.columns + STEP_COLUMNS : 1 << 30;
+                }
                 c.split = backward && !ch.bwd_split.empty() && !helpers_off;
                 for (int attempt = 0; attempt < 2 && c.source.empty(); ++attempt) {
                     if (attempt == 1) { if (!c.split) break; c.split = false; }
                     const std::vector<CompPlan>& members = chain_members(ch, c);
                     const int share = std::min(256, max_workgroups()) / (int)members.size();
                     c.G.clear(); c.J.clear();
+                    int slowest = 0;
                     for (const CompPlan& m : members) {
-                        int pg = 0, pj = 0, best_rows = -1;
-                        for (int J : {4, 3, 2, 1}) {
-                            for (int G : {128, 64, 32, 16}) {
-                                if (G * J > share) continue;
-                                size_t lds = 0; int rows = 0;
-                                if (jit_mstep_source(plan, m, backward, N, G, J, &lds, &rows).empty()) continue;
-                                if (best_rows < 0 || (best_rows < 16 && rows > best_rows)) { pg = G; pj = J; best_rows = rows; }
-                                if (best_rows >= 16) break;
-                            }
-                            if (pg) break;
-                        }
-                        if (!pg) break;
-                        c.G.push_back(pg); c.J.push_back(pj);
+                        MstepPick p;
+                        for (int J = 4; J >= 1 && !p.G; --J) p = pick_mstep(m, backward, N, J, share / J, false);
+                        if (!p.G) break;
+                        c.G.push_back(p.G); c.J.push_back(p.J);
+                        slowest = std::max(slowest, p.columns);
                     }
-                    if (c.G.size() == members.size()) {
+                    if (c.G.size() == members.size() && slowest + STEP_COLUMNS <= apart) {
                         c.source = jit_mstep_chain_source(plan, members, backward, N, c.G, c.J, &c.lds_bytes, &c.threads, &c.blocked);
                         c.mstep = !c.source.empty();
                         if (c.split && !c.blocked) { c.source.clear(); c.mstep = false; }      // (helpers pay only with the tile-blocked exchange's full tiles)
@@ -554,6 +613,16 @@ struct rnn_graph {
                 }
                 if (c.source.empty()) c.split = false;
             }
+        };
+        if (use_jit && use_chains && force_step_G <= 0 && !prefer_streaming) {
+            // From 5 streams on the matrix cores come first: where every layer is exchanged as one vector of more than 48 columns, or as
+            // several of more than 320 together.  us a step, registers against matrix cores: forward 2 x 64 / 128 units, N = 5 1.70 / 1.66 against
+            // 1.27 / 1.25, N = 4 2 x 32 / 160 1.13 / 1.68 against 1.29 / 1.96, 2 x 32, N = 5 1.47 against 1.36; backward, N = 5, 2 x 64 / 100 / 128 1.76 / 1.94 / 2.07 against 1.73 / 1.76 / 1.73.
+            bool first = N >= 5;
+            for (int m = ch.first; m <= ch.last && first; ++m) first = local_streams(plan.comps[m], backward, N, 320, 48);
+            if (first) matrix_cores(true);
+            registers();
+            matrix_cores(N > 8);
         }
         return chain_choices.emplace(key, c).first->second;
     }
@@ -681,16 +750,17 @@ hipError_t ensure_xcd_map(unsigned* scratch, hipStream_t s, const XcdMap** out) 
     return hipSuccess;
 }
 
-// The control word for the XCDs of the next launch that exchanges through an XCD's L2, or -1.
-hipError_t xcd_word(rnn_graph* g, hipStream_t s, int* word) {
+// The first of `count` control words for the XCDs of the next launch that exchanges through an XCD's L2 (four groups a word), or -1.
+hipError_t xcd_word(rnn_graph* g, hipStream_t s, int* word, int count = 1) {
     *word = -1;
     if (!g_xcd_local || !g->xcd || !g->xcd->ok) return hipSuccess;
-    if (g->xcd_words_used == XCD_WORDS) {
+    if (g->xcd_words_used + count > XCD_WORDS) {
         hipError_t e = launch_xcd_words_fold(g->ctrl_ptr(), s);
         if (e != hipSuccess) return e;
         g->xcd_words_used = 0;
     }
-    *word = XCD_WORDS_FIRST + g->xcd_words_used++;
+    *word = XCD_WORDS_FIRST + g->xcd_words_used;
+    g->xcd_words_used += count;
     return hipSuccess;
 }
 
@@ -863,13 +933,14 @@ StepRun run_phases(rnn_graph* g, int comp, bool backward, hipStream_t s, int t0,
                     }
             }
         }
-        if (jc->wave && jc->lp.xcd_stride == 8) {
-            hipError_t we = xcd_word(g, s, &a.xcd_word);
+        if (jc->local || (jc->wave && jc->lp.xcd_stride == 8)) {
+            hipError_t we = xcd_word(g, s, &a.xcd_word, (jc->J + 3) / 4);
             if (we != hipSuccess) return step_error(we, "XCD words");
         }
         StepLaunchPlan lp_all = jc->lp;
         lp_all.G = jc->lp.G * jc->J;       // launch size; a.G stays the number of unit chunks
         if (!launch_fits_device(g, lp_all.G, why)) return step_error(hipSuccess, why);
+        if (jc->local) { lp_all.G = mstep_local_blocks(jc->lp.G, jc->J); lp_all.xcd_stride = 1; }
         hipError_t e = jit_launch(fn, a, lp_all, s);
         if (e != hipSuccess) { (void)hipGetLastError(); return step_error(e, "specialised step kernel launch"); }
         served = jc->wave ? RNN_BUILD_WAVE : jc->two_d ? RNN_BUILD_MATRIX_2D : jc->stream ? RNN_BUILD_STREAMING : jc->mstep ? RNN_BUILD_MATRIX : RNN_BUILD_LDS;
@@ -990,6 +1061,7 @@ int rnn_graph_create(const rnn_node_desc* nodes, int32_t n_nodes, const rnn_edge
     g->grad_groups.reserve(g->plan.grad_gemms.size() / GEMM_MAX_PROBLEMS + 1);
     g->grad_owned.reserve(g->plan.grad_gemms.size());
     if (const char* env = std::getenv("RNNG_SPIN_LIMIT")) g->spin_limit = std::max(1, std::atoi(env));
+    if (const char* env = std::getenv("RNNG_MSTEP_LOCAL")) g->local_env = std::atoi(env);
     if (const char* env = std::getenv("RNNG_STEP_WORKGROUPS")) g->force_step_G = std::atoi(env);
     if (const char* env = std::getenv("RNNG_STEP_STREAM_GROUPS")) g->force_step_J = std::atoi(env);
     if (const char* env = std::getenv("RNNG_CHAIN")) g->use_chains = std::atoi(env) != 0;

@@ -472,8 +472,9 @@ namespace {
 // One component of a matrix-core kernel: descriptors PH0 and MM inside namespace ns.
 // blocked: exchange through the tile-blocked twins (only if every exchanged tensor has one and the
 // streams come in whole 16-stream tiles).
+// local: the G workgroups of each stream group sit on one XCD.
 bool emit_mstep_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, bool backward, int N_all, int G, int J, int NW, bool blocked,
-                      const std::string& ns, size_t* lds_bytes, int* rows) {
+                      const std::string& ns, size_t* lds_bytes, int* rows, bool local, int* NE, bool* in_registers = nullptr) {
     const std::vector<PhasePlan>& phases = backward ? cp.bwd_phases : cp.fwd_phases;
     if (phases.size() != 1 || N_all < 1 || J < 1 || G * J > 256) return false;
     // streams per workgroup; several stream groups are made of whole 16-stream tiles (without twins
@@ -535,6 +536,13 @@ bool emit_mstep_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, 
     const StepPhase& ph = lay.ph[0];
     const int MT = (N + 15) / 16, NTU = (ph.n_tasks * ph.cmax + 15) / 16;
     if (MT * NTU > 16) return false;     // accumulator registers
+    if (lds_bytes) *lds_bytes = (size_t)ml.total_floats * 4;
+    if (rows) *rows = ph.n_tasks * ph.cmax;
+    if (in_registers) *in_registers = reg_mask != 0;
+    if (*NE < 0) {      // asked only whether the component fits, and for the wavefronts that its element-wise items need
+        *NE = reg_mask ? 0 : (ph.item_chunk * N + 63) / 64;
+        return true;
+    }
     // D register sets, D - 1 chunks in flight (see the kernel): about a dozen 128-bit loads per lane
     // (measured: more in flight is slower), and among the depths up to that the one that pads the
     // sources' chunk sequences least
@@ -565,7 +573,7 @@ bool emit_mstep_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, 
         o << "            default: return " << dflt << ";\n        }\n    }\n";
     };
     o << "struct MM {\n    static constexpr int NJ = " << N << ", MT = " << MT << ", NSRC = " << ml.n_src << ", NTU = " << NTU
-      << ", D = " << D << ", CMAX = " << ml.cmax << ", ACCS = " << ml.accstride << ", NW = " << NW << ", NCH = " << nch << ";\n"
+      << ", D = " << D << ", CMAX = " << ml.cmax << ", ACCS = " << ml.accstride << ", NW = " << NW << ", NE = " << *NE << ", NCH = " << nch << ";\n"
       << "    static constexpr bool FLAT = " << (flat ? "true" : "false") << ", XB = " << (blocked ? "true" : "false")
       << ", TAIL = " << (N_all % 16 != 0 ? "true" : "false") << ", HELPER = " << (cp.helper ? "true" : "false") << ";\n"
       ;
@@ -613,12 +621,21 @@ bool emit_mstep_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, 
             for (int nt = 0; nt < NTU; ++nt)
                 if (std::find(used.begin(), used.end(), std::make_pair(cs.second * 16 + nt, 1)) != used.end()) { const int i = (int)widx.size(); widx.push_back({cs.first * 16 + nt, i}); }
     emit_switch("widx", "key", widx, 0);
+    // How long (units of 64 clocks) the first loads of the previous step's values are held back where those cross XCDs: a load that comes
+    // back too early costs a second round trip, and the stores it waits for arrive later the more is polled.  The line through the best of
+    // 0 to 16 units at 0.25 to 8 MiB polled per step: LSTM forward, 16 streams, us a step without / with: 256 units 1.94 / 1.53, 512
+    // 2.41 / 1.98; backward 512 5.34 / 3.84, 320 4.84 / 3.21; 2 x 256, 8 streams 1.86 + 2.42 / 1.71 + 2.40.  Inside one XCD, and for a
+    // helper, which starts late by itself, any holding back only costs (128 units 1.20 / 1.28).
+    double polled_mib = 0;
+    for (int s = 0; s < ml.n_src; ++s) polled_mib += (double)G * N_all * lay.src[s].k_len * 4 / (1 << 20);
+    int hold = local || cp.helper ? 0 : std::min(12, (int)(3 + 1.9 * polled_mib));
+    if (const char* env = std::getenv("RNNG_MSTEP_HOLD")) hold = std::max(0, std::min(127, std::atoi(env)));
+    o << "    static constexpr int HOLD = " << hold << ";\n";
+    o << "    static constexpr int LG = " << (local ? G : 0) << ";\n";
     o << "    static constexpr unsigned REGMASK = " << reg_mask << "u;\n    static constexpr int NRW = " << widx.size() << ", CLATE = " << clate << ";\n";
     o << "    static __device__ __forceinline__ constexpr int blk(int s, int task) { return blk_(s * " << STEP_MAX_TASKS << " + task); }\n";
     o << "    static __device__ __forceinline__ constexpr bool used(int s, int nt) { return used_(s * 16 + nt) != 0; }\n};\n";
     o << "}  // namespace " << ns << "\n";
-    if (lds_bytes) *lds_bytes = (size_t)ml.total_floats * 4;
-    if (rows) *rows = ph.n_tasks * ph.cmax;
     return true;
 }
 }  // namespace
@@ -629,9 +646,25 @@ static std::vector<int> mstep_wave_counts() {
     if (const char* env = std::getenv("RNNG_MSTEP_WAVES")) { const int v = std::atoi(env); if (v == 4 || v == 8) return {v}; }
     return {8, 4};
 }
-static const char* mstep_kernel_attributes(int NW) {
-    return NW == 8 ? "extern \"C\" __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))\n"
-                   : "extern \"C\" __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))\n";
+static std::string mstep_kernel_attributes(int waves) {
+    const std::string eu = std::to_string((waves + 3) / 4);
+    return "extern \"C\" __global__ __launch_bounds__(" + std::to_string(64 * waves) + ") __attribute__((amdgpu_waves_per_eu(" + eu + ", " + eu + ")))\n";
+}
+// Wavefronts of a launch that run the element-wise programs and nothing else: as many as the items of its members need, none where a
+// member keeps weights in registers (more than eight wavefronts leave each fewer than 256).  -1: a member is not eligible.  With against
+// without, us a step: LSTM of 256 units, 16 streams 1.53 + 2.27 / 1.65 + 2.37 forward + backward, 128 1.21 + 1.68 / 1.39 + 1.87.  RNNG_MSTEP_EW = 0: none.
+static int mstep_ew_waves(const Plan& P, const std::vector<const CompPlan*>& members, bool backward, int N, const std::vector<int>& G, const std::vector<int>& J,
+                          int NW, bool blocked, bool local) {
+    int most = 0;
+    bool none = std::getenv("RNNG_MSTEP_EW") && std::atoi(std::getenv("RNNG_MSTEP_EW")) == 0;
+    for (size_t i = 0; i < members.size(); ++i) {
+        std::ostringstream o;
+        int ne = -1;
+        if (!emit_mstep_group(o, P, *members[i], backward, N, G[i], J[i], NW, blocked, "grp0", nullptr, nullptr, local, &ne)) return -1;
+        none = none || ne == 0;
+        most = std::max(most, ne);
+    }
+    return none ? 0 : most;
 }
 
 // RNNG_MSTEP_BLOCKED = 0: no exchange through tile-blocked twins (the row-major path).
@@ -640,30 +673,43 @@ static std::vector<int> mstep_blocked_choices() {
     return {1, 0};
 }
 
-std::string jit_mstep_source(const Plan& P, const CompPlan& cp, bool backward, int N_all, int G, int J, size_t* lds_bytes, int* rows, int* threads,
-                             bool* blocked) {
+bool jit_mstep_fits(const Plan& P, const CompPlan& cp, bool backward, int N_all, int G, int J, bool local, int* rows, bool* in_registers) {
+    std::ostringstream none;
+    for (int nw : mstep_wave_counts())
+        for (int b : mstep_blocked_choices()) {
+            int ne = -1;
+            if ((b || !local) && emit_mstep_group(none, P, cp, backward, N_all, G, J, nw, b != 0, "grp0", nullptr, rows, local, &ne, in_registers)) return true;
+        }
+    return false;
+}
+
+std::string jit_mstep_source(const Plan& P, const CompPlan& cp, bool backward, int N_all, int G, int J, size_t* lds_bytes, int* threads,
+                             bool* blocked, bool local) {
     std::ostringstream o;
-    int NW = 0; bool xb = false;
+    int NW = 0, NE = 0; bool xb = false;
     for (int nw : mstep_wave_counts()) {
         for (int b : mstep_blocked_choices()) {
+            if (local && !b) continue;
             o.str("");
             o << "#include \"step_device.h\"\nusing namespace rnng;\n";
-            if (emit_mstep_group(o, P, cp, backward, N_all, G, J, nw, b != 0, "grp0", lds_bytes, rows)) { NW = nw; xb = b != 0; break; }
+            NE = mstep_ew_waves(P, {&cp}, backward, N_all, {G}, {J}, nw, b != 0, local);
+            if (NE >= 0 && emit_mstep_group(o, P, cp, backward, N_all, G, J, nw, b != 0, "grp0", lds_bytes, nullptr, local, &NE)) { NW = nw; xb = b != 0; break; }
         }
         if (NW) break;
     }
     if (!NW) return "";
-    if (threads) *threads = 64 * NW;
+    if (threads) *threads = 64 * (NW + NE);
     if (blocked) *blocked = xb;
-    o << mstep_kernel_attributes(NW) <<
+    o << mstep_kernel_attributes(NW + NE) <<
          "void rnng_step_jit(StepArgs a) {\n"
          "    extern __shared__ __attribute__((aligned(16))) float lds[];\n"
          "    __shared__ MShared ms;\n"
          "    int w = blockIdx.x;\n"
-         "    if (a.xcd_stride > 1) {\n"
-         "        if (w % a.xcd_stride) return;\n"
-         "        w /= a.xcd_stride;\n"
-         "    }\n"
+      << (local ? "    w = mstep_local_unit<grp0::MM::LG>() * grp0::MM::LG + mstep_local_part<grp0::MM::LG>();\n"
+                : "    if (a.xcd_stride > 1) {\n"
+                  "        if (w % a.xcd_stride) return;\n"
+                  "        w /= a.xcd_stride;\n"
+                  "    }\n") <<
          "    mstep_kernel_body<grp0::PH0, grp0::MM>(a, ms, lds, w);\n"
          "}\n";
     return o.str();
@@ -736,16 +782,19 @@ std::string jit_mstep_chain_source(const Plan& P, const std::vector<CompPlan>& m
     const int n = (int)members.size();
     if (n < 2 || n > STEP_MAX_GROUPS || (int)G.size() != n || (int)J.size() != n) return "";
     size_t lds_max = 0;
-    int total = 0, NW = 0; bool xb = false;
+    int total = 0, NW = 0, NE = 0; bool xb = false;
+    std::vector<const CompPlan*> list;
+    for (const CompPlan& m : members) list.push_back(&m);
     for (int nw : mstep_wave_counts()) {      // one launch: the same number of wavefronts and the same exchange for all members
         for (int b : mstep_blocked_choices()) {
             o.str("");
             o << "#include \"step_device.h\"\nusing namespace rnng;\n";
             lds_max = 0; total = 0;
-            bool all = true;
+            NE = mstep_ew_waves(P, list, backward, N, G, J, nw, b != 0, false);
+            bool all = NE >= 0;
             for (int g = 0; g < n && all; ++g) {
                 size_t lds = 0;
-                all = emit_mstep_group(o, P, members[g], backward, N, G[g], J[g], nw, b != 0, "grp" + std::to_string(g), &lds, nullptr);
+                all = emit_mstep_group(o, P, members[g], backward, N, G[g], J[g], nw, b != 0, "grp" + std::to_string(g), &lds, nullptr, false, &NE);
                 lds_max = std::max(lds_max, lds);
                 total += G[g] * J[g];
             }
@@ -756,8 +805,8 @@ std::string jit_mstep_chain_source(const Plan& P, const std::vector<CompPlan>& m
     if (!NW) return "";
     if (blocked) *blocked = xb;
     if (total > 256) return "";      // every workgroup must be resident: they wait for each other
-    if (threads) *threads = 64 * NW;
-    o << mstep_kernel_attributes(NW) <<
+    if (threads) *threads = 64 * (NW + NE);
+    o << mstep_kernel_attributes(NW + NE) <<
          "void rnng_step_jit(StepArgs a) {\n"
          "    extern __shared__ __attribute__((aligned(16))) float lds[];\n"
          "    __shared__ MShared ms;\n"

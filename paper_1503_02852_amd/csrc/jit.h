@@ -21,11 +21,15 @@ std::string jit_wave_source(const Plan& P, const CompPlan& cp, bool backward, in
 std::string jit_chain_source(const Plan& P, const std::vector<CompPlan>& members, bool backward, int N, const std::vector<int>& G);
 // Matrix-core variant for many streams; *lds_bytes receives the dynamic LDS size.
 // G unit chunks x J stream groups (N / J streams each).
-// *rows receives the accumulator rows per workgroup (tasks x units per chunk).
-// *threads: threads per workgroup of the launch (512 where eight wavefronts fit, else 256);
+// *threads: threads per workgroup of the launch (up to eight wavefronts that contract, and those that only run the element-wise program);
 // *blocked: the kernel exchanges through the tile-blocked twins of the shared tensors.
-std::string jit_mstep_source(const Plan& P, const CompPlan& cp, bool backward, int N, int G, int J, size_t* lds_bytes, int* rows = nullptr,
-                             int* threads = nullptr, bool* blocked = nullptr);
+// local: each stream group's G <= 32 workgroups sit on one XCD and exchange through its L2 (only with the twins); the launch has
+// mstep_local_blocks(G, J) workgroups.
+std::string jit_mstep_source(const Plan& P, const CompPlan& cp, bool backward, int N, int G, int J, size_t* lds_bytes, int* threads = nullptr,
+                             bool* blocked = nullptr, bool local = false);
+// Whether that variant exists; *rows: accumulator rows per workgroup (tasks x units per chunk), *in_registers: weight rows of whole sources
+// are kept in vector registers.
+bool jit_mstep_fits(const Plan& P, const CompPlan& cp, bool backward, int N, int G, int J, bool local, int* rows, bool* in_registers);
 // Matrix-core variant with the two-dimensional split (row groups of GJ workgroups that share
 // the columns of every source; partial sums travel through a tensor of *partial_floats floats per frame).
 std::string jit_mstep2_source(const Plan& P, const CompPlan& cp, bool backward, int N, int G, int GJ, size_t* lds_bytes,
@@ -35,6 +39,8 @@ std::string jit_mstep2_source(const Plan& P, const CompPlan& cp, bool backward, 
 // members (ChainPlan::bwd_split).  Empty if some member is not eligible.
 std::string jit_mstep_chain_source(const Plan& P, const std::vector<CompPlan>& members, bool backward, int N, const std::vector<int>& G,
                                    const std::vector<int>& J, size_t* lds_bytes, int* threads = nullptr, bool* blocked = nullptr);
+// Workgroups of a launch whose stream groups (units in all) of G workgroups sit on one XCD each.
+inline int mstep_local_blocks(int G, int units) { return 8 * G * ((units + 7) / 8); }
 // Streaming variant (N <= 8 streams; weights read from memory every step, for layers too wide to
 // keep on chip): G unit chunks.  *transposed: the kernel reads transposed copies of some matrices.
 std::string jit_sstep_source(const Plan& P, const CompPlan& cp, bool backward, int N, int G, size_t* lds_bytes, bool* transposed);

@@ -463,11 +463,13 @@ __device__ __forceinline__ void phase_setup(PhaseRegs<PH>& r, const StepArgs& a,
 #if !defined(RNNG_STEP_TRACE_AT)
 #define RNNG_STEP_TRACE_AT 64
 #endif
-#define RNNG_STAMP(i)                                                                                       \
-    if (blockIdx.x == RNNG_STEP_TRACE - 1 && tid == 0 && step >= RNNG_STEP_TRACE_AT && step < RNNG_STEP_TRACE_AT + 8)         \
+#define RNNG_STAMP(i) RNNG_STAMP_BY(i, 0)
+#define RNNG_STAMP_BY(i, thread)                                                                            \
+    if (blockIdx.x == RNNG_STEP_TRACE - 1 && tid == (thread) && step >= RNNG_STEP_TRACE_AT && step < RNNG_STEP_TRACE_AT + 8)         \
         reinterpret_cast<unsigned long long*>(a.ctrl + 16)[(step - RNNG_STEP_TRACE_AT) * 8 + (i)] = clock64()
 #else
 #define RNNG_STAMP(i)
+#define RNNG_STAMP_BY(i, thread)
 #endif
 
 template <class PH, int NB, int NPHASES>
@@ -1466,6 +1468,13 @@ struct MStore { static constexpr bool SW = RNNG_STORE_WINDOW != 0; };
 // (leaner than StepShared: one phase, so that more of the 160 KiB is left for weight rows)
 struct MShared { StepLayout lay; unsigned iteminfo[1][STEP_THREADS]; MLayout ml; unsigned retried[2]; };
 
+// Launches whose stream groups each sit on one XCD: units (stream groups of the members, one member after the other) of LG
+// workgroups; workgroups b, b + 8, ... of a launch share an XCD, so unit u takes the workgroups of residue u % 8.
+template <int LG>
+__device__ __forceinline__ int mstep_local_unit() { return (int)(blockIdx.x & 7) + 8 * ((int)(blockIdx.x >> 3) / (LG > 0 ? LG : 1)); }
+template <int LG>
+__device__ __forceinline__ int mstep_local_part() { return (int)(blockIdx.x >> 3) % (LG > 0 ? LG : 1); }
+
 template <class PH, class MM>
 // w: index of this workgroup among the a.G * a.J workgroups of the component.
 __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms, float* lds, int w) {
@@ -1477,12 +1486,22 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
     const int n0 = wj * MM::NJ;                                            // first stream of this workgroup
     const int N = a.N - n0 < MM::NJ ? a.N - n0 : MM::NJ;                   // its streams
     MShared& sh = ms;
-    constexpr int NW = MM::NW, NTHR = 64 * NW, CW = 16 * NW;      // wavefronts, threads, columns of a chunk
+    // wavefronts that contract, all threads, columns of a chunk; MM::NE more wavefronts run the element-wise program (0: the first ones
+    // of the others do)
+    constexpr int NW = MM::NW, NTHR = 64 * (NW + MM::NE), CW = 16 * NW;
+    const int itid = MM::NE == 0 ? tid : tid >= 64 * NW ? tid - 64 * NW : STEP_THREADS;      // the element-wise item of this thread
+    // MM::LG: the workgroups of a stream group sit on one XCD (their launch puts them there; each leaves its XCD's id, and the host
+    // reports a group on several), so twins are stored plainly; without the words everything is written through
+    const bool local = MM::LG > 0 && suni(a.xcd_word) >= 0;
+    if (local && tid == 0) {
+        const int u = mstep_local_unit<MM::LG>();
+        atomicOr(a.ctrl + suni(a.xcd_word) + (u >> 2), 1u << (8 * (u & 3) + (step_xcc_id() & 7)));
+    }
     if (tid == 0) { compute_step_layout(a.words, a.desc_off, a.G, 1, MM::NJ, sh.lay); compute_mstep_layout(sh.lay, MM::NJ, NW, MM::REGMASK, (int)(MSTEP_LDS_LIMIT / 4), ms.ml); }
     __syncthreads();
     const StepPhase& ph = sh.lay.ph[0];
     const MLayout& ml = ms.ml;
-    if (tid < STEP_THREADS) {      // the element-wise items sit on the first STEP_THREADS threads
+    if (tid < STEP_THREADS) {      // at most STEP_THREADS element-wise items
         const int ic = ph.item_chunk;
         const int il = tid % ic, n = tid / ic;
         sh.iteminfo[0][tid] = (unsigned)il | ((unsigned)(n < N ? n0 + n : 0xFFFF) << 16);      // global stream index
@@ -1514,13 +1533,13 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
         }
     }
     PhaseRegs<PH> r;
-    phase_setup<PH, 1, 2>(r, a, sh, lds, w, tid);
+    phase_setup<PH, 1, 2>(r, a, sh, lds, w, itid);
     __syncthreads();
 
     constexpr int D = MM::D, NPAD = MM::MT * 16, ACCS = MM::ACCS;
     const int accbase = suni(ml.accbase);
-    const int item_il = tid < STEP_THREADS ? (int)(sh.iteminfo[0][tid] & 0xFFFF) : 0;
-    const int item_n = tid / suni(ph.item_chunk);                          // local stream of this thread's item
+    const int item_il = itid < STEP_THREADS ? (int)(sh.iteminfo[0][itid] & 0xFFFF) : 0;
+    const int item_n = itid / suni(ph.item_chunk);                         // local stream of this thread's item
     // LDS address of the weight row behind each of this lane's tile columns, per source
     int brow[MM::NSRC][MM::NTU];
 #pragma unroll
@@ -1657,6 +1676,11 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
         return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rg, off, 0, PH::gkind(g) == GA_KIND_STATIC ? 0 : STEP_COHERENT_AUX));
     };
 
+    auto twin_rsrc = [&](int q) {
+        return MStore::SW ? __builtin_amdgcn_make_buffer_rsrc(a.store_base, 0, (int)a.store_bytes, STEP_RSRC_FLAGS)
+                          : __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(xbase[q]), 0, a.T * xstride[q] * 4, STEP_RSRC_FLAGS);
+    };
+
     bool dead = false;
     int pdelay = 0;
     float sn[PH::NG > 0 ? PH::NG : 1];      // STATIC inputs of the next step, loaded one step ahead
@@ -1666,18 +1690,17 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
             constexpr int g = decltype(gg)::value;
             if (PH::gkind(g) == GA_KIND_STATIC) sn[g] = gather_at(gg, step_frame(a, 0) + r.goff[g]);
         });
-    for (int step = 0; step < nsteps; ++step) {
-        const int t = step_frame(a, step);
-        float s[MAX_SLOTS];
+    float s[MAX_SLOTS];
+    // element-wise inputs from the thread's own earlier frames, and a helper member's sums: coherent loads, issued first
+    auto ew_loads = [&](int t) {
+        step_static_for<0, PH::NG>([&](auto gg) {
+            constexpr int g = decltype(gg)::value;
+            if (PH::gkind(g) == GA_KIND_FRAMES || PH::gkind(g) == GA_KIND_POLLED) s[g] = gather_at(gg, t + r.goff[g]);
+        });
+    };
+    // one step's contraction: this wavefront's partial tile in LDS
+    auto contract = [&](int step, int t, bool& retried) {
         RNNG_STAMP(0);
-        // element-wise inputs from the thread's own earlier frames: coherent loads, issued first
-        if (wave_items)
-            step_static_for<0, PH::NG>([&](auto gg) {
-                constexpr int g = decltype(gg)::value;
-                if (PH::gkind(g) == GA_KIND_FRAMES || PH::gkind(g) == GA_KIND_POLLED) s[g] = gather_at(gg, t + r.goff[g]);
-            });
-        RNNG_STAMP(1);
-
         // one buffer descriptor per source tensor; a frame outside the window gets an empty one
         // (all its loads return zeros, which pass the sentinel check and contribute nothing)
         __amdgpu_buffer_rsrc_t rs[MM::NSRC];
@@ -1745,7 +1768,6 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
             }
             return __builtin_amdgcn_ballot_w64(m == STEP_SENTINEL) != 0;
         };
-        bool retried = false;
         // the retry loads into registers of its own (a reload of the pipelined set would make
         // every later use of it wait for all loads in flight)
         auto reload = [&](muintx4 (&dst)[MM::MT], auto ss, int k0) {
@@ -1783,8 +1805,10 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
         // whole extra round trip); chunks in front of them (MM::CLATE) are not.
         // (With the unrolled sequence, where the multiplications of the early chunks fill that time,
         // holding back measured slower than retrying: charlm_n32 forward 1.26 against 0.89 ms.)
-        constexpr int POLL_INC = MM::FLAT ? 0 : MSTEP_POLL_INC;
-        auto hold_off = [&]() { for (int i = 0; i < pdelay; ++i) __builtin_amdgcn_s_sleep(1); };
+        auto hold_off = [&]() {
+            if constexpr (MM::FLAT) { if (MM::HOLD > 0) __builtin_amdgcn_s_sleep(MM::HOLD); }
+            else for (int i = 0; i < pdelay; ++i) __builtin_amdgcn_s_sleep(1);
+        };
         if constexpr (MM::FLAT) {
             constexpr int NCH = MM::NCH;
             step_static_for<0, D - 1>([&](auto ii) {
@@ -1813,10 +1837,16 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
                         else opb[nt] = *reinterpret_cast<const mfloatx4*>(&lds[brow[sidx][nt] + k0 + wave * 16]);
                     }
                 });
-                if (bad && !dead) reload(v[i], StepIntC<sidx>{}, k0);
+                if (bad && !dead) {
+                    reload(v[i], StepIntC<sidx>{}, k0);
+                    // the chunks behind it were asked for as early: again, all at once (one after the other, each cost a round trip of its own)
+                    step_static_for<c + 1, (c + D - 1 < NCH ? c + D - 1 : NCH)>([&](auto nn) {
+                        constexpr int n = decltype(nn)::value, sn2 = MM::csrc(n);
+                        load_chunk(v[n % D], rs[sn2], aoff[sn2], MM::KP(sn2), MM::KP(sn2) % CW != 0, rot(StepIntC<sn2>{}, MM::ck0(n)), true);
+                    });
+                }
                 if (c == 0) { RNNG_STAMP(2); }
-                if (c == 1) { RNNG_STAMP(6); RNNG_STAMP(7); }
-                if (c + D - 1 == MM::CLATE) hold_off();
+                if (c == 1) { RNNG_STAMP(6); }
                 if (c + D - 1 < NCH) load_chunk(v[j], rs[sa], aoff[sa], MM::KP(sa), MM::KP(sa) % CW != 0, rot(StepIntC<sa>{}, MM::ck0(ca)), true);
                 bad = c + 1 < NCH ? incomplete(v[i1]) : false;
                 multiply(StepIntC<sidx>{}, v[i], opb);
@@ -1889,7 +1919,80 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
                         lds[tb + (mt * 16 + 4 * (lane >> 4) + i) * ACCS + nt * 16 + (lane & 15)] = acc[mt][nt][i];
         }
         RNNG_STAMP(3);
-        // did any wavefront have to load a chunk again?  (word `step & 1`; the other one is cleared for the next step)
+    };
+    // the matrix-vector sums of this thread's item, from the wavefronts' tiles
+    auto ew_sums = [&]() {
+        step_static_for<0, PH::NG>([&](auto gg) {
+            constexpr int g = decltype(gg)::value;
+            if (PH::gkind(g) == GA_KIND_ACC) {
+                const int tb = accbase + item_n_safe * ACCS + PH::gaux(g) * CMAX + item_il;
+                float x = (lds[tb] + lds[tb + NPAD * ACCS]) + (lds[tb + 2 * NPAD * ACCS] + lds[tb + 3 * NPAD * ACCS]);
+                if constexpr (NW == 8)
+                    x += (lds[tb + 4 * NPAD * ACCS] + lds[tb + 5 * NPAD * ACCS]) + (lds[tb + 6 * NPAD * ACCS] + lds[tb + 7 * NPAD * ACCS]);
+                s[g] = r.gptr[g] != nullptr ? x : 0.0f;
+            }
+        });
+    };
+    // the element-wise program: one thread per (stream, unit); what other workgroups wait for goes out
+    auto ew_exchange = [&](int t) {
+#pragma unroll
+        for (int v = 0; v < PH::NI; ++v) s[PH::NG + v] = r.inv[v];
+        step_static_for<0, PH::NG>([&](auto gg) {
+            constexpr int g = decltype(gg)::value;
+            if (PH::gkind(g) == GA_KIND_CARRY) s[g] = r.carry[PH::cidx(g)];
+            else if (PH::gkind(g) == GA_KIND_STATIC) s[g] = sn[g];
+        });
+        // sums that a helper member of the launch computes ahead of this member: loaded at the
+        // step's start, here they have normally arrived (the wavefront repeats while one is missing)
+        step_static_for<0, PH::NG>([&](auto gg) {
+            constexpr int g = decltype(gg)::value;
+            if constexpr (PH::gkind(g) == GA_KIND_POLLED) {
+                int spins = 0;
+                while (__builtin_amdgcn_ballot_w64(__float_as_uint(s[g]) == STEP_SENTINEL) != 0 && !dead) {
+                    if (++spins > a.spin_limit) { dead = true; if (lane == 0) atomicExch(a.ctrl, 1u); break; }
+                    s[g] = gather_at(gg, t + r.goff[g]);
+                }
+            }
+        });
+        PH::ops(s);
+#pragma unroll
+        for (int q = 0; q < PH::NST; ++q) {
+            if (!PH::stshared(q)) continue;
+            if (MM::XB && PH::sttwin(q)) {
+                const unsigned bits = step_shared_bits(s[PH::stslot(q)]);
+                if (!local) __builtin_amdgcn_raw_buffer_store_b32(bits, twin_rsrc(q), (int)xvrun[q], 0, STEP_COHERENT_AUX);
+                else __builtin_amdgcn_raw_buffer_store_b32(bits, twin_rsrc(q), (int)xvrun[q], 0, 0);
+            } else {
+                wave_store<PH, MStore>(r, q, s[PH::stslot(q)], 2, a);
+            }
+        }
+    };
+    auto ew_rest = [&](int step, int t) {
+#pragma unroll
+        for (int q = 0; q < PH::NST; ++q)
+            if (!PH::stshared(q) || (MM::XB && PH::sttwin(q))) wave_store<PH, MStore>(r, q, s[PH::stslot(q)], 0, a);
+#pragma unroll
+        for (int g = 0; g < PH::NG; ++g)
+            if (PH::gkind(g) == GA_KIND_CARRY) r.carry[PH::cidx(g)] = s[PH::gaux(g)];
+        // the next step's STATIC inputs, behind this step's stores: they arrive during that
+        // step's contraction (behind the last step: outside the window, nothing is loaded)
+        const int t2 = a.backward ? t - 1 : t + 1;
+        const bool more = step + 1 < nsteps;
+        step_static_for<0, PH::NG>([&](auto gg) {
+            constexpr int g = decltype(gg)::value;
+            if (PH::gkind(g) == GA_KIND_STATIC) sn[g] = gather_at(gg, more ? t2 + r.goff[g] : -1);
+        });
+        wave_store_advance<PH>(r);
+        if constexpr (MM::XB) {
+#pragma unroll
+            for (int q = 0; q < PH::NST; ++q) xvrun[q] += (unsigned)((a.backward ? -xstride[q] : xstride[q]) * 4);
+        }
+    };
+    // Two barriers a step: behind the first the tiles hold the step's sums, behind the second the element-wise threads have read them.
+    // The other wavefronts go on to the next step's polls from there.
+    // did a wavefront have to load a chunk again?  (word `step & 1`; the other one is cleared for the next step)
+    constexpr int POLL_INC = MM::FLAT ? 0 : MSTEP_POLL_INC;
+    auto tiles_full = [&](int step, bool retried) {
         if (POLL_INC > 0 && retried && lane == 0) atomicOr(&ms.retried[step & 1], 1u);
         step_lds_barrier();
         if (POLL_INC > 0) {
@@ -1897,65 +2000,43 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
             else if ((step & 63) == 63 && pdelay > 0) --pdelay;
             if (tid == 0) ms.retried[(step + 1) & 1] = 0u;
         }
-        RNNG_STAMP(4);
-        // ---- element-wise program: one thread per (stream, unit) ----
-        if (wave_items) {
-#pragma unroll
-            for (int v = 0; v < PH::NI; ++v) s[PH::NG + v] = r.inv[v];
-            step_static_for<0, PH::NG>([&](auto gg) {
-                constexpr int g = decltype(gg)::value;
-                if (PH::gkind(g) == GA_KIND_CARRY) s[g] = r.carry[PH::cidx(g)];
-                else if (PH::gkind(g) == GA_KIND_STATIC) s[g] = sn[g];
-                if (PH::gkind(g) == GA_KIND_ACC) {
-                    const int tb = accbase + item_n_safe * ACCS + PH::gaux(g) * CMAX + item_il;
-                    float x = (lds[tb] + lds[tb + NPAD * ACCS]) + (lds[tb + 2 * NPAD * ACCS] + lds[tb + 3 * NPAD * ACCS]);
-                    if constexpr (NW == 8)
-                        x += (lds[tb + 4 * NPAD * ACCS] + lds[tb + 5 * NPAD * ACCS]) + (lds[tb + 6 * NPAD * ACCS] + lds[tb + 7 * NPAD * ACCS]);
-                    s[g] = r.gptr[g] != nullptr ? x : 0.0f;
-                }
-            });
-            // sums that a helper member of the launch computes ahead of this member: loaded at the
-            // step's start, here they have normally arrived (the wavefront repeats while one is missing)
-            step_static_for<0, PH::NG>([&](auto gg) {
-                constexpr int g = decltype(gg)::value;
-                if constexpr (PH::gkind(g) == GA_KIND_POLLED) {
-                    int spins = 0;
-                    while (__builtin_amdgcn_ballot_w64(__float_as_uint(s[g]) == STEP_SENTINEL) != 0 && !dead) {
-                        if (++spins > a.spin_limit) { dead = true; if (lane == 0) atomicExch(a.ctrl, 1u); break; }
-                        s[g] = gather_at(gg, t + r.goff[g]);
-                    }
-                }
-            });
-            PH::ops(s);
-#pragma unroll
-            for (int q = 0; q < PH::NST; ++q) {
-                const bool twin = MM::XB && PH::stshared(q) && PH::sttwin(q);
-                wave_store<PH, MStore>(r, q, s[PH::stslot(q)], PH::stshared(q) && !twin ? 2 : 0, a);
-                if (twin) {
-                    const __amdgpu_buffer_rsrc_t rx = MStore::SW ? __builtin_amdgcn_make_buffer_rsrc(a.store_base, 0, (int)a.store_bytes, STEP_RSRC_FLAGS)
-                                                                 : __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(xbase[q]), 0, a.T * xstride[q] * 4, STEP_RSRC_FLAGS);
-                    __builtin_amdgcn_raw_buffer_store_b32(step_shared_bits(s[PH::stslot(q)]), rx, (int)xvrun[q], 0, STEP_COHERENT_AUX);
-                }
+    };
+    if constexpr (MM::NE > 0) {
+        if (suni(wave) < NW) {
+            for (int step = 0; step < nsteps; ++step) {
+                bool retried = false;
+                contract(step, step_frame(a, step), retried);
+                tiles_full(step, retried);
+                RNNG_STAMP(4);
+                step_lds_barrier();
             }
-#pragma unroll
-            for (int g = 0; g < PH::NG; ++g)
-                if (PH::gkind(g) == GA_KIND_CARRY) r.carry[PH::cidx(g)] = s[PH::gaux(g)];
-            // the next step's STATIC inputs, behind this step's stores: they arrive during that
-            // step's contraction (behind the last step: outside the window, nothing is loaded)
-            const int t2 = a.backward ? t - 1 : t + 1;
-            const bool more = step + 1 < nsteps;
-            step_static_for<0, PH::NG>([&](auto gg) {
-                constexpr int g = decltype(gg)::value;
-                if (PH::gkind(g) == GA_KIND_STATIC) sn[g] = gather_at(gg, more ? t2 + r.goff[g] : -1);
-            });
+        } else {
+            for (int step = 0; step < nsteps; ++step) {
+                const int t = step_frame(a, step);
+                RNNG_STAMP_BY(7, 64 * NW);
+                if (wave_items) ew_loads(t);
+                tiles_full(step, false);
+                if (wave_items) { ew_sums(); ew_exchange(t); }
+                step_lds_barrier();
+                RNNG_STAMP_BY(5, 64 * NW);
+                if (wave_items) ew_rest(step, t);
+                RNNG_STAMP_BY(1, 64 * NW);
+            }
         }
-        wave_store_advance<PH>(r);
-        if constexpr (MM::XB) {
-#pragma unroll
-            for (int q = 0; q < PH::NST; ++q) xvrun[q] += (unsigned)((a.backward ? -xstride[q] : xstride[q]) * 4);
+    } else {
+        for (int step = 0; step < nsteps; ++step) {
+            const int t = step_frame(a, step);
+            bool retried = false;
+            if (wave_items) ew_loads(t);
+            contract(step, t, retried);
+            tiles_full(step, retried);
+            RNNG_STAMP(4);
+            if (wave_items) { ew_sums(); ew_exchange(t); }
+            step_lds_barrier();
+            RNNG_STAMP(5);
+            if (wave_items) ew_rest(step, t);
+            RNNG_STAMP(1);
         }
-        RNNG_STAMP(5);
-        step_lds_barrier();   // the tiles are written again in the next step
     }
 }
 

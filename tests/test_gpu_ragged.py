@@ -31,6 +31,22 @@ def test_few_streams_where_the_register_build_needs_several_xcds(layers, N, buil
     assert rec and all((win.g.step_build(k)[0], win.g.step_build(k, True)[0]) == builds for k in rec)
 
 
+@pytest.mark.parametrize("env", [{"RNNG_MSTEP_LOCAL": "1"}, {"RNNG_MSTEP_LOCAL": "0"}, {"RNNG_MSTEP_LOCAL": "1", "RNNG_XCD_LOCAL": "0"},
+                                 {"RNNG_MSTEP_LOCAL": "1", "RNNG_MSTEP_EW": "0"}, {"RNNG_MSTEP_LOCAL": "0", "RNNG_MSTEP_EW": "0", "RNNG_MSTEP_HOLD": "0"}])
+@pytest.mark.parametrize("net,hidden,N", [("lstm", 3, 9), ("lstm", 18, 33), ("lstm", 250, 20), ("lstm", 384, 16), ("elman", 16, 9), ("elman", 512, 16), ("elman", 41, 140)])
+def test_exchange_inside_and_across_xcds(monkeypatch, net, hidden, N, env):
+    """One layer on the matrix cores: its stream groups each on an XCD (one to nine of them, several of an XCD's workgroups left over) or
+    spread over all, written through or not, with wavefronts for the element-wise program alone or without."""
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    spec = wl.elman_net(7, hidden, 5) if net == "elman" else wl.lstm_net(7, [hidden], 5)
+    win, _ = run_both(wl.make_workload("exchange", spec, T=21, N=N, seed=73, scale=0.4 / hidden ** 0.5, bias_scale=0.2, masked_fraction=0.2),
+                      label=f"{net} {hidden}, N={N}, {env}")
+    win.check()
+    rec = [k for k in range(len(spec.nodes)) if win.g.step_build(k)[0] != "none"]
+    assert rec and all(win.g.step_build(k, b)[0] == "matrix" for k in rec for b in (False, True))
+
+
 @pytest.mark.parametrize("N,T", [(3, 16400), (17, 8200)])
 def test_long_windows_keep_their_step_kernel(N, T):
     """Tensors far below the 1 GiB that a step kernel addresses, with copies that 16-stream tiles
