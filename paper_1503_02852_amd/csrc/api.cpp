@@ -371,7 +371,7 @@ struct rnn_graph {
         return cached_layout;
     }
     void drop_choices() { jit_choices.clear(); chain_choices.clear(); cached_T = cached_N = 0; lay = StepLayouts(); }
-    // The layouts (step_layout.h) of the weights-in-registers launches of a window with N streams, one after the other as the kernels
+    // The layouts (step_layout.h) of the weights-in-registers and the matrix-core launches of a window with N streams, one after the other as the kernels
     // load them, and where the first one of a component's or chain's launch lies (direction: 2 c + d; -1: none).  sizes_ok: wave_tensor_sizes_ok.
     struct StepLayouts { std::vector<int32_t> words; std::vector<int> comp, chain; int N = 0; bool sizes_ok = false; };
     StepLayouts lay;      // of the current window
@@ -380,11 +380,11 @@ struct rnn_graph {
         r.comp.assign(2 * plan.comps.size(), -1); r.chain.assign(2 * plan.chains.size(), -1);
         r.N = N; r.sizes_ok = sizes_ok;
         if (!use_jit || framewise) return r;
-        auto add = [&](const CompPlan& cp, bool backward, int G) {
+        auto add = [&](const CompPlan& cp, bool backward, int G, int NB, int streams) {
             const int at = (int)(r.words.size() / STEP_LAYOUT_WORDS);
             StepLayout l;
             std::memset(&l, 0, sizeof(l));
-            compute_step_layout(plan.words.data(), backward ? cp.bwd_desc_off : cp.fwd_desc_off, G, step_nb_for(N), N, l);
+            compute_step_layout(plan.words.data(), backward ? cp.bwd_desc_off : cp.fwd_desc_off, G, NB, streams, l);
             r.words.resize((size_t)(at + 1) * STEP_LAYOUT_WORDS);
             std::memcpy(&r.words[(size_t)at * STEP_LAYOUT_WORDS], &l, STEP_LAYOUT_HEAD * 4);
             std::memcpy(&r.words[(size_t)at * STEP_LAYOUT_WORDS + STEP_LAYOUT_HEAD], l.src, sizeof(l.src));
@@ -399,17 +399,20 @@ struct rnn_graph {
                     const ChainPlan& ch = plan.chains[cp.chain];
                     const ChainChoice& cc = chain_choice(cp.chain, d != 0, N);
                     if (!cc.source.empty()) {
-                        if ((int)c != ch.first || cc.mstep) continue;
+                        if ((int)c != ch.first) continue;
                         const std::vector<CompPlan>& members = chain_members(ch, cc);
                         for (size_t i = 0; i < members.size(); ++i) {
-                            const int at = add(members[i], d != 0, cc.G[i]);
+                            const int at = cc.mstep ? add(members[i], d != 0, cc.G[i], 1, mstep_streams(N, cc.J[i], cc.blocked))
+                                                    : add(members[i], d != 0, cc.G[i], step_nb_for(N), N);
                             if (i == 0) r.chain[2 * cp.chain + d] = at;
                         }
                         continue;
                     }
                 }
                 const JitChoice& jc = jit_choice((int)c, d != 0, N);
-                if (!jc.source.empty() && jc.wave) r.comp[2 * c + d] = add(cp, d != 0, jc.lp.G);
+                if (jc.source.empty()) continue;
+                if (jc.wave) r.comp[2 * c + d] = add(cp, d != 0, jc.lp.G, step_nb_for(N), N);
+                else if (jc.mstep && !jc.two_d) r.comp[2 * c + d] = add(cp, d != 0, jc.lp.G, 1, mstep_streams(N, jc.J, jc.blocked));
             }
         }
         return r;

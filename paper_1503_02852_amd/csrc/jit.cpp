@@ -479,7 +479,7 @@ bool emit_mstep_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, 
     if (phases.size() != 1 || N_all < 1 || J < 1 || G * J > 256) return false;
     // streams per workgroup; several stream groups are made of whole 16-stream tiles (without twins
     // equally many in each, else the last group may have fewer)
-    const int N = J > 1 && blocked ? ((N_all + 15) / 16 + J - 1) / J * 16 : (N_all + J - 1) / J;
+    const int N = mstep_streams(N_all, J, blocked);
     if (J > 1 && (blocked ? (J - 1) * N >= N_all : N_all % (16 * J) != 0)) return false;
     StepLayout lay;
     compute_step_layout(P.words.data(), backward ? cp.bwd_desc_off : cp.fwd_desc_off, G, 1, N, lay);
@@ -577,7 +577,8 @@ bool emit_mstep_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, 
       << "    static constexpr bool FLAT = " << (flat ? "true" : "false") << ", XB = " << (blocked ? "true" : "false")
       << ", TAIL = " << (N_all % 16 != 0 ? "true" : "false") << ", HELPER = " << (cp.helper ? "true" : "false") << ";\n"
       ;
-    std::vector<std::pair<int, int>> ks, kps, blk, used, ngr, csrc, ck0;
+    std::vector<std::pair<int, int>> ks, kps, blk, used, ngr, csrc, ck0, wb, wst;
+    for (int s = 0; s < ml.n_src; ++s) { wb.push_back({s, ml.wbase[s]}); wst.push_back({s, ml.wstride[s]}); }
     // The unrolled chunk sequence takes the sources in the order in which their values arrive: what
     // another component of the launch produces (it runs ahead) and the component's own values of
     // older frames first, the values that the other workgroups have produced in the step before
@@ -613,6 +614,29 @@ bool emit_mstep_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, 
     }
     emit_switch("K", "s", ks, 0); emit_switch("KP", "s", kps, 0); emit_switch("blk_", "key", blk, -1); emit_switch("used_", "key", used, 0);
     emit_switch("ngr", "s", ngr, 0); emit_switch("csrc", "c", csrc, 0); emit_switch("ck0", "c", ck0, 0);
+    emit_switch("wbase", "s", wb, 0); emit_switch("wstride", "s", wst, 0);
+    o << "    static constexpr int ZROW = " << ml.zrow << ", ACCBASE = " << ml.accbase << ", LDSF = " << ml.total_floats << ";\n";
+    // the edges whose weights are read at the start, those that add to another's rows last: into LDS (we_), into registers (re_)
+    for (int in_regs = 0; in_regs < 2; ++in_regs) {
+        const std::string x = in_regs ? "re_" : "we_";
+        std::vector<std::pair<int, int>> es, et, ee, eadd, etr;
+        int n = 0;
+        for (int add = 0; add < 2; ++add)
+            for (int s = 0; s < ml.n_src; ++s)
+                for (int t = 0; t < ph.n_tasks; ++t) {
+                    bool first = true;
+                    for (int e = 0; e < ph.task[t].n_edges; ++e) {
+                        if (ph.task[t].e[e].src != s) continue;
+                        if ((int)((reg_mask >> s) & 1) == in_regs && (first ? 0 : 1) == add) {
+                            es.push_back({n, s}); et.push_back({n, t}); ee.push_back({n, e}); eadd.push_back({n, add}); etr.push_back({n, ph.task[t].e[e].transposed}); ++n;
+                        }
+                        first = false;
+                    }
+                }
+        emit_switch((x + "src").c_str(), "i", es, 0); emit_switch((x + "task").c_str(), "i", et, 0); emit_switch((x + "edge").c_str(), "i", ee, 0);
+        emit_switch((x + "add").c_str(), "i", eadd, 0); emit_switch((x + "tr").c_str(), "i", etr, 0);
+        o << "    static constexpr int " << (in_regs ? "NRE" : "NWE") << " = " << n << ";\n";
+    }
     // register-resident weights: index of (chunk, row tile) in the lane's register array
     std::vector<std::pair<int, int>> widx;
     if (reg_mask && !flat) return false;
@@ -814,7 +838,7 @@ std::string jit_mstep_chain_source(const Plan& P, const std::vector<CompPlan>& m
          "    StepArgs c = a;\n";
     for (int g = 0; g < n; ++g)
         o << "    if (b >= a.grp_first[" << g << "] && b < a.grp_first[" << g << "] + a.grp_G[" << g << "] * a.grp_J[" << g << "]) {\n"
-             "        c.desc_off = a.grp_desc_off[" << g << "]; c.G = a.grp_G[" << g << "]; c.J = a.grp_J[" << g << "];\n"
+             "        c.desc_off = a.grp_desc_off[" << g << "]; c.lay = a.grp_lay[" << g << "]; c.G = a.grp_G[" << g << "]; c.J = a.grp_J[" << g << "];\n"
              "        mstep_kernel_body<grp" << g << "::PH0, grp" << g << "::MM>(c, ms, lds, b - a.grp_first[" << g << "]);\n"
              "        return;\n"
              "    }\n";

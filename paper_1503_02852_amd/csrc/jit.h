@@ -39,6 +39,8 @@ std::string jit_mstep2_source(const Plan& P, const CompPlan& cp, bool backward, 
 // members (ChainPlan::bwd_split).  Empty if some member is not eligible.
 std::string jit_mstep_chain_source(const Plan& P, const std::vector<CompPlan>& members, bool backward, int N, const std::vector<int>& G,
                                    const std::vector<int>& J, size_t* lds_bytes, int* threads = nullptr, bool* blocked = nullptr);
+// Streams of a matrix-core workgroup (the last of several stream groups may have fewer).
+inline int mstep_streams(int N, int J, bool blocked) { return J > 1 && blocked ? ((N + 15) / 16 + J - 1) / J * 16 : (N + J - 1) / J; }
 // Workgroups of a launch whose stream groups (units in all) of G workgroups sit on one XCD each.
 inline int mstep_local_blocks(int G, int units) { return 8 * G * ((units + 7) / 8); }
 // Streaming variant (N <= 8 streams; weights read from memory every step, for layers too wide to

@@ -1466,7 +1466,7 @@ RNNG_HD inline void compute_mstep_layout(const StepLayout& lay, int N, int nw, u
 // element-wise part's instructions and spilled scalar registers.
 struct MStore { static constexpr bool SW = RNNG_STORE_WINDOW != 0; };
 // (leaner than StepShared: one phase, so that more of the 160 KiB is left for weight rows)
-struct MShared { StepLayout lay; unsigned iteminfo[1][STEP_THREADS]; MLayout ml; unsigned retried[2]; };
+struct MShared { StepLayout lay; unsigned iteminfo[1][STEP_THREADS]; unsigned retried[2]; };
 
 // Launches whose stream groups each sit on one XCD: units (stream groups of the members, one member after the other) of LG
 // workgroups; workgroups b, b + 8, ... of a launch share an XCD, so unit u takes the workgroups of residue u % 8.
@@ -1497,47 +1497,77 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
         const int u = mstep_local_unit<MM::LG>();
         atomicOr(a.ctrl + suni(a.xcd_word) + (u >> 2), 1u << (8 * (u & 3) + (step_xcc_id() & 7)));
     }
-    if (tid == 0) { compute_step_layout(a.words, a.desc_off, a.G, 1, MM::NJ, sh.lay); compute_mstep_layout(sh.lay, MM::NJ, NW, MM::REGMASK, (int)(MSTEP_LDS_LIMIT / 4), ms.ml); }
+    load_step_layout(a, 1, MM::NJ, sh.lay, tid, NTHR);
+    for (int i = 4 * tid; i < MM::LDSF; i += 4 * NTHR) *reinterpret_cast<mfloatx4*>(&lds[i]) = mfloatx4{0.0f, 0.0f, 0.0f, 0.0f};
     __syncthreads();
     const StepPhase& ph = sh.lay.ph[0];
-    const MLayout& ml = ms.ml;
     if (tid < STEP_THREADS) {      // at most STEP_THREADS element-wise items
         const int ic = ph.item_chunk;
         const int il = tid % ic, n = tid / ic;
         sh.iteminfo[0][tid] = (unsigned)il | ((unsigned)(n < N ? n0 + n : 0xFFFF) << 16);      // global stream index
     }
-    for (int i = tid; i < ml.total_floats; i += NTHR) lds[i] = 0.0f;
     if (tid < 2) ms.retried[tid] = 0u;
-    __syncthreads();
     // resident weights: W_lds[s][blk(s, task) * cmax + ul][k]; edges of one task that share a
-    // source add up in one row
+    // source add up in one row.  Eight loads of a thread in flight, none behind a branch, 16 bytes each where the matrix' rows (transposed:
+    // this workgroup's units) lie side by side; one element after the other, each behind the last one's addition, took 20 to 40 us a launch.
     constexpr int CMAX = MM::CMAX;
-    for (int s = 0; s < ml.n_src; ++s) {
-        if ((MM::REGMASK >> s) & 1) continue;      // (in registers, below)
-        const int K = sh.lay.src[s].k_len;
-        for (int t = 0; t < ph.n_tasks; ++t) {
-            const StepTask& task = ph.task[t];
-            for (int e = 0; e < task.n_edges; ++e) {
-                const StepEdge ed = task.e[e];
-                if (ed.src != s) continue;
-                const float* W = a.weights + ed.w_off;
-                for (int i = tid; i < CMAX * K; i += NTHR) {
-                    const int ul = i / K, k = i - ul * K;
-                    const int u = w * task.chunk + ul;
-                    float v = 0.0f;
-                    if (ul < task.chunk && u < task.n_out) v = ed.transposed ? W[(size_t)k * task.n_out + u] : W[(size_t)u * K + k];
-                    lds[ml.wbase[s] + (ml.blk[s][t] * CMAX + ul) * ml.wstride[s] + k] += v;
+    step_static_for<0, MM::NWE>([&](auto ii) {
+        constexpr int i = decltype(ii)::value, sidx = MM::we_src(i), t = MM::we_task(i), K = MM::K(sidx), WS = MM::wstride(sidx);
+        constexpr int row0 = MM::wbase(sidx) + MM::blk(sidx, t) * CMAX * WS;
+        const StepTask& tk = ph.task[t];
+        const int chunk = suni(tk.chunk), n_out = suni(tk.n_out), u0 = w * chunk, mine = chunk < n_out - u0 ? chunk : n_out - u0;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.weights) + suni(tk.e[MM::we_edge(i)].w_off), 0, n_out * K * 4, STEP_RSRC_FLAGS);
+        constexpr int NONE = (int)0xC0000000u, FLIGHT = 8;
+        if (MM::we_add(i)) __syncthreads();
+        auto put = [&](int at, float v) { if (MM::we_add(i)) lds[at] += v; else lds[at] = v; };
+        if constexpr (MM::we_tr(i) == 0) {
+            constexpr int V = K % 4 == 0 ? 4 : 1, Q = K / V;
+            for (int b = 0; b < CMAX * Q; b += FLIGHT * NTHR) {
+                muintx4 v[FLIGHT];
+#pragma unroll
+                for (int j = 0; j < FLIGHT; ++j) {
+                    const int at = b + j * NTHR + tid, ul = at / Q, off = at < CMAX * Q && ul < mine ? ((u0 + ul) * K + (at - ul * Q) * V) * 4 : NONE;
+                    if constexpr (V == 4) v[j] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+                    else v[j].x = __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0);
                 }
-                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < FLIGHT; ++j) {
+                    const int at = b + j * NTHR + tid, ul = at / Q, to = row0 + ul * WS + (at - ul * Q) * V;
+                    if (at >= CMAX * Q) continue;
+                    if constexpr (V == 4) { put(to, __uint_as_float(v[j].x)); put(to + 1, __uint_as_float(v[j].y)); put(to + 2, __uint_as_float(v[j].z)); put(to + 3, __uint_as_float(v[j].w)); }
+                    else put(to, __uint_as_float(v[j].x));
+                }
             }
+        } else {
+            auto columns = [&](auto vv) {
+                constexpr int V = decltype(vv)::value, Q = CMAX / V;      // V units of one column k at a time
+                for (int b = 0; b < K * Q; b += FLIGHT * NTHR) {
+                    muintx4 v[FLIGHT];
+#pragma unroll
+                    for (int j = 0; j < FLIGHT; ++j) {
+                        const int at = b + j * NTHR + tid, k = at / Q, ul = (at - k * Q) * V, off = k < K && ul < mine ? (k * n_out + u0 + ul) * 4 : NONE;
+                        if constexpr (V == 4) v[j] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+                        else v[j].x = __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0);
+                    }
+#pragma unroll
+                    for (int j = 0; j < FLIGHT; ++j) {
+                        const int at = b + j * NTHR + tid, k = at / Q, ul = (at - k * Q) * V, to = row0 + ul * WS + k;
+                        if (k >= K) continue;
+                        put(to, __uint_as_float(v[j].x));
+                        if constexpr (V == 4) { put(to + WS, __uint_as_float(v[j].y)); put(to + 2 * WS, __uint_as_float(v[j].z)); put(to + 3 * WS, __uint_as_float(v[j].w)); }
+                    }
+                }
+            };
+            if (CMAX % 4 == 0 && mine == CMAX && n_out % 4 == 0) columns(StepIntC<CMAX % 4 == 0 ? 4 : 1>{});
+            else columns(StepIntC<1>{});
         }
-    }
+    });
     PhaseRegs<PH> r;
     phase_setup<PH, 1, 2>(r, a, sh, lds, w, itid);
     __syncthreads();
 
     constexpr int D = MM::D, NPAD = MM::MT * 16, ACCS = MM::ACCS;
-    const int accbase = suni(ml.accbase);
+    constexpr int accbase = MM::ACCBASE;
     const int item_il = itid < STEP_THREADS ? (int)(sh.iteminfo[0][itid] & 0xFFFF) : 0;
     const int item_n = itid / suni(ph.item_chunk);                         // local stream of this thread's item
     // LDS address of the weight row behind each of this lane's tile columns, per source
@@ -1551,7 +1581,7 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
             int b = -1;
 #pragma unroll
             for (int t2 = 0; t2 < STEP_MAX_TASKS; ++t2) if (task == t2) b = MM::blk(sidx, t2);
-            brow[sidx][nt] = (b >= 0 ? suni(ml.wbase[sidx]) + (b * CMAX + ul) * suni(ml.wstride[sidx]) : suni(ml.zrow)) + 4 * (lane >> 4);
+            brow[sidx][nt] = (b >= 0 ? MM::wbase(sidx) + (b * CMAX + ul) * MM::wstride(sidx) : MM::ZROW) + 4 * (lane >> 4);
         }
     // Weight rows that do not fit LDS stay in vector registers for the whole launch (sources in
     // MM::REGMASK; only with the unrolled chunk sequence, where every register index is static):
@@ -1582,33 +1612,41 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
     };
     mfloatx4 wr[MM::NRW > 0 ? MM::NRW : 1];
     if constexpr (MM::NRW > 0) {
-        step_static_for<0, MM::NCH>([&](auto cc) {
-            constexpr int c = decltype(cc)::value, sidx = MM::csrc(c);
-            const int k0 = rot(StepIntC<sidx>{}, MM::ck0(c));
-            if constexpr (((MM::REGMASK >> sidx) & 1) != 0) {
-                step_static_for<0, MM::NTU>([&](auto tt) {
-                    constexpr int nt = decltype(tt)::value;
-                    if constexpr (MM::used(sidx, nt)) {
-                        const int col = nt * 16 + (lane & 15);
-                        const int task = col / CMAX, ul = col - task * CMAX;
-                        const int kk = k0 + wave * 16 + 4 * (lane >> 4);
-                        mfloatx4 wv = {0.0f, 0.0f, 0.0f, 0.0f};
-                        if (task < ph.n_tasks) {
-                            const StepTask& tk = ph.task[task];
-                            const int u = w * tk.chunk + ul;
-                            for (int e = 0; e < tk.n_edges; ++e) {
-                                const StepEdge ed = tk.e[e];
-                                if (ed.src != sidx || ul >= tk.chunk || u >= tk.n_out) continue;
-                                const float* W = a.weights + ed.w_off;
 #pragma unroll
-                                for (int j = 0; j < 4; ++j)
-                                    if (kk + j < MM::K(sidx)) wv[j] += ed.transposed ? W[(size_t)(kk + j) * tk.n_out + u] : W[(size_t)u * MM::K(sidx) + kk + j];
+        for (int i = 0; i < MM::NRW; ++i) wr[i] = mfloatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        // All loads of an edge without a branch between them: a lane whose row has none reads the buffer's first words and drops them.
+        step_static_for<0, MM::NRE>([&](auto ii) {
+            constexpr int i = decltype(ii)::value, sidx = MM::re_src(i), t = MM::re_task(i), K = MM::K(sidx);
+            const StepTask& tk = ph.task[t];
+            const int chunk = suni(tk.chunk), n_out = suni(tk.n_out);
+            const float* W = a.weights + suni(tk.e[MM::re_edge(i)].w_off);
+            step_static_for<0, MM::NTU>([&](auto tt) {
+                constexpr int nt = decltype(tt)::value;
+                if constexpr (nt * 16 < (t + 1) * CMAX && nt * 16 + 16 > t * CMAX) {
+                    const int ul = nt * 16 + (lane & 15) - t * CMAX, u = w * chunk + ul;
+                    const bool row = ul >= 0 && ul < chunk && u < n_out;
+                    step_static_for<0, MM::NCH>([&](auto cc) {
+                        constexpr int c = decltype(cc)::value;
+                        if constexpr (MM::csrc(c) == sidx) {
+                            const int kk = rot(StepIntC<sidx>{}, MM::ck0(c)) + wave * 16 + 4 * (lane >> 4);
+                            mfloatx4 x;
+                            if constexpr (MM::re_tr(i) == 0 && K % 4 == 0) {
+                                const bool on = row && kk < K;
+                                x = *reinterpret_cast<const mfloatx4*>(on ? W + (size_t)u * K + kk : a.weights);
+                                if (!on) x = mfloatx4{0.0f, 0.0f, 0.0f, 0.0f};
+                            } else {
+#pragma unroll
+                                for (int j = 0; j < 4; ++j) {
+                                    const bool on = row && kk + j < K;
+                                    const float y = *(on ? W + (MM::re_tr(i) ? (size_t)(kk + j) * n_out + u : (size_t)u * K + kk + j) : a.weights);
+                                    x[j] = on ? y : 0.0f;
+                                }
                             }
+                            wr[MM::widx(c * 16 + nt)] += x;
                         }
-                        wr[MM::widx(c * 16 + nt)] = wv;
-                    }
-                });
-            }
+                    });
+                }
+            });
         });
     }
     // this lane's A-operand element inside a chunk: stream 16 mt + (lane & 15), columns wcol ... wcol + 3;
