@@ -646,13 +646,16 @@ bool emit_mstep_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, 
                 if (std::find(used.begin(), used.end(), std::make_pair(cs.second * 16 + nt, 1)) != used.end()) { const int i = (int)widx.size(); widx.push_back({cs.first * 16 + nt, i}); }
     emit_switch("widx", "key", widx, 0);
     // How long (units of 64 clocks) the first loads of the previous step's values are held back where those cross XCDs: a load that comes
-    // back too early costs a second round trip, and the stores it waits for arrive later the more is polled.  The line through the best of
-    // 0 to 16 units at 0.25 to 8 MiB polled per step: LSTM forward, 16 streams, us a step without / with: 256 units 1.94 / 1.53, 512
-    // 2.41 / 1.98; backward 512 5.34 / 3.84, 320 4.84 / 3.21; 2 x 256, 8 streams 1.86 + 2.42 / 1.71 + 2.40.  Inside one XCD, and for a
-    // helper, which starts late by itself, any holding back only costs (128 units 1.20 / 1.28).
+    // back too early costs a second round trip, and the stores it waits for arrive later the more is polled.  Two lines close to the best of
+    // 0 to 16 units at 0.25 to 8 MiB polled per step, for one exchanged vector and for several; us a step without / with: LSTM forward, 16
+    // streams, 256 units 1.94 / 1.53, 512 2.41 / 1.88, 2 x 250, 20 streams 2.10 / 1.57; backward 512 5.34 / 3.84, 320 4.84 / 3.21.  Inside
+    // one XCD, and for a helper, which starts late by itself, any holding back only costs (128 units 1.20 / 1.28).
     double polled_mib = 0;
     for (int s = 0; s < ml.n_src; ++s) polled_mib += (double)G * N_all * lay.src[s].k_len * 4 / (1 << 20);
-    int hold = local || cp.helper ? 0 : std::min(12, (int)(3 + 1.9 * polled_mib));
+    int n_late = 0;
+    const std::vector<int>& own_bufs = backward ? cp.bwd_shared_bufs : cp.fwd_shared_bufs;
+    for (int s = 0; s < ml.n_src; ++s) n_late += std::find(own_bufs.begin(), own_bufs.end(), lay.src[s].buf) != own_bufs.end();
+    int hold = local || cp.helper ? 0 : n_late == 1 ? std::min(10, (int)(5.5 + 1.9 * polled_mib)) : std::min(12, (int)(3 + 1.9 * polled_mib));
     if (const char* env = std::getenv("RNNG_MSTEP_HOLD")) hold = std::max(0, std::min(127, std::atoi(env)));
     o << "    static constexpr int HOLD = " << hold << ";\n";
     o << "    static constexpr int LG = " << (local ? G : 0) << ";\n";
