@@ -931,6 +931,8 @@ std::string jit_sstep_source(const Plan& P, const CompPlan& cp, bool backward, i
 }
 
 // Streaming matrix-core variant for N >= 9 streams and layers whose weights do not fit on chip.
+// Of a lane's 256 registers: resident weights and their source values (LSTM of 4,096 units, three / four chunks a source: 37.0 + 44.2 / 40.4 + 47.4 us a step).
+constexpr int SMSTEP_KEPT_REGISTERS = 60;
 std::string jit_smstep_source(const Plan& P, const CompPlan& cp, bool backward, int N, int G, size_t* lds_bytes, bool* transposed, bool* blocked,
                               int* threads) {
     const std::vector<PhasePlan>& phases = backward ? cp.bwd_phases : cp.fwd_phases;
@@ -978,8 +980,46 @@ std::string jit_smstep_source(const Plan& P, const CompPlan& cp, bool backward, 
         if (slots < best_slots) { best_slots = slots; D = d; }
     }
     const int ACCS = NTU * 16 + 4;
-    const size_t lds = (size_t)NW * MT * 16 * ACCS * 4;
+    size_t lds = (size_t)NW * MT * 16 * ACCS * 4;
     if (lds > STEP_LDS_LIMIT) return "";
+    // Resident chunks (see the kernel): PR per source in registers, LRES per source in LDS, from the weights on that leave the
+    // memory-side cache something to gain (RNNG_SMSTEP_RESIDENT = 0: never, 1: always).  us a step with / without, 16 streams: one source
+    // (LSTM forward) 151 MB 20.6 / 23.6, 268 MB 37.0 / 49.2, 400 MB 77.7 / 90.5, 64 streams 67 MB 25.5 / 25.1; four (backward) 151 MB 31.4 / 30.5,
+    // 268 MB 44.2 / 57.2, 400 MB 114 / 120, 64 streams 67 MB 49.6 / 47.7, 268 MB 98 / 107.
+    int64_t weight_bytes = 0;
+    for (int t = 0; t < NT; ++t) for (int e = 0; e < ph.task[t].n_edges; ++e) weight_bytes += (int64_t)ph.task[t].n_out * ph.task[t].e[e].k_len * 4;
+    bool keep = weight_bytes >= (lay.n_sources == 1 ? 100 : 200) * 1000000ll;
+    if (const char* env = std::getenv("RNNG_SMSTEP_RESIDENT")) keep = std::atoi(env) != 0;
+    const int RES0 = (int)(lds / 4), chunk_bytes = NTU * 64 * NW * 16;
+    int PR = keep && NW == 8 ? SMSTEP_KEPT_REGISTERS / (4 * (NTU * lay.n_sources + MT)) : 0, room = keep ? (int)((STEP_LDS_LIMIT - lds) / chunk_bytes) : 0;
+    std::vector<int> walk(lay.n_sources);      // streamed columns
+    int least = 1 << 30, most = 0;
+    for (int sidx = 0; sidx < lay.n_sources; ++sidx) {
+        const int n = (lay.src[sidx].k_len + CW - 1) / CW;
+        least = std::min(least, n); most = std::max(most, n);
+    }
+    PR = std::max(0, std::min(PR, least - 1));
+    for (int sidx = 0; sidx < lay.n_sources; ++sidx) {
+        const int K = lay.src[sidx].k_len;
+        walk[sidx] = PR > 0 ? ((K + CW - 1) / CW - PR) * CW : K;
+    }
+    unsigned long long LMASK = 0;
+    const int n_walk = most - PR, pairs = least == most && n_walk <= 64 ? std::min(room / lay.n_sources, n_walk / 2) / 2 : 0;
+    for (int j = 0; j < pairs; ++j) {
+        const int at = (2 * j + 1) * (n_walk / 2) / (2 * pairs);
+        LMASK |= 1ull << at | 1ull << (n_walk - 1 - at);
+    }
+    const bool middle = least == most && n_walk <= 64 && n_walk % 2 == 1 && room / lay.n_sources >= 2 * pairs + 1;
+    if (middle) LMASK |= 1ull << n_walk / 2;
+    const int LRES = 2 * pairs + (middle ? 1 : 0);
+    lds += (size_t)LRES * lay.n_sources * chunk_bytes;
+    // the depth that pads the walk's groups least
+    best_slots = 1 << 30;
+    for (int d = dmax; d >= std::max(2, dmax - 2); --d) {
+        int slots = 0;
+        for (int sidx = 0; sidx < lay.n_sources; ++sidx) slots += ((walk[sidx] + CW - 1) / CW + d - 1) / d * d;
+        if (slots < best_slots) { best_slots = slots; D = d; }
+    }
     // exchange through the tile-blocked twins: whole 16-stream tiles in the window and in every
     // pass of the element-wise part, every exchanged tensor with a twin
     bool xb = N % 16 == 0 && (IPT == 1 || SPP % 16 == 0) && P.twin_base >= 0 && !mstep_blocked_choices().empty() && mstep_blocked_choices()[0] != 0;
@@ -1008,7 +1048,7 @@ std::string jit_smstep_source(const Plan& P, const CompPlan& cp, bool backward, 
             }
             if (any) used.push_back({sidx * 16 + nt, 1});
         }
-        ngr.push_back({sidx, ((lay.src[sidx].k_len + CW - 1) / CW + D - 1) / D});
+        ngr.push_back({sidx, ((walk[sidx] + CW - 1) / CW + D - 1) / D});
     }
     bool symmetric = true;      // sources of one width that feed the same row tiles
     for (int sidx = 0; sidx < lay.n_sources; ++sidx) {
@@ -1018,6 +1058,10 @@ std::string jit_smstep_source(const Plan& P, const CompPlan& cp, bool backward, 
             symmetric = symmetric && feeds(sidx) == feeds(0);
         }
     }
+    std::vector<std::pair<int, int>> kw;
+    for (int sidx = 0; sidx < lay.n_sources; ++sidx) kw.push_back({sidx, walk[sidx]});
+    emit_switch("KS", "s", kw, 0);
+    o << "    static constexpr int PR = " << PR << ", LRES = " << LRES << ", RES0 = " << RES0 << ";\n    static constexpr unsigned long long LMASK = " << LMASK << "ull;\n";
     o << "    static constexpr bool SYMMETRIC = " << (symmetric ? "true" : "false") << ";\n";
     emit_switch("K", "s", ks, 0); emit_switch("edge_", "key", edge_of, -1); emit_switch("used_", "key", used, 0); emit_switch("ngr", "s", ngr, 0);
     o << "    static __device__ __forceinline__ constexpr int edge(int s, int task) { return edge_(s * " << STEP_MAX_TASKS << " + task); }\n";

@@ -2690,7 +2690,8 @@ __device__ __forceinline__ void sstep_kernel_body(const StepArgs& a, SShared& ms
 //   static constexpr int NJ (streams), MT, NSRC, NTU, D, CMAX, ACCS, NW (wavefronts: 8, or 4 where the
 //   operand registers of 8 do not fit), TR (1: the matrices are read from the transposed copy), IPT,
 //   SPP, XB (exchange through the tile-blocked twins); constexpr K(s), ngr(s), edge(s, task) (edge of the task
-//   that reads source s, -1: none), used(s, nt).
+//   that reads source s, -1: none), used(s, nt), KS(s) (columns of the walk: without the chunks kept in registers); PR, LRES (chunks of a
+//   source kept in registers, in LDS), RES0 (their place in LDS), LMASK (which chunks of the walk LDS keeps).
 // =============================================================================================
 template <class PH, class SM>
 __device__ __forceinline__ void smstep_kernel_body(const StepArgs& a, SShared& ms, float* lds, int w) {
@@ -2754,6 +2755,33 @@ __device__ __forceinline__ void smstep_kernel_body(const StepArgs& a, SShared& m
             if (SM::XB) aoff[sidx][mt] = ((mt * (SM::K(sidx) / 16) + wave) * 256 + lane * 4) * 4;
             else aoff[sidx][mt] = n < N ? (n * SM::K(sidx) + wcol) * 4 : 0x7FFFFFF0;
         }
+    // Resident chunks: what there is room for is read once per launch.  Bound by the weights' way from the memory-side cache: 268 MB of
+    // them per step do not fit its 256 MiB, what is left of them does.  In LDS, [chunk][tile][thread][4]: SM::LMASK's chunks of the walk
+    // through a source, alike from both ends.  In registers: the last SM::PR chunks of a source, which the walk leaves out.  16 streams,
+    // 4,096 LSTM units, us a step forward / backward: none 49.3 / 56.9; LDS alone 44.8 / 48.4; both
+    // 37.0 / 44.2 (7.3 / 6.1 TB/s of all weights).
+    auto operand = [&](int sidx, int nt, int c) {
+        const bool on = SM::K(sidx) % CW == 0 || c * CW + wcol < SM::K(sidx);
+        const muintx4 x = __builtin_amdgcn_raw_buffer_load_b128(rwb, on ? (int)(boff[sidx][nt] + (unsigned)(c * CW * 4)) : (int)0xC0000000u, 0, 0);
+        return mfloatx4{__uint_as_float(x.x), __uint_as_float(x.y), __uint_as_float(x.z), __uint_as_float(x.w)};
+    };
+    auto resident_at = [&](int i, int nt) { return SM::RES0 + ((i * SM::NTU + nt) * NTHR + tid) * 4; };
+    constexpr int PR = SM::PR;
+    mfloatx4 wkeep[SM::NSRC][PR > 0 ? PR : 1][SM::NTU];
+    step_static_for<0, SM::NSRC>([&](auto ss) {
+        constexpr int sidx = decltype(ss)::value;
+#pragma unroll
+        for (int i = 0; i < PR; ++i)
+#pragma unroll
+            for (int nt = 0; nt < SM::NTU; ++nt) wkeep[sidx][i][nt] = operand(sidx, nt, SM::KS(sidx) / CW + i);
+        int slot = sidx * SM::LRES;
+        for (int c = 0; c < 64; ++c) {
+            if (!((SM::LMASK >> c) & 1)) continue;
+#pragma unroll
+            for (int nt = 0; nt < SM::NTU; ++nt) *reinterpret_cast<mfloatx4*>(&lds[resident_at(slot, nt)]) = operand(sidx, nt, c);
+            ++slot;
+        }
+    });
     // the twin's element of this thread's item (pass 0) per exchanged store, frame 0
     float* xptr[PH::NST > 0 ? PH::NST : 1];
     if constexpr (SM::XB) {
@@ -2841,30 +2869,63 @@ __device__ __forceinline__ void smstep_kernel_body(const StepArgs& a, SShared& m
             }
             return __builtin_amdgcn_ballot_w64(m == STEP_SENTINEL) != 0;
         };
+        mfloatx4 acc[SM::MT][SM::NTU];
+        bool retried = false;
+        auto clear = [&]() {
+#pragma unroll
+            for (int mt = 0; mt < SM::MT; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < SM::NTU; ++nt) acc[mt][nt] = mfloatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        };
+        auto multiply = [&](auto ss, const muintx4 (&x)[SM::MT], const mfloatx4 (&opb)[SM::NTU]) {
+            constexpr int sidx = decltype(ss)::value;
+#pragma unroll
+            for (int mt = 0; mt < SM::MT; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < SM::NTU; ++nt)
+                    if (SM::used(sidx, nt)) {
+                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x[mt].x), opb[nt][0], acc[mt][nt], 0, 0, 0);
+                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x[mt].y), opb[nt][1], acc[mt][nt], 0, 0, 0);
+                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x[mt].z), opb[nt][2], acc[mt][nt], 0, 0, 0);
+                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x[mt].w), opb[nt][3], acc[mt][nt], 0, 0, 0);
+                    }
+        };
+        // is the chunk at column k0 of the walk resident? (LMASK is alike from both ends)
+        auto kept = [&](int k0) { return SM::LMASK != 0 && ((SM::LMASK >> (k0 / CW)) & 1) != 0; };
         // the weights of the first chunks do not wait for the exchange
         step_static_for<0, D - 1>([&](auto ii) {
             constexpr int i = decltype(ii)::value;
-            load_b(wb[i], bo[0], SM::K(0), SM::K(0) % CW != 0, i * CW, i * CW < (SM::K(0) + CW - 1) / CW * CW);
+            load_b(wb[i], bo[0], SM::KS(0), SM::KS(0) % CW != 0, i * CW, i * CW < (SM::KS(0) + CW - 1) / CW * CW && !kept(i * CW));
         });
         for (int i = 0; i < pdelay; ++i) __builtin_amdgcn_s_sleep(1);
-        bool retried = false;
         step_static_for<0, D - 1>([&](auto ii) {
             constexpr int i = decltype(ii)::value;
-            load_a(v[i], rs[0], ao[0], SM::K(0), SM::K(0) % CW != 0, i * CW, i * CW < (SM::K(0) + CW - 1) / CW * CW);
+            load_a(v[i], rs[0], ao[0], SM::KS(0), SM::KS(0) % CW != 0, i * CW, i * CW < (SM::KS(0) + CW - 1) / CW * CW);
         });
-        mfloatx4 acc[SM::MT][SM::NTU];
-#pragma unroll
-        for (int mt = 0; mt < SM::MT; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < SM::NTU; ++nt) acc[mt][nt] = mfloatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        clear();
         bool bad = incomplete(v[0]);
 
         step_static_for<0, SM::NSRC>([&](auto ss) {
             constexpr int sidx = decltype(ss)::value;
             constexpr int NGR = SM::ngr(sidx);
-            constexpr int KP = (SM::K(sidx) + CW - 1) / CW * CW;
+            constexpr int KP = (SM::KS(sidx) + CW - 1) / CW * CW;
             constexpr int snext = sidx + 1 < SM::NSRC ? sidx + 1 : sidx;
-            constexpr int KPN = (SM::K(snext) + CW - 1) / CW * CW;
+            constexpr int KPN = (SM::KS(snext) + CW - 1) / CW * CW;
+            // the kept chunks' source values are asked for here and multiplied behind the walk
+            muintx4 vk[PR > 0 ? PR : 1][SM::MT];
+            auto poll_kept = [&](int i) {
+                constexpr int so = SM::SYMMETRIC ? SM::NSRC - 1 - sidx : sidx;
+                const __amdgpu_buffer_rsrc_t r0 = rev ? rs[so] : rs[sidx];
+                const int k0 = SM::KS(sidx) + i * CW;
+#pragma unroll
+                for (int mt = 0; mt < SM::MT; ++mt) {
+                    int off = aoff[sidx][mt] + (SM::XB ? k0 * 64 : k0 * 4);
+                    if (SM::K(sidx) % CW != 0) off = k0 + (SM::XB ? wave * 16 : wcol) < SM::K(sidx) ? off : 0x7FFFFFF0;
+                    vk[i][mt] = __builtin_amdgcn_raw_buffer_load_b128(r0, off, 0, STEP_COHERENT_AUX);
+                }
+            };
+#pragma unroll
+            for (int i = 0; i < PR; ++i) poll_kept(i);
 #pragma unroll 1
             for (int g = 0; g < NGR; ++g) {
                 step_static_for<0, D>([&](auto ii) {
@@ -2878,11 +2939,11 @@ __device__ __forceinline__ void smstep_kernel_body(const StepArgs& a, SShared& m
                     const bool on = same ? kj < KP : (sidx + 1 < SM::NSRC && kj < KPN);
                     auto ahead = [&]() {
                         if (same) {
-                            load_b(wb[j], bo[sidx], SM::K(sidx), SM::K(sidx) % CW != 0, kj, on);
-                            load_a(v[j], rs[sidx], ao[sidx], SM::K(sidx), SM::K(sidx) % CW != 0, kj, on);
+                            load_b(wb[j], bo[sidx], SM::KS(sidx), SM::KS(sidx) % CW != 0, kj, on && !kept(kj));
+                            load_a(v[j], rs[sidx], ao[sidx], SM::KS(sidx), SM::KS(sidx) % CW != 0, kj, on);
                         } else {
-                            load_b(wb[j], bo[snext], SM::K(snext), SM::K(snext) % CW != 0, kj, on);
-                            load_a(v[j], rs[snext], ao[snext], SM::K(snext), SM::K(snext) % CW != 0, kj, on);
+                            load_b(wb[j], bo[snext], SM::KS(snext), SM::KS(snext) % CW != 0, kj, on && !kept(kj));
+                            load_a(v[j], rs[snext], ao[snext], SM::KS(snext), SM::KS(snext) % CW != 0, kj, on);
                         }
                     };
                     if (k0 < KP) {
@@ -2894,7 +2955,7 @@ __device__ __forceinline__ void smstep_kernel_body(const StepArgs& a, SShared& m
                                 if (++spins > a.spin_limit) { dead = true; if (lane == 0) atomicExch(a.ctrl, 1u); break; }
                                 __builtin_amdgcn_s_sleep(MSTEP_RETRY_SLEEP);
                                 step_compiler_barrier();
-                                load_a(again, rs[sidx], ao[sidx], SM::K(sidx), SM::K(sidx) % CW != 0, k0, true);
+                                load_a(again, rs[sidx], ao[sidx], SM::KS(sidx), SM::KS(sidx) % CW != 0, k0, true);
                                 if (!incomplete(again)) break;
                             }
 #pragma unroll
@@ -2905,23 +2966,32 @@ __device__ __forceinline__ void smstep_kernel_body(const StepArgs& a, SShared& m
                         mfloatx4 opb[SM::NTU];
 #pragma unroll
                         for (int nt = 0; nt < SM::NTU; ++nt) opb[nt] = wb[i][nt];
+                        if (kept(k0)) {
+                            constexpr int so = SM::SYMMETRIC ? SM::NSRC - 1 - sidx : sidx;
+                            const int c = at(k0, SM::KS(sidx)) / CW, slot = (rev ? so : sidx) * SM::LRES + __builtin_popcountll(SM::LMASK & ((1ull << c) - 1));
+#pragma unroll
+                            for (int nt = 0; nt < SM::NTU; ++nt) opb[nt] = *reinterpret_cast<const mfloatx4*>(&lds[resident_at(slot, nt)]);
+                        }
                         ahead();
                         bad = incomplete(v[i1]);
-#pragma unroll
-                        for (int mt = 0; mt < SM::MT; ++mt)
-#pragma unroll
-                            for (int nt = 0; nt < SM::NTU; ++nt)
-                                if (SM::used(sidx, nt)) {
-                                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(v[i][mt].x), opb[nt][0], acc[mt][nt], 0, 0, 0);
-                                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(v[i][mt].y), opb[nt][1], acc[mt][nt], 0, 0, 0);
-                                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(v[i][mt].z), opb[nt][2], acc[mt][nt], 0, 0, 0);
-                                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(v[i][mt].w), opb[nt][3], acc[mt][nt], 0, 0, 0);
-                                }
+                        multiply(ss, v[i], opb);
                     } else {
                         ahead();
                         bad = incomplete(v[i1]);
                     }
                 });
+            }
+#pragma unroll
+            for (int i = 0; i < PR; ++i) {
+                int spins = 0;
+                while (incomplete(vk[i]) && !dead) {
+                    retried = true;
+                    if (++spins > a.spin_limit) { dead = true; if (lane == 0) atomicExch(a.ctrl, 1u); break; }
+                    __builtin_amdgcn_s_sleep(MSTEP_RETRY_SLEEP);
+                    step_compiler_barrier();
+                    poll_kept(i);
+                }
+                multiply(ss, vk[i], wkeep[sidx][i]);
             }
         });
         // ---- hand the accumulators to the element-wise threads: one partial tile per wavefront ----

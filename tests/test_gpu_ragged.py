@@ -47,6 +47,24 @@ def test_exchange_inside_and_across_xcds(monkeypatch, net, hidden, N, env):
     assert rec and all(win.g.step_build(k, b)[0] == "matrix" for k in rec for b in (False, True))
 
 
+@pytest.mark.parametrize("net,hidden,N", [("lstm", 512, 16), ("lstm", 300, 40), ("elman", 1100, 33), ("elman", 2052, 9), ("elman", 132, 16), ("generalized", 260, 20)])
+def test_streamed_weights_with_resident_chunks(monkeypatch, net, hidden, N):
+    """Chunks of a source kept in registers and LDS: one to all but one of them, a ragged one among them, in one launch and in pieces."""
+    monkeypatch.setenv("RNNG_STEP_BUILD", "stream")
+    monkeypatch.setenv("RNNG_SMSTEP_RESIDENT", "1")
+    from paper_1503_02852_amd.runner import window_for
+    spec = {"lstm": lambda: wl.lstm_net(7, [hidden], 5), "elman": lambda: wl.elman_net(7, hidden, 5), "generalized": lambda: wl.generalized_net(8, hidden, 2, 4)}[net]()
+    w = wl.make_workload("resident", spec, T=8, N=N, seed=74, scale=0.4 / hidden ** 0.5, bias_scale=0.2, masked_fraction=0.2)
+    win, _ = run_both(w, label=f"resident {net} {hidden}, N={N}")
+    rec = [k for k in range(len(spec.nodes)) if win.g.step_build(k)[0] != "none"]
+    assert rec and all(win.g.step_build(k, b)[0] == "streaming" for k in rec for b in (False, True))
+    pieces = window_for(w)
+    for a, b in ((0, 1), (1, 4), (4, 8)):
+        pieces.forward_range(a, b)
+    pieces.check()
+    assert all(np.array_equal(pieces.node_output(k), win.node_output(k)) for k in rec)
+
+
 @pytest.mark.parametrize("N,T", [(3, 16400), (17, 8200)])
 def test_long_windows_keep_their_step_kernel(N, T):
     """Tensors far below the 1 GiB that a step kernel addresses, with copies that 16-stream tiles
