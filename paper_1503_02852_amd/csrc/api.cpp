@@ -370,7 +370,7 @@ struct rnn_graph {
         }
         return cached_layout;
     }
-    void drop_choices() { jit_choices.clear(); chain_choices.clear(); cached_T = cached_N = 0; lay = StepLayouts(); }
+    void drop_choices() { jit_choices.clear(); chain_choices.clear(); mstep_picks.clear(); cached_T = cached_N = 0; lay = StepLayouts(); }
     // The layouts (step_layout.h) of the weights-in-registers and the matrix-core launches of a window with N streams, one after the other as the kernels
     // load them, and where the first one of a component's or chain's launch lies (direction: 2 c + d; -1: none).  sizes_ok: wave_tensor_sizes_ok.
     struct StepLayouts { std::vector<int32_t> words; std::vector<int> comp, chain; int N = 0; bool sizes_ok = false; };
@@ -443,8 +443,15 @@ struct rnn_graph {
     // third of a tile empty than weight rows in registers.
     struct MstepPick { int G = 0, J = 0, rows = 0, columns = 0; };      // columns: contracted by a workgroup per step, once per 16 x 16 tile; G = 0: does not fit
     static constexpr int MSTEP_MIN_ROWS = 11;
-    MstepPick pick_mstep(const CompPlan& cp, bool backward, int N, int J, int limit, bool local) const {
+    std::map<std::tuple<const CompPlan*, bool, int, int, int, bool>, MstepPick> mstep_picks;
+    const MstepPick& pick_mstep(const CompPlan& cp, bool backward, int N, int J, int limit, bool local) {
+        const auto key = std::make_tuple(&cp, backward, N, J, limit, local);
+        const auto it = mstep_picks.find(key);
+        return it != mstep_picks.end() ? it->second : mstep_picks.emplace(key, find_mstep(cp, backward, N, J, limit, local)).first->second;
+    }
+    MstepPick find_mstep(const CompPlan& cp, bool backward, int N, int J, int limit, bool local) const {
         MstepPick best;
+        if (J > 1 && J > (N + 15) / 16) return best;      // (stream groups are whole 16-stream tiles)
         StepLayout lay;
         compute_step_layout(plan.words.data(), backward ? cp.bwd_desc_off : cp.fwd_desc_off, 256, 1, 1, lay);
         if (!lay.ok || lay.n_phases != 1 || lay.ph[0].n_tasks < 1) return best;
@@ -459,6 +466,7 @@ struct rnn_graph {
                 MstepPick p;
                 p.G = force_step_G > 0 ? force_step_G : (dim + chunk - 1) / chunk; p.J = J;
                 if (p.G > limit) break;
+                if (force_step_G <= 0 && chunk * mstep_streams(N, J, true) > STEP_THREADS) continue;      // (more element-wise items than threads)
                 bool regs = false;
                 const bool fits = jit_mstep_fits(plan, cp, backward, N, p.G, J, local, &p.rows, &regs);
                 p.columns = k * ((p.rows + 15) / 16) * (((N + 15) / 16 + J - 1) / J);
