@@ -167,6 +167,7 @@ struct rnn_graph {
     int fwd_upto = 0;                     // frames [0, fwd_upto) of the current window hold forward results
     bool framewise = false;               // benchmark mode: every frame on its own, no batching over frames
     bool deterministic = false;           // rnn_set_deterministic: one writer per gradient element, fixed summation order
+    bool prefilled = false;               // inside a call: the tensors of all of its step launches are filled already (all_shared)
     bool no_alloc = false;                // inside rnn_forward_static: load no code, create no events, stage no host copies
     PlanView view() const {
         PlanView pv;
@@ -827,7 +828,7 @@ const std::string& windowed(const std::string& source, std::string& cache) {
 // kernel polls the interleaved bundle tensors instead of bundled members; the members are filled as
 // well, so that a fall-back to another kernel build finds them prepared.
 // A kernel with tile-blocked exchange polls the twins and nothing else.
-hipError_t fill_shared(rnn_graph* g, const std::vector<int>& bufs, bool with_bundles, int t0, int t1, hipStream_t s, bool twins = false) {
+std::vector<int> shared_tensors(const rnn_graph* g, const std::vector<int>& bufs, bool with_bundles, bool twins) {
     std::vector<int> list(bufs);
     if (twins) for (int& b : list) if (g->plan.buf_alloc[g->plan.twin_base + b] == 3) b += g->plan.twin_base;      // (tensors without a twin are polled as they are)
     if (with_bundles)
@@ -835,13 +836,21 @@ hipError_t fill_shared(rnn_graph* g, const std::vector<int>& bufs, bool with_bun
             const int bi = g->plan.bundle_of[b];
             if (bi >= 0 && std::find(list.begin(), list.end(), g->plan.bundles[bi].ebuf) == list.end()) list.push_back(g->plan.bundles[bi].ebuf);
         }
+    return list;
+}
+void add_range(const rnn_graph* g, FillRanges& fr, int b, int t0, int t1) {
+    const int64_t frame = g->plan.frame_floats(b, g->N);
+    const bool ragged = g->plan.buf_alloc[b] == 3 && frame != (int64_t)g->N * g->plan.buf_dim[b];
+    fr.twin_n[fr.count] = ragged ? g->N : 0; fr.twin_dim[fr.count] = ragged ? g->plan.buf_dim[b] : 0;
+    fr.p[fr.count] = g->buf(b) + t0 * frame; fr.n[fr.count] = (t1 - t0) * frame;
+    ++fr.count;
+}
+hipError_t fill_shared(rnn_graph* g, const std::vector<int>& bufs, bool with_bundles, int t0, int t1, hipStream_t s, bool twins = false) {
+    if (g->prefilled) return hipSuccess;
     FillRanges fr; fr.count = 0;
-    for (int b : list) {
-        const int64_t frame = g->plan.frame_floats(b, g->N);
-        const bool ragged = g->plan.buf_alloc[b] == 3 && frame != (int64_t)g->N * g->plan.buf_dim[b];
-        fr.twin_n[fr.count] = ragged ? g->N : 0; fr.twin_dim[fr.count] = ragged ? g->plan.buf_dim[b] : 0;
-        fr.p[fr.count] = g->buf(b) + t0 * frame; fr.n[fr.count] = (t1 - t0) * frame;
-        if (++fr.count == FILL_MAX_RANGES) {
+    for (int b : shared_tensors(g, bufs, with_bundles, twins)) {
+        add_range(g, fr, b, t0, t1);
+        if (fr.count == FILL_MAX_RANGES) {
             hipError_t e = launch_fill_sentinel_ranges(fr, s);
             if (e != hipSuccess) return e;
             fr.count = 0;
@@ -1049,6 +1058,48 @@ StepRun run_chain(rnn_graph* g, int chain, bool backward, hipStream_t s, int t0,
     return ok;
 }
 
+// The tensors that all step launches of a direction poll during frames [t0, t1), if they are few and small: a call fills them with its first
+// launch, together with what it clears, instead of with one launch per step launch.  (Up to 16 MiB: what is filled stays in the caches until it is polled.)
+bool all_shared(rnn_graph* g, bool backward, int t0, int t1, FillRanges& fr) {
+    fr.count = 0;
+    if (g->framewise) return false;
+    int64_t floats = 0;
+    auto add = [&](const std::vector<int>& list) {
+        for (int b : list) {
+            if (fr.count == FILL_MAX_RANGES) return false;
+            add_range(g, fr, b, t0, t1);
+            floats += fr.n[fr.count - 1];
+        }
+        return floats <= (4 << 20);
+    };
+    const Plan& P = g->plan;
+    const bool jit = g->use_jit && jit_available();
+    for (size_t c = 0; c < P.comps.size(); ++c) {
+        const CompPlan& cp = P.comps[c];
+        if (!cp.recurrent || !(backward ? cp.has_bwd_program : cp.has_fwd_program)) continue;
+        if (cp.chain >= 0 && jit && wave_tensor_sizes_ok(g)) {
+            const ChainPlan& ch = P.chains[cp.chain];
+            const rnn_graph::ChainChoice& cc = g->chain_choice(cp.chain, backward, g->N);
+            if (!cc.source.empty()) {
+                if ((int)c != ch.first) continue;
+                std::vector<int> exchanged;
+                for (const CompPlan& m : rnn_graph::chain_members(ch, cc))
+                    for (int b : backward ? m.bwd_shared_bufs : m.fwd_shared_bufs) exchanged.push_back(b);
+                if (!add(shared_tensors(g, exchanged, !cc.mstep, cc.blocked))) return false;
+                continue;
+            }
+        }
+        const std::vector<int>& bufs = backward ? cp.bwd_shared_bufs : cp.fwd_shared_bufs;
+        const rnn_graph::JitChoice* jc = jit ? &g->jit_choice((int)c, backward, g->N) : nullptr;
+        if (jc && !jc->source.empty() && (!(jc->wave || (jc->mstep && !jc->two_d)) || wave_tensor_sizes_ok(g))) {
+            if (!add(shared_tensors(g, bufs, jc->wave, jc->blocked))) return false;
+        } else {
+            return false;      // (other builds fill their own)
+        }
+    }
+    return true;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1225,7 +1276,7 @@ int rnn_forward_range(rnn_graph* g, const float* d_weights, const float* const* 
             return fail(RNN_ERR_SEQUENCE, "frames before t_begin have not been computed in this workspace");
     }
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    g->fwd_done = g->bptt_done = false;
+    g->fwd_done = g->bptt_done = g->prefilled = false;
 
     g->T = T; g->N = N; g->ws = static_cast<char*>(d_workspace); g->layout = L; g->weights = d_weights;
     g->inputs.assign(P.xnodes.size(), nullptr);
@@ -1261,9 +1312,14 @@ int rnn_forward_range(rnn_graph* g, const float* d_weights, const float* const* 
         // frames in front of every frame tensor (the state before a fresh window is zero).  Pieces
         // of a window computed later keep the flags an earlier piece has raised.
         g->xcd_words_used = 0;
-        e = launch_zero_history(g->view().buf_ptr, reinterpret_cast<const int64_t*>(g->ws + L.frames_off), P.n_bufs, H,
+        FillRanges fr;
+        const bool few = all_shared(g, false, H, H + t_end, fr);
+        if (few) e = launch_fill_sentinel_and_clear(fr, g->view().buf_ptr, reinterpret_cast<const int64_t*>(g->ws + L.frames_off), H > 0 ? P.n_bufs : 0, H,
+                                                    reinterpret_cast<unsigned*>(g->ws + L.sync_off), (int)(SYNC_BYTES / 4), s);
+        else e = launch_zero_history(g->view().buf_ptr, reinterpret_cast<const int64_t*>(g->ws + L.frames_off), P.n_bufs, H,
                                 reinterpret_cast<unsigned*>(g->ws + L.sync_off), (int)(SYNC_BYTES / 4), s);
         if (e != hipSuccess) return fail_hip(e, "window reset");
+        g->prefilled = few;
     }
     // one-hot inputs with delayed connections: their class indices likewise (-1, the zero vector, in a fresh window's history)
     for (size_t i = 0; i < P.input_nodes.size(); ++i) {
@@ -1295,6 +1351,7 @@ int rnn_forward_range(rnn_graph* g, const float* d_weights, const float* const* 
         }
     } else {
         const int rc = forward_frames(g, H + t_begin, H + t_end, s);
+        g->prefilled = false;
         if (rc != RNN_OK) return rc;
     }
     g->fwd_upto = t_end;
@@ -1438,8 +1495,13 @@ int rnn_bptt(rnn_graph* g, const float* d_weights, const void* const* d_targets,
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     g->weights = d_weights;
     const int T = g->T, N = g->N, H = g->hist();
-    hipError_t e = launch_fill(reinterpret_cast<float*>(g->loss_ptr()), 2, 0.0f, s);
+    FillRanges fr;
+    g->prefilled = false;
+    const bool few = all_shared(g, true, H, H + T, fr);
+    hipError_t e = few ? launch_fill_sentinel_and_clear(fr, nullptr, nullptr, 0, 0, reinterpret_cast<unsigned*>(g->loss_ptr()), 2, s)
+                       : launch_fill(reinterpret_cast<float*>(g->loss_ptr()), 2, 0.0f, s);
     if (e != hipSuccess) return fail_hip(e, "loss reset");
+    g->prefilled = few;
     // the output deltas of all frames first (they depend on the forward pass only)
     for (const CompPlan& cp : P.comps) {
         const int k = cp.softmax_node >= 0 ? cp.softmax_node : cp.sqerr_node;
@@ -1484,6 +1546,7 @@ int rnn_bptt(rnn_graph* g, const float* d_weights, const void* const* d_targets,
         }
     } else {
         const int rc = backward_frames(H, H + T);
+        g->prefilled = false;
         if (rc != RNN_OK) return rc;
     }
     g->bptt_done = true;

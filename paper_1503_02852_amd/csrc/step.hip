@@ -97,13 +97,12 @@ __global__ __launch_bounds__(256) void fill_bits_kernel(unsigned* __restrict__ p
     for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += 256LL * gridDim.x) p[i] = v;
 }
 
-// blockIdx.y: the range
-__global__ __launch_bounds__(256) void fill_ranges_kernel(const FillRanges r, unsigned v) {
-    unsigned* __restrict__ p = reinterpret_cast<unsigned*>(r.p[blockIdx.y]);
-    const long long n = r.n[blockIdx.y];
-    const int dim = r.twin_dim[blockIdx.y];
+__device__ __forceinline__ void fill_range(const FillRanges& r, int range, unsigned v) {
+    unsigned* __restrict__ p = reinterpret_cast<unsigned*>(r.p[range]);
+    const long long n = r.n[range];
+    const int dim = r.twin_dim[range];
     if (dim > 0) {      // the inverse of twin_offset, in a tensor below 2 GiB
-        const unsigned N = r.twin_n[blockIdx.y], width = twin_pad(dim);
+        const unsigned N = r.twin_n[range], width = twin_pad(dim);
         for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < (unsigned)n; i += 256 * gridDim.x) {
             const unsigned at = i % (N * width), first = at / (16 * width) * 16, rows = N - first < 16 ? N - first : 16;
             const unsigned unit = (at - first * width) / (4 * rows) * 4 + (i & 3);
@@ -112,6 +111,21 @@ __global__ __launch_bounds__(256) void fill_ranges_kernel(const FillRanges r, un
         return;
     }
     for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += 256LL * gridDim.x) p[i] = v;
+}
+// blockIdx.y: the range
+__global__ __launch_bounds__(256) void fill_ranges_kernel(const FillRanges r, unsigned v) { fill_range(r, blockIdx.y, v); }
+// The same, and behind the ranges what a call clears: the control words, the history frames of the buffers (a launch of its own for each cost
+// 3 us: 8 % of the smallest window's training call).
+__global__ __launch_bounds__(256) void fill_ranges_and_clear_kernel(const FillRanges r, unsigned v, float* const* __restrict__ buf_ptr, const int64_t* __restrict__ frame_floats,
+                                                                    int n_bufs, int frames, unsigned* __restrict__ words, int n_words) {
+    if ((int)blockIdx.y < r.count) { fill_range(r, blockIdx.y, v); return; }
+    for (int b = blockIdx.x; b <= n_bufs; b += gridDim.x) {
+        if (b == n_bufs) { for (int i = threadIdx.x; i < n_words; i += 256) words[i] = 0u; continue; }
+        const long long n = (long long)frames * frame_floats[b];
+        if (n <= 0) continue;
+        float* p = buf_ptr[b];
+        for (long long i = threadIdx.x; i < n; i += 256) p[i] = 0.0f;
+    }
 }
 
 }  // namespace
@@ -214,6 +228,16 @@ hipError_t launch_fill_sentinel_ranges(const FillRanges& r, hipStream_t stream) 
     long long blocks = (most + 255) / 256;
     if (blocks > 1024) blocks = 1024;
     hipLaunchKernelGGL(fill_ranges_kernel, dim3((unsigned)blocks, (unsigned)r.count), dim3(256), 0, stream, r, STEP_SENTINEL);
+    return hipGetLastError();
+}
+
+hipError_t launch_fill_sentinel_and_clear(const FillRanges& r, float* const* buf_ptr, const int64_t* frame_floats, int n_bufs, int frames, unsigned* words, int n_words,
+                                          hipStream_t stream) {
+    if (r.count > FILL_MAX_RANGES) return hipErrorInvalidValue;
+    long long blocks = n_bufs + 1;
+    for (int i = 0; i < r.count; ++i) blocks = std::max(blocks, std::min<long long>((r.n[i] + 255) / 256, 1024));
+    hipLaunchKernelGGL(fill_ranges_and_clear_kernel, dim3((unsigned)blocks, (unsigned)r.count + 1), dim3(256), 0, stream, r, STEP_SENTINEL, buf_ptr, frame_floats, n_bufs, frames, words,
+                       n_words);
     return hipGetLastError();
 }
 
