@@ -202,7 +202,7 @@ struct rnn_graph {
     bool use_jit = true;
     bool use_store_window = true;
     // Run-time specialised step kernels, chosen once per (component, direction, stream count).
-    struct JitChoice { bool wave = false, mstep = false, stream = false, needs_t = false, blocked = false, local = false; int J = 1; StepLaunchPlan lp; std::string source, source_window; bool two_d = false; int64_t partial_floats = 0; };
+    struct JitChoice { bool wave = false, mstep = false, stream = false, needs_t = false, blocked = false, local = false, element_wise = false; int J = 1; StepLaunchPlan lp; std::string source, source_window; bool two_d = false; int64_t partial_floats = 0; };
     int force_step_J = 0, local_env = -1;      // RNNG_MSTEP_LOCAL: 0 never, 1 wherever it can run
     bool prefer_streaming = false;        // RNNG_STEP_BUILD=stream
     // the workgroups of a step launch wait for each other, so all of them must be resident at once:
@@ -245,9 +245,17 @@ struct rnn_graph {
             const MstepPick p = pick_mstep(cp, backward, N, J, 32, true);
             if (p.G && J <= 8 * (32 / p.G) && p.G * J <= max_workgroups() && (local_env == 1 || p.rows <= (N >= 16 ? 48 : 32))) take_mstep(c, cp, backward, N, p, true);
         };
+        // Recurrences without a full connection inside: a thread per stream and unit.  LSTM without output recurrence, us a launch against the
+        // weights-in-registers build: forward 512 units, N = 1, 2,048 frames 358 / 449, 64 units, N = 4, 512 frames 93 / 118; backward
+        // 512, N = 8, 256 frames 76 / 104, but 512, N = 1 534 / 493, 1,024, N = 4, 256 frames 76 / 67.  From 9 streams on the other is a launch
+        // per frame: 64 units, N = 10 0.19 + 0.28 against 6.1 + 7.7 us a frame forward + backward, 1,000 units, N = 64 0.62 + 0.82 against 6.8 + 8.6.
+        if (c.source.empty() && force_step_G <= 0 && (!backward || N >= 5)) {
+            c.source = jit_estep_source(plan, cp, backward, N, &c.lp.G, &c.J);
+            if (c.source.empty()) { c.J = 1; c.lp = StepLaunchPlan(); }
+            else { c.element_wise = true; c.lp.ok = true; c.lp.NB = 1; c.lp.lds_bytes = 0; c.lp.threads = 64; c.lp.xcd_stride = 1; }
+        }
         if (N >= 5 || local_env == 1) try_local();
         try_wave(force_step_G > 0 ? force_step_G : 32);
-        if (N >= 4) try_local();
         if (force_step_G <= 0 && register_over_xcds(cp, backward, N)) try_wave(64);
         try_local();
         // 2. matrix-core variants for many streams (weights in LDS or registers, MFMA)
@@ -413,6 +421,7 @@ struct rnn_graph {
                 const JitChoice& jc = jit_choice((int)c, d != 0, N);
                 if (jc.source.empty()) continue;
                 if (jc.wave) r.comp[2 * c + d] = add(cp, d != 0, jc.lp.G, step_nb_for(N), N);
+                else if (jc.element_wise) r.comp[2 * c + d] = add(cp, d != 0, jc.lp.G, 1, 1);
                 else if (jc.mstep && !jc.two_d) r.comp[2 * c + d] = add(cp, d != 0, jc.lp.G, 1, mstep_streams(N, jc.J, jc.blocked));
             }
         }
@@ -492,8 +501,8 @@ struct rnn_graph {
     // (LSTM forward 384 units, N = 8 2.24 / 1.97, N = 16 2.31 / 2.41), never with four (512 units, N = 16 3.30 / 1.89).
     // Up to 8 streams against the weights-in-registers build on one XCD: one source from N = 5 on (LSTM forward 16 / 100 units, N = 5
     // 1.00 / 1.03 against 1.11 / 1.41, N = 4 1.00 / 1.05 against 0.89 / 0.98); several from 400 columns on (LSTM backward, N = 8, 48 / 100 / 128 units 1.64 / 1.66 / 1.76
-    // against 1.18 / 1.77 / 1.92).  N = 2 to 4: after that build on one XCD;
-    // before it on two at N = 4 (LSTM backward, 384 units 2.7 / 3.7).
+    // against 1.18 / 1.77 / 1.92).  N = 2 to 4: after that build,
+    // also where it takes two XCDs.
     bool local_streams(const CompPlan& cp, bool backward, int N, int several_from = 400, int one_from = 0) const {
         if (local_env == 0 || N < 2 || !matrix_streams(cp, backward, N)) return false;
         if (N > 8 || local_env == 1) return true;
@@ -907,7 +916,7 @@ StepRun run_phases(rnn_graph* g, int comp, bool backward, hipStream_t s, int t0,
     const int desc_off = backward ? cp.bwd_desc_off : cp.fwd_desc_off;
     rnn_graph::JitChoice* jc = (g->use_jit && jit_available()) ? const_cast<rnn_graph::JitChoice*>(&g->jit_choice(comp, backward, N)) : nullptr;
     const bool have_jit = jc && !jc->source.empty() && !g->framewise &&
-                          (!(jc->wave || (jc->mstep && !jc->two_d)) || wave_tensor_sizes_ok(g));
+                          (!(jc->wave || jc->element_wise || (jc->mstep && !jc->two_d)) || wave_tensor_sizes_ok(g));
     const bool have_interp = !g->framewise && plan_step_launch(g->plan.words.data(), desc_off, N, g->force_step_G, lp);
     const int spin_limit = g->spin_limit;
     if (have_jit) {
@@ -915,7 +924,7 @@ StepRun run_phases(rnn_graph* g, int comp, bool backward, hipStream_t s, int t0,
         if (fe != hipSuccess) return step_error(fe, "sentinel fill");
         // (matrix-core build: measured per direction; backward loops, with more stores and loads per
         // step, gain 3 %, forward loops lose 4 to 6 %)
-        const bool window = (jc->wave || (jc->mstep && !jc->two_d && backward && gathers_in_workspace(g, cp.bwd_phases))) && wave_store_window_ok(g);
+        const bool window = (jc->wave || (((jc->mstep && !jc->two_d && backward) || jc->element_wise) && gathers_in_workspace(g, phases))) && wave_store_window_ok(g);
         std::string why;
         hipFunction_t fn = jit_step_function(window ? windowed(jc->source, jc->source_window) : jc->source, &why, !g->no_alloc,
                                              jc->mstep && !jc->two_d ? MSTEP_LDS_LIMIT : STEP_LDS_LIMIT);
@@ -959,11 +968,11 @@ StepRun run_phases(rnn_graph* g, int comp, bool backward, hipStream_t s, int t0,
         }
         StepLaunchPlan lp_all = jc->lp;
         lp_all.G = jc->lp.G * jc->J;       // launch size; a.G stays the number of unit chunks
-        if (!launch_fits_device(g, lp_all.G, why)) return step_error(hipSuccess, why);
+        if (!jc->element_wise && !launch_fits_device(g, lp_all.G, why)) return step_error(hipSuccess, why);
         if (jc->local) { lp_all.G = mstep_local_blocks(jc->lp.G, jc->J); lp_all.xcd_stride = 1; }
         hipError_t e = jit_launch(fn, a, lp_all, s);
         if (e != hipSuccess) { (void)hipGetLastError(); return step_error(e, "specialised step kernel launch"); }
-        served = jc->wave ? RNN_BUILD_WAVE : jc->two_d ? RNN_BUILD_MATRIX_2D : jc->stream ? RNN_BUILD_STREAMING : jc->mstep ? RNN_BUILD_MATRIX : RNN_BUILD_LDS;
+        served = jc->wave || jc->element_wise ? RNN_BUILD_WAVE : jc->two_d ? RNN_BUILD_MATRIX_2D : jc->stream ? RNN_BUILD_STREAMING : jc->mstep ? RNN_BUILD_MATRIX : RNN_BUILD_LDS;
         g->prof.end(prof, 1, s);
         return ok;
     }
@@ -1091,7 +1100,7 @@ bool all_shared(rnn_graph* g, bool backward, int t0, int t1, FillRanges& fr) {
         }
         const std::vector<int>& bufs = backward ? cp.bwd_shared_bufs : cp.fwd_shared_bufs;
         const rnn_graph::JitChoice* jc = jit ? &g->jit_choice((int)c, backward, g->N) : nullptr;
-        if (jc && !jc->source.empty() && (!(jc->wave || (jc->mstep && !jc->two_d)) || wave_tensor_sizes_ok(g))) {
+        if (jc && !jc->source.empty() && (!(jc->wave || jc->element_wise || (jc->mstep && !jc->two_d)) || wave_tensor_sizes_ok(g))) {
             if (!add(shared_tensors(g, bufs, jc->wave, jc->blocked))) return false;
         } else {
             return false;      // (other builds fill their own)

@@ -87,7 +87,8 @@ void emit_ops(std::ostringstream& o, const int32_t* pw) {
 
 namespace {
 
-void emit_phase_descriptor(std::ostringstream& o, const Plan& P, const PhasePlan& ph, int p, int acc_phase) {
+// fused: products and sums of different statements may be fused (which of them are is up to the compiler, copy by copy of an unrolled loop).
+void emit_phase_descriptor(std::ostringstream& o, const Plan& P, const PhasePlan& ph, int p, int acc_phase, bool fused = true) {
     const int32_t* pw = &P.words[ph.prog_off];
     const int ng = pw[PG_NGATHER], ni = pw[PG_NINV], nops = pw[PG_NOPS], nst = pw[PG_NSTORES];
     o << "struct PH" << p << " {\n";
@@ -122,6 +123,7 @@ void emit_phase_descriptor(std::ostringstream& o, const Plan& P, const PhasePlan
     // (sttwin: the stored tensor has a tile-blocked twin, which many-stream kernels poll instead of it)
     emit_switch("stslot", "q", slots); emit_switch("stshared", "q", shareds); emit_switch("sttwin", "q", twins);
     o << "    static __device__ __forceinline__ void ops(float* s) {\n";
+    if (!fused) o << "#pragma clang fp contract(off)\n";
     emit_ops(o, pw);
     o << "    }\n};\n";
 }
@@ -738,6 +740,32 @@ std::string jit_mstep_source(const Plan& P, const CompPlan& cp, bool backward, i
                   "        w /= a.xcd_stride;\n"
                   "    }\n") <<
          "    mstep_kernel_body<grp0::PH0, grp0::MM>(a, ms, lds, w);\n"
+         "}\n";
+    return o.str();
+}
+
+std::string jit_estep_source(const Plan& P, const CompPlan& cp, bool backward, int N, int* G, int* J) {
+    const std::vector<PhasePlan>& phases = backward ? cp.bwd_phases : cp.fwd_phases;
+    if (phases.size() != 1 || phases[0].mv_off >= 0 || N < 1) return "";
+    const int32_t* pw = P.words.data() + phases[0].prog_off;
+    const int dim = pw[PG_MAXDIM];
+    for (int g = 0; g < pw[PG_NGATHER]; ++g) {
+        const int kind = pw[PG_HEADER_WORDS + g * GA_WORDS + GA_KIND];
+        if (kind == GA_KIND_ACC || kind == GA_KIND_POLLED) return "";
+    }
+    *G = (dim + 63) / 64;
+    const int chunk = (dim + *G - 1) / *G, SPW = 64 / chunk;
+    *J = (N + SPW - 1) / SPW;
+    StepLayout lay;
+    compute_step_layout(P.words.data(), backward ? cp.bwd_desc_off : cp.fwd_desc_off, *G, 1, 1, lay);
+    if (!lay.ok || lay.n_sources > 0 || lay.ph[0].n_tasks > 0) return "";
+    std::ostringstream o;
+    o << "#include \"step_device.h\"\nusing namespace rnng;\n";
+    emit_phase_descriptor(o, P, phases[0], 0, 0, false);      // (a frame's bits do not depend on where its call begins)
+    o << "extern \"C\" __global__ __launch_bounds__(64)\n"
+         "void rnng_step_jit(StepArgs a) {\n"
+         "    __shared__ MShared ms;\n"
+         "    estep_kernel_body<PH0, " << SPW << ">(a, ms, (int)blockIdx.x);\n"
          "}\n";
     return o.str();
 }

@@ -30,6 +30,8 @@ std::string jit_mstep_source(const Plan& P, const CompPlan& cp, bool backward, i
 // Whether that variant exists; *rows: accumulator rows per workgroup (tasks x units per chunk), *in_registers: weight rows of whole sources
 // are kept in vector registers.
 bool jit_mstep_fits(const Plan& P, const CompPlan& cp, bool backward, int N, int G, int J, bool local, int* rows, bool* in_registers);
+// Element-wise recurrences: a thread per (stream, unit), no workgroup waits for another (*G unit chunks x *J stream groups of one wavefront each).
+std::string jit_estep_source(const Plan& P, const CompPlan& cp, bool backward, int N, int* G, int* J);
 // Matrix-core variant with the two-dimensional split (row groups of GJ workgroups that share
 // the columns of every source; partial sums travel through a tensor of *partial_floats floats per frame).
 std::string jit_mstep2_source(const Plan& P, const CompPlan& cp, bool backward, int N, int G, int GJ, size_t* lds_bytes,

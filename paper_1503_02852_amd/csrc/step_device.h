@@ -2079,6 +2079,79 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
 }
 
 // =============================================================================================
+// Element-wise recurrences (run-time specialised, single-phase components without a full connection inside, any number of streams).
+//
+// A unit of a stream depends on nothing but its own earlier values, so no workgroup waits for another: a thread takes one (stream, unit)
+// through all steps, a workgroup is one wavefront of up to 64 units, times the SPW streams that fit beside each other.  Bound by a
+// thread's serial chain of a step, about 80 instructions and the activations' latency; inputs are loaded EPD steps ahead.  An LSTM
+// without output recurrence takes 0.19 + 0.28 us a step forward + backward at 64 units and 10 streams, 0.62 + 0.82 at 1,000 units and 64
+// streams (where a launch per frame took 6 to 9).
+// =============================================================================================
+template <class PH, int SPW>
+__device__ __forceinline__ void estep_kernel_body(const StepArgs& a, MShared& ms, int w) {
+    const int tid = threadIdx.x, T = a.T, wj = w / a.G;
+    w -= wj * a.G;
+    load_step_layout(a, 1, 1, ms.lay, tid, 64);
+    __syncthreads();
+    {
+        const int ic = ms.lay.ph[0].item_chunk, j = tid / ic, n = wj * SPW + j;
+        ms.iteminfo[0][tid] = (unsigned)(tid - j * ic) | ((unsigned)(j < SPW && n < a.N ? n : 0xFFFF) << 16);
+    }
+    __syncthreads();
+    PhaseRegs<PH> r;
+    phase_setup<PH, 1, 2>(r, a, ms, nullptr, w, tid);
+    wave_store_setup<PH, MStore>(r, a);
+    wave_carry_init<PH>(r, a);
+    if constexpr (MStore::SW) {      // gather offsets relative to the window (parked lanes stay outside)
+#pragma unroll
+        for (int g = 0; g < PH::NG; ++g)
+            if (r.gvoff[g] != 0xC0000000u) r.gvoff[g] += (unsigned)((r.gbase[g] - a.store_base) * 4);
+    }
+    auto gather_at = [&](auto gg, int frame) -> float {      // zero outside the window and for a thread without an element
+        constexpr int g = decltype(gg)::value;
+        const __amdgpu_buffer_rsrc_t rg = MStore::SW ? __builtin_amdgcn_make_buffer_rsrc(a.store_base, 0, (int)a.store_bytes, STEP_RSRC_FLAGS)
+                                                     : __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(r.gbase[g]), 0, T * r.gstride[g] * 4, STEP_RSRC_FLAGS);
+        const int off = frame >= 0 && frame < T ? (int)(r.gvoff[g] + (unsigned)(frame * r.gstride[g] * 4)) : (int)WAVE_NO_STORE;
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rg, off, 0, PH::gkind(g) == GA_KIND_STATIC ? 0 : STEP_COHERENT_AUX));
+    };
+    constexpr int EPD = 8;
+    const int nsteps = step_count(a);
+    float sn[EPD][PH::NG > 0 ? PH::NG : 1];
+    auto ahead = [&](auto jj, int step) {
+        constexpr int j = decltype(jj)::value;
+        step_static_for<0, PH::NG>([&](auto gg) {
+            constexpr int g = decltype(gg)::value;
+            if (PH::gkind(g) == GA_KIND_STATIC) sn[j][g] = gather_at(gg, step < nsteps ? step_frame(a, step) + r.goff[g] : -1);
+        });
+    };
+    auto one = [&](auto jj, int step) {
+        constexpr int j = decltype(jj)::value;
+        const int t = step_frame(a, step);
+        float s[MAX_SLOTS];
+        step_static_for<0, PH::NG>([&](auto gg) {
+            constexpr int g = decltype(gg)::value;
+            if (PH::gkind(g) == GA_KIND_STATIC) s[g] = sn[j][g];
+            else if (PH::gkind(g) == GA_KIND_CARRY) s[g] = r.carry[PH::cidx(g)];
+            else s[g] = gather_at(gg, t + r.goff[g]);
+        });
+#pragma unroll
+        for (int v = 0; v < PH::NI; ++v) s[PH::NG + v] = r.inv[v];
+        PH::ops(s);
+#pragma unroll
+        for (int q = 0; q < PH::NST; ++q) wave_store<PH, MStore>(r, q, s[PH::stslot(q)], 0, a);
+        wave_store_advance<PH>(r);
+#pragma unroll
+        for (int g = 0; g < PH::NG; ++g)
+            if (PH::gkind(g) == GA_KIND_CARRY) r.carry[PH::cidx(g)] = s[PH::gaux(g)];
+        ahead(jj, step + EPD);
+    };
+    step_static_for<0, EPD>([&](auto jj) { ahead(jj, decltype(jj)::value); });
+    int base = 0;
+    for (; base + EPD <= nsteps; base += EPD) step_static_for<0, EPD>([&](auto jj) { one(jj, base + decltype(jj)::value); });
+    step_static_for<0, EPD>([&](auto jj) { if (base + decltype(jj)::value < nsteps) one(jj, base + decltype(jj)::value); });
+}
+
+// =============================================================================================
 // Matrix-core variant with a two-dimensional split (many streams, wide layers).
 //
 // In the variant above every workgroup polls every source tensor whole (N * K values per source

@@ -47,6 +47,24 @@ def test_exchange_inside_and_across_xcds(monkeypatch, net, hidden, N, env):
     assert rec and all(win.g.step_build(k, b)[0] == "matrix" for k in rec for b in (False, True))
 
 
+@pytest.mark.parametrize("layers,N,T", [([3], 9, 1), ([16], 33, 7), ([64], 10, 8), ([65], 9, 9), ([70, 130], 14, 25), ([200], 70, 17)])
+def test_element_wise_recurrences_at_many_streams(layers, N, T):
+    """LSTM layers without output recurrence beyond the streams of the weights-in-registers build: units and streams that fill no wavefront,
+    windows of fewer steps than are loaded ahead, at once and in pieces."""
+    from paper_1503_02852_amd.runner import window_for
+    spec = wl.lstm_net(7, layers, 5, output_recurrence=False)
+    w = wl.make_workload("element_wise", spec, T=T, N=N, seed=75, scale=0.3, bias_scale=0.2, masked_fraction=0.2)
+    win, _ = run_both(w, label=f"element-wise {layers}, N={N}")
+    rec = [k for k in range(len(spec.nodes)) if win.g.step_build(k)[0] != "none"]
+    assert rec and all(win.g.step_build(k, b) == ("wave", False) for k in rec for b in (False, True))
+    pieces = window_for(w)
+    for a, b in ((0, T // 3), (T // 3, T - 1), (T - 1, T)):
+        if a < b:
+            pieces.forward_range(a, b)
+    pieces.check()
+    assert all(np.array_equal(pieces.node_output(k), win.node_output(k)) for k in rec)
+
+
 @pytest.mark.parametrize("net,hidden,N", [("lstm", 512, 16), ("lstm", 300, 40), ("elman", 1100, 33), ("elman", 2052, 9), ("elman", 132, 16), ("generalized", 260, 20)])
 def test_streamed_weights_with_resident_chunks(monkeypatch, net, hidden, N):
     """Chunks of a source kept in registers and LDS: one to all but one of them, a ragged one among them, in one launch and in pieces."""
