@@ -155,7 +155,8 @@ struct rnn_graph {
     int Ti() const { return T + plan.hist; }
     char* ws = nullptr;
     Layout layout;
-    std::vector<char> blob;               // host copy of the plan tables (kept alive for the async upload)
+    std::vector<char> blob, blob_next;    // host copy of the plan tables (kept alive for the async upload), the next call's while they are compared
+    bool tables_there = false;            // blob is what the current window's workspace holds
     std::vector<const float*> inputs;     // per exec node id (input nodes only)
     const XcdMap* xcd = nullptr;          // set by the first forward call on this device
     std::vector<const int32_t*> onehot;   // per exec node id: class indices of a one-hot input, or nullptr
@@ -1300,21 +1301,30 @@ int rnn_forward_range(rnn_graph* g, const float* d_weights, const float* const* 
     const bool sizes_ok = wave_tensor_sizes_ok(g);
     if (g->lay.N != N || g->lay.sizes_ok != sizes_ok) g->lay = g->step_layouts(N, sizes_ok);
     const int64_t blob_bytes = L.lay_off + (int64_t)g->lay.words.size() * 4;
-    g->blob.assign(blob_bytes, 0);
-    if (!g->lay.words.empty()) std::memcpy(&g->blob[L.lay_off], g->lay.words.data(), g->lay.words.size() * 4);
+    std::vector<char>& blob = g->blob_next;
+    blob.assign(blob_bytes, 0);
+    if (!g->lay.words.empty()) std::memcpy(&blob[L.lay_off], g->lay.words.data(), g->lay.words.size() * 4);
     for (int b = 0; b < P.n_bufs; ++b) {
         float* p = g->buf(b);
-        std::memcpy(&g->blob[L.table_off + 8 * (int64_t)b], &p, 8);
+        std::memcpy(&blob[L.table_off + 8 * (int64_t)b], &p, 8);
     }
-    std::memcpy(&g->blob[L.dims_off], P.buf_dim.data(), (size_t)P.n_bufs * 4);
+    std::memcpy(&blob[L.dims_off], P.buf_dim.data(), (size_t)P.n_bufs * 4);
     for (int b = 0; b < P.n_bufs; ++b) {
         const int64_t frame = ((P.buf_alloc[b] == 1 || P.buf_alloc[b] == 3) && L.buf_off[b] >= 0) ? P.frame_floats(b, N) : 0;
-        std::memcpy(&g->blob[L.frames_off + 8 * (int64_t)b], &frame, 8);
+        std::memcpy(&blob[L.frames_off + 8 * (int64_t)b], &frame, 8);
     }
-    if (!P.words.empty()) std::memcpy(&g->blob[L.words_off], P.words.data(), P.words.size() * 4);
-    // (without allocations: as kernel arguments, which need no staging buffer of the runtime's)
-    hipError_t e = g->no_alloc ? launch_upload_words(reinterpret_cast<uint32_t*>(g->ws), reinterpret_cast<const uint32_t*>(g->blob.data()), blob_bytes / 4, s)
-                               : hipMemcpyAsync(g->ws, g->blob.data(), (size_t)blob_bytes, hipMemcpyHostToDevice, s);
+    if (!P.words.empty()) std::memcpy(&blob[L.words_off], P.words.data(), P.words.size() * 4);
+    // A later piece of a window finds the tables where its first one put them, as it finds that one's frames, unless an address has changed
+    // (one new frame of 2 x 512 LSTM units: 52.8 us with the upload, 42.6 without).
+    hipError_t e = hipSuccess;
+    if (t_begin == 0 || !g->tables_there || blob != g->blob) {
+        g->tables_there = false;
+        g->blob.swap(blob);
+        // (without allocations: as kernel arguments, which need no staging buffer of the runtime's)
+        e = g->no_alloc ? launch_upload_words(reinterpret_cast<uint32_t*>(g->ws), reinterpret_cast<const uint32_t*>(g->blob.data()), blob_bytes / 4, s)
+                        : hipMemcpyAsync(g->ws, g->blob.data(), (size_t)blob_bytes, hipMemcpyHostToDevice, s);
+        g->tables_there = e == hipSuccess;
+    }
     if (e != hipSuccess) return fail_hip(e, "plan table upload");
     if (!g->xcd) {
         e = ensure_xcd_map(reinterpret_cast<unsigned*>(g->ws + L.sync_off), s, &g->xcd);
