@@ -244,7 +244,7 @@ struct rnn_graph {
             if (!c.source.empty() || c.stream || force_step_G > 0 || force_step_J > 0 || !local_streams(cp, backward, N)) return;
             const int J = (N + 15) / 16;
             const MstepPick p = pick_mstep(cp, backward, N, J, 32, true);
-            if (p.G && J <= 8 * (32 / p.G) && p.G * J <= max_workgroups() && (local_env == 1 || p.rows <= (N >= 16 ? 48 : 32))) take_mstep(c, cp, backward, N, p, true);
+            if (p.G && J <= std::min(8 * (32 / p.G), 4 * XCD_WORDS / 2) && p.G * J <= max_workgroups() && (local_env == 1 || p.rows <= (N >= 16 ? 48 : 32))) take_mstep(c, cp, backward, N, p, true);
         };
         // Recurrences without a full connection inside: a thread per stream and unit.  LSTM without output recurrence, us a launch against the
         // weights-in-registers build: forward 512 units, N = 1, 2,048 frames 358 / 449, 64 units, N = 4, 512 frames 93 / 118; backward
