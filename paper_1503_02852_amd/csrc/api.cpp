@@ -637,10 +637,11 @@ struct rnn_graph {
             }
         };
         if (use_jit && use_chains && force_step_G <= 0 && !prefer_streaming) {
-            // From 5 streams on the matrix cores come first: where every layer is exchanged as one vector of more than 48 columns, or as
-            // several of more than 320 together.  us a step, registers against matrix cores: forward 2 x 64 / 128 units, N = 5 1.70 / 1.66 against
-            // 1.27 / 1.25, N = 4 2 x 32 / 160 1.13 / 1.68 against 1.29 / 1.96, 2 x 32, N = 5 1.47 against 1.36; backward, N = 5, 2 x 64 / 100 / 128 1.76 / 1.94 / 2.07 against 1.73 / 1.76 / 1.73.
-            bool first = N >= 5;
+            // Forward from 3, backward from 5 streams on the matrix cores come first: where every layer is exchanged as one vector of more than
+            // 48 columns, or as several of more than 320 together.  us a step, registers against matrix cores: forward 2 x 50 / 100 / 256 units, N = 4
+            // 1.42 / 1.75 / 1.91 against 1.22 / 1.22 / 1.39, N = 3 1.36 / 1.58 / 1.87 against 1.22 / 1.23 / 1.39, 2 x 32, N = 5 1.47 against 1.36;
+            // backward, N = 5, 2 x 64 / 100 / 128 1.76 / 1.94 / 2.07 against 1.73 / 1.76 / 1.73.
+            bool first = N >= (backward ? 5 : 3);
             for (int m = ch.first; m <= ch.last && first; ++m) first = local_streams(plan.comps[m], backward, N, 320, 48);
             if (first) matrix_cores(true);
             registers();
