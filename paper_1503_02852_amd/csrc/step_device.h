@@ -377,15 +377,13 @@ __device__ __forceinline__ void ring_fill(const PhaseRegs<PH>& r, const StepArgs
 
 // MODE 0: LDS variant (static gathers through the workgroup ring); 1: wave-autonomous variant
 // (per-wavefront ring, own matrix-vector set-up); 2: static gathers are loaded directly.
-// SH: StepShared, or a leaner table set with the members lay and iteminfo (threads beyond
-// STEP_THREADS, which some variants have, own no item).
-template <class PH, int NB, int MODE = 0, class SH = StepShared>
-__device__ __forceinline__ void phase_setup(PhaseRegs<PH>& r, const StepArgs& a, const SH& sh, float* lds, int w, int tid) {
+// SH: StepShared, or a leaner table set with the member lay.
+// il, n: local unit and stream of the thread's element-wise item (n = -1: none).
+template <class PH, int NB, int MODE, class SH>
+__device__ __forceinline__ void phase_setup_item(PhaseRegs<PH>& r, const StepArgs& a, const SH& sh, float* lds, int w, int tid, int il, int n) {
     const StepPhase& ph = sh.lay.ph[PH::P];
     cwords_t pw = (cwords_t)a.words + suni(ph.prog_off);
-    const unsigned item = tid < STEP_THREADS ? sh.iteminfo[PH::P][tid] : 0xFFFF0000u;
-    const int il = (int)(item & 0xFFFF);
-    r.n = (item >> 16) == 0xFFFF ? -1 : (int)(item >> 16);
+    r.n = n;
     const int G = a.G, N = a.N;
     const StepPhase& aph = sh.lay.ph[PH::ACC_PHASE];
     const int item_chunk = suni(ph.item_chunk), items = item_chunk * N;
@@ -454,6 +452,12 @@ __device__ __forceinline__ void phase_setup(PhaseRegs<PH>& r, const StepArgs& a,
         if (PH::HAS_TASKS) { matvec_setup<NB>(r.mv, sh, PH::P, tid); sources_setup(r.src, a, sh, PH::P); }
         if (PH::NS > 0 && r.pf_steps > 0) ring_fill<PH>(r, a, lds, 0, 0, tid);
     }
+}
+// The item as iteminfo holds it: at most 65,535 streams (threads beyond STEP_THREADS, which some variants have, own no item).
+template <class PH, int NB, int MODE = 0, class SH = StepShared>
+__device__ __forceinline__ void phase_setup(PhaseRegs<PH>& r, const StepArgs& a, const SH& sh, float* lds, int w, int tid) {
+    const unsigned item = tid < STEP_THREADS ? sh.iteminfo[PH::P][tid] : 0xFFFF0000u;
+    phase_setup_item<PH, NB, MODE>(r, a, sh, lds, w, tid, (int)(item & 0xFFFF), (item >> 16) == 0xFFFF ? -1 : (int)(item >> 16));
 }
 
 // Optional cycle stamps of one workgroup's steps 64..71 (8 stamps per step, written behind the
@@ -2093,13 +2097,9 @@ __device__ __forceinline__ void estep_kernel_body(const StepArgs& a, MShared& ms
     w -= wj * a.G;
     load_step_layout(a, 1, 1, ms.lay, tid, 64);
     __syncthreads();
-    {
-        const int ic = ms.lay.ph[0].item_chunk, j = tid / ic, n = wj * SPW + j;
-        ms.iteminfo[0][tid] = (unsigned)(tid - j * ic) | ((unsigned)(j < SPW && n < a.N ? n : 0xFFFF) << 16);
-    }
-    __syncthreads();
+    const int ic = ms.lay.ph[0].item_chunk, j = tid / ic, n = wj * SPW + j;
     PhaseRegs<PH> r;
-    phase_setup<PH, 1, 2>(r, a, ms, nullptr, w, tid);
+    phase_setup_item<PH, 1, 2>(r, a, ms, nullptr, w, tid, tid - j * ic, j < SPW && n < a.N ? n : -1);      // (any number of streams: more than iteminfo holds)
     wave_store_setup<PH, MStore>(r, a);
     wave_carry_init<PH>(r, a);
     if constexpr (MStore::SW) {      // gather offsets relative to the window (parked lanes stay outside)

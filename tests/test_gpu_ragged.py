@@ -65,6 +65,18 @@ def test_element_wise_recurrences_at_many_streams(layers, N, T):
     assert all(np.array_equal(pieces.node_output(k), win.node_output(k)) for k in rec)
 
 
+@pytest.mark.parametrize("N", [65535, 65536, 70000])
+def test_element_wise_recurrences_beyond_16_bits_of_streams(N):
+    """Every stream has a thread of its own, also where its number does not fit 16 bits."""
+    spec = wl.lstm_net(2, [3], 2, output_recurrence=False)
+    win, ref = run_both(wl.make_workload("element_wise", spec, T=3, N=N, seed=76, scale=0.3, bias_scale=0.2, masked_fraction=0.2), label=f"element-wise [3], N={N}")
+    rec = [k for k in range(len(spec.nodes)) if win.g.step_build(k)[0] != "none"]
+    assert rec and all(win.g.step_build(k, b) == ("wave", False) for k in rec for b in (False, True))
+    for k in rec:      # the upper streams by themselves: a tensor's maximum need not lie among them
+        assert np.abs(win.node_output(k)[:, 65530:] - ref["y"][k][:, 65530:]).max() < 1e-6
+        assert np.abs(win.node_state_grad(k)[:, 65530:] + ref["delta"][k][:, 65530:]).max() < 1e-6
+
+
 @pytest.mark.parametrize("net,hidden,N", [("lstm", 512, 16), ("lstm", 300, 40), ("elman", 1100, 33), ("elman", 2052, 9), ("elman", 132, 16), ("generalized", 260, 20)])
 def test_streamed_weights_with_resident_chunks(monkeypatch, net, hidden, N):
     """Chunks of a source kept in registers and LDS: one to all but one of them, a ragged one among them, in one launch and in pieces."""
