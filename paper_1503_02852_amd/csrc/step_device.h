@@ -1470,7 +1470,7 @@ RNNG_HD inline void compute_mstep_layout(const StepLayout& lay, int N, int nw, u
 // element-wise part's instructions and spilled scalar registers.
 struct MStore { static constexpr bool SW = RNNG_STORE_WINDOW != 0; };
 // (leaner than StepShared: one phase, so that more of the 160 KiB is left for weight rows)
-struct MShared { StepLayout lay; unsigned iteminfo[1][STEP_THREADS]; unsigned retried[2]; };
+struct MShared { StepLayout lay; unsigned retried[2]; };
 
 // Launches whose stream groups each sit on one XCD: units (stream groups of the members, one member after the other) of LG
 // workgroups; workgroups b, b + 8, ... of a launch share an XCD, so unit u takes the workgroups of residue u % 8.
@@ -1505,11 +1505,6 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
     for (int i = 4 * tid; i < MM::LDSF; i += 4 * NTHR) *reinterpret_cast<mfloatx4*>(&lds[i]) = mfloatx4{0.0f, 0.0f, 0.0f, 0.0f};
     __syncthreads();
     const StepPhase& ph = sh.lay.ph[0];
-    if (tid < STEP_THREADS) {      // at most STEP_THREADS element-wise items
-        const int ic = ph.item_chunk;
-        const int il = tid % ic, n = tid / ic;
-        sh.iteminfo[0][tid] = (unsigned)il | ((unsigned)(n < N ? n0 + n : 0xFFFF) << 16);      // global stream index
-    }
     if (tid < 2) ms.retried[tid] = 0u;
     // resident weights: W_lds[s][blk(s, task) * cmax + ul][k]; edges of one task that share a
     // source add up in one row.  Eight loads of a thread in flight, none behind a branch, 16 bytes each where the matrix' rows (transposed:
@@ -1566,14 +1561,14 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
             else columns(StepIntC<1>{});
         }
     });
+    // the thread's element-wise item: local unit and stream, from its own index (nothing that another wavefront would have to leave in LDS first)
+    const int item_n = itid / suni(ph.item_chunk), item_il = itid < STEP_THREADS ? itid - item_n * suni(ph.item_chunk) : 0;
     PhaseRegs<PH> r;
-    phase_setup<PH, 1, 2>(r, a, sh, lds, w, itid);
+    phase_setup_item<PH, 1, 2>(r, a, sh, lds, w, itid, item_il, itid < STEP_THREADS && item_n < N ? n0 + item_n : -1);      // (r.n: global stream index)
     __syncthreads();
 
     constexpr int D = MM::D, NPAD = MM::MT * 16, ACCS = MM::ACCS;
     constexpr int accbase = MM::ACCBASE;
-    const int item_il = itid < STEP_THREADS ? (int)(sh.iteminfo[0][itid] & 0xFFFF) : 0;
-    const int item_n = itid / suni(ph.item_chunk);                         // local stream of this thread's item
     // LDS address of the weight row behind each of this lane's tile columns, per source
     int brow[MM::NSRC][MM::NTU];
 #pragma unroll

@@ -47,6 +47,30 @@ def test_exchange_inside_and_across_xcds(monkeypatch, net, hidden, N, env):
     assert rec and all(win.g.step_build(k, b)[0] == "matrix" for k in rec for b in (False, True))
 
 
+@pytest.mark.parametrize("env", [{}, {"RNNG_MSTEP_LOCAL": "0"}])
+@pytest.mark.parametrize("layers,N", [([1], 9), ([3], 16), ([8], 64), ([17], 40), ([5, 9], 12)])
+def test_small_layers_set_up_their_element_wise_wavefronts(monkeypatch, layers, N, env):
+    """Layers whose weights are a load or two of a thread: the wavefronts for the element-wise program reach their items before the others have
+    left anything behind.  The same bits in every window (a launch each), at other streams' values too."""
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    spec = wl.lstm_net(5, layers, 4)
+    w = wl.make_workload("small", spec, T=3, N=N, seed=77, scale=0.5, bias_scale=0.2)
+    win, _ = run_both(w, label=f"small {layers}, N={N}, {env}")
+    rec = [k for k in range(len(spec.nodes)) if win.g.step_build(k)[0] != "none"]
+    assert rec and all(win.g.step_build(k, b)[0] == "matrix" for k in rec for b in (False, True))
+    (x,) = spec.input_nodes()
+    first = [win.node_output(k) for k in rec] + [win.node_state_grad(k) for k in rec]
+    other = {x: -w.inputs[x]}
+    for _ in range(20):
+        win.set_inputs(other)
+        win.forward(); win.bptt()
+        win.set_inputs(w.inputs)
+        win.forward(); win.bptt()
+        win.check()
+        assert all(np.array_equal(a, b) for a, b in zip(first, [win.node_output(k) for k in rec] + [win.node_state_grad(k) for k in rec]))
+
+
 @pytest.mark.parametrize("layers,N,T", [([3], 9, 1), ([16], 33, 7), ([64], 10, 8), ([65], 9, 9), ([70, 130], 14, 25), ([200], 70, 17)])
 def test_element_wise_recurrences_at_many_streams(layers, N, T):
     """LSTM layers without output recurrence beyond the streams of the weights-in-registers build: units and streams that fill no wavefront,
