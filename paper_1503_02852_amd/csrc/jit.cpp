@@ -56,22 +56,39 @@ std::mutex g_mutex;
 Rtc g_rtc;
 std::map<std::string, CacheEntry> g_cache;   // key: generated source
 
-void emit_ops(std::ostringstream& o, const int32_t* pw) {
+// written_out: a product that an addition takes in is written as a fused operation there (two products: the second), and the square of
+// MOP_DTANH with the subtraction it goes into, as the compiler may fuse them but need not.
+void emit_ops(std::ostringstream& o, const int32_t* pw, bool written_out) {
     const int ng = pw[PG_NGATHER], ni = pw[PG_NINV], nops = pw[PG_NOPS];
     const int32_t* mo = pw + PG_HEADER_WORDS + ng * GA_WORDS + ni * IV_WORDS;
+    struct Product { std::string x, y; int a = -1, b = -1; };      // what a slot holds, while the slots a and b that its factors name stay as they are
+    std::map<int, Product> products;
     for (int p = 0; p < nops; ++p) {
         const int packed = mo[p * MO_WORDS + MO_PACKED], c = mo[p * MO_WORDS + MO_C];
         const int opc = packed & 0xFF, d = (packed >> 8) & 0xFF, a = (packed >> 16) & 0xFF, b = (packed >> 24) & 0xFF;
+        const std::string sa = "s[" + std::to_string(a) + "]", sb = "s[" + std::to_string(b) + "]";
+        Product made;
+        if (written_out) {
+            if (opc == MOP_MUL) made = Product{sa, sb, a, b};
+            if (opc == MOP_DSIG) made = Product{sa + " * " + sb, "1.0f - " + sb, a, b};
+            if (opc == MOP_DTANH) made = Product{sa, "fmaf(-" + sb + ", " + sb + ", 1.0f)", a, b};
+        }
         o << "        s[" << d << "] = ";
         switch (opc) {
             case MOP_MOV: o << "s[" << a << "]"; break;
-            case MOP_ADD: o << "s[" << a << "] + s[" << b << "]"; break;
+            case MOP_ADD: {
+                const auto ia = products.find(a), ib = products.find(b);
+                if (ib != products.end()) o << "fmaf(" << ib->second.x << ", " << ib->second.y << ", " << sa << ")";
+                else if (ia != products.end()) o << "fmaf(" << ia->second.x << ", " << ia->second.y << ", " << sb << ")";
+                else o << sa << " + " << sb;
+                break;
+            }
             case MOP_MUL: o << "s[" << a << "] * s[" << b << "]"; break;
             case MOP_FMA: o << "fmaf(s[" << a << "], s[" << b << "], s[" << c << "])"; break;
             case MOP_SIG: o << "step_sigmoid(s[" << a << "])"; break;
             case MOP_TANH: o << "step_tanh(s[" << a << "])"; break;
             case MOP_DSIG: o << "s[" << a << "] * s[" << b << "] * (1.0f - s[" << b << "])"; break;
-            case MOP_DTANH: o << "s[" << a << "] * (1.0f - s[" << b << "] * s[" << b << "])"; break;
+            case MOP_DTANH: if (written_out) o << made.x << " * " << made.y; else o << "s[" << a << "] * (1.0f - s[" << b << "] * s[" << b << "])"; break;
             case MOP_RELU: o << "fmaxf(s[" << a << "], 0.0f)"; break;
             case MOP_DRELU: o << "(s[" << b << "] > 0.0f ? s[" << a << "] : 0.0f)"; break;
             case MOP_MAX: o << "fmaxf(s[" << a << "], s[" << b << "])"; break;
@@ -80,6 +97,9 @@ void emit_ops(std::ostringstream& o, const int32_t* pw) {
             default: o << "0.0f"; break;
         }
         o << ";\n";
+        products.erase(d);
+        for (auto it = products.begin(); it != products.end();) it = it->second.a == d || it->second.b == d ? products.erase(it) : std::next(it);
+        if (made.a >= 0 && a != d && b != d) products[d] = made;
     }
 }
 
@@ -87,8 +107,8 @@ void emit_ops(std::ostringstream& o, const int32_t* pw) {
 
 namespace {
 
-// fused: products and sums of different statements may be fused (which of them are is up to the compiler, copy by copy of an unrolled loop).
-void emit_phase_descriptor(std::ostringstream& o, const Plan& P, const PhasePlan& ph, int p, int acc_phase, bool fused = true) {
+// fixed: which products and sums are fused is written out, else it is up to the compiler, copy by copy of an unrolled loop.
+void emit_phase_descriptor(std::ostringstream& o, const Plan& P, const PhasePlan& ph, int p, int acc_phase, bool fixed = false) {
     const int32_t* pw = &P.words[ph.prog_off];
     const int ng = pw[PG_NGATHER], ni = pw[PG_NINV], nops = pw[PG_NOPS], nst = pw[PG_NSTORES];
     o << "struct PH" << p << " {\n";
@@ -123,8 +143,8 @@ void emit_phase_descriptor(std::ostringstream& o, const Plan& P, const PhasePlan
     // (sttwin: the stored tensor has a tile-blocked twin, which many-stream kernels poll instead of it)
     emit_switch("stslot", "q", slots); emit_switch("stshared", "q", shareds); emit_switch("sttwin", "q", twins);
     o << "    static __device__ __forceinline__ void ops(float* s) {\n";
-    if (!fused) o << "#pragma clang fp contract(off)\n";
-    emit_ops(o, pw);
+    if (fixed) o << "#pragma clang fp contract(off)\n";
+    emit_ops(o, pw, fixed);
     o << "    }\n};\n";
 }
 
@@ -761,7 +781,7 @@ std::string jit_estep_source(const Plan& P, const CompPlan& cp, bool backward, i
     if (!lay.ok || lay.n_sources > 0 || lay.ph[0].n_tasks > 0) return "";
     std::ostringstream o;
     o << "#include \"step_device.h\"\nusing namespace rnng;\n";
-    emit_phase_descriptor(o, P, phases[0], 0, 0, false);      // (a frame's bits do not depend on where its call begins)
+    emit_phase_descriptor(o, P, phases[0], 0, 0, true);      // (a frame's bits do not depend on where its call begins)
     o << "extern \"C\" __global__ __launch_bounds__(64)\n"
          "void rnng_step_jit(StepArgs a) {\n"
          "    __shared__ MShared ms;\n"

@@ -89,6 +89,31 @@ def test_element_wise_recurrences_at_many_streams(layers, N, T):
     assert all(np.array_equal(pieces.node_output(k), win.node_output(k)) for k in rec)
 
 
+def saturated_tanh_net(dim):
+    g = wl.GraphSpec()
+    x = g.add_node(wl.INPUT, wl.LINEAR, dim, name="x")
+    h = g.add_node(wl.ADD, wl.TANH, dim, name="h")
+    out = g.add_node(wl.ADD, wl.LINEAR, dim, is_output=wl.SQUARED_ERROR, name="out")
+    g.add_edge(x, h, wl.IDENTITY, 0); g.add_edge(h, h, wl.DIAG, 1); g.add_edge(h, out, wl.IDENTITY, 0)
+    return g
+
+
+@pytest.mark.parametrize("N", [1, 6, 40])
+def test_derivative_of_a_saturated_tanh(N):
+    """f'(s) = 1 - y^2 from the stored y, element by element: y^2 is not rounded before it is subtracted.  Of the window's last frame, whose
+    error term is the output's alone, 1 - y^2 is rounded once and its product once: 2 x 2^-24 relative; a rounded square would cost 2^-25 / (1 - y^2)."""
+    spec = saturated_tanh_net(37)
+    w = wl.make_workload("saturated", spec, T=3, N=N, seed=78, scale=0.01)
+    x, h, out = (spec.node_by_name(k) for k in ("x", "h", "out"))
+    w.inputs[x][...] = np.sign(w.inputs[x]) * (3.0 + np.abs(w.inputs[x]) % 1.5)
+    win, _ = run_both(w, label=f"saturated tanh, N={N}")
+    assert win.g.step_build(h)[0] == "wave" and win.g.step_build(h, True)[0] == "wave"
+    y = win.node_output(h)[-1].astype(np.float64)
+    assert (1 - y * y).max() < 0.02
+    expected = win.node_state_grad(out)[-1].astype(np.float64) * (1 - y * y)
+    assert np.abs(win.node_state_grad(h)[-1] / expected - 1).max() < 2.1 * 2.0 ** -24
+
+
 @pytest.mark.parametrize("N", [65535, 65536, 70000])
 def test_element_wise_recurrences_beyond_16_bits_of_streams(N):
     """Every stream has a thread of its own, also where its number does not fit 16 bits."""
