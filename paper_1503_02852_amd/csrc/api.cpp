@@ -1321,6 +1321,7 @@ int rnn_forward_range(rnn_graph* g, const float* d_weights, const float* const* 
     if (t_begin == 0 || !g->tables_there || blob != g->blob) {
         g->tables_there = false;
         g->blob.swap(blob);
+        blob.resize(blob_bytes);      // (the next call's, here and not in a window's first later piece)
         // (without allocations: as kernel arguments, which need no staging buffer of the runtime's)
         e = g->no_alloc ? launch_upload_words(reinterpret_cast<uint32_t*>(g->ws), reinterpret_cast<const uint32_t*>(g->blob.data()), blob_bytes / 4, s)
                         : hipMemcpyAsync(g->ws, g->blob.data(), (size_t)blob_bytes, hipMemcpyHostToDevice, s);
