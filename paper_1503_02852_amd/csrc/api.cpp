@@ -196,6 +196,7 @@ struct rnn_graph {
     unsigned* ctrl_ptr() const { return reinterpret_cast<unsigned*>(ws + layout.sync_off + 16); }
     int force_step_G = 0;
     int xcd_words_used = 0;               // of the current window (step_layout.h)
+    int xcd_fields_used = 0;              // of the current call
     int spin_limit = 1 << 22;             // bound of every wait inside a step kernel (polling attempts)
     int cu_count = 0;                     // compute units of the device of the current window (0: not asked yet)
     // which build ran the step loop of component c in direction d at its last launch (RNN_BUILD_*, 0: none yet)
@@ -204,7 +205,7 @@ struct rnn_graph {
     bool use_store_window = true;
     // Run-time specialised step kernels, chosen once per (component, direction, stream count).
     struct JitChoice { bool wave = false, mstep = false, stream = false, needs_t = false, blocked = false, local = false, element_wise = false; int J = 1; StepLaunchPlan lp; std::string source, source_window; bool two_d = false; int64_t partial_floats = 0; };
-    int force_step_J = 0, local_env = -1;      // RNNG_MSTEP_LOCAL: 0 never, 1 wherever it can run
+    int force_step_J = 0, local_env = -1;      // RNNG_MSTEP_LOCAL: 0 never, 1 wherever it can run, 2 the same with its groups dealt over the XCDs
     bool prefer_streaming = false;        // RNNG_STEP_BUILD=stream
     // the workgroups of a step launch wait for each other, so all of them must be resident at once:
     // one per compute unit (256 on a whole MI355X, fewer on a partition)
@@ -244,7 +245,7 @@ struct rnn_graph {
             if (!c.source.empty() || c.stream || force_step_G > 0 || force_step_J > 0 || !local_streams(cp, backward, N)) return;
             const int J = (N + 15) / 16;
             const MstepPick p = pick_mstep(cp, backward, N, J, 32, true);
-            if (p.G && J <= std::min(8 * (32 / p.G), 4 * XCD_WORDS / 2) && p.G * J <= max_workgroups() && (local_env == 1 || p.rows <= (N >= 16 ? 48 : 32))) take_mstep(c, cp, backward, N, p, true);
+            if (p.G && J <= std::min(8 * (32 / p.G), MSTEP_LOCAL_MAX_UNITS) && p.G * J <= max_workgroups() && (local_env >= 1 || p.rows <= (N >= 16 ? 48 : 32))) take_mstep(c, cp, backward, N, p, true);
         };
         // Recurrences without a full connection inside: a thread per stream and unit.  LSTM without output recurrence, us a launch against the
         // weights-in-registers build: forward 512 units, N = 1, 2,048 frames 358 / 449, 64 units, N = 4, 512 frames 93 / 118; backward
@@ -255,7 +256,7 @@ struct rnn_graph {
             if (c.source.empty()) { c.J = 1; c.lp = StepLaunchPlan(); }
             else { c.element_wise = true; c.lp.ok = true; c.lp.NB = 1; c.lp.lds_bytes = 0; c.lp.threads = 64; c.lp.xcd_stride = 1; }
         }
-        if (N >= 5 || local_env == 1) try_local();
+        if (N >= 5 || local_env >= 1) try_local();
         try_wave(force_step_G > 0 ? force_step_G : 32);
         if (force_step_G <= 0 && register_over_xcds(cp, backward, N)) try_wave(64);
         try_local();
@@ -506,7 +507,7 @@ struct rnn_graph {
     // also where it takes two XCDs.
     bool local_streams(const CompPlan& cp, bool backward, int N, int several_from = 400, int one_from = 0) const {
         if (local_env == 0 || N < 2 || !matrix_streams(cp, backward, N)) return false;
-        if (N > 8 || local_env == 1) return true;
+        if (N > 8 || local_env >= 1) return true;
         StepLayout lay;
         compute_step_layout(plan.words.data(), backward ? cp.bwd_desc_off : cp.fwd_desc_off, 256, 1, 1, lay);
         int columns = 0;
@@ -773,17 +774,33 @@ hipError_t ensure_xcd_map(unsigned* scratch, hipStream_t s, const XcdMap** out) 
     return hipSuccess;
 }
 
-// The first of `count` control words for the XCDs of the next launch that exchanges through an XCD's L2 (four groups a word), or -1.
-hipError_t xcd_word(rnn_graph* g, hipStream_t s, int* word, int count = 1) {
+// The control word for the XCDs of the next launch that exchanges through an XCD's L2, or -1.
+hipError_t xcd_word(rnn_graph* g, hipStream_t s, int* word) {
     *word = -1;
     if (!g_xcd_local || !g->xcd || !g->xcd->ok) return hipSuccess;
-    if (g->xcd_words_used + count > XCD_WORDS) {
+    if (g->xcd_words_used == XCD_WORDS) {
         hipError_t e = launch_xcd_words_fold(g->ctrl_ptr(), s);
         if (e != hipSuccess) return e;
         g->xcd_words_used = 0;
     }
-    *word = XCD_WORDS_FIRST + g->xcd_words_used;
-    g->xcd_words_used += count;
+    *word = XCD_WORDS_FIRST + g->xcd_words_used++;
+    return hipSuccess;
+}
+
+// The first of the field words (step_layout.h) of the next matrix-core launch with its stream groups on one XCD each, or -1.  They are zero:
+// cleared with what is filled for this launch, or at the start of the call for all of its launches.  (In every call, so also in every replay of
+// a captured one.)
+hipError_t xcd_field_word(rnn_graph* g, hipStream_t s, int count, int* word) {
+    *word = -1;
+    if (!g_xcd_local || !g->xcd || !g->xcd->ok) return hipSuccess;
+    if (!g->prefilled) g->xcd_fields_used = 0;
+    if (g->xcd_fields_used + count > XCD_FIELD_WORDS) {
+        hipError_t e = launch_fill(reinterpret_cast<float*>(g->ctrl_ptr() + XCD_FIELD_WORDS_FIRST), XCD_FIELD_WORDS, 0.0f, s);
+        if (e != hipSuccess) return e;
+        g->xcd_fields_used = 0;
+    }
+    *word = XCD_FIELD_WORDS_FIRST + g->xcd_fields_used;
+    g->xcd_fields_used += count;
     return hipSuccess;
 }
 
@@ -856,7 +873,8 @@ void add_range(const rnn_graph* g, FillRanges& fr, int b, int t0, int t1) {
     fr.p[fr.count] = g->buf(b) + t0 * frame; fr.n[fr.count] = (t1 - t0) * frame;
     ++fr.count;
 }
-hipError_t fill_shared(rnn_graph* g, const std::vector<int>& bufs, bool with_bundles, int t0, int t1, hipStream_t s, bool twins = false) {
+// fields: the launch's field words (xcd_field_word) are cleared along.
+hipError_t fill_shared(rnn_graph* g, const std::vector<int>& bufs, bool with_bundles, int t0, int t1, hipStream_t s, bool twins = false, bool fields = false) {
     if (g->prefilled) return hipSuccess;
     FillRanges fr; fr.count = 0;
     for (int b : shared_tensors(g, bufs, with_bundles, twins)) {
@@ -867,7 +885,8 @@ hipError_t fill_shared(rnn_graph* g, const std::vector<int>& bufs, bool with_bun
             fr.count = 0;
         }
     }
-    return launch_fill_sentinel_ranges(fr, s);
+    return fields ? launch_fill_sentinel_and_clear(fr, nullptr, nullptr, 0, 0, nullptr, 0, g->ctrl_ptr() + XCD_FIELD_WORDS_FIRST, XCD_FIELD_WORDS, s)
+                  : launch_fill_sentinel_ranges(fr, s);
 }
 
 // The workgroups of a persistent step launch wait for each other's results, so every one that takes
@@ -922,7 +941,7 @@ StepRun run_phases(rnn_graph* g, int comp, bool backward, hipStream_t s, int t0,
     const bool have_interp = !g->framewise && plan_step_launch(g->plan.words.data(), desc_off, N, g->force_step_G, lp);
     const int spin_limit = g->spin_limit;
     if (have_jit) {
-        hipError_t fe = fill_shared(g, backward ? cp.bwd_shared_bufs : cp.fwd_shared_bufs, jc->wave, t0, t1, s, jc->blocked);
+        hipError_t fe = fill_shared(g, backward ? cp.bwd_shared_bufs : cp.fwd_shared_bufs, jc->wave, t0, t1, s, jc->blocked, jc->local);
         if (fe != hipSuccess) return step_error(fe, "sentinel fill");
         // (matrix-core build: measured per direction; backward loops, with more stores and loads per
         // step, gain 3 %, forward loops lose 4 to 6 %)
@@ -965,7 +984,7 @@ StepRun run_phases(rnn_graph* g, int comp, bool backward, hipStream_t s, int t0,
             }
         }
         if (jc->local || (jc->wave && jc->lp.xcd_stride == 8)) {
-            hipError_t we = xcd_word(g, s, &a.xcd_word, (jc->J + 3) / 4);
+            hipError_t we = jc->local ? xcd_field_word(g, s, xcd_field_words(jc->lp.G, jc->J), &a.xcd_word) : xcd_word(g, s, &a.xcd_word);
             if (we != hipSuccess) return step_error(we, "XCD words");
         }
         StepLaunchPlan lp_all = jc->lp;
@@ -1341,11 +1360,12 @@ int rnn_forward_range(rnn_graph* g, const float* d_weights, const float* const* 
         FillRanges fr;
         const bool few = all_shared(g, false, H, H + t_end, fr);
         if (few) e = launch_fill_sentinel_and_clear(fr, g->view().buf_ptr, reinterpret_cast<const int64_t*>(g->ws + L.frames_off), H > 0 ? P.n_bufs : 0, H,
-                                                    reinterpret_cast<unsigned*>(g->ws + L.sync_off), (int)(SYNC_BYTES / 4), s);
+                                                    reinterpret_cast<unsigned*>(g->ws + L.sync_off), (int)(SYNC_BYTES / 4), nullptr, 0, s);
         else e = launch_zero_history(g->view().buf_ptr, reinterpret_cast<const int64_t*>(g->ws + L.frames_off), P.n_bufs, H,
                                 reinterpret_cast<unsigned*>(g->ws + L.sync_off), (int)(SYNC_BYTES / 4), s);
         if (e != hipSuccess) return fail_hip(e, "window reset");
         g->prefilled = few;
+        g->xcd_fields_used = 0;
     }
     // one-hot inputs with delayed connections: their class indices likewise (-1, the zero vector, in a fresh window's history)
     for (size_t i = 0; i < P.input_nodes.size(); ++i) {
@@ -1524,10 +1544,12 @@ int rnn_bptt(rnn_graph* g, const float* d_weights, const void* const* d_targets,
     FillRanges fr;
     g->prefilled = false;
     const bool few = all_shared(g, true, H, H + T, fr);
-    hipError_t e = few ? launch_fill_sentinel_and_clear(fr, nullptr, nullptr, 0, 0, reinterpret_cast<unsigned*>(g->loss_ptr()), 2, s)
+    hipError_t e = few ? launch_fill_sentinel_and_clear(fr, nullptr, nullptr, 0, 0, reinterpret_cast<unsigned*>(g->loss_ptr()), 2,
+                                                        g->ctrl_ptr() + XCD_FIELD_WORDS_FIRST, XCD_FIELD_WORDS, s)
                        : launch_fill(reinterpret_cast<float*>(g->loss_ptr()), 2, 0.0f, s);
     if (e != hipSuccess) return fail_hip(e, "loss reset");
     g->prefilled = few;
+    g->xcd_fields_used = 0;
     // the output deltas of all frames first (they depend on the forward pass only)
     for (const CompPlan& cp : P.comps) {
         const int k = cp.softmax_node >= 0 ? cp.softmax_node : cp.sqerr_node;

@@ -680,7 +680,9 @@ bool emit_mstep_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, 
     int hold = local || cp.helper ? 0 : n_late == 1 ? std::min(10, (int)(5.5 + 1.9 * polled_mib)) : std::min(12, (int)(3 + 1.9 * polled_mib));
     if (const char* env = std::getenv("RNNG_MSTEP_HOLD")) hold = std::max(0, std::min(127, std::atoi(env)));
     o << "    static constexpr int HOLD = " << hold << ";\n";
-    o << "    static constexpr int LG = " << (local ? G : 0) << ";\n";
+    // RNNG_MSTEP_LOCAL = 2: such a launch, its groups dealt over the XCDs all the same (which its workgroups have to find out)
+    const char* deal = std::getenv("RNNG_MSTEP_LOCAL");
+    o << "    static constexpr int LG = " << (local ? G : 0) << ";\n    static constexpr bool LDEAL = " << (deal && std::atoi(deal) == 2 ? "true" : "false") << ";\n";
     o << "    static constexpr unsigned REGMASK = " << reg_mask << "u;\n    static constexpr int NRW = " << widx.size() << ", CLATE = " << clate << ";\n";
     o << "    static __device__ __forceinline__ constexpr int blk(int s, int task) { return blk_(s * " << STEP_MAX_TASKS << " + task); }\n";
     o << "    static __device__ __forceinline__ constexpr bool used(int s, int nt) { return used_(s * 16 + nt) != 0; }\n};\n";
@@ -754,7 +756,7 @@ std::string jit_mstep_source(const Plan& P, const CompPlan& cp, bool backward, i
          "    extern __shared__ __attribute__((aligned(16))) float lds[];\n"
          "    __shared__ MShared ms;\n"
          "    int w = blockIdx.x;\n"
-      << (local ? "    w = mstep_local_unit<grp0::MM::LG>() * grp0::MM::LG + mstep_local_part<grp0::MM::LG>();\n"
+      << (local ? "    w = mstep_local_unit<grp0::MM::LG, grp0::MM::LDEAL>() * grp0::MM::LG + mstep_local_part<grp0::MM::LG, grp0::MM::LDEAL>();\n"
                 : "    if (a.xcd_stride > 1) {\n"
                   "        if (w % a.xcd_stride) return;\n"
                   "        w /= a.xcd_stride;\n"

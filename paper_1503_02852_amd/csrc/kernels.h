@@ -136,8 +136,8 @@ constexpr int FILL_MAX_RANGES = 16;
 // pollers neither wait for it nor add anything.
 struct FillRanges { float* p[FILL_MAX_RANGES]; long long n[FILL_MAX_RANGES]; int twin_n[FILL_MAX_RANGES], twin_dim[FILL_MAX_RANGES], count; };
 hipError_t launch_fill_sentinel_ranges(const FillRanges& r, hipStream_t stream);
-// The same and launch_zero_history's work (n_bufs 0: the words alone) in one launch.
+// The same and launch_zero_history's work (n_bufs 0: the words alone) in one launch; fields, n_fields: more words to clear.
 hipError_t launch_fill_sentinel_and_clear(const FillRanges& r, float* const* buf_ptr, const int64_t* frame_floats, int n_bufs, int frames, unsigned* words, int n_words,
-                                          hipStream_t stream);
+                                          unsigned* fields, int n_fields, hipStream_t stream);
 
 }  // namespace rnng

@@ -117,10 +117,15 @@ __global__ __launch_bounds__(256) void fill_ranges_kernel(const FillRanges r, un
 // The same, and behind the ranges what a call clears: the control words, the history frames of the buffers (a launch of its own for each cost
 // 3 us: 8 % of the smallest window's training call).
 __global__ __launch_bounds__(256) void fill_ranges_and_clear_kernel(const FillRanges r, unsigned v, float* const* __restrict__ buf_ptr, const int64_t* __restrict__ frame_floats,
-                                                                    int n_bufs, int frames, unsigned* __restrict__ words, int n_words) {
+                                                                    int n_bufs, int frames, unsigned* __restrict__ words, int n_words, unsigned* __restrict__ fields,
+                                                                    int n_fields) {
     if ((int)blockIdx.y < r.count) { fill_range(r, blockIdx.y, v); return; }
     for (int b = blockIdx.x; b <= n_bufs; b += gridDim.x) {
-        if (b == n_bufs) { for (int i = threadIdx.x; i < n_words; i += 256) words[i] = 0u; continue; }
+        if (b == n_bufs) {
+            for (int i = threadIdx.x; i < n_words; i += 256) words[i] = 0u;
+            for (int i = threadIdx.x; i < n_fields; i += 256) fields[i] = 0u;
+            continue;
+        }
         const long long n = (long long)frames * frame_floats[b];
         if (n <= 0) continue;
         float* p = buf_ptr[b];
@@ -232,12 +237,12 @@ hipError_t launch_fill_sentinel_ranges(const FillRanges& r, hipStream_t stream) 
 }
 
 hipError_t launch_fill_sentinel_and_clear(const FillRanges& r, float* const* buf_ptr, const int64_t* frame_floats, int n_bufs, int frames, unsigned* words, int n_words,
-                                          hipStream_t stream) {
+                                          unsigned* fields, int n_fields, hipStream_t stream) {
     if (r.count > FILL_MAX_RANGES) return hipErrorInvalidValue;
     long long blocks = n_bufs + 1;
     for (int i = 0; i < r.count; ++i) blocks = std::max(blocks, std::min<long long>((r.n[i] + 255) / 256, 1024));
     hipLaunchKernelGGL(fill_ranges_and_clear_kernel, dim3((unsigned)blocks, (unsigned)r.count + 1), dim3(256), 0, stream, r, STEP_SENTINEL, buf_ptr, frame_floats, n_bufs, frames, words,
-                       n_words);
+                       n_words, fields, n_fields);
     return hipGetLastError();
 }
 

@@ -1474,10 +1474,14 @@ struct MShared { StepLayout lay; unsigned retried[2]; };
 
 // Launches whose stream groups each sit on one XCD: units (stream groups of the members, one member after the other) of LG
 // workgroups; workgroups b, b + 8, ... of a launch share an XCD, so unit u takes the workgroups of residue u % 8.
-template <int LG>
-__device__ __forceinline__ int mstep_local_unit() { return (int)(blockIdx.x & 7) + 8 * ((int)(blockIdx.x >> 3) / (LG > 0 ? LG : 1)); }
-template <int LG>
-__device__ __forceinline__ int mstep_local_part() { return (int)(blockIdx.x >> 3) % (LG > 0 ? LG : 1); }
+// LDEAL: a unit's workgroups follow each other instead, dealt over the XCDs (tests).
+template <int LG, bool LDEAL>
+__device__ __forceinline__ int mstep_local_unit() {
+    constexpr int G = LG > 0 ? LG : 1;
+    return LDEAL ? (int)blockIdx.x / G : (int)(blockIdx.x & 7) + 8 * ((int)(blockIdx.x >> 3) / G);
+}
+template <int LG, bool LDEAL>
+__device__ __forceinline__ int mstep_local_part() { return (int)(LDEAL ? blockIdx.x : blockIdx.x >> 3) % (LG > 0 ? LG : 1); }
 
 template <class PH, class MM>
 // w: index of this workgroup among the a.G * a.J workgroups of the component.
@@ -1494,12 +1498,16 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
     // of the others do)
     constexpr int NW = MM::NW, NTHR = 64 * (NW + MM::NE), CW = 16 * NW;
     const int itid = MM::NE == 0 ? tid : tid >= 64 * NW ? tid - 64 * NW : STEP_THREADS;      // the element-wise item of this thread
-    // MM::LG: the workgroups of a stream group sit on one XCD (their launch puts them there; each leaves its XCD's id, and the host
-    // reports a group on several), so twins are stored plainly; without the words everything is written through
-    const bool local = MM::LG > 0 && suni(a.xcd_word) >= 0;
-    if (local && tid == 0) {
-        const int u = mstep_local_unit<MM::LG>();
-        atomicOr(a.ctrl + suni(a.xcd_word) + (u >> 2), 1u << (8 * (u & 3) + (step_xcc_id() & 7)));
+    // MM::LG: the workgroups of a stream group sit on one XCD where they are dealt to the XCDs in turn, and twins are then stored plainly.
+    // Each leaves its XCD's id in the group's field and is counted behind it (one word, so in this order); once all are, all know
+    // whether they share an XCD.  If not, or without the fields, everything is written through.
+    constexpr int FIELDS = xcd_fields(MM::LG);
+    const bool fields = MM::LG > 0 && suni(a.xcd_word) >= 0;
+    const int lunit = mstep_local_unit<MM::LG, MM::LDEAL>(), lshift = lunit % FIELDS * (32 / FIELDS);
+    unsigned* const field = a.ctrl + (fields ? suni(a.xcd_word) + lunit / FIELDS : 0);
+    if (fields && tid == 0) {
+        __hip_atomic_fetch_or(field, 1u << (lshift + (step_xcc_id() & 7)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(field, 1u << (lshift + 8), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     load_step_layout(a, 1, MM::NJ, sh.lay, tid, NTHR);
     for (int i = 4 * tid; i < MM::LDSF; i += 4 * NTHR) *reinterpret_cast<mfloatx4*>(&lds[i]) = mfloatx4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -1567,6 +1575,20 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
     phase_setup_item<PH, 1, 2>(r, a, sh, lds, w, itid, item_il, itid < STEP_THREADS && item_n < N ? n0 + item_n : -1);      // (r.n: global stream index)
     __syncthreads();
 
+    const bool wave_items = __builtin_amdgcn_ballot_w64(r.n >= 0) != 0;      // wavefronts without items skip the element-wise part
+    // Does the stream group share an XCD?  Asked by the wavefronts that store, the others go on; the rest of the group has normally arrived
+    // while the weights were read.  (Asked in front of the set-up that follows: behind it, what has to stay in scalar registers was spilled in the
+    // time loop, 272 / 292 us of 256 steps of 64 LSTM units, 64 streams.  As it is 273, 20 steps 0.6 us more than without asking.)
+    unsigned seen = 0;
+    if (fields && wave_items) {
+        for (int spins = 0;;) {
+            seen = (unsigned)suni((int)(__hip_atomic_load(field, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> lshift));
+            if ((int)((seen >> 8) & ((1u << (32 / FIELDS - 8)) - 1)) >= MM::LG) break;
+            if (++spins > a.spin_limit) { seen = 0; if (lane == 0) atomicExch(a.ctrl, 1u); break; }
+        }
+    }
+    const unsigned ids = (unsigned)suni((int)seen) & 0xFF;
+    const bool local = ids != 0 && (ids & (ids - 1)) == 0;
     constexpr int D = MM::D, NPAD = MM::MT * 16, ACCS = MM::ACCS;
     constexpr int accbase = MM::ACCBASE;
     // LDS address of the weight row behind each of this lane's tile columns, per source
@@ -1700,7 +1722,6 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
             }
         }
     }
-    const bool wave_items = __builtin_amdgcn_ballot_w64(r.n >= 0) != 0;      // wavefronts without items skip the element-wise part
     const int item_n_safe = r.n >= 0 ? item_n : 0;
     // value of gather g (STATIC or FRAMES kind) at `frame`; zero outside the window or for an idle
     // lane (a buffer load outside the descriptor's range)

@@ -73,6 +73,13 @@ constexpr int STEP_MAX_GROUPS = 4;
 
 // Control words behind ctrl that hold the XCDs of one launch each (behind those of the step trace).
 constexpr int XCD_WORDS_FIRST = 192, XCD_WORDS = 60;
+// Matrix-core launches whose stream groups each sit on one XCD: control words in which the groups' workgroups find out whether they do, in front
+// of those.  A field of 32 / xcd_fields(G) bits a group of G <= 32 workgroups: which XCDs (8 bits), how many workgroups have said so.
+constexpr int XCD_FIELD_WORDS_FIRST = 144, XCD_FIELD_WORDS = 48, MSTEP_LOCAL_MAX_UNITS = 120;
+RNNG_HD constexpr int xcd_fields(int G) { return G <= 3 ? 3 : 2; }
+RNNG_HD constexpr int xcd_field_words(int G, int units) { return (units + xcd_fields(G) - 1) / xcd_fields(G); }
+static_assert(XCD_FIELD_WORDS_FIRST + XCD_FIELD_WORDS <= XCD_WORDS_FIRST, "control words");
+static_assert(xcd_field_words(3, MSTEP_LOCAL_MAX_UNITS) <= XCD_FIELD_WORDS && xcd_field_words(4, 8 * (32 / 4)) <= XCD_FIELD_WORDS, "a launch's fields");
 RNNG_HD inline bool xcd_word_split(unsigned w) {      // has a group been on more than one XCD?
     bool split = false;
     for (int g = 0; g < STEP_MAX_GROUPS; ++g) { const unsigned b = (w >> (8 * g)) & 0xFF; split = split || (b & (b - 1)) != 0; }
@@ -101,6 +108,8 @@ struct StepArgs {
     // Matrix-core build: the streams are split into J groups of N / J; workgroup w owns unit chunk
     // w % G of stream group w / G (G * J workgroups in all).  1 elsewhere.
     int J;
+    // Matrix-core build with its stream groups on one XCD each: the first of the launch's field words (zero before it), or -1: everything is
+    // written through.
     // Wave-autonomous builds: word (behind ctrl) in which this launch's workgroups leave the XCDs they run
     // on, bit 8 g + id for group g, or -1.  With a word, tensors exchanged inside a group are written
     // with plain stores (the XCD's L2 holds them, and the group's polling loads are served there), and

@@ -47,6 +47,45 @@ def test_exchange_inside_and_across_xcds(monkeypatch, net, hidden, N, env):
     assert rec and all(win.g.step_build(k, b)[0] == "matrix" for k in rec for b in (False, True))
 
 
+@pytest.mark.parametrize("net,hidden,N", [("lstm", 3, 9), ("lstm", 18, 33), ("lstm", 250, 20), ("elman", 512, 16), ("elman", 41, 140), ("elman", 17, 500)])
+def test_stream_groups_found_on_several_xcds(monkeypatch, net, hidden, N):
+    """A launch that exchanges inside an XCD finds out that its groups do not share one, and writes through: the same bits, and no error."""
+    spec = wl.elman_net(7, hidden, 5) if net == "elman" else wl.lstm_net(7, [hidden], 5)
+    w = wl.make_workload("dealt", spec, T=21, N=N, seed=79, scale=0.4 / hidden ** 0.5, bias_scale=0.2, masked_fraction=0.2)
+    wins = []
+    for local in ("1", "2"):
+        monkeypatch.setenv("RNNG_MSTEP_LOCAL", local)
+        wins.append(run_both(w, label=f"{net} {hidden}, N={N}, RNNG_MSTEP_LOCAL={local}")[0])
+    rec = [k for k in range(len(spec.nodes)) if wins[0].g.step_build(k)[0] != "none"]
+    for k in rec:
+        assert all(win.g.step_build(k, b)[0] == "matrix" for win in wins for b in (False, True))
+        assert np.array_equal(wins[0].node_output(k), wins[1].node_output(k)) and np.array_equal(wins[0].node_state_grad(k), wins[1].node_state_grad(k))
+
+
+@pytest.mark.parametrize("local", ["1", "2"])
+@pytest.mark.parametrize("N", [20, 500])
+def test_replayed_launches_find_out_about_their_xcds_anew(monkeypatch, local, N):
+    """Captured backward passes, replayed: what the workgroups of a launch tell each other is cleared in every replay."""
+    import torch
+    monkeypatch.setenv("RNNG_MSTEP_LOCAL", local)
+    spec = wl.lstm_net(7, [18], 5)
+    w = wl.make_workload("replayed", spec, T=9, N=N, seed=80, scale=0.1, bias_scale=0.2, masked_fraction=0.2)
+    win, _ = run_both(w, label=f"replayed, N={N}, RNNG_MSTEP_LOCAL={local}")
+    rec = [k for k in range(len(spec.nodes)) if win.g.step_build(k)[0] != "none"]
+    first = [win.node_state_grad(k) for k in rec]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        win.bptt()
+    for _ in range(4):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(np.array_equal(a, win.node_state_grad(k)) for a, k in zip(first, rec))
+        win.check()
+        win.forward()
+        win.bptt()
+
+
 @pytest.mark.parametrize("env", [{}, {"RNNG_MSTEP_LOCAL": "0"}])
 @pytest.mark.parametrize("layers,N", [([1], 9), ([3], 16), ([8], 64), ([17], 40), ([5, 9], 12)])
 def test_small_layers_set_up_their_element_wise_wavefronts(monkeypatch, layers, N, env):
