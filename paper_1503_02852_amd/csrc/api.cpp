@@ -155,7 +155,7 @@ struct rnn_graph {
     int Ti() const { return T + plan.hist; }
     char* ws = nullptr;
     Layout layout;
-    std::vector<char> blob, blob_next;    // host copy of the plan tables (kept alive for the async upload), the next call's while they are compared
+    std::vector<char> blob;               // host copy of the plan tables (kept alive for the async upload)
     bool tables_there = false;            // blob is what the current window's workspace holds
     std::vector<const float*> inputs;     // per exec node id (input nodes only)
     const XcdMap* xcd = nullptr;          // set by the first forward call on this device
@@ -1321,29 +1321,32 @@ int rnn_forward_range(rnn_graph* g, const float* d_weights, const float* const* 
     const bool sizes_ok = wave_tensor_sizes_ok(g);
     if (g->lay.N != N || g->lay.sizes_ok != sizes_ok) g->lay = g->step_layouts(N, sizes_ok);
     const int64_t blob_bytes = L.lay_off + (int64_t)g->lay.words.size() * 4;
-    std::vector<char>& blob = g->blob_next;
-    blob.assign(blob_bytes, 0);
-    if (!g->lay.words.empty()) std::memcpy(&blob[L.lay_off], g->lay.words.data(), g->lay.words.size() * 4);
+    // A later piece of a window finds the tables where its first one put them, as it finds that one's frames, unless an address has changed
+    // (one new frame of 2 x 512 LSTM units: 52.8 us with the upload, 41.3 without).
+    std::vector<char>& blob = g->blob;
+    bool there = t_begin > 0 && g->tables_there && (int64_t)blob.size() == blob_bytes;
+    if ((int64_t)blob.size() != blob_bytes) blob.assign(blob_bytes, 0);
+    auto put = [&](int64_t off, const void* p, size_t bytes) {
+        if (bytes == 0 || (there && std::memcmp(&blob[off], p, bytes) == 0)) return;
+        there = false;
+        std::memcpy(&blob[off], p, bytes);
+    };
+    put(L.lay_off, g->lay.words.data(), g->lay.words.size() * 4);
     for (int b = 0; b < P.n_bufs; ++b) {
         float* p = g->buf(b);
-        std::memcpy(&blob[L.table_off + 8 * (int64_t)b], &p, 8);
+        put(L.table_off + 8 * (int64_t)b, &p, 8);
     }
-    std::memcpy(&blob[L.dims_off], P.buf_dim.data(), (size_t)P.n_bufs * 4);
+    put(L.dims_off, P.buf_dim.data(), (size_t)P.n_bufs * 4);
     for (int b = 0; b < P.n_bufs; ++b) {
         const int64_t frame = ((P.buf_alloc[b] == 1 || P.buf_alloc[b] == 3) && L.buf_off[b] >= 0) ? P.frame_floats(b, N) : 0;
-        std::memcpy(&blob[L.frames_off + 8 * (int64_t)b], &frame, 8);
+        put(L.frames_off + 8 * (int64_t)b, &frame, 8);
     }
-    if (!P.words.empty()) std::memcpy(&blob[L.words_off], P.words.data(), P.words.size() * 4);
-    // A later piece of a window finds the tables where its first one put them, as it finds that one's frames, unless an address has changed
-    // (one new frame of 2 x 512 LSTM units: 52.8 us with the upload, 42.6 without).
+    put(L.words_off, P.words.data(), P.words.size() * 4);
     hipError_t e = hipSuccess;
-    if (t_begin == 0 || !g->tables_there || blob != g->blob) {
-        g->tables_there = false;
-        g->blob.swap(blob);
-        blob.resize(blob_bytes);      // (the next call's, here and not in a window's first later piece)
+    if (!there) {
         // (without allocations: as kernel arguments, which need no staging buffer of the runtime's)
-        e = g->no_alloc ? launch_upload_words(reinterpret_cast<uint32_t*>(g->ws), reinterpret_cast<const uint32_t*>(g->blob.data()), blob_bytes / 4, s)
-                        : hipMemcpyAsync(g->ws, g->blob.data(), (size_t)blob_bytes, hipMemcpyHostToDevice, s);
+        e = g->no_alloc ? launch_upload_words(reinterpret_cast<uint32_t*>(g->ws), reinterpret_cast<const uint32_t*>(blob.data()), blob_bytes / 4, s)
+                        : hipMemcpyAsync(g->ws, blob.data(), (size_t)blob_bytes, hipMemcpyHostToDevice, s);
         g->tables_there = e == hipSuccess;
     }
     if (e != hipSuccess) return fail_hip(e, "plan table upload");

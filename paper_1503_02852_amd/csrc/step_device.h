@@ -1502,7 +1502,7 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
     // Each leaves its XCD's id in the group's field and is counted behind it (one word, so in this order); once all are, all know
     // whether they share an XCD.  If not, or without the fields, everything is written through.
     constexpr int FIELDS = xcd_fields(MM::LG);
-    const bool fields = MM::LG > 0 && suni(a.xcd_word) >= 0;
+    const bool fields = MM::LG > 1 && suni(a.xcd_word) >= 0;      // (one workgroup shares an XCD with itself)
     const int lunit = mstep_local_unit<MM::LG, MM::LDEAL>(), lshift = lunit % FIELDS * (32 / FIELDS);
     unsigned* const field = a.ctrl + (fields ? suni(a.xcd_word) + lunit / FIELDS : 0);
     if (fields && tid == 0) {
@@ -1588,7 +1588,7 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
         }
     }
     const unsigned ids = (unsigned)suni((int)seen) & 0xFF;
-    const bool local = ids != 0 && (ids & (ids - 1)) == 0;
+    const bool local = MM::LG == 1 ? suni(a.xcd_word) >= 0 : ids != 0 && (ids & (ids - 1)) == 0;
     constexpr int D = MM::D, NPAD = MM::MT * 16, ACCS = MM::ACCS;
     constexpr int accbase = MM::ACCBASE;
     // LDS address of the weight row behind each of this lane's tile columns, per source
