@@ -1,0 +1,67 @@
+"""Which variant of a recurrent-step kernel a layer gets, read off the generated sources (the run-time compiler needs no GPU)."""
+import os
+import re
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+CHILD = """
+import os, sys
+import workloads as wl
+from paper_1503_02852_amd import Graph
+for i, shape in enumerate(sys.argv[2:]):
+    net, hidden, N = shape.split(":")
+    hidden = [int(h) for h in hidden.split(",")]
+    os.environ["RNNG_JIT_DUMP"] = os.path.join(sys.argv[1], str(i))
+    os.mkdir(os.environ["RNNG_JIT_DUMP"])
+    spec = wl.elman_net(7, hidden[0], 5) if net == "elman" else wl.lstm_net(7, hidden, 5, output_recurrence=net != "element_wise")
+    Graph(spec.node_array(), spec.edge_array()).specialise(int(N))
+"""
+
+
+def sources(tmp_path, shapes, **env):
+    """Per shape the sources of its forward and its backward launch (one of them, if they are the same)."""
+    clean = {k: v for k, v in os.environ.items() if not k.startswith("RNNG_")}
+    subprocess.run([sys.executable, "-c", CHILD, str(tmp_path)] + shapes, check=True, cwd=ROOT, env={**clean, **env})
+    got = []
+    for i in range(len(shapes)):
+        d = tmp_path / str(i)
+        got.append([(d / f).read_text() for f in sorted(os.listdir(d), key=lambda f: int(re.findall(r"_(\d+)\.hip", f)[0]))])
+        assert 1 <= len(got[-1]) <= 2, shapes[i]
+    return got
+
+
+def constant(source, name):
+    (value,) = set(re.findall(rf"\b{name} = (\w+)", source))
+    return int(value.rstrip("ul"))
+
+
+@pytest.mark.parametrize("local,ew", [("1", "1"), ("1", "0"), ("0", "1")])
+def test_exchange_inside_one_xcd_and_wavefronts_for_the_element_wise_program(tmp_path, local, ew):
+    shapes = ["lstm:18:33", "lstm:250:20"] if ew == "1" else ["lstm:3:9", "elman:41:140"]
+    for shape, both in zip(shapes, sources(tmp_path, shapes, RNNG_MSTEP_LOCAL=local, RNNG_MSTEP_EW=ew)):
+        for source in both:
+            assert "mstep_kernel_body<grp0" in source, shape
+            assert (constant(source, "LG") > 0) == (local == "1"), shape
+            assert (constant(source, "NE") > 0) == (ew == "1"), shape
+            assert (constant(source, "HOLD") > 0) == (local == "0"), shape
+
+
+def test_resident_chunks_of_streamed_weights(tmp_path):
+    """Of 17 chunks, the last one 4 columns wide, 7 in registers (that one among them) and 4 in LDS; of two chunks one each."""
+    shapes = ["elman:2052:9", "elman:132:16"]
+    expected = {"elman:2052:9": (7, 4), "elman:132:16": (1, 1)}
+    for shape, both in zip(shapes, sources(tmp_path, shapes, RNNG_STEP_BUILD="stream", RNNG_SMSTEP_RESIDENT="1")):
+        for source in both:
+            assert "smstep_kernel_body" in source and (constant(source, "PR"), constant(source, "LRES")) == expected[shape], shape
+
+
+def test_element_wise_recurrences_have_a_kernel_of_their_own(tmp_path):
+    """A thread per stream and unit: forward at any number of streams, backward from five on (below, on the lanes of the register build)."""
+    shapes = ["element_wise:9:4", "element_wise:11:5", "element_wise:13:8", "element_wise:20:9"]
+    for shape, (forward, backward) in zip(shapes, sources(tmp_path, shapes)):
+        assert "estep_kernel_body" in forward, shape
+        assert ("estep_kernel_body" in backward) == (int(shape.split(":")[2]) >= 5), shape
