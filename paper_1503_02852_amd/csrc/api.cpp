@@ -258,6 +258,7 @@ struct rnn_graph {
         }
         if (N >= 5 || local_env >= 1) try_local();
         try_wave(force_step_G > 0 ? force_step_G : 32);
+        if (N >= 4) try_local();
         if (force_step_G <= 0 && register_over_xcds(cp, backward, N)) try_wave(64);
         try_local();
         // 2. matrix-core variants for many streams (weights in LDS or registers, MFMA)
@@ -503,8 +504,8 @@ struct rnn_graph {
     // (LSTM forward 384 units, N = 8 2.24 / 1.97, N = 16 2.31 / 2.41), never with four (512 units, N = 16 3.30 / 1.89).
     // Up to 8 streams against the weights-in-registers build on one XCD: one source from N = 5 on (LSTM forward 16 / 100 units, N = 5
     // 1.00 / 1.03 against 1.11 / 1.41, N = 4 1.00 / 1.05 against 0.89 / 0.98); several from 400 columns on (LSTM backward, N = 8, 48 / 100 / 128 units 1.64 / 1.66 / 1.76
-    // against 1.18 / 1.77 / 1.92).  N = 2 to 4: after that build,
-    // also where it takes two XCDs.
+    // against 1.18 / 1.77 / 1.92).  N = 2 to 4: after that build on one XCD; at N = 4 before it on two (LSTM backward, 288 / 384 / 512 units
+    // 2.5 / 2.5 / 3.0 against 3.5 / 3.7 / 3.5).
     bool local_streams(const CompPlan& cp, bool backward, int N, int several_from = 400, int one_from = 0) const {
         if (local_env == 0 || N < 2 || !matrix_streams(cp, backward, N)) return false;
         if (N > 8 || local_env >= 1) return true;
