@@ -128,6 +128,30 @@ def test_element_wise_recurrences_at_many_streams(layers, N, T):
     assert all(np.array_equal(pieces.node_output(k), win.node_output(k)) for k in rec)
 
 
+@pytest.mark.parametrize("window", ["1", "0"])
+@pytest.mark.parametrize("layers,N", [([20], 1), ([65], 4), ([20], 5), ([70, 33], 8), ([33], 12)])
+def test_element_wise_recurrences_in_every_form(monkeypatch, layers, N, window):
+    """At few streams (backward below five on the lanes of the register build), tensors in one window or stored one by one, windows moved ahead."""
+    monkeypatch.setenv("RNNG_STORE_WINDOW", window)
+    spec = wl.lstm_net(8, layers, 4, output_recurrence=False)
+    run_both(wl.make_workload("element_wise", spec, T=19, N=N, seed=81, scale=0.3, bias_scale=0.2, masked_fraction=0.2), label=f"element-wise {layers}, N={N}, RNNG_STORE_WINDOW={window}")
+    monkeypatch.setitem(tw.WINDOW_NETS, "element_wise", lambda: (spec, N))
+    tw.test_window_computed_in_pieces_equals_the_window_at_once("element_wise")
+    tw.test_window_moved_ahead_with_carried_state("element_wise")
+
+
+@pytest.mark.parametrize("env", [{"RNNG_MSTEP_EW": "0"}, {"RNNG_MSTEP_HOLD": "0"}, {"RNNG_MSTEP_HOLD": "20"}, {"RNNG_MSTEP_EW": "0", "RNNG_MSTEP_HOLD": "20"}])
+@pytest.mark.parametrize("layers,N", [([128, 128], 16), ([40, 56], 35)])
+def test_stacks_with_helper_members_without_wavefronts_of_their_own_or_held_back(monkeypatch, layers, N, env):
+    for k, v in {**env, "RNNG_CHAIN_HELPERS": "1"}.items():
+        monkeypatch.setenv(k, v)
+    spec = wl.lstm_net(12, layers, 5)
+    win, _ = run_both(wl.make_workload("stack", spec, T=17, N=N, seed=82, scale=0.4 / max(layers) ** 0.5, bias_scale=0.2, masked_fraction=0.2), label=f"stack {layers}, N={N}, {env}")
+    rec = [k for k in range(len(spec.nodes)) if win.g.step_build(k)[0] != "none"]
+    assert rec and all(win.g.step_build(k, b) == ("matrix", True) for k in rec for b in (False, True))
+    assert all(win.g.step_build_has_helpers(k, True) for k in rec)
+
+
 def saturated_tanh_net(dim):
     g = wl.GraphSpec()
     x = g.add_node(wl.INPUT, wl.LINEAR, dim, name="x")
