@@ -1033,13 +1033,15 @@ std::string jit_smstep_source(const Plan& P, const CompPlan& cp, bool backward, 
     size_t lds = (size_t)NW * MT * 16 * ACCS * 4;
     if (lds > STEP_LDS_LIMIT) return "";
     // Resident chunks (see the kernel): PR per source in registers, LRES per source in LDS, from the weights on that leave the
-    // memory-side cache something to gain (RNNG_SMSTEP_RESIDENT = 0: never, 1: always).  us a step with / without, 16 streams: one source
-    // (LSTM forward) 151 MB 20.6 / 23.6, 268 MB 37.0 / 49.2, 400 MB 77.7 / 90.5, 64 streams 67 MB 25.5 / 25.1; four (backward) 151 MB 31.4 / 30.5,
-    // 268 MB 44.2 / 57.2, 400 MB 114 / 120, 64 streams 67 MB 49.6 / 47.7, 268 MB 98 / 107.
+    // memory-side cache something to gain (RNNG_SMSTEP_RESIDENT = 0: never, 1: always).  24 steps with / without, ms.  One source (LSTM
+    // forward, Elman), 16 streams: 105 MB 0.41 / 0.46, 174 MB 0.73 / 0.85, 268 MB 1.03 / 1.29, 419 MB 1.90 / 2.22; 20 and 32: 100 MB 0.67 / 0.65, 151 MB 0.69 /
+    // 0.73, 268 MB 1.25 / 1.44; 33 to 64: 205 MB 1.34 / 1.28, 236 MB 2.11 / 1.82, 252 MB 1.41 / 1.52, 268 MB 1.44 / 1.56, but 340 MB with five row tiles (spilled
+    // registers) 2.17 / 2.00.  Several (LSTM backward): 205 MB 1.02 / 0.98, 213 MB 1.04 / 1.06, 268 MB 1.15 / 1.45, 419 MB 2.86 / 3.01.
     int64_t weight_bytes = 0;
     for (int t = 0; t < NT; ++t) for (int e = 0; e < ph.task[t].n_edges; ++e) weight_bytes += (int64_t)ph.task[t].n_out * ph.task[t].e[e].k_len * 4;
-    bool keep = weight_bytes >= (lay.n_sources == 1 ? 100 : 200) * 1000000ll;
-    if (const char* env = std::getenv("RNNG_SMSTEP_RESIDENT")) keep = std::atoi(env) != 0;
+    const bool one = lay.n_sources == 1;
+    bool keep = weight_bytes >= (!one ? 210 : MT == 1 ? 100 : MT == 2 ? 140 : 240) * 1000000ll && !(one && MT >= 3 && NTU >= 5), keep_always = false;
+    if (const char* env = std::getenv("RNNG_SMSTEP_RESIDENT")) keep = keep_always = std::atoi(env) != 0;
     const int RES0 = (int)(lds / 4), chunk_bytes = NTU * 64 * NW * 16;
     int PR = keep && NW == 8 ? SMSTEP_KEPT_REGISTERS / (4 * (NTU * lay.n_sources + MT)) : 0, room = keep ? (int)((STEP_LDS_LIMIT - lds) / chunk_bytes) : 0;
     std::vector<int> walk(lay.n_sources);      // streamed columns
@@ -1061,15 +1063,21 @@ std::string jit_smstep_source(const Plan& P, const CompPlan& cp, bool backward, 
     }
     const bool middle = least == most && n_walk <= 64 && n_walk % 2 == 1 && room / lay.n_sources >= 2 * pairs + 1;
     if (middle) LMASK |= 1ull << n_walk / 2;
-    const int LRES = 2 * pairs + (middle ? 1 : 0);
-    lds += (size_t)LRES * lay.n_sources * chunk_bytes;
+    int LRES = 2 * pairs + (middle ? 1 : 0);
     // the depth that pads the walk's groups least
+    const int D_all = D;
     best_slots = 1 << 30;
     for (int d = dmax; d >= std::max(2, dmax - 2); --d) {
         int slots = 0;
         for (int sidx = 0; sidx < lay.n_sources; ++sidx) slots += ((walk[sidx] + CW - 1) / CW + d - 1) / d * d;
         if (slots < best_slots) { best_slots = slots; D = d; }
     }
+    // one chunk in flight instead of several costs more than residents give (Elman, 9,216 units, 33 streams 2.85 / 2.43 ms, LSTM forward 3,584 units, 20 streams 1.05 / 0.98)
+    if (PR > 0 && D == 2 && D_all > 2 && !keep_always) {
+        PR = LRES = 0; LMASK = 0; D = D_all;
+        for (int sidx = 0; sidx < lay.n_sources; ++sidx) walk[sidx] = lay.src[sidx].k_len;
+    }
+    lds += (size_t)LRES * lay.n_sources * chunk_bytes;
     // exchange through the tile-blocked twins: whole 16-stream tiles in the window and in every
     // pass of the element-wise part, every exchanged tensor with a twin
     bool xb = N % 16 == 0 && (IPT == 1 || SPP % 16 == 0) && P.twin_base >= 0 && !mstep_blocked_choices().empty() && mstep_blocked_choices()[0] != 0;

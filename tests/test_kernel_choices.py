@@ -71,3 +71,11 @@ def test_four_streams_backward_exchange_inside_one_xcd_before_registers_of_two(t
     """An LSTM layer whose weights take the registers of two XCDs: at four streams the matrix cores of one are ahead."""
     ((_, backward),) = sources(tmp_path, ["lstm:290:4"])
     assert "mstep_kernel_body<grp0" in backward and constant(backward, "LG") > 0
+
+
+def test_streamed_weights_keep_residents_only_where_they_pay(tmp_path):
+    """Forward / backward: 16 streams; the cache's size at 33; a walk left with one chunk in flight (20 streams); more weights than the cache and their residents hold (33)."""
+    shapes = {"lstm:3200:16": (True, False), "lstm:4096:33": (True, True), "lstm:3584:20": (False, False), "elman:9216:33": (False, False)}
+    for shape, both in zip(shapes, sources(tmp_path, list(shapes))):
+        assert all("smstep_kernel_body" in source for source in both), shape
+        assert tuple(constant(source, "PR") > 0 for source in (both[0], both[-1])) == shapes[shape], shape
