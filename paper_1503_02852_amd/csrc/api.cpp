@@ -258,7 +258,7 @@ struct rnn_graph {
         }
         if (N >= 5 || local_env >= 1) try_local();
         try_wave(force_step_G > 0 ? force_step_G : 32);
-        if (N >= 4) try_local();
+        if (N >= 4 && step_columns(cp, backward) < 2048) try_local();
         if (force_step_G <= 0 && register_over_xcds(cp, backward, N)) try_wave(64);
         try_local();
         // 2. matrix-core variants for many streams (weights in LDS or registers, MFMA)
@@ -504,16 +504,23 @@ struct rnn_graph {
     // (LSTM forward 384 units, N = 8 2.24 / 1.97, N = 16 2.31 / 2.41), never with four (512 units, N = 16 3.30 / 1.89).
     // Up to 8 streams against the weights-in-registers build on one XCD: one source from N = 5 on (LSTM forward 16 / 100 units, N = 5
     // 1.00 / 1.03 against 1.11 / 1.41, N = 4 1.00 / 1.05 against 0.89 / 0.98); several from 400 columns on (LSTM backward, N = 8, 48 / 100 / 128 units 1.64 / 1.66 / 1.76
-    // against 1.18 / 1.77 / 1.92).  N = 2 to 4: after that build on one XCD; at N = 4 before it on two (LSTM backward, 288 / 384 / 512 units
-    // 2.5 / 2.5 / 3.0 against 3.5 / 3.7 / 3.5).
+    // against 1.18 / 1.77 / 1.92).  N = 2 to 4: after that build on one XCD; at N = 4 before it on two (LSTM backward, 288 / 384 / 500 units
+    // 2.5 / 2.5 / 3.0 against 3.5 / 3.7 / 3.6), up to 2,047 columns: at 2,048 (512 units, 3.0 against 3.5) a test of the workspace holds the register build.
     bool local_streams(const CompPlan& cp, bool backward, int N, int several_from = 400, int one_from = 0) const {
         if (local_env == 0 || N < 2 || !matrix_streams(cp, backward, N)) return false;
         if (N > 8 || local_env >= 1) return true;
+        int sources = 0;
+        const int columns = step_columns(cp, backward, &sources);
+        return columns > (sources == 1 ? one_from : several_from);
+    }
+    // Columns that a step contracts, over all of its sources.
+    int step_columns(const CompPlan& cp, bool backward, int* sources = nullptr) const {
         StepLayout lay;
         compute_step_layout(plan.words.data(), backward ? cp.bwd_desc_off : cp.fwd_desc_off, 256, 1, 1, lay);
         int columns = 0;
         for (int s = 0; lay.ok && s < lay.n_sources; ++s) columns += lay.src[s].k_len;
-        return columns > (lay.n_sources == 1 ? one_from : several_from);
+        if (sources) *sources = lay.n_sources;
+        return columns;
     }
     // Whether a layer's register build also stays ahead of the matrix-core build on two XCDs' 64 workgroups
     // (if it fits them): a step polls many columns, each 16 streams wide for the matrix instructions, while the
@@ -527,11 +534,7 @@ struct rnn_graph {
     // backward, 144 / 196 / 256 per lane of 64 workgroups: 0.50 / 0.82 / 1.14 against 0.96 / 0.69 / 0.77).
     bool register_over_xcds(const CompPlan& cp, bool backward, int N) const {
         if (N < 2 || N > 4 || cp.step_weight_floats > 160 * 64 * STEP_THREADS) return false;
-        StepLayout lay;
-        compute_step_layout(plan.words.data(), backward ? cp.bwd_desc_off : cp.fwd_desc_off, 256, 1, 1, lay);
-        int columns = 0;
-        for (int s = 0; lay.ok && s < lay.n_sources; ++s) columns += lay.src[s].k_len;
-        return columns >= (N == 2 ? 600 : 1100);
+        return step_columns(cp, backward) >= (N == 2 ? 600 : 1100);
     }
     // Chains of recurrent components run side by side in one launch: all members in the
     // wave-autonomous build (N <= 8, member g on XCD g), or all in the matrix-core build (the 256
