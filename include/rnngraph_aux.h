@@ -19,7 +19,8 @@ extern "C" {
  * that launch had helper members). */
 enum {
     RNN_BUILD_NONE = 0,
-    RNN_BUILD_WAVE = 1,         /* run-time specialised, weights in registers (few streams) */
+    RNN_BUILD_WAVE = 1,         /* run-time specialised, weights in registers (few streams); also recurrences without a full
+                                   connection inside, a thread per stream and unit (any number of streams) */
     RNN_BUILD_MATRIX = 2,       /* run-time specialised, matrix cores, weights in LDS (many streams) */
     RNN_BUILD_MATRIX_2D = 3,    /* the same with the two-dimensional split of wide layers */
     RNN_BUILD_LDS = 4,          /* run-time specialised, weights in LDS, several phases per step */

@@ -610,7 +610,9 @@ struct rnn_graph {
                 // take those products (RNNG_CHAIN_HELPERS = 0: never).
                 // Apart, each layer has all compute units: side by side pays while the slowest member's step (its matrix instructions, the
                 // exchange counted as STEP_COLUMNS) is no longer than theirs together.  2 x 700 units, N = 40, backward: 28 us a step side
-                // by side (groups of 40 streams on 6 rows), 12.6 apart; 2 x 512, N = 64, forward 5.6 against 6.0.
+                // by side (groups of 40 streams on 6 rows), 12.6 apart; 2 x 512, N = 64, forward 5.6 against 6.0.  Where the line lies (32 steps, us
+                // forward + backward, side by side / apart): 2 x 700, N = 24 242 + 340 / 303 + 399, N = 40 392 + 961 / 367 + 438, 2 x 1,024, N = 12 222 + 238 / 281 + 451, N = 24
+                // 378 / 359 forward.
                 constexpr int STEP_COLUMNS = 2200;
                 int apart = 0;
                 for (int m = ch.first; m <= ch.last; ++m) {
@@ -1095,7 +1097,8 @@ StepRun run_chain(rnn_graph* g, int chain, bool backward, hipStream_t s, int t0,
 // The tensors that all step launches of a direction poll during frames [t0, t1), if they are few and small: a call fills them with its first
 // launch, together with what it clears, instead of with one launch per step launch.  Only where all that the call touches is far less than the
 // 256 MiB memory-side cache: what is filled must still be there when it is polled (Elman 38,000-512-20,000, 2,048 frames, whose products
-// move 400 MB before the step loop: 5.00 -> 5.69 ms).
+// move 400 MB before the step loop: 5.00 -> 5.69 ms).  Apart / together, us forward + backward: 64 units, one stream, 64 frames (1 MiB) 70 + 61 / 69 + 60, 256 units, 64 streams,
+// 4 frames (9 MiB) 44 + 34 / 44 + 31, 16 frames (29 MiB) 62 + 63 / 63 + 62, 64 frames (111 MiB) 136 + 166 / 137 + 164: on both sides of the limits the difference is a per cent.
 bool all_shared(rnn_graph* g, bool backward, int t0, int t1, FillRanges& fr) {
     fr.count = 0;
     if (g->framewise) return false;

@@ -677,8 +677,10 @@ bool emit_mstep_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, 
     int n_late = 0;
     const std::vector<int>& own_bufs = backward ? cp.bwd_shared_bufs : cp.fwd_shared_bufs;
     for (int s = 0; s < ml.n_src; ++s) n_late += std::find(own_bufs.begin(), own_bufs.end(), lay.src[s].buf) != own_bufs.end();
+    // (Nothing is held back where the first such chunk is not among those asked for before the first multiplication.)
     int hold = local || cp.helper ? 0 : n_late == 1 ? std::min(10, (int)(5.5 + 1.9 * polled_mib)) : std::min(12, (int)(3 + 1.9 * polled_mib));
     if (const char* env = std::getenv("RNNG_MSTEP_HOLD")) hold = std::max(0, std::min(127, std::atoi(env)));
+    if (!flat || clate >= D - 1) hold = 0;
     o << "    static constexpr int HOLD = " << hold << ";\n";
     // RNNG_MSTEP_LOCAL = 2: such a launch, its groups dealt over the XCDs all the same (which its workgroups have to find out)
     const char* deal = std::getenv("RNNG_MSTEP_LOCAL");
@@ -981,7 +983,9 @@ std::string jit_sstep_source(const Plan& P, const CompPlan& cp, bool backward, i
 }
 
 // Streaming matrix-core variant for N >= 9 streams and layers whose weights do not fit on chip.
-// Of a lane's 256 registers: resident weights and their source values (LSTM of 4,096 units, three / four chunks a source: 37.0 + 44.2 / 40.4 + 47.4 us a step).
+// Of a lane's 256 registers: resident weights and their source values.  24 steps of 16 streams with 40 / 60 / 80, ms forward + backward: LSTM 3,072 units
+// 0.53 + 0.77 / 0.51 + 0.77 / 0.48 + 0.77, 3,584 0.73 + 1.02 / 0.70 + 1.02 / 0.76 + 1.07, 4,096 1.12 + 1.18 / 1.04 + 1.16 / 1.10 + 1.24, 5,120 2.03 + 2.86 / 1.90 +
+// 2.86 / 1.88 + 2.82; Elman 5,120 0.60 + 0.61 / 0.58 + 0.60 / 0.60 + 0.61, 8,192 1.08 + 1.20 / 1.06 + 1.18 / 1.06 + 1.18.
 constexpr int SMSTEP_KEPT_REGISTERS = 60;
 std::string jit_smstep_source(const Plan& P, const CompPlan& cp, bool backward, int N, int G, size_t* lds_bytes, bool* transposed, bool* blocked,
                               int* threads) {

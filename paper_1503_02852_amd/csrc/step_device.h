@@ -1396,18 +1396,22 @@ __device__ __forceinline__ void wave_step(PhaseRegs<PH>& r, const WaveRegs<MV>& 
 // and whose last block has only the streams there are, so that any stream count and any width takes
 // this path (without twins a row of a source must be a multiple of 16 bytes).  One accumulator set serves all sources; the
 // NW partial tiles meet in LDS, where the element-wise program runs with one thread per
-// (stream, unit) on the first STEP_THREADS threads.
+// (stream, unit): on MM::NE wavefronts of their own behind the NW, whose stores nobody waits for run under the next
+// contraction, or (NE = 0) on the first of the NW.
 //
 // MM is a generated descriptor:
 //   static constexpr int NJ (streams per workgroup), MT (16-stream tiles), NSRC, NTU (16-row
 //   tiles), D (register sets of chunks), CMAX, ACCS (row stride of an accumulator tile), NW
-//   (wavefronts), NCH (chunks of all sources), CLATE (first chunk that holds the previous step's
+//   (wavefronts that contract), NE (wavefronts that run the element-wise program alone), HOLD (hold_off), LG (workgroups of a stream group on one
+//   XCD, 0: spread over all), LDSF, ACCBASE, ZROW (floats of LDS, where the partial tiles and the row of zeros lie), NWE / NRE
+//   (edges whose weights go to LDS / registers), NCH (chunks of all sources), CLATE (first chunk that holds the previous step's
 //   own values), NRW (weight quads in registers); bool FLAT (the chunk sequence is unrolled whole),
-//   XB, TAIL (the window's last 16-stream block is not full), HELPER (a chain's helper member: its program only stores the sums of its products, which
+//   LDEAL (such a group's workgroups are dealt over the XCDs all the same), XB, TAIL (the window's last 16-stream block is not full), HELPER (a chain's helper member: its program only stores the sums of its products, which
 //   another member's program polls element by element); unsigned REGMASK; constexpr K(s) (columns of
 //   source s), KP(s) (the same, padded to whole quads with XB), ngr(s) (groups of D chunks of source s), blk(s, task)
 //   (row block of the task in source s, -1: none), used(s, nt), csrc(c) / ck0(c) (source and first
-//   column of chunk c), widx(c * 16 + nt) (register index of a weight quad).
+//   column of chunk c), widx(c * 16 + nt) (register index of a weight quad), wbase(s) / wstride(s) (a source's weight rows in LDS), we_*(i) / re_*(i)
+//   (the i-th edge into LDS / registers: source, task, edge of the task, whether it adds to another's rows, whether it is transposed).
 // =============================================================================================
 
 #if !defined(MSTEP_POLL_INC)
@@ -1859,10 +1863,10 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
                     }
         };
         // The loads of what the other workgroups produced in the step before are held back until
-        // those stores are usually visible (a first attempt that comes back with a sentinel costs a
-        // whole extra round trip); chunks in front of them (MM::CLATE) are not.
-        // (With the unrolled sequence, where the multiplications of the early chunks fill that time,
-        // holding back measured slower than retrying: charlm_n32 forward 1.26 against 0.89 ms.)
+        // those stores are usually visible: a first attempt that comes back with a sentinel costs a
+        // whole extra round trip.  The unrolled sequence waits MM::HOLD units of 64 clocks, known beforehand, in front of the first of
+        // these chunks, if that is among the D - 1 asked for before the first multiplication; behind that, multiplications
+        // fill the time (HOLD is 0).  The grouped sequence waits as long as its retries have taught it.
         auto hold_off = [&]() {
             if constexpr (MM::FLAT) { if (MM::HOLD > 0) __builtin_amdgcn_s_sleep(MM::HOLD); }
             else for (int i = 0; i < pdelay; ++i) __builtin_amdgcn_s_sleep(1);
@@ -1952,7 +1956,7 @@ __device__ __forceinline__ void mstep_kernel_body(const StepArgs& a, MShared& ms
                             if (MM::used(sidx, nt)) opb[nt] = *reinterpret_cast<const mfloatx4*>(&lds[brow[sidx][nt] + k0 + wave * 16]);
                         if (bad && !dead) reload(v[i], ss, k0);
                         if (sidx == 0 && i == 0 && g == 0) { RNNG_STAMP(2); }
-                        if (sidx == 0 && i == 1 && g == 0) { RNNG_STAMP(6); RNNG_STAMP(7); }
+                        if (sidx == 0 && i == 1 && g == 0) { RNNG_STAMP(6); }
                         ahead();
                         bad = incomplete(v[i1]);
                         multiply(ss, v[i], opb);
