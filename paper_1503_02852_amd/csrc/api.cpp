@@ -138,8 +138,9 @@ struct Profiler {
 // Whether the workgroups of a launch are dealt to the XCDs in turn, observed once per device: ok if every
 // workgroup b of a probe launch with the same b % 8 ran on one XCD.  The step kernels that keep a group of
 // workgroups on one residue class then exchange through that XCD's L2 with plain stores.  Which XCD it is
-// may change between launches (it does once several streams have been used), so each launch leaves
-// the ids it ran on in a control word, and a group on more than one XCD is reported.
+// may change between launches (it does once several streams have been used), so each launch of the weights-in-registers build
+// leaves the ids it ran on in a control word, and a group on more than one XCD is reported; the workgroups of the matrix-core build find out by
+// themselves before they store (xcd_field_word).
 struct XcdMap { bool known = false, ok = false; };
 
 struct rnn_graph;
