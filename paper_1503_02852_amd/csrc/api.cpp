@@ -947,12 +947,16 @@ StepRun run_phases(rnn_graph* g, int comp, bool backward, hipStream_t s, int t0,
                           (!(jc->wave || jc->element_wise || (jc->mstep && !jc->two_d)) || wave_tensor_sizes_ok(g));
     const bool have_interp = !g->framewise && plan_step_launch(g->plan.words.data(), desc_off, N, g->force_step_G, lp);
     const int spin_limit = g->spin_limit;
-    if (have_jit) {
+    // (measured for matrix-core launches per direction; backward loops, with more stores and loads per
+    // step, gain 3 %, forward loops lose 4 to 6 %)
+    const bool window = have_jit && (jc->wave || (((jc->mstep && !jc->two_d && backward) || jc->element_wise) && gathers_in_workspace(g, phases))) && wave_store_window_ok(g);
+    // Element-wise recurrences beyond the register build's streams can also go frame by frame, without code that has to be loaded first: a
+    // call that may load none takes that way where nothing has.
+    const bool have_fn = have_jit && !(g->no_alloc && jc->element_wise && N > 8 &&
+                                       !jit_step_function(window ? windowed(jc->source, jc->source_window) : jc->source, nullptr, false, STEP_LDS_LIMIT));
+    if (have_fn) {
         hipError_t fe = fill_shared(g, backward ? cp.bwd_shared_bufs : cp.fwd_shared_bufs, jc->wave, t0, t1, s, jc->blocked, jc->local);
         if (fe != hipSuccess) return step_error(fe, "sentinel fill");
-        // (matrix-core build: measured per direction; backward loops, with more stores and loads per
-        // step, gain 3 %, forward loops lose 4 to 6 %)
-        const bool window = (jc->wave || (((jc->mstep && !jc->two_d && backward) || jc->element_wise) && gathers_in_workspace(g, phases))) && wave_store_window_ok(g);
         std::string why;
         hipFunction_t fn = jit_step_function(window ? windowed(jc->source, jc->source_window) : jc->source, &why, !g->no_alloc,
                                              jc->mstep && !jc->two_d ? MSTEP_LDS_LIMIT : STEP_LDS_LIMIT);

@@ -72,6 +72,33 @@ def test_static_workspace_does_not_count_the_copies_of_ragged_tiles(spec_fn, T, 
         assert np.array_equal(got[k], ref[k])
 
 
+def test_static_call_of_an_element_wise_recurrence_needs_no_code_that_is_loaded_first():
+    """Beyond eight streams such a recurrence can go frame by frame: the first call on a handle may be a static one; with the
+    kernel loaded it is used.  Up to eight streams there is no such way, and the call is refused."""
+    import torch
+    from paper_1503_02852_amd import RnnError
+    from paper_1503_02852_amd.runner import window_for
+    spec = wl.lstm_net(11, [29], 5, output_recurrence=False)
+    (out,) = spec.output_nodes()
+    for N in (8, 12):
+        w = wl.make_workload("static_first", spec, T=7, N=N, seed=83, scale=0.4, bias_scale=0.3)
+        win = window_for(w)
+        got = torch.full((w.T, N, spec.nodes[out]["dim"]), float("nan"), dtype=torch.float32, device=win.dev)
+        call = lambda: win.g.forward_static(win.weights.data_ptr(), win._input_ptrs(), [got.data_ptr()], w.T, w.N, win._stream())
+        if N == 8:
+            with pytest.raises(RnnError):
+                call()
+            continue
+        y, _ = go.forward(spec.nodes, spec.edges, w.weights, w.biases, w.inputs, w.T, N)
+        for build in ("per_frame", "wave"):
+            call()
+            win.check()
+            rec = [k for k in range(len(spec.nodes)) if win.g.step_build(k)[0] != "none"]
+            assert rec and all(win.g.step_build(k)[0] == build for k in rec)
+            assert nerr(got.cpu().numpy(), y[out]) < OUT_TOL
+            win.forward()
+
+
 def test_static_call_under_capture_with_copies_beyond_the_workspace():
     """A captured rnn_forward_static in the larger array, replayed with other work in between."""
     import torch
