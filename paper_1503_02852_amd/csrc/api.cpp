@@ -243,6 +243,9 @@ struct rnn_graph {
             }
         };
         auto try_local = [&]() {
+            // Only on a whole device, whose eight XCDs of 32 compute units each take an eighth of the launch: on a partition of two XCDs, three groups
+            // of 21 workgroups would put 42 on the first, not all resident, and wait for each other in vain.
+            if (max_workgroups() < 256) return;
             if (!c.source.empty() || c.stream || force_step_G > 0 || force_step_J > 0 || !local_streams(cp, backward, N)) return;
             const int J = (N + 15) / 16;
             const MstepPick p = pick_mstep(cp, backward, N, J, 32, true);
