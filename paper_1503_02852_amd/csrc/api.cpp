@@ -251,11 +251,15 @@ struct rnn_graph {
             const MstepPick p = pick_mstep(cp, backward, N, J, 32, true);
             if (p.G && J <= std::min(8 * (32 / p.G), MSTEP_LOCAL_MAX_UNITS) && p.G * J <= max_workgroups() && (local_env >= 1 || p.rows <= (N >= 16 ? 48 : 32))) take_mstep(c, cp, backward, N, p, true);
         };
-        // Recurrences without a full connection inside: a thread per stream and unit.  LSTM without output recurrence, us a launch against the
-        // weights-in-registers build: forward 512 units, N = 1, 2,048 frames 358 / 449, 64 units, N = 4, 512 frames 93 / 118; backward
-        // 512, N = 8, 256 frames 76 / 104, but 512, N = 1 534 / 493, 1,024, N = 4, 256 frames 76 / 67.  From 9 streams on the other is a launch
+        // Recurrences without a full connection inside: a thread per stream and unit.  LSTM without output recurrence, 512 frames, us a call against the
+        // weights-in-registers build: forward, any width, 10 to 15 % ahead (one stream, 8 / 100 / 300 units 129 / 137, 129 / 149, 131 / 154).  Backward the
+        // other is ahead while its wavefronts have few units and streams: five streams 512 / 700 units 181 / 165, 186 / 187, six 450 / 512 200 / 193, 183 / 206, seven 150 /
+        // 200 180 / 175, 174 / 188, eight 64 / 100 167 / 160, 170 / 174; up to four always.  From 9 streams on the other is a launch
         // per frame: 64 units, N = 10 0.19 + 0.28 against 6.1 + 7.7 us a frame forward + backward, 1,000 units, N = 64 0.62 + 0.82 against 6.8 + 8.6.
-        if (c.source.empty() && force_step_G <= 0 && (!backward || N >= 5)) {
+        const std::vector<PhasePlan>& program = backward ? cp.bwd_phases : cp.fwd_phases;
+        const int units = program.empty() ? 0 : program[0].max_dim;
+        if (c.source.empty() && force_step_G <= 0 &&
+            (!backward || N >= 9 || (N >= 5 && units >= (N == 5 ? 700 : N == 6 ? 512 : N == 7 ? 200 : 100)))) {
             c.source = jit_estep_source(plan, cp, backward, N, &c.lp.G, &c.J);
             if (c.source.empty()) { c.J = 1; c.lp = StepLaunchPlan(); }
             else { c.element_wise = true; c.lp.ok = true; c.lp.NB = 1; c.lp.lds_bytes = 0; c.lp.threads = 64; c.lp.xcd_stride = 1; }

@@ -9,28 +9,26 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 CHILD = """
-import os, sys
+import sys
 import workloads as wl
 from paper_1503_02852_amd import Graph
-for i, shape in enumerate(sys.argv[2:]):
-    net, hidden, N = shape.split(":")
-    hidden = [int(h) for h in hidden.split(",")]
-    os.environ["RNNG_JIT_DUMP"] = os.path.join(sys.argv[1], str(i))
-    os.mkdir(os.environ["RNNG_JIT_DUMP"])
-    spec = wl.elman_net(7, hidden[0], 5) if net == "elman" else wl.lstm_net(7, hidden, 5, output_recurrence=net != "element_wise")
-    Graph(spec.node_array(), spec.edge_array()).specialise(int(N))
+net, hidden, N = sys.argv[1].split(":")
+hidden = [int(h) for h in hidden.split(",")]
+spec = wl.elman_net(7, hidden[0], 5) if net == "elman" else wl.lstm_net(7, hidden, 5, output_recurrence=net != "element_wise")
+Graph(spec.node_array(), spec.edge_array()).specialise(int(N))
 """
 
 
 def sources(tmp_path, shapes, **env):
-    """Per shape the sources of its forward and its backward launch (one of them, if they are the same)."""
+    """Per shape the sources of its forward and its backward launch (one of them, if they are the same); a process each, since a source is generated once."""
     clean = {k: v for k, v in os.environ.items() if not k.startswith("RNNG_")}
-    subprocess.run([sys.executable, "-c", CHILD, str(tmp_path)] + shapes, check=True, cwd=ROOT, env={**clean, **env})
     got = []
-    for i in range(len(shapes)):
+    for i, shape in enumerate(shapes):
         d = tmp_path / str(i)
+        d.mkdir()
+        subprocess.run([sys.executable, "-c", CHILD, shape], check=True, cwd=ROOT, env={**clean, **env, "RNNG_JIT_DUMP": str(d)})
         got.append([(d / f).read_text() for f in sorted(os.listdir(d), key=lambda f: int(re.findall(r"_(\d+)\.hip", f)[0]))])
-        assert 1 <= len(got[-1]) <= 2, shapes[i]
+        assert 1 <= len(got[-1]) <= 2, shape
     return got
 
 
@@ -60,11 +58,11 @@ def test_resident_chunks_of_streamed_weights(tmp_path):
 
 
 def test_element_wise_recurrences_have_a_kernel_of_their_own(tmp_path):
-    """A thread per stream and unit: forward at any number of streams, backward from five on (below, on the lanes of the register build)."""
-    shapes = ["element_wise:9:4", "element_wise:11:5", "element_wise:13:8", "element_wise:20:9"]
-    for shape, (forward, backward) in zip(shapes, sources(tmp_path, shapes)):
+    """A thread per stream and unit: forward at any number of streams, backward from nine on, below with many units (else on the lanes of the register build)."""
+    shapes = {"element_wise:7:4": False, "element_wise:511:6": False, "element_wise:512:6": True, "element_wise:99:8": False, "element_wise:100:8": True, "element_wise:20:9": True}
+    for (shape, expected), (forward, backward) in zip(shapes.items(), sources(tmp_path, list(shapes))):
         assert "estep_kernel_body" in forward, shape
-        assert ("estep_kernel_body" in backward) == (int(shape.split(":")[2]) >= 5), shape
+        assert ("estep_kernel_body" in backward) == expected, shape
 
 
 def test_four_streams_backward_exchange_inside_one_xcd_before_registers_of_two(tmp_path):
