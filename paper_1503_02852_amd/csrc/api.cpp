@@ -480,20 +480,25 @@ struct rnn_graph {
         int dim = plan.words[lay.ph[0].prog_off + PG_MAXDIM], k = 0;
         for (int t = 0; t < nt; ++t) dim = std::max(dim, lay.ph[0].task[t].n_out);
         for (int s = 0; s < lay.n_sources; ++s) k += lay.src[s].k_len;
+        int best_chunk = 0, best_regs = 0;
         for (int tiles = 1; tiles <= 16 && !best.G; ++tiles) {
             const int most = 16 * tiles / nt;
+            // With three tiles of streams a second source in registers spills others (LSTM backward, 1,500 units, 33 streams: 7 rows 39 us a step, 6 rows, one
+            // source, 30; with one tile, 520 units, 9 streams, 28 rows and three sources 6.8, 26 and two 7.1).
+            auto several = [&]() { return best_regs > 1 && mstep_streams(N, J, true) > 32; };
             for (int chunk = most; chunk >= 1 && chunk * nt > 16 * (tiles - 1); --chunk) {
-                if (chunk * 3 < most * 2 && best.G) break;
+                if (chunk * 3 < (several() ? best_chunk : most) * 2 && best.G) break;
                 MstepPick p;
                 p.G = force_step_G > 0 ? force_step_G : (dim + chunk - 1) / chunk; p.J = J;
                 if (p.G > limit) break;
                 if (force_step_G <= 0 && chunk * mstep_streams(N, J, true) > STEP_THREADS) continue;      // (more element-wise items than threads)
-                bool regs = false;
+                int regs = 0;
                 const bool fits = jit_mstep_fits(plan, cp, backward, N, p.G, J, local, &p.rows, &regs);
                 p.columns = k * ((p.rows + 15) / 16) * (((N + 15) / 16 + J - 1) / J);
                 if (force_step_G > 0) return fits ? p : best;
-                if (!fits || (regs && best.G)) continue;
-                best = p;
+                if (!fits || (best.G && regs >= (several() ? best_regs : 1))) continue;
+                if (!best.G) best_chunk = chunk;
+                best = p; best_regs = regs;
                 if (!regs) break;
             }
         }

@@ -496,7 +496,7 @@ namespace {
 // streams come in whole 16-stream tiles).
 // local: the G workgroups of each stream group sit on one XCD.
 bool emit_mstep_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, bool backward, int N_all, int G, int J, int NW, bool blocked,
-                      const std::string& ns, size_t* lds_bytes, int* rows, bool local, int* NE, bool* in_registers = nullptr) {
+                      const std::string& ns, size_t* lds_bytes, int* rows, bool local, int* NE, int* in_registers = nullptr) {
     const std::vector<PhasePlan>& phases = backward ? cp.bwd_phases : cp.fwd_phases;
     if (phases.size() != 1 || N_all < 1 || J < 1 || G * J > 256) return false;
     // streams per workgroup; several stream groups are made of whole 16-stream tiles (without twins
@@ -560,7 +560,7 @@ bool emit_mstep_group(std::ostringstream& o, const Plan& P, const CompPlan& cp, 
     if (MT * NTU > 16) return false;     // accumulator registers
     if (lds_bytes) *lds_bytes = (size_t)ml.total_floats * 4;
     if (rows) *rows = ph.n_tasks * ph.cmax;
-    if (in_registers) *in_registers = reg_mask != 0;
+    if (in_registers) *in_registers = __builtin_popcount(reg_mask);
     if (*NE < 0) {      // asked only whether the component fits, and for the wavefronts that its element-wise items need
         *NE = reg_mask ? 0 : (ph.item_chunk * N + 63) / 64;
         return true;
@@ -726,7 +726,7 @@ static std::vector<int> mstep_blocked_choices() {
     return {1, 0};
 }
 
-bool jit_mstep_fits(const Plan& P, const CompPlan& cp, bool backward, int N_all, int G, int J, bool local, int* rows, bool* in_registers) {
+bool jit_mstep_fits(const Plan& P, const CompPlan& cp, bool backward, int N_all, int G, int J, bool local, int* rows, int* in_registers) {
     std::ostringstream none;
     for (int nw : mstep_wave_counts())
         for (int b : mstep_blocked_choices()) {

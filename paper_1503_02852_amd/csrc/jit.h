@@ -27,9 +27,9 @@ std::string jit_chain_source(const Plan& P, const std::vector<CompPlan>& members
 // mstep_local_blocks(G, J) workgroups.
 std::string jit_mstep_source(const Plan& P, const CompPlan& cp, bool backward, int N, int G, int J, size_t* lds_bytes, int* threads = nullptr,
                              bool* blocked = nullptr, bool local = false);
-// Whether that variant exists; *rows: accumulator rows per workgroup (tasks x units per chunk), *in_registers: weight rows of whole sources
+// Whether that variant exists; *rows: accumulator rows per workgroup (tasks x units per chunk), *in_registers: sources whose weight rows
 // are kept in vector registers.
-bool jit_mstep_fits(const Plan& P, const CompPlan& cp, bool backward, int N, int G, int J, bool local, int* rows, bool* in_registers);
+bool jit_mstep_fits(const Plan& P, const CompPlan& cp, bool backward, int N, int G, int J, bool local, int* rows, int* in_registers);
 // Element-wise recurrences: a thread per (stream, unit), no workgroup waits for another (*G unit chunks x *J stream groups of one wavefront each).
 std::string jit_estep_source(const Plan& P, const CompPlan& cp, bool backward, int N, int* G, int* J);
 // Matrix-core variant with the two-dimensional split (row groups of GJ workgroups that share

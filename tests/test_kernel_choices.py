@@ -77,3 +77,10 @@ def test_streamed_weights_keep_residents_only_where_they_pay(tmp_path):
     for shape, both in zip(shapes, sources(tmp_path, list(shapes))):
         assert all("smstep_kernel_body" in source for source in both), shape
         assert tuple(constant(source, "PR") > 0 for source in (both[0], both[-1])) == shapes[shape], shape
+
+
+def test_three_tiles_of_streams_keep_one_source_in_registers(tmp_path):
+    """LSTM backward, four sources: a smaller unit chunk rather than two of them in registers, which spilled others."""
+    ((_, backward),) = sources(tmp_path, ["lstm:1500:33"])
+    assert "mstep_kernel_body<grp0" in backward and constant(backward, "MT") == 3
+    assert bin(constant(backward, "REGMASK")).count("1") == 1
